@@ -1,0 +1,193 @@
+"""What a user of the SwitchBack layer has it do, as a set of measured cases over the public Python entry points.
+
+A case is a dict of plain values.  "kind" names the path:
+
+  step       one training step of one linear layer: forward, input gradient, weight gradient (Algorithm 1)
+  step_m     the same with SwitchBackM (the weight gradient works on X rebuilt from its int8 codes)
+  step_q     the same with SwitchBackQ (row-wise / column-wise weight quantization)
+  step_f8    the same with the float8 quantizer (E4M3 for X and W, E5M2 for dY)
+  block      training steps of the four linear layers of a transformer block of width n: qkv (n -> 3n), proj (n -> n),
+             fc1 (n -> 4n), fc2 (4n -> n)
+  forward    serving: X quantized row-wise, then the product with a weight quantized once, bias and layer-scale in its
+             epilogue
+  adamw      one StableAdamW step over a block's parameters of width n (four weights, four biases, two layer-scales)
+
+b is the number of tokens, n -> m the layer's widths, "dw" the type of the weight gradient (and the optimizer's
+gradients), "data" the distribution of X and dY: "normal" (X ~ N(0,1), dY ~ N(0, 1e-2)) or "outlier" (0.1 % of the feature
+columns of X a hundred times larger, dY heavy-tailed), the two families of workloads of this package's inputs.
+"""
+import math
+
+import torch
+
+from paper_2304_13013_amd import switchback as sb
+
+#: The optimizer's settings (rate, betas, eps, weight decay) of a CLIP-like pretraining run.
+ADAMW = (1e-3, 0.9, 0.98, 1e-6, 0.2)
+
+
+def _case(name, kind, b, n, m, dw="bf16", data="normal"):
+    return {"name": name, "kind": kind, "b": b, "n": n, "m": m, "dw": dw, "data": data}
+
+
+def listed():
+    return [
+        # A unit-test sized layer: launches and host work are all there is.
+        _case("tiny step", "step", 512, 256, 1024),
+        # Serving one 224-pixel image with ViT-B/16: 197 tokens through fc1.
+        _case("image fc1 forward", "forward", 197, 768, 3072),
+        # ViT-B/16 training with 32 images on the GPU: few output tiles, short kernels.
+        _case("vit_b16 fc1 step", "step", 6304, 768, 3072),
+        _case("vit_b16 fc2 step_q", "step_q", 6304, 3072, 768),
+        # Widths that are multiples of 64 but not of 128 and an odd number of tokens (packed variable-length sequences).
+        _case("ragged step", "step", 11237, 1088, 2880),
+        # ViT-L/14 training with 64 images: each variant of the layer on another of its linear layers, and binary32
+        # weight gradients as an accumulating optimizer wants them.
+        _case("vit_l14 fc2 step f32", "step", 16448, 4096, 1024, dw="f32"),
+        _case("vit_l14 qkv step_m", "step_m", 16448, 1024, 3072),
+        _case("vit_l14 fc1 step_f8", "step_f8", 16448, 1024, 4096),
+        # The headline workload: all four linear layers of a ViT-H/14 block, 128 images.
+        _case("vit_h14 block", "block", 32896, 1280, 0),
+        # A large-language-model sized layer with emergent outlier features.
+        _case("outlier up step", "step", 16384, 4096, 16384, data="outlier"),
+        # The optimizer step of a ViT-B/16 and of a ViT-H/14 block.
+        _case("vit_b16 adamw f32", "adamw", 0, 768, 0, dw="f32"),
+        _case("vit_h14 adamw", "adamw", 0, 1280, 0),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return math.exp(rng.uniform(math.log(lo), math.log(hi)))
+
+
+def draw(rng):
+    kind = rng.choice(["step", "step", "step", "step", "step_m", "step_q", "step_f8", "block", "forward", "forward", "adamw"])
+    dw = rng.choice(["bf16", "bf16", "f32"])
+    data = rng.choice(["normal", "normal", "normal", "outlier"])
+    unit = 128 if kind == "step_f8" else 64  # the float8 product contracts multiples of 128
+    if kind == "adamw":
+        return {"kind": kind, "b": 0, "n": unit * round(_log_uniform(rng, 128, 2048) / unit), "m": 0, "dw": dw, "data": "normal"}
+    while True:
+        b = round(_log_uniform(rng, 100, 34000))
+        if rng.random() < 0.4:  # whole images or sequences
+            b = max(64, b // 64 * 64)
+        n = unit * max(1, round(_log_uniform(rng, 128, 1600 if kind == "block" else 8192) / unit))
+        m = 0 if kind == "block" else unit * max(1, round(_log_uniform(rng, 128, 8192) / unit))
+        if b * n * (12 * n if kind == "block" else m) <= 32896 * 12 * 1280 * 1280:
+            return {"kind": kind, "b": b, "n": n, "m": m, "dw": dw, "data": data}
+
+
+def _layers(case):
+    n = case["n"]
+    return [(n, 3 * n), (n, n), (n, 4 * n), (4 * n, n)] if case["kind"] == "block" else [(n, case["m"])]
+
+
+def _adamw_counts(n):
+    return [3 * n * n, n * n, 4 * n * n, 4 * n * n, 3 * n, n, 4 * n, n, n, n]
+
+
+def _activations(case, gen, b, n, m):
+    dev = "cuda"
+    x = torch.randn(b, n, generator=gen, device=dev)
+    dy = torch.randn(b, m, generator=gen, device=dev)
+    if case["data"] == "outlier":
+        cols = torch.randperm(n, generator=gen, device=dev)[: -(-n // 1000)]
+        x[:, cols] *= 100.0
+        chi2 = torch.zeros_like(dy)
+        for _ in range(3):
+            chi2 += torch.randn(b, m, generator=gen, device=dev).square_()
+        dy = dy.mul_(0.01).div_(chi2.div_(3.0).sqrt_())
+    else:
+        dy.mul_(0.1)
+    return x.bfloat16(), dy.bfloat16()
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    kind, b = case["kind"], case["b"]
+    state = {"kind": kind, "dw_dtype": torch.bfloat16 if case["dw"] == "bf16" else torch.float32}
+    if kind == "adamw":
+        tensors = []
+        for count in _adamw_counts(case["n"]):
+            normal = lambda: torch.randn(count, generator=gen, device="cuda")
+            grad = (normal() * 1e-3).to(state["dw_dtype"])
+            u = torch.rand(count, generator=gen, device="cuda") * 2.7e-6 + 0.3e-6
+            tensors.append((normal() * 0.02, normal() * 3e-4, u, grad))
+        state.update(tensors=tensors, plan=sb.AdamwPlan(tensors), t=1000)
+        return state
+    state["layers"] = []
+    for n, m in _layers(case):
+        x, dy = _activations(case, gen, b, n, m)
+        w = (torch.randn(m, n, generator=gen, device="cuda") / math.sqrt(n)).bfloat16()
+        if kind == "forward":
+            wq, _, state_w = sb.quantize_tensorwise(w, transpose=False)
+            bias, gamma = (torch.rand(m, generator=gen, device="cuda") for _ in range(2))
+            state["layers"].append({"x": x, "wq": wq, "state_w": state_w, "bias": bias, "gamma": gamma})
+        else:
+            bufs = (sb.LayerBuffersQ if kind == "step_q" else sb.LayerBuffers)(b, n, m)
+            state["layers"].append({"x": x, "dy": dy, "w": w, "bufs": bufs})
+    return state
+
+
+def run(state):
+    kind, dw_dtype = state["kind"], state["dw_dtype"]
+    if kind == "adamw":
+        state["t"] += 1
+        rms = sb.stable_adamw_step_multi(state["plan"], *ADAMW, state["t"])
+        return {"rms": rms, "tensors": [t[:3] for t in state["tensors"]]}
+    out = []
+    for layer in state["layers"]:
+        if kind == "forward":
+            xq, state_x = sb.quantize_rowwise(layer["x"])
+            y = sb.matmul_int8_dequant_bias_layerscale(xq, state_x, layer["wq"], layer["state_w"], layer["bias"],
+                                                       layer["gamma"])
+            out.append({"y": y})
+            continue
+        x, w, dy, bufs = layer["x"], layer["w"], layer["dy"], layer["bufs"]
+        if kind == "step_q":
+            y, _ = sb.forward_q(x, w, bufs)
+            dx = sb.backward_input_q(dy, w, bufs)
+            dw = sb.backward_weight(dy, x, dw_dtype=dw_dtype)
+            out.append({"y": y, "dx": dx, "dw": dw})
+        elif kind == "step_f8":
+            y, _ = sb.forward_f8(x, w, bufs)
+            dx = sb.backward_input_f8(dy, bufs)
+            dw = sb.backward_weight(dy, x, bufs, dw_dtype=dw_dtype)
+            out.append({"y": y, "dx": dx, "dw": dw})
+        elif kind == "step_m":
+            y, _ = sb.forward(x, w, bufs)
+            dx = sb.backward_input(dy, bufs)
+            dw, _ = sb.backward_weight_m(dy, bufs, dw_dtype=dw_dtype)
+            out.append({"y": y, "dx": dx, "dw": dw})
+        else:
+            y, _ = sb.forward(x, w, bufs)
+            dx = sb.backward_input(dy, bufs)
+            dw = sb.backward_weight(dy, x, bufs, dw_dtype=dw_dtype)
+            out.append({"y": y, "dx": dx, "dw": dw})
+    return out
+
+
+def work(case):
+    grad_bytes = 2 if case["dw"] == "bf16" else 4
+    if case["kind"] == "adamw":
+        count = sum(_adamw_counts(case["n"]))
+        return {"bytes": (grad_bytes + 24) * count, "flops": 20 * count}
+    b, nbytes, flops = case["b"], 0, 0
+    for n, m in _layers(case):
+        if case["kind"] == "forward":
+            nbytes += 2 * b * n + m * n + 2 * b * m + 8 * m
+            flops += 2 * b * n * m
+        else:
+            nbytes += 4 * (b * n + b * m) + (2 + grad_bytes) * m * n
+            flops += 6 * b * n * m
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    # Four times what was measured against the same path evaluated in binary64 and rounded to the output's type: bf16
+    # outputs differ by one rounding (2^-7 of the value at most) in the few elements whose exact value lies near the
+    # middle of two bf16 values (relative 1e-5 to 4e-5 over a tensor; 1.8e-4 for the float8 product, whose matrix
+    # instruction truncates small products); the optimizer's binary32 state by one rounding (relative 3.7e-8).
+    if case["kind"] == "adamw":
+        return {"rel": 1.5e-7, "max": 7e-7}
+    return {"rel": 8e-4 if case["kind"] == "step_f8" else 2e-4, "max": 1.6e-2}
