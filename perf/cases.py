@@ -102,26 +102,39 @@ def _activations(case, gen, b, n, m):
     return x.bfloat16(), dy.bfloat16()
 
 
+def _adamw_tensors(case, gen, dw_dtype):
+    tensors = []
+    for count in _adamw_counts(case["n"]):
+        normal = lambda: torch.randn(count, generator=gen, device="cuda")
+        grad = (normal() * 1e-3).to(dw_dtype)
+        u = torch.rand(count, generator=gen, device="cuda") * 2.7e-6 + 0.3e-6
+        tensors.append((normal() * 0.02, normal() * 3e-4, u, grad))
+    return tensors
+
+
+def _layer_inputs(case, gen, n, m):
+    b = case["b"]
+    x, dy = _activations(case, gen, b, n, m)
+    w = (torch.randn(m, n, generator=gen, device="cuda") / math.sqrt(n)).bfloat16()
+    bias = gamma = None
+    if case["kind"] == "forward":
+        bias, gamma = (torch.rand(m, generator=gen, device="cuda") for _ in range(2))
+    return x, dy, w, bias, gamma
+
+
 def prepare(case, seed):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     kind, b = case["kind"], case["b"]
     state = {"kind": kind, "dw_dtype": torch.bfloat16 if case["dw"] == "bf16" else torch.float32}
     if kind == "adamw":
-        tensors = []
-        for count in _adamw_counts(case["n"]):
-            normal = lambda: torch.randn(count, generator=gen, device="cuda")
-            grad = (normal() * 1e-3).to(state["dw_dtype"])
-            u = torch.rand(count, generator=gen, device="cuda") * 2.7e-6 + 0.3e-6
-            tensors.append((normal() * 0.02, normal() * 3e-4, u, grad))
+        tensors = _adamw_tensors(case, gen, state["dw_dtype"])
         state.update(tensors=tensors, plan=sb.AdamwPlan(tensors), t=1000)
         return state
     state["layers"] = []
     for n, m in _layers(case):
-        x, dy = _activations(case, gen, b, n, m)
-        w = (torch.randn(m, n, generator=gen, device="cuda") / math.sqrt(n)).bfloat16()
+        x, dy, w, bias, gamma = _layer_inputs(case, gen, n, m)
         if kind == "forward":
             wq, _, state_w = sb.quantize_tensorwise(w, transpose=False)
-            bias, gamma = (torch.rand(m, generator=gen, device="cuda") for _ in range(2))
             state["layers"].append({"x": x, "wq": wq, "state_w": state_w, "bias": bias, "gamma": gamma})
         else:
             bufs = (sb.LayerBuffersQ if kind == "step_q" else sb.LayerBuffers)(b, n, m)
@@ -191,3 +204,53 @@ def tolerance(case):
     if case["kind"] == "adamw":
         return {"rel": 1.5e-7, "max": 7e-7}
     return {"rel": 8e-4 if case["kind"] == "step_f8" else 2e-4, "max": 1.6e-2}
+
+
+def _codes(a, dim, kind, float8=None):
+    """The layer's quantizer: codes (as binary64 numbers) and absmax of `a` along dim (None: of the whole tensor)."""
+    a = a.float()
+    absmax = a.abs().amax() if dim is None else a.abs().amax(dim, keepdim=True)
+    if kind == "step_f8":
+        return (a * (1.0 / absmax.double()).float()).to(float8).double(), absmax.double()
+    return (a * (127.0 / absmax.double()).float()).round().double(), absmax.double()
+
+
+def _exact_adamw(case, gen):
+    alpha, beta1, beta2, eps, lam = (float(torch.tensor(v, dtype=torch.float32)) for v in ADAMW)  # the call takes binary32
+    t, states, rms = 1001, [], []
+    b1, b2 = (beta * (1 - beta ** (t - 1)) / (1 - beta ** t) for beta in (beta1, beta2))
+    for theta, v, u, g in _adamw_tensors(case, gen, torch.bfloat16 if case["dw"] == "bf16" else torch.float32):
+        theta, v, u, g = (a.double() for a in (theta, v, u, g))
+        v, u = b1 * v + (1 - b1) * g, b2 * u + (1 - b2) * g * g
+        rms.append((g * g / u.clamp(min=eps * eps)).mean().sqrt())
+        eta = alpha / rms[-1].clamp(min=1.0)
+        states.append((theta - eta * lam * theta - eta * v / (u.sqrt() + eps), v, u))
+    return {"rms": torch.stack(rms), "tensors": states}
+
+
+def exact(case, seed):
+    # The codes are whole numbers that the layer defines by binary32 roundings, so they are formed that way here too;
+    # products, sums and everything after them are binary64.
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    kind = case["kind"]
+    if kind == "adamw":
+        return _exact_adamw(case, gen)
+    unit = 1.0 if kind == "step_f8" else 127.0
+    out = []
+    for n, m in _layers(case):
+        x, dy, w, bias, gamma = _layer_inputs(case, gen, n, m)
+        xq, sx = _codes(x, 1, kind, torch.float8_e4m3fn)
+        wq, sw = _codes(w, 1 if kind == "step_q" else None, kind, torch.float8_e4m3fn)
+        y = (xq @ wq.t()) * (sx / unit) * (sw.reshape(1, -1) / unit)
+        if kind == "forward":
+            out.append({"y": gamma.double() * (y + bias.double())})
+            continue
+        gq, sg = _codes(dy, 1, kind, torch.float8_e5m2)
+        if kind == "step_q":
+            wq, sw = _codes(w, 0, kind)
+        dx = (gq @ wq) * (sg / unit) * (sw.reshape(1, -1) / unit)
+        if kind == "step_m":  # X as the variant rebuilds it: a bf16 tensor
+            x = (xq.float() * (sx / 127.0).float()).bfloat16()
+        del xq, gq
+        out.append({"y": y, "dx": dx, "dw": dy.double().t() @ x.double()})
+    return out
