@@ -134,19 +134,36 @@ __device__ __forceinline__ void absmax_partial_body(const v4u *__restrict__ w, i
     if (threadIdx.x == 0) partials[block] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
 
+// A second matrix with the same number of columns whose rows follow the first one's in the same launch (SwitchBackQ
+// quantizes X and W row-wise in one forward pass; 6304 and 768 rows of 3072: 11.1 + 4.2 us in two launches, 12.1 us in
+// one).  rows == 0: none.
+struct SecondRows {
+    const v4u *x;
+    v2u *q;
+    float *state;
+    int64_t rows;
+};
+
 // ---- row-wise: one wavefront per row (cols <= 64*8*NCH) ---------------------------------------------------
 template <int NCH, int CODE>
 __global__ __launch_bounds__(256) void quantize_rowwise_wave_kernel(const v4u *__restrict__ x, int64_t rows,
                                                                     int chunks, v2u *__restrict__ q,
-                                                                    float *__restrict__ state, TensorAbsmaxJob job) {
+                                                                    float *__restrict__ state, TensorAbsmaxJob job,
+                                                                    SecondRows second) {
     __shared__ unsigned int rider_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, rider_max);
         return;
     }
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;  // whole wavefront leaves; the kernel has no block-level barrier
+    int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rows) {  // uniform per wavefront; the kernel has no block-level barrier
+        row -= rows;
+        if (row >= second.rows) return;
+        x = second.x;
+        q = second.q;
+        state = second.state;
+    }
     const v4u *xr = x + row * chunks;
     v4u v[NCH];
 #pragma unroll
@@ -173,13 +190,20 @@ __global__ __launch_bounds__(256) void quantize_rowwise_wave_kernel(const v4u *_
 template <int NCH, int CODE>
 __global__ __launch_bounds__(256) void quantize_rowwise_block_kernel(const v4u *__restrict__ x, int chunks,
                                                                      v2u *__restrict__ q,
-                                                                     float *__restrict__ state, TensorAbsmaxJob job) {
+                                                                     float *__restrict__ state, TensorAbsmaxJob job,
+                                                                     int64_t rows, SecondRows second) {
     __shared__ unsigned int wave_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, wave_max);
         return;
     }
-    const int64_t row = blockIdx.x;
+    int64_t row = blockIdx.x;
+    if (row >= rows) {  // uniform per workgroup; the grid has rows + second.rows of them
+        row -= rows;
+        x = second.x;
+        q = second.q;
+        state = second.state;
+    }
     const v4u *xr = x + row * chunks;
     v4u v[NCH];
 #pragma unroll
@@ -209,13 +233,20 @@ __global__ __launch_bounds__(256) void quantize_rowwise_block_kernel(const v4u *
 template <int CODE>
 __global__ __launch_bounds__(256) void quantize_rowwise_wide_kernel(const v4u *__restrict__ x, int chunks,
                                                                     v2u *__restrict__ q,
-                                                                    float *__restrict__ state, TensorAbsmaxJob job) {
+                                                                    float *__restrict__ state, TensorAbsmaxJob job,
+                                                                    int64_t rows, SecondRows second) {
     __shared__ unsigned int wave_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, wave_max);
         return;
     }
-    const int64_t row = blockIdx.x;
+    int64_t row = blockIdx.x;
+    if (row >= rows) {  // uniform per workgroup; the grid has rows + second.rows of them
+        row -= rows;
+        x = second.x;
+        q = second.q;
+        state = second.state;
+    }
     const v4u *xr = x + row * chunks;
     unsigned int m = 0;
     for (int c = threadIdx.x; c < chunks; c += 256) m = absmax_of_chunk(m, xr[c]);
@@ -321,37 +352,82 @@ __global__ __launch_bounds__(256) void quantize_tensorwise_kernel(const v4u *__r
 // 16-bit maxima over its run (no atomics, deterministic).  Pass 2: a 128x128 tile; its 128 column scales are
 // finished from the partial maxima first, then the tile is quantized element by element with its column's scale
 // and written out through the same LDS transpose as the tensor-wise kernel.
+// Both passes are bound by the latency of a few dependent loads at the sizes of a layer's weights (a 768 x 3072
+// weight is 4.7 MB): pass 1 spreads a run over 8 row lanes of 32 chunks each (512 contiguous bytes per row, every
+// thread's rows in flight together) and pass 2 requests its tile before it finishes the scales, whose partial maxima
+// all 256 threads fetch at once.  768 x 3072: 9.2 + 17.0 us with one thread per chunk and a serial loop over the
+// partial maxima, 3.9 + 4.8 us so.
+constexpr int kColChunks = 32, kColRowLanes = 8;  // threads of a pass-1 block: chunks side by side, row lanes
+
+__device__ __forceinline__ v4u pk_absmax_chunk(v4u m, v4u v) {
+    return v4u{pk_absmax_u16(m.x, v.x), pk_absmax_u16(m.y, v.y), pk_absmax_u16(m.z, v.z), pk_absmax_u16(m.w, v.w)};
+}
+
 __global__ __launch_bounds__(256) void col_absmax_partial_kernel(const v4u *__restrict__ w, int rows, int chunks,
                                                                  v4u *__restrict__ partials) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= chunks) return;
+    __shared__ v4u lane_max[kColRowLanes][kColChunks];
+    const int lc = threadIdx.x % kColChunks, lr = threadIdx.x / kColChunks;
+    const int c = blockIdx.x * kColChunks + lc;
     const int per = (rows + gridDim.y - 1) / gridDim.y;
     const int r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
     v4u m = {0u, 0u, 0u, 0u};
-    for (int r = r0; r < r1; ++r) {
-        const v4u v = w[(int64_t)r * chunks + c];
-        m.x = pk_absmax_u16(m.x, v.x);
-        m.y = pk_absmax_u16(m.y, v.y);
-        m.z = pk_absmax_u16(m.z, v.z);
-        m.w = pk_absmax_u16(m.w, v.w);
+    if (c < chunks) {
+        const v4u *src = w + c;
+        int r = r0 + lr;
+        for (; r + 7 * kColRowLanes < r1; r += 8 * kColRowLanes) {
+            v4u v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)(r + i * kColRowLanes) * chunks];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = pk_absmax_chunk(m, v[i]);
+        }
+        for (; r < r1; r += kColRowLanes) m = pk_absmax_chunk(m, src[(int64_t)r * chunks]);
     }
-    partials[(int64_t)blockIdx.y * chunks + c] = m;
+    lane_max[lr][lc] = m;
+    __syncthreads();
+    if (lr == 0 && c < chunks) {
+#pragma unroll
+        for (int i = 1; i < kColRowLanes; ++i) m = pk_absmax_chunk(m, lane_max[i][lc]);
+        partials[(int64_t)blockIdx.y * chunks + c] = m;
+    }
 }
 
 __global__ __launch_bounds__(256) void quantize_colwise_transpose_kernel(const v4u *__restrict__ w, int rows, int cols,
                                                                          int8_t *__restrict__ q_t,
                                                                          float *__restrict__ state,
-                                                                         const unsigned short *__restrict__ partials,
-                                                                         int nparts) {
+                                                                         const v4u *__restrict__ partials, int nparts) {
+    constexpr int kTileChunks = kTile / 8, kRunLanes = 256 / kTileChunks;
     __shared__ float tcol[kTile];
+    __shared__ v4u run_max[kRunLanes][kTileChunks];
     __shared__ unsigned int tile[kTileDwords];
     const int r0 = blockIdx.y * kTile, c0 = blockIdx.x * kTile;
+    const int chunks_per_row = cols >> 3;
+    // The tile first: its loads are in flight while the scales are finished.
+    v4u v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int id = threadIdx.x + 256 * i;
+        const int r = r0 + (id >> 4), c = c0 + ((id & 15) << 3);
+        v[i] = r < rows && c < cols ? w[(int64_t)r * chunks_per_row + (c >> 3)] : v4u{0u, 0u, 0u, 0u};
+    }
+    {
+        const int lc = threadIdx.x % kTileChunks, run = threadIdx.x / kTileChunks;
+        const int c = (c0 >> 3) + lc;
+        v4u m = {0u, 0u, 0u, 0u};
+        if (c < chunks_per_row)
+            for (int i = run; i < nparts; i += kRunLanes) m = pk_absmax_chunk(m, partials[(int64_t)i * chunks_per_row + c]);
+        run_max[run][lc] = m;
+    }
+    __syncthreads();
     if (threadIdx.x < kTile) {
         const int c = c0 + threadIdx.x;
         float t = 0.0f;
         if (c < cols) {
-            unsigned int m = 0;  // partials: [run][column] 16-bit patterns (the packed chunks, read back per column)
-            for (int i = 0; i < nparts; ++i) m = max(m, (unsigned int)partials[(int64_t)i * cols + c]);
+            // The packed chunks read back per column: [run lane][column] 16-bit patterns.
+            const unsigned short *bits = reinterpret_cast<const unsigned short *>(&run_max[0][0]);
+            unsigned int m = 0;
+#pragma unroll
+            for (int i = 0; i < kRunLanes; ++i) m = max(m, (unsigned int)bits[i * kTile + threadIdx.x]);
             float s;
             t = scale_from_absmax_bits(m, &s);
             if (blockIdx.y == 0) state[c] = s;
@@ -359,15 +435,13 @@ __global__ __launch_bounds__(256) void quantize_colwise_transpose_kernel(const v
         tcol[threadIdx.x] = t;
     }
     __syncthreads();
-    const int chunks_per_row = cols >> 3;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int id = threadIdx.x + 256 * i;
         const int lr = id >> 4, lc = (id & 15) << 3;  // local row, local first column of the 8-element chunk
         const int r = r0 + lr, c = c0 + lc;
         if (r < rows && c < cols) {
-            const v4u v = w[(int64_t)r * chunks_per_row + (c >> 3)];
-            const unsigned int d[4] = {v.x, v.y, v.z, v.w};
+            const unsigned int d[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
             unsigned int code[8];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -417,6 +491,7 @@ hipError_t launch_dequantize_rowwise(const int8_t *q, const float *state, int64_
     return hipGetLastError();
 }
 
+// Upper bound of the row runs of pass 1; what the workspace is sized for.
 int colwise_row_runs(int64_t rows) {
     const int64_t r = (rows + 15) / 16;
     return (int)(r < 1 ? 1 : (r > kColwiseRuns ? kColwiseRuns : r));
@@ -428,15 +503,19 @@ size_t quantize_colwise_workspace_bytes(int64_t rows, int64_t cols) {
 
 hipError_t launch_quantize_colwise_transpose(const void *w, int64_t rows, int64_t cols, int8_t *q_t, float *state,
                                              void *partials, hipStream_t stream) {
-    const int chunks = (int)(cols / 8), runs = colwise_row_runs(rows);
+    // 64 rows per run, eight loads in flight per thread: at most a quarter of the runs the workspace has room for,
+    // until the bound on the runs makes them longer.
+    const int chunks = (int)(cols / 8);
+    const int64_t wanted = (rows + 8 * kColRowLanes - 1) / (8 * kColRowLanes);
+    const int runs = (int)(wanted > kColwiseRuns ? kColwiseRuns : wanted);
     const v4u *wp = static_cast<const v4u *>(w);
-    col_absmax_partial_kernel<<<dim3((unsigned int)((chunks + 255) / 256), (unsigned int)runs), 256, 0, stream>>>(
-        wp, (int)rows, chunks, static_cast<v4u *>(partials));
+    col_absmax_partial_kernel<<<dim3((unsigned int)((chunks + kColChunks - 1) / kColChunks), (unsigned int)runs), 256, 0,
+                                stream>>>(wp, (int)rows, chunks, static_cast<v4u *>(partials));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 grid((unsigned int)((cols + kTile - 1) / kTile), (unsigned int)((rows + kTile - 1) / kTile));
     quantize_colwise_transpose_kernel<<<grid, 256, 0, stream>>>(wp, (int)rows, (int)cols, q_t, state,
-                                                                static_cast<const unsigned short *>(partials), runs);
+                                                                static_cast<const v4u *>(partials), runs);
     return hipGetLastError();
 }
 
@@ -449,18 +528,21 @@ int tensorwise_partial_blocks(int64_t nchunks) {
 
 template <int CODE>
 hipError_t launch_quantize_rowwise_t(const void *x, int64_t rows, int64_t cols, void *q, float *state,
-                                     hipStream_t stream, TensorAbsmaxJob job = TensorAbsmaxJob{nullptr, 0, nullptr, 0, 0}) {
+                                     hipStream_t stream, TensorAbsmaxJob job = TensorAbsmaxJob{nullptr, 0, nullptr, 0, 0},
+                                     SecondRows second = SecondRows{nullptr, nullptr, nullptr, 0}) {
     const int chunks = (int)(cols / 8);
     const v4u *xp = static_cast<const v4u *>(x);
     v2u *qp = static_cast<v2u *>(q);
-    unsigned int wave_grid = (unsigned int)((rows + 3) / 4), block_grid = (unsigned int)rows;
+    const int64_t all_rows = rows + second.rows;
+    unsigned int wave_grid = (unsigned int)((all_rows + 3) / 4), block_grid = (unsigned int)all_rows;
     // The rider's workgroups follow the rows' in the grid.
     job.first_block = (int)(chunks <= 256 ? wave_grid : block_grid);
     wave_grid += (unsigned int)job.nblocks;
     block_grid += (unsigned int)job.nblocks;
 #define SB_WAVE(N)                                                                                          \
-    quantize_rowwise_wave_kernel<N, CODE><<<wave_grid, 256, 0, stream>>>(xp, rows, chunks, qp, state, job)
-#define SB_BLOCK(N) quantize_rowwise_block_kernel<N, CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job)
+    quantize_rowwise_wave_kernel<N, CODE><<<wave_grid, 256, 0, stream>>>(xp, rows, chunks, qp, state, job, second)
+#define SB_BLOCK(N)                                                                                         \
+    quantize_rowwise_block_kernel<N, CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, rows, second)
     if (chunks <= 64) SB_WAVE(1);
     else if (chunks <= 128) SB_WAVE(2);
     else if (chunks <= 192) SB_WAVE(3);
@@ -470,7 +552,7 @@ hipError_t launch_quantize_rowwise_t(const void *x, int64_t rows, int64_t cols, 
     else if (chunks <= 1024) SB_BLOCK(4);
     else if (chunks <= 1536) SB_BLOCK(6);
     else if (chunks <= 2048) SB_BLOCK(8);
-    else quantize_rowwise_wide_kernel<CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job);
+    else quantize_rowwise_wide_kernel<CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, rows, second);
 #undef SB_WAVE
 #undef SB_BLOCK
     return hipGetLastError();
@@ -480,6 +562,14 @@ hipError_t launch_quantize_rowwise(const void *x, int64_t rows, int64_t cols, in
                                    hipStream_t stream) {
     if (rows == 0) return hipSuccess;
     return launch_quantize_rowwise_t<CODE_INT8>(x, rows, cols, q, state, stream);
+}
+
+// Two matrices [rows, cols] and [rows2, cols] in one launch (rows + rows2 > 0; either may be 0).
+hipError_t launch_quantize_rowwise_pair(const void *x, int64_t rows, int8_t *q, float *state, const void *x2,
+                                        int64_t rows2, int8_t *q2, float *state2, int64_t cols, hipStream_t stream) {
+    return launch_quantize_rowwise_t<CODE_INT8>(
+        x, rows, cols, q, state, stream, TensorAbsmaxJob{nullptr, 0, nullptr, 0, 0},
+        SecondRows{static_cast<const v4u *>(x2), reinterpret_cast<v2u *>(q2), state2, rows2});
 }
 
 hipError_t launch_quantize_rowwise_f8(const void *x, int64_t rows, int64_t cols, int fmt, uint8_t *codes, float *state,

@@ -32,6 +32,9 @@ __device__ __forceinline__ float bf16_bits_to_float(unsigned int bits16) { retur
 // Launchers (each validates nothing: the C-ABI layer has already checked shapes and pointers).
 hipError_t launch_quantize_rowwise(const void *x, int64_t rows, int64_t cols, int8_t *q, float *state,
                                    hipStream_t stream);
+// Two matrices with the same number of columns, row-wise, in one launch: results of the separate calls, bit for bit.
+hipError_t launch_quantize_rowwise_pair(const void *x, int64_t rows, int8_t *q, float *state, const void *x2,
+                                        int64_t rows2, int8_t *q2, float *state2, int64_t cols, hipStream_t stream);
 hipError_t launch_dequantize_rowwise(const int8_t *q, const float *state, int64_t rows, int64_t cols, void *x_hat,
                                      hipStream_t stream);
 size_t quantize_colwise_workspace_bytes(int64_t rows, int64_t cols);

@@ -275,13 +275,11 @@ int switchback_forward_q(const void *x_bf16, const void *w_bf16, int64_t b, int6
     if (!ok_ptr(w_bf16) || !ok_ptr(wq) || !ok_ptr(state_w_row)) return SB_INVALID_ARG;
     if (b > 0 && (!ok_ptr(x_bf16) || !ok_ptr(y) || !ok_ptr(xq) || state_x == nullptr)) return SB_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // SwitchBackQ forward: X_int8, state_X = row-wise quantize(X); W_int8, state_W = row-wise quantize(W); int8
-    // matmul fused with the row-and-column dequantization.
-    hipError_t e = sb::launch_quantize_rowwise(w_bf16, m, n, wq, state_w_row, s);
+    // SwitchBackQ forward: X_int8, state_X = row-wise quantize(X); W_int8, state_W = row-wise quantize(W), both in one
+    // launch (W's rows follow X's); int8 matmul fused with the row-and-column dequantization.
+    hipError_t e = sb::launch_quantize_rowwise_pair(x_bf16, b, xq, state_x, w_bf16, m, wq, state_w_row, n, s);
     if (e != hipSuccess) return SB_HIP_ERROR;
     if (b == 0) return SB_OK;
-    e = sb::launch_quantize_rowwise(x_bf16, b, n, xq, state_x, s);
-    if (e != hipSuccess) return SB_HIP_ERROR;
     return from_hip(sb::launch_gemm_i8_dequant(xq, state_x, wq, nullptr, state_w_row, b, m, n, y, y_dtype, s));
 }
 
