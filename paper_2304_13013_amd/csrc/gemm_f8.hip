@@ -1,6 +1,6 @@
 // Host-side dispatch of the 8-bit float GEMM with dequantizing epilogue (the float8 variant of SwitchBack; kernel:
 // gemm_i8_kernel.h with the float8 arithmetic selected).
-#include "gemm_i8_kernel.h"
+#include "gemm_i8_direct_kernel.h"
 
 #include <atomic>
 
@@ -32,6 +32,10 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
                                   const float *state_tensor, int64_t M, int64_t N, int64_t K, void *out,
                                   sb_dtype out_dtype, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
+    GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
+                    nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
+    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
+    if (split != DIRECT_NONE) return launch_gemm_f8_direct(split, args, fmt_a, fmt_b, out_dtype, stream);
     typedef void (*Kernel)(GemmI8Args);
     static const Kernel kernels[8] = {gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32,
                                       gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32, gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32};
@@ -43,8 +47,6 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
         if (e != hipSuccess) return e;
         attr_set[which].store(true, std::memory_order_release);
     }
-    GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
-                    nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8};
     int grid = 0;
     gemm_i8_prepare<F8Cfg>(args, num_compute_units(), &grid);
     kernels[which]<<<grid, F8Cfg::THREADS, F8Cfg::LDS_BYTES, stream>>>(args);

@@ -1,5 +1,5 @@
 // Host-side dispatch of the int8 GEMM with dequantizing epilogue (kernel: gemm_i8_kernel.h).
-#include "gemm_i8_kernel.h"
+#include "gemm_i8_direct_kernel.h"
 
 #include <atomic>
 
@@ -81,13 +81,13 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     return hipGetLastError();
 }
 
+}  // namespace
+
 // Few large tiles: fewer than half as many 256x256 tiles as compute units.
 bool few_tiles(int64_t M, int64_t N) {
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
     return tiles * 2 <= num_compute_units();
 }
-
-}  // namespace
 
 // Compute units of the current device (queried once per process; the library serves one GPU).  Host threads may race
 // to the first query: both store the same value.
@@ -112,6 +112,8 @@ hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row,
     GemmI8Args args{aq, bq, state_row, state_tensor, nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, bias, gamma};
     static std::atomic<bool> attr_set[6];  // zero-initialized
     const bool bf = out_dtype == SB_BF16;
+    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
+    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, true, out_dtype, stream);
     if (K % 128 != 0)
         return bf ? launch<K64>(gemm_i8p_k64_bf16, &attr_set[0], args, stream)
                   : launch<K64>(gemm_i8p_k64_f32, &attr_set[1], args, stream);
@@ -126,7 +128,9 @@ hipError_t launch_gemm_i8_dequant(const int8_t *aq, const float *state_row, cons
                                   const float *state_tensor, const float *state_col, int64_t M, int64_t N,
                                   int64_t K, void *out, sb_dtype out_dtype, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
-    GemmI8Args args{aq, bq, state_row, state_tensor, state_col, out, (int)M, (int)N, (int)K, 0, 0, 8};
+    GemmI8Args args{aq, bq, state_row, state_tensor, state_col, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
+    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
+    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, false, out_dtype, stream);
     if (state_col != nullptr && out_dtype != SB_I32_RAW) {
         static std::atomic<bool> q_attr_set[6];  // zero-initialized
         // The same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large tiles, 27 us on 300 small ones).

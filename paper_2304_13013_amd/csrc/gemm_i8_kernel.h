@@ -132,6 +132,9 @@ __device__ __forceinline__ bool gemm_tile_of(int wg, int round, int nwg, int til
     return true;
 }
 
+// Fewer 256x256 tiles than half of the compute units (gemm_i8.hip).
+bool few_tiles(int64_t M, int64_t N);
+
 // Workgroup barrier WITHOUT the memory fence of __syncthreads(): the fence would drain every outstanding
 // global->LDS request (vmcnt(0)) and serialize the pipeline.  Explicit vmcnt / lgkmcnt waits order the LDS traffic.
 __device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }

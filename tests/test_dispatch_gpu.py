@@ -57,3 +57,49 @@ def test_colwise_quantizer_row_runs(oracle, rows, cols):
     qo, so = oracle.quantize_colwise_transpose(w)
     np.testing.assert_array_equal(host(s).view(np.uint32), so.view(np.uint32))
     np.testing.assert_array_equal(host(q_t), qo)
+
+
+# The small-product kernel, all three of its splits: one row, rows and columns past a block's edge, a contraction shorter
+# than one stage, one that leaves waves idle, an odd number of half stages (K = 64 mod 128), and every output and scale.
+SMALL = [(1, 64, 64), (33, 64, 192), (197, 192, 4096), (64, 1024, 576), (300, 1024, 8192), (197, 3072, 768),
+         (512, 2048, 320), (2000, 768, 768), (1990, 768, 3008)]
+
+
+@pytest.mark.parametrize("M,N,K", SMALL)
+def test_small_int8_products(oracle, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    b = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
+    sr = (np.abs(rng.standard_normal(M)) + 0.01).astype(np.float32)
+    sc = (np.abs(rng.standard_normal(N)) + 0.01).astype(np.float32)
+    bias, gamma = rng.standard_normal((2, N)).astype(np.float32)
+    dev = [torch.from_numpy(v).to(DEV) for v in (a, sr, b, sc)]
+    st = torch.full((1,), 0.37, device=DEV)
+    acc = oracle.matmul_int8(a, b)
+    np.testing.assert_array_equal(host(sb.matmul_int8_dequant(dev[0], None, dev[2], None, out_dtype=torch.int32)), acc)
+    ref = oracle.dequantize(acc, sr, np.float32(0.37))
+    y32 = host(sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st, out_dtype=torch.float32))
+    np.testing.assert_array_equal(y32, ref)
+    ybf = sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st).view(torch.int16)
+    np.testing.assert_array_equal(host(ybf).view(np.uint16), oracle.round_to_bf16(ref))
+    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, torch.from_numpy(bias).to(DEV),
+                                                  torch.from_numpy(gamma).to(DEV), out_dtype=torch.float32)
+    np.testing.assert_array_equal(host(post), oracle.bias_layerscale(ref, bias, gamma))
+    rc = host(sb.matmul_int8_dequant_rc(*dev, out_dtype=torch.float32))
+    np.testing.assert_array_equal(rc, oracle.dequantize_rowcol(acc, sr, sc))
+
+
+# Codes 0, +-1/4, +-1/2, +-1: no product is truncated and binary32 holds every partial sum, so the float8 sum is exact.
+@pytest.mark.parametrize("fa,fb", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 64, 128), (197, 192, 4096), (300, 1024, 640), (1990, 768, 768)])
+def test_small_float8_products(M, N, K, fa, fb):
+    rng = np.random.default_rng(M + N + K)
+    vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)
+    a, b = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
+    types = (torch.float8_e4m3fn, torch.float8_e5m2)
+    sr = torch.rand(M, device=DEV) + 0.5
+    st = torch.full((1,), 0.37, device=DEV)
+    got = sb.matmul_f8_dequant(a.to(types[fa]).view(torch.uint8), fa, sr, b.to(types[fb]).view(torch.uint8), fb, st,
+                               out_dtype=torch.float32)
+    want = (a.double() @ b.double().t()).float() * (sr * st)[:, None]
+    assert torch.equal(got, want)
