@@ -104,21 +104,26 @@ def _check(status):
                               % (load_library().switchback_status_string(status).decode(), status))
 
 
+# A small layer's pass is bound by the host (host time of forward, backward_input and backward_weight at 64 tokens,
+# 64 -> 64: 16.8 + 13.1 + 10.4 us with Stream and c_void_p objects, 13.1 + 9.9 + 7.4 us without), so the
+# pointers go to ctypes as plain integers and the current stream is asked for its handle without a Stream object.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t, dtype, ndim=None):
+    """Device address of a contiguous GPU tensor of this type (and rank)."""
     if not t.is_cuda:
         raise SwitchBackError("tensors must live on the GPU")
     if t.dtype != dtype or not t.is_contiguous() or (ndim is not None and t.dim() != ndim):
         raise SwitchBackError("expected a contiguous %d-d %s tensor, got %s %s"
                               % (ndim or t.dim(), dtype, tuple(t.shape), t.dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    return t.data_ptr() if t is not None else None
 
 
 def _out(t, shape, dtype, device, name):
