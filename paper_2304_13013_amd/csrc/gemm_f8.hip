@@ -34,7 +34,7 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     if (M == 0 || N == 0) return hipSuccess;
     GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
                     nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
-    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
+    int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
     if (split != DIRECT_NONE) return launch_gemm_f8_direct(split, args, fmt_a, fmt_b, out_dtype, stream);
     typedef void (*Kernel)(GemmI8Args);
     static const Kernel kernels[8] = {gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32,
@@ -48,9 +48,15 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
         attr_set[which].store(true, std::memory_order_release);
     }
     int grid = 0;
-    gemm_i8_prepare<F8Cfg>(args, num_compute_units(), &grid);
-    kernels[which]<<<grid, F8Cfg::THREADS, F8Cfg::LDS_BYTES, stream>>>(args);
-    return hipGetLastError();
+    // The last rows as a small product where that saves a round of the grid, as for the int8 product.
+    const int64_t rows = rows_for_tiles(M, N, K, &split);
+    GemmI8Args tiled = args;
+    tiled.M = (int)rows;
+    gemm_i8_prepare<F8Cfg>(tiled, num_compute_units(), &grid);
+    kernels[which]<<<grid, F8Cfg::THREADS, F8Cfg::LDS_BYTES, stream>>>(tiled);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || rows == M) return e;
+    return launch_gemm_f8_direct(split, rows_from(args, rows, out_dtype == SB_BF16 ? 2 : 4), fmt_a, fmt_b, out_dtype, stream);
 }
 
 }  // namespace sb

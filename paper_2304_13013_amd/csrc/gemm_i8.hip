@@ -6,11 +6,12 @@
 namespace sb {
 namespace {
 
-// 128-byte k-steps (whole cache lines per row; two LDS stages plus the epilogue patch = 160 KiB) when K allows
-// it: four loader waves with a 3-block wave tile, their SIMD partners take 5 blocks (see the kernel header).  Else
-// 64-byte k-steps with four stages, every wave loading.
+// 128-byte k-steps (whole cache lines per row; two LDS stages plus the epilogue patch = 160 KiB): four loader waves with
+// a 3-block wave tile, their SIMD partners take 5 blocks (see the kernel header).  An odd multiple of 64 ends in a stage
+// whose second half reads as zero; an instance with 64-byte k-steps, four stages and every wave loading, which needs no
+// such stage, measures 65.3 against 52.0 us (11237 x 2880, K = 1088) and 54.7 against 43.8 (11237 x 1088, K = 2880), and
+// no better at K = 64 (9.4 against 9.6 us, 8000 x 2048).
 typedef GemmI8Cfg<128, 2, 4, 3, 1> K128;
-typedef GemmI8Cfg<64, 4, 8, 4, 1> K64;
 // Row-and-column scales (SwitchBackQ): the 32 column states a lane keeps need the registers of the even split.
 typedef GemmI8Cfg<128, 2, 4, 4, 1> K128Q;
 // Products with few output tiles (ViT-B/16's 768-wide outputs make 75 tiles of 256x256 for 256 compute units):
@@ -24,9 +25,6 @@ typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> K128S;
 SB_GEMM_I8_ENTRY(gemm_i8_k128_bf16, K128, OUT_BF16)
 SB_GEMM_I8_ENTRY(gemm_i8_k128_f32, K128, OUT_F32)
 SB_GEMM_I8_ENTRY(gemm_i8_k128_i32, K128, OUT_I32)
-SB_GEMM_I8_ENTRY(gemm_i8_k64_bf16, K64, OUT_BF16)
-SB_GEMM_I8_ENTRY(gemm_i8_k64_f32, K64, OUT_F32)
-SB_GEMM_I8_ENTRY(gemm_i8_k64_i32, K64, OUT_I32)
 // Two waves per SIMD for the four-wave configuration (two workgroups per compute unit): at most 256 registers per lane.
 #define SB_GEMM_I8_ENTRY_S(name, CFG, OUT)                                                                     \
     __global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name(GemmI8Args p) { \
@@ -40,8 +38,6 @@ SB_GEMM_I8_ENTRY_S(gemm_i8_k128s_i32, K128S, OUT_I32)
     __global__ __launch_bounds__(CFG::THREADS) void name(GemmI8Args p) { gemm_i8_dequant_body<CFG, OUT, true>(p); }
 SB_GEMM_I8_ENTRY_Q(gemm_i8q_k128_bf16, K128Q, OUT_BF16)
 SB_GEMM_I8_ENTRY_Q(gemm_i8q_k128_f32, K128Q, OUT_F32)
-SB_GEMM_I8_ENTRY_Q(gemm_i8q_k64_bf16, K64, OUT_BF16)
-SB_GEMM_I8_ENTRY_Q(gemm_i8q_k64_f32, K64, OUT_F32)
 #undef SB_GEMM_I8_ENTRY_Q
 #undef SB_GEMM_I8_ENTRY
 // ... and on the small tile, for products with few tiles.
@@ -59,8 +55,6 @@ SB_GEMM_I8_ENTRY_QS(gemm_i8q_k128s_f32, K128S, OUT_F32)
     }
 SB_GEMM_I8_ENTRY_P(gemm_i8p_k128_bf16, K128Q, OUT_BF16)
 SB_GEMM_I8_ENTRY_P(gemm_i8p_k128_f32, K128Q, OUT_F32)
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k64_bf16, K64, OUT_BF16)
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k64_f32, K64, OUT_F32)
 SB_GEMM_I8_ENTRY_P(gemm_i8p_k128s_bf16, K128S, OUT_BF16)
 SB_GEMM_I8_ENTRY_P(gemm_i8p_k128s_f32, K128S, OUT_F32)
 #undef SB_GEMM_I8_ENTRY_P
@@ -105,64 +99,95 @@ int num_compute_units() {
     return n;
 }
 
+// Rows that go to the tiles.  When the last, partial row of tiles starts another round of the persistent grid, that
+// round keeps a few workgroups busy with tiles that are mostly past the end: the small-product kernel does those rows
+// in less time than the round takes, if it is estimated below 6 us per 1024 of K.  Measured, one launch against two:
+// 16448 x 1024, K = 4096 (260 tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7, K = 1024 28.4 / 23.7;
+// 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0; 8200 x 2048, K = 512 18.8 / 17.1.
+// Where the number of rounds stays (21000 x 800, K = 1536: 41.0 / 45.8) nothing is split off.
+int64_t rows_for_tiles(int64_t M, int64_t N, int64_t K, int *split) {
+    const int64_t full = M / 256 * 256, tiles_n = (N + 255) / 256, ncu = num_compute_units();
+    if (full == M || few_tiles(M, N)) return M;
+    const int64_t tiles = full / 256 * tiles_n;
+    if ((tiles + ncu - 1) / ncu == (tiles + tiles_n + ncu - 1) / ncu) return M;
+    return direct_product_time(M - full, N, K, split) < 6.0 / 1024.0 * (double)K ? full : M;
+}
+
+GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes) {
+    GemmI8Args r = a;
+    r.a += (size_t)first * (size_t)a.K;
+    if (r.state_row != nullptr) r.state_row += first;
+    r.out = static_cast<char *>(a.out) + (size_t)first * (size_t)a.N * out_bytes;
+    r.M = a.M - (int)first;
+    return r;
+}
+
+// The tiled kernel's instances.
+static hipError_t launch_tiled_post(const GemmI8Args &args, bool bf, hipStream_t stream) {
+    static std::atomic<bool> attr_set[4];  // zero-initialized
+    if (few_tiles(args.M, args.N))
+        return bf ? launch<K128S>(gemm_i8p_k128s_bf16, &attr_set[0], args, stream)
+                  : launch<K128S>(gemm_i8p_k128s_f32, &attr_set[1], args, stream);
+    return bf ? launch<K128Q>(gemm_i8p_k128_bf16, &attr_set[2], args, stream)
+              : launch<K128Q>(gemm_i8p_k128_f32, &attr_set[3], args, stream);
+}
+
+static hipError_t launch_tiled_rowcol(const GemmI8Args &args, bool bf, hipStream_t stream) {
+    static std::atomic<bool> attr_set[4];  // zero-initialized
+    // The same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large tiles, 27 us on 300
+    // small ones).
+    if (few_tiles(args.M, args.N))
+        return bf ? launch<K128S>(gemm_i8q_k128s_bf16, &attr_set[0], args, stream)
+                  : launch<K128S>(gemm_i8q_k128s_f32, &attr_set[1], args, stream);
+    return bf ? launch<K128Q>(gemm_i8q_k128_bf16, &attr_set[2], args, stream)
+              : launch<K128Q>(gemm_i8q_k128_f32, &attr_set[3], args, stream);
+}
+
+static hipError_t launch_tiled(const GemmI8Args &args, sb_dtype out_dtype, hipStream_t stream) {
+    static std::atomic<bool> attr_set[6];  // zero-initialized
+    const bool few = few_tiles(args.M, args.N);
+    switch (out_dtype) {
+        case SB_BF16:
+            return few ? launch<K128S>(gemm_i8_k128s_bf16, &attr_set[0], args, stream)
+                       : launch<K128>(gemm_i8_k128_bf16, &attr_set[3], args, stream);
+        case SB_F32:
+            return few ? launch<K128S>(gemm_i8_k128s_f32, &attr_set[1], args, stream)
+                       : launch<K128>(gemm_i8_k128_f32, &attr_set[4], args, stream);
+        default:
+            return few ? launch<K128S>(gemm_i8_k128s_i32, &attr_set[2], args, stream)
+                       : launch<K128>(gemm_i8_k128_i32, &attr_set[5], args, stream);
+    }
+}
+
+// Small product, tiles, or tiles and a small product for the last rows.
+static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
+    int split = few_tiles(args.M, args.N) ? direct_split_for(args.M, args.N, args.K) : DIRECT_NONE;
+    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, post, out_dtype, stream);
+    const int64_t rows = rows_for_tiles(args.M, args.N, args.K, &split);
+    GemmI8Args tiled = args;
+    tiled.M = (int)rows;
+    const hipError_t e = post ? launch_tiled_post(tiled, out_dtype == SB_BF16, stream)
+                         : args.state_col != nullptr && out_dtype != SB_I32_RAW
+                             ? launch_tiled_rowcol(tiled, out_dtype == SB_BF16, stream)
+                             : launch_tiled(tiled, out_dtype, stream);
+    if (e != hipSuccess || rows == args.M) return e;
+    return launch_gemm_i8_direct(split, rows_from(args, rows, out_dtype == SB_BF16 ? 2 : 4), post, out_dtype, stream);
+}
+
 hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row, const int8_t *bq,
                                        const float *state_tensor, const float *bias, const float *gamma, int64_t M,
                                        int64_t N, int64_t K, void *out, sb_dtype out_dtype, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
-    GemmI8Args args{aq, bq, state_row, state_tensor, nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, bias, gamma};
-    static std::atomic<bool> attr_set[6];  // zero-initialized
-    const bool bf = out_dtype == SB_BF16;
-    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
-    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, true, out_dtype, stream);
-    if (K % 128 != 0)
-        return bf ? launch<K64>(gemm_i8p_k64_bf16, &attr_set[0], args, stream)
-                  : launch<K64>(gemm_i8p_k64_f32, &attr_set[1], args, stream);
-    if (few_tiles(M, N))
-        return bf ? launch<K128S>(gemm_i8p_k128s_bf16, &attr_set[2], args, stream)
-                  : launch<K128S>(gemm_i8p_k128s_f32, &attr_set[3], args, stream);
-    return bf ? launch<K128Q>(gemm_i8p_k128_bf16, &attr_set[4], args, stream)
-              : launch<K128Q>(gemm_i8p_k128_f32, &attr_set[5], args, stream);
+    return launch_product(GemmI8Args{aq, bq, state_row, state_tensor, nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, bias,
+                                     gamma}, true, out_dtype, stream);
 }
 
 hipError_t launch_gemm_i8_dequant(const int8_t *aq, const float *state_row, const int8_t *bq,
                                   const float *state_tensor, const float *state_col, int64_t M, int64_t N,
                                   int64_t K, void *out, sb_dtype out_dtype, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
-    GemmI8Args args{aq, bq, state_row, state_tensor, state_col, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
-    const int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
-    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, false, out_dtype, stream);
-    if (state_col != nullptr && out_dtype != SB_I32_RAW) {
-        static std::atomic<bool> q_attr_set[6];  // zero-initialized
-        // The same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large tiles, 27 us on 300 small ones).
-        if (K % 128 == 0 && few_tiles(M, N))
-            return out_dtype == SB_BF16 ? launch<K128S>(gemm_i8q_k128s_bf16, &q_attr_set[4], args, stream)
-                                        : launch<K128S>(gemm_i8q_k128s_f32, &q_attr_set[5], args, stream);
-        if (K % 128 == 0)
-            return out_dtype == SB_BF16 ? launch<K128Q>(gemm_i8q_k128_bf16, &q_attr_set[0], args, stream)
-                                        : launch<K128Q>(gemm_i8q_k128_f32, &q_attr_set[1], args, stream);
-        return out_dtype == SB_BF16 ? launch<K64>(gemm_i8q_k64_bf16, &q_attr_set[2], args, stream)
-                                    : launch<K64>(gemm_i8q_k64_f32, &q_attr_set[3], args, stream);
-    }
-    static std::atomic<bool> attr_set[9];  // zero-initialized
-    const bool wide = K % 128 == 0;
-    if (wide && few_tiles(M, N)) {
-        switch (out_dtype) {
-            case SB_BF16: return launch<K128S>(gemm_i8_k128s_bf16, &attr_set[6], args, stream);
-            case SB_F32: return launch<K128S>(gemm_i8_k128s_f32, &attr_set[7], args, stream);
-            default: return launch<K128S>(gemm_i8_k128s_i32, &attr_set[8], args, stream);
-        }
-    }
-    switch (out_dtype) {
-        case SB_BF16:
-            return wide ? launch<K128>(gemm_i8_k128_bf16, &attr_set[0], args, stream)
-                        : launch<K64>(gemm_i8_k64_bf16, &attr_set[3], args, stream);
-        case SB_F32:
-            return wide ? launch<K128>(gemm_i8_k128_f32, &attr_set[1], args, stream)
-                        : launch<K64>(gemm_i8_k64_f32, &attr_set[4], args, stream);
-        default:
-            return wide ? launch<K128>(gemm_i8_k128_i32, &attr_set[2], args, stream)
-                        : launch<K64>(gemm_i8_k64_i32, &attr_set[5], args, stream);
-    }
+    return launch_product(GemmI8Args{aq, bq, state_row, state_tensor, state_col, out, (int)M, (int)N, (int)K, 0, 0, 8,
+                                     nullptr, nullptr}, false, out_dtype, stream);
 }
 
 }  // namespace sb

@@ -244,6 +244,10 @@ enum { DIRECT_NONE = 0, DIRECT_32, DIRECT_64, DIRECT_64H };
 double direct_product_time(int64_t M, int64_t N, int64_t K, int *split);
 // The split that beats the 128x128-tile instance, or DIRECT_NONE.
 int direct_split_for(int64_t M, int64_t N, int64_t K);
+// Rows of a product that the 256x256 tiles take (gemm_i8.hip); the rest, if any, is a small product with that split.
+int64_t rows_for_tiles(int64_t M, int64_t N, int64_t K, int *split);
+// The product's rows from `first` on (out_bytes: size of an output element).
+GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes);
 // out_dtype SB_I32_RAW ignores the states; a.state_col != nullptr: row-and-column scales; post: a.bias / a.gamma follow.
 hipError_t launch_gemm_i8_direct(int split, const GemmI8Args &a, bool post, sb_dtype out_dtype, hipStream_t stream);
 hipError_t launch_gemm_f8_direct(int split, const GemmI8Args &a, int fmt_a, int fmt_b, sb_dtype out_dtype,

@@ -199,7 +199,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wn0 = (wave % C::WAVES_N) * C::WTN;
-    const int KT = p.K / C::BK;
+    const int KT = (p.K + C::BK - 1) / C::BK;  // K is a multiple of 64: the last stage may be half a stage
     const bool loader = wave < C::LOADERS;
 
     // Per-lane byte offset of its MFMA operand chunk inside a 32-row block of a stage, one per k-step.
@@ -217,11 +217,15 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     const bool loads_a = wave * C::RPL < C::BM;
     const int lrow = lane / C::CPR, lpos = lane % C::CPR;
     const int row0_in_tile = (wave * C::RPL) % C::BM;
-    unsigned voff[C::NVAR];
+    // voff_last: the same for the last k-tile, whose chunks past K (the next row's bytes) are sent out of the buffer's
+    // bounds and read as zero.
+    unsigned voff[C::NVAR], voff_last[C::NVAR];
 #pragma unroll
     for (int v = 0; v < C::NVAR; ++v) {
         const int r = v * C::RPS + lrow;  // row within the wave's share, for requests i with i % NVAR == v
-        voff[v] = (unsigned)(row0_in_tile + lrow) * (unsigned)p.K + ((lpos ^ ((r / C::SWZ_DIV) % C::CPR)) << 4);
+        const int chunk = lpos ^ ((r / C::SWZ_DIV) % C::CPR);
+        voff[v] = (unsigned)(row0_in_tile + lrow) * (unsigned)p.K + (chunk << 4);
+        voff_last[v] = (KT - 1) * C::BK + (chunk << 4) < p.K ? voff[v] : 0xfffffff0u;
     }
     const unsigned req_step = (unsigned)C::RPS * (unsigned)p.K;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -233,9 +237,12 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     auto issue_stage = [&](int slot, int kt) {
         unsigned char *dst = smem + slot * C::STAGE_BYTES + wave * C::RPL * C::BK;
         const unsigned soff = tile_soff + (unsigned)kt * C::BK;
+        unsigned off[C::NVAR];
+#pragma unroll
+        for (int v = 0; v < C::NVAR; ++v) off[v] = kt + 1 == KT ? voff_last[v] : voff[v];
 #pragma unroll
         for (int i = 0; i < C::LPW; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, voff[i % C::NVAR],
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, off[i % C::NVAR],
                                                      soff + (unsigned)i * req_step, 0, 0);
     };
 

@@ -103,3 +103,45 @@ def test_small_float8_products(M, N, K, fa, fb):
                                out_dtype=torch.float32)
     want = (a.double() @ b.double().t()).float() * (sr * st)[:, None]
     assert torch.equal(got, want)
+
+
+# The tiled kernel with a last stage of half zeros (K = 64 mod 128) on its large and small tile, and products whose last
+# rows leave the tiles because they would start another round of the grid: 1 row, a tile row less one, a width that is no
+# multiple of the tile; every output type and scale.
+SPLIT = [(11237, 2880, 192), (5000, 1088, 320), (16385, 1024, 1024), (16639, 1024, 1536), (16448, 960, 1216),
+         (32896, 2048, 1088)]
+
+
+@pytest.mark.parametrize("M,N,K", SPLIT)
+def test_half_stages_and_last_rows(oracle, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    b = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
+    sr = (np.abs(rng.standard_normal(M)) + 0.01).astype(np.float32)
+    sc = (np.abs(rng.standard_normal(N)) + 0.01).astype(np.float32)
+    bias, gamma = rng.standard_normal((2, N)).astype(np.float32)
+    dev = [torch.from_numpy(v).to(DEV) for v in (a, sr, b, sc)]
+    st = torch.full((1,), 0.37, device=DEV)
+    acc = host(sb.matmul_int8_dequant(dev[0], None, dev[2], None, out_dtype=torch.int32))
+    # |acc| <= 127^2 K < 2^53: the binary64 product is the whole number itself.
+    np.testing.assert_array_equal(acc, host(dev[0].double() @ dev[2].double().t()).astype(np.int32))
+    ref = oracle.dequantize(acc, sr, np.float32(0.37))
+    ybf = sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st).view(torch.int16)
+    np.testing.assert_array_equal(host(ybf).view(np.uint16), oracle.round_to_bf16(ref))
+    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, torch.from_numpy(bias).to(DEV),
+                                                  torch.from_numpy(gamma).to(DEV), out_dtype=torch.float32)
+    np.testing.assert_array_equal(host(post), oracle.bias_layerscale(ref, bias, gamma))
+    rc = host(sb.matmul_int8_dequant_rc(*dev, out_dtype=torch.float32))
+    np.testing.assert_array_equal(rc, oracle.dequantize_rowcol(acc, sr, sc))
+
+
+# Exact sums, as for the small float8 products.
+@pytest.mark.parametrize("M,N,K", [(16448, 1024, 1024), (16385, 960, 1152)])
+def test_last_rows_of_a_float8_product(M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)
+    a, b = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
+    sr, st = torch.rand(M, device=DEV) + 0.5, torch.full((1,), 0.37, device=DEV)
+    got = sb.matmul_f8_dequant(a.to(torch.float8_e5m2).view(torch.uint8), 1, sr,
+                               b.to(torch.float8_e4m3fn).view(torch.uint8), 0, st, out_dtype=torch.float32)
+    assert torch.equal(got, (a.double() @ b.double().t()).float() * (sr * st)[:, None])
