@@ -145,3 +145,34 @@ def test_last_rows_of_a_float8_product(M, N, K):
     got = sb.matmul_f8_dequant(a.to(torch.float8_e5m2).view(torch.uint8), 1, sr,
                                b.to(torch.float8_e4m3fn).view(torch.uint8), 0, st, out_dtype=torch.float32)
     assert torch.equal(got, (a.double() @ b.double().t()).float() * (sr * st)[:, None])
+
+
+# A step whose arrays exceed the last-level cache (28 or 32 million elements: the second pass runs backwards and
+# non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
+# agrees with the binary64 evaluation; ragged counts, so that the last workgroups are partial.
+@pytest.mark.parametrize("grad_dtype", [torch.bfloat16, torch.float32])
+def test_adamw_step_larger_than_the_last_level_cache(grad_dtype):
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    rand = lambda c: torch.randn(c, generator=gen, device=DEV)
+    counts = [9_000_001, 7_000_003, 5, 8_388_608 + 4099]
+    sets = [(rand(c) * 0.02, rand(c) * 3e-4, rand(c).square() * 1e-6, (rand(c) * 1e-3).to(grad_dtype)) for c in counts]
+    single = [tuple(t.clone() for t in s) for s in sets]
+    args = (1e-3, 0.9, 0.98, 1e-6, 0.2, 7)
+    rms = sb.stable_adamw_step_multi(sb.AdamwPlan(sets), *args)
+    for i, (a, s) in enumerate(zip(sets, single)):
+        assert torch.equal(rms[i:i + 1], sb.stable_adamw_step(*s, *args)), counts[i]
+        for x, y in zip(a[:3], s[:3]):
+            assert torch.equal(x, y), counts[i]
+    c = 20_000_007
+    big = (rand(c) * 0.02, rand(c) * 3e-4, rand(c).square() * 1e-6, (rand(c) * 1e-3).to(grad_dtype))
+    th, v, u, g = (t.double() for t in big)
+    alpha, b1, b2, eps, lam = (float(np.float32(x)) for x in args[:5])
+    b1, b2 = (b * (1 - b ** 6) / (1 - b ** 7) for b in (b1, b2))
+    v, u = b1 * v + (1 - b1) * g, b2 * u + (1 - b2) * g * g
+    want_rms = (g * g / u.clamp(min=eps * eps)).mean().sqrt()
+    eta = alpha / want_rms.clamp(min=1.0)
+    want = (th - eta * lam * th - eta * v / (u.sqrt() + eps), v, u)
+    rms = sb.stable_adamw_step(*big, *args)
+    assert abs(rms.item() - want_rms.item()) <= 2e-6 * want_rms.item()
+    for got, ref in zip(big[:3], want):  # a handful of binary32 roundings (2^-24 each) of the tensor's values
+        assert (got.double() - ref).norm() <= 4 * 2.0 ** -24 * ref.norm()
