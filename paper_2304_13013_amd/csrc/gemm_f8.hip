@@ -11,9 +11,17 @@ namespace {
 // 8 registers, so the 5-block wave tile of the int8 kernel's uneven split does not fit the register file.
 typedef GemmI8Cfg<128, 2, 4, 4, 1> F8Cfg;
 
-#define SB_GEMM_F8_ENTRY(name, OUT, FW, FX)                                      \
-    __global__ __launch_bounds__(F8Cfg::THREADS) void name(GemmI8Args p) {      \
-        gemm_i8_dequant_body<F8Cfg, OUT, false, MATH_F8 + 2 * FW + FX>(p);       \
+// 128x128 tiles, four waves, two workgroups per compute unit: products with few large tiles, the same line as for the
+// int8 product (6304 x 768, K = 3072: 34.0 us on 75 large tiles, 26.8 us on 300 small ones).
+typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> F8Small;
+
+#define SB_GEMM_F8_ENTRY(name, OUT, FW, FX)                                                                \
+    __global__ __launch_bounds__(F8Cfg::THREADS) void name(GemmI8Args p) {                                \
+        gemm_i8_dequant_body<F8Cfg, OUT, false, MATH_F8 + 2 * FW + FX>(p);                                 \
+    }                                                                                                      \
+    __global__ __launch_bounds__(F8Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name##_s(  \
+        GemmI8Args p) {                                                                                    \
+        gemm_i8_dequant_body<F8Small, OUT, false, MATH_F8 + 2 * FW + FX>(p);                               \
     }
 // name suffix: format of the token-side operand a, then of the weight-side operand b (4 = E4M3, 5 = E5M2)
 SB_GEMM_F8_ENTRY(gemm_f8_a4b4_bf16, OUT_BF16, 0, 0)
@@ -37,23 +45,32 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
     if (split != DIRECT_NONE) return launch_gemm_f8_direct(split, args, fmt_a, fmt_b, out_dtype, stream);
     typedef void (*Kernel)(GemmI8Args);
-    static const Kernel kernels[8] = {gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32,
-                                      gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32, gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32};
-    static std::atomic<bool> attr_set[8];  // zero-initialized; a racing second set is harmless
-    const int which = (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
+    static const Kernel kernels[16] = {
+        gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32, gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32,
+        gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32, gemm_f8_a4b4_bf16_s, gemm_f8_a4b4_f32_s, gemm_f8_a5b4_bf16_s,
+        gemm_f8_a5b4_f32_s, gemm_f8_a4b5_bf16_s, gemm_f8_a4b5_f32_s, gemm_f8_a5b5_bf16_s, gemm_f8_a5b5_f32_s};
+    static std::atomic<bool> attr_set[16];  // zero-initialized; a racing second set is harmless
+    const bool small = few_tiles(M, N);
+    const int which = (small ? 8 : 0) + (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
+    const int lds = small ? F8Small::LDS_BYTES : F8Cfg::LDS_BYTES;
     if (!attr_set[which].load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[which]),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, F8Cfg::LDS_BYTES);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set[which].store(true, std::memory_order_release);
     }
     int grid = 0;
+    if (small) {
+        gemm_i8_prepare<F8Small>(args, 2 * num_compute_units(), &grid);
+        kernels[which]<<<grid, F8Small::THREADS, lds, stream>>>(args);
+        return hipGetLastError();
+    }
     // The last rows as a small product where that saves a round of the grid, as for the int8 product.
     const int64_t rows = rows_for_tiles(M, N, K, &split);
     GemmI8Args tiled = args;
     tiled.M = (int)rows;
     gemm_i8_prepare<F8Cfg>(tiled, num_compute_units(), &grid);
-    kernels[which]<<<grid, F8Cfg::THREADS, F8Cfg::LDS_BYTES, stream>>>(tiled);
+    kernels[which]<<<grid, F8Cfg::THREADS, lds, stream>>>(tiled);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || rows == M) return e;
     return launch_gemm_f8_direct(split, rows_from(args, rows, out_dtype == SB_BF16 ? 2 : 4), fmt_a, fmt_b, out_dtype, stream);

@@ -135,9 +135,9 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
     np.testing.assert_array_equal(rc, oracle.dequantize_rowcol(acc, sr, sc))
 
 
-# Exact sums, as for the small float8 products.
-@pytest.mark.parametrize("M,N,K", [(16448, 1024, 1024), (16385, 960, 1152)])
-def test_last_rows_of_a_float8_product(M, N, K):
+# Exact sums, as for the small float8 products: last rows, and the small tile with ragged edges.
+@pytest.mark.parametrize("M,N,K", [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2112, 384)])
+def test_tiles_of_a_float8_product(M, N, K):
     rng = np.random.default_rng(M + N + K)
     vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)
     a, b = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
