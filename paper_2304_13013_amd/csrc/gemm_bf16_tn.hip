@@ -61,7 +61,8 @@ int choose_splits_big(int64_t b, int tiles, int ncu) {
 // every round of the persistent grid costs the stages of an item, at 0.64 of the unit while the round has at most one
 // workgroup per compute unit and rising linearly to the full unit at two; the partial sums are written once and read
 // once per split, plus the output pass, at 2.9 TB/s, by a launch that costs 3 us (2.7 units) besides: without that term
-// 512 tokens of a 256 -> 1024 layer were split in two (7.3 + 2.4 us and the second launch's host time; 7.7 us unsplit, the step 35.2 -> 32.4 us).
+// 512 tokens of a 256 -> 1024 layer were split in two (7.3 + 2.4 us and the second launch's host time; 7.7 us unsplit,
+// the step 35.2 -> 32.4 us).
 int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n) {
     const int64_t stages = (b + Small::BKT - 1) / Small::BKT;
     const double pass = (double)m * (double)n * 4.0 / (2.9e12 * 1.1e-6);  // one pass over m x n floats, in stage units
