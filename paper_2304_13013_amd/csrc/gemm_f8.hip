@@ -42,15 +42,17 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     if (M == 0 || N == 0) return hipSuccess;
     GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
                     nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
-    int split = few_tiles(M, N) ? direct_split_for(M, N, K) : DIRECT_NONE;
-    if (split != DIRECT_NONE) return launch_gemm_f8_direct(split, args, fmt_a, fmt_b, out_dtype, stream);
+    // Tiles, a small product, or tiles and a small product for the last rows, by the rules of the int8 product.
+    const ProductPlan plan = plan_product(M, N, K, num_compute_units());
+    const GemmI8Args rest = rows_from(args, plan.tile_rows, out_dtype == SB_BF16 ? 2 : 4);
+    if (plan.tile_rows == 0) return launch_gemm_f8_direct(plan.split, rest, fmt_a, fmt_b, out_dtype, stream);
     typedef void (*Kernel)(GemmI8Args);
     static const Kernel kernels[16] = {
         gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32, gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32,
         gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32, gemm_f8_a4b4_bf16_s, gemm_f8_a4b4_f32_s, gemm_f8_a5b4_bf16_s,
         gemm_f8_a5b4_f32_s, gemm_f8_a4b5_bf16_s, gemm_f8_a4b5_f32_s, gemm_f8_a5b5_bf16_s, gemm_f8_a5b5_f32_s};
     static std::atomic<bool> attr_set[16];  // zero-initialized; a racing second set is harmless
-    const bool small = few_tiles(M, N);
+    const bool small = few_tiles(M, N, num_compute_units());
     const int which = (small ? 8 : 0) + (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
     const int lds = small ? F8Small::LDS_BYTES : F8Cfg::LDS_BYTES;
     if (!attr_set[which].load(std::memory_order_acquire)) {
@@ -60,20 +62,17 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
         attr_set[which].store(true, std::memory_order_release);
     }
     int grid = 0;
+    args.M = (int)plan.tile_rows;
     if (small) {
         gemm_i8_prepare<F8Small>(args, 2 * num_compute_units(), &grid);
         kernels[which]<<<grid, F8Small::THREADS, lds, stream>>>(args);
-        return hipGetLastError();
+    } else {
+        gemm_i8_prepare<F8Cfg>(args, num_compute_units(), &grid);
+        kernels[which]<<<grid, F8Cfg::THREADS, lds, stream>>>(args);
     }
-    // The last rows as a small product where that saves a round of the grid, as for the int8 product.
-    const int64_t rows = rows_for_tiles(M, N, K, &split);
-    GemmI8Args tiled = args;
-    tiled.M = (int)rows;
-    gemm_i8_prepare<F8Cfg>(tiled, num_compute_units(), &grid);
-    kernels[which]<<<grid, F8Cfg::THREADS, lds, stream>>>(tiled);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || rows == M) return e;
-    return launch_gemm_f8_direct(split, rows_from(args, rows, out_dtype == SB_BF16 ? 2 : 4), fmt_a, fmt_b, out_dtype, stream);
+    if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
+    return launch_gemm_f8_direct(plan.split, rest, fmt_a, fmt_b, out_dtype, stream);
 }
 
 }  // namespace sb

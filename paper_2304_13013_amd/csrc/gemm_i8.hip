@@ -77,12 +77,6 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
 
 }  // namespace
 
-// Few large tiles: fewer than half as many 256x256 tiles as compute units.
-bool few_tiles(int64_t M, int64_t N) {
-    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    return tiles * 2 <= num_compute_units();
-}
-
 // Compute units of the current device (queried once per process; the library serves one GPU).  Host threads may race
 // to the first query: both store the same value.
 int num_compute_units() {
@@ -99,20 +93,6 @@ int num_compute_units() {
     return n;
 }
 
-// Rows that go to the tiles.  When the last, partial row of tiles starts another round of the persistent grid, that
-// round keeps a few workgroups busy with tiles that are mostly past the end: the small-product kernel does those rows
-// in less time than the round takes, if it is estimated below 6 us per 1024 of K.  Measured, one launch against two:
-// 16448 x 1024, K = 4096 (260 tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7, K = 1024 28.4 / 23.7;
-// 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0; 8200 x 2048, K = 512 18.8 / 17.1.
-// Where the number of rounds stays (21000 x 800, K = 1536: 41.0 / 45.8) nothing is split off.
-int64_t rows_for_tiles(int64_t M, int64_t N, int64_t K, int *split) {
-    const int64_t full = M / 256 * 256, tiles_n = (N + 255) / 256, ncu = num_compute_units();
-    if (full == M || few_tiles(M, N)) return M;
-    const int64_t tiles = full / 256 * tiles_n;
-    if ((tiles + ncu - 1) / ncu == (tiles + tiles_n + ncu - 1) / ncu) return M;
-    return direct_product_time(M - full, N, K, split) < 6.0 / 1024.0 * (double)K ? full : M;
-}
-
 GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes) {
     GemmI8Args r = a;
     r.a += (size_t)first * (size_t)a.K;
@@ -125,7 +105,7 @@ GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes) {
 // The tiled kernel's instances.
 static hipError_t launch_tiled_post(const GemmI8Args &args, bool bf, hipStream_t stream) {
     static std::atomic<bool> attr_set[4];  // zero-initialized
-    if (few_tiles(args.M, args.N))
+    if (few_tiles(args.M, args.N, num_compute_units()))
         return bf ? launch<K128S>(gemm_i8p_k128s_bf16, &attr_set[0], args, stream)
                   : launch<K128S>(gemm_i8p_k128s_f32, &attr_set[1], args, stream);
     return bf ? launch<K128Q>(gemm_i8p_k128_bf16, &attr_set[2], args, stream)
@@ -136,7 +116,7 @@ static hipError_t launch_tiled_rowcol(const GemmI8Args &args, bool bf, hipStream
     static std::atomic<bool> attr_set[4];  // zero-initialized
     // The same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large tiles, 27 us on 300
     // small ones).
-    if (few_tiles(args.M, args.N))
+    if (few_tiles(args.M, args.N, num_compute_units()))
         return bf ? launch<K128S>(gemm_i8q_k128s_bf16, &attr_set[0], args, stream)
                   : launch<K128S>(gemm_i8q_k128s_f32, &attr_set[1], args, stream);
     return bf ? launch<K128Q>(gemm_i8q_k128_bf16, &attr_set[2], args, stream)
@@ -145,7 +125,7 @@ static hipError_t launch_tiled_rowcol(const GemmI8Args &args, bool bf, hipStream
 
 static hipError_t launch_tiled(const GemmI8Args &args, sb_dtype out_dtype, hipStream_t stream) {
     static std::atomic<bool> attr_set[6];  // zero-initialized
-    const bool few = few_tiles(args.M, args.N);
+    const bool few = few_tiles(args.M, args.N, num_compute_units());
     switch (out_dtype) {
         case SB_BF16:
             return few ? launch<K128S>(gemm_i8_k128s_bf16, &attr_set[0], args, stream)
@@ -159,19 +139,20 @@ static hipError_t launch_tiled(const GemmI8Args &args, sb_dtype out_dtype, hipSt
     }
 }
 
-// Small product, tiles, or tiles and a small product for the last rows.
+// Tiles, a small product, or tiles and a small product for the last rows.
 static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
-    int split = few_tiles(args.M, args.N) ? direct_split_for(args.M, args.N, args.K) : DIRECT_NONE;
-    if (split != DIRECT_NONE) return launch_gemm_i8_direct(split, args, post, out_dtype, stream);
-    const int64_t rows = rows_for_tiles(args.M, args.N, args.K, &split);
-    GemmI8Args tiled = args;
-    tiled.M = (int)rows;
-    const hipError_t e = post ? launch_tiled_post(tiled, out_dtype == SB_BF16, stream)
-                         : args.state_col != nullptr && out_dtype != SB_I32_RAW
-                             ? launch_tiled_rowcol(tiled, out_dtype == SB_BF16, stream)
-                             : launch_tiled(tiled, out_dtype, stream);
-    if (e != hipSuccess || rows == args.M) return e;
-    return launch_gemm_i8_direct(split, rows_from(args, rows, out_dtype == SB_BF16 ? 2 : 4), post, out_dtype, stream);
+    const ProductPlan plan = plan_product(args.M, args.N, args.K, num_compute_units());
+    if (plan.tile_rows > 0) {
+        GemmI8Args tiled = args;
+        tiled.M = (int)plan.tile_rows;
+        const hipError_t e = post ? launch_tiled_post(tiled, out_dtype == SB_BF16, stream)
+                             : args.state_col != nullptr && out_dtype != SB_I32_RAW
+                                 ? launch_tiled_rowcol(tiled, out_dtype == SB_BF16, stream)
+                                 : launch_tiled(tiled, out_dtype, stream);
+        if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
+    }
+    return launch_gemm_i8_direct(plan.split, rows_from(args, plan.tile_rows, out_dtype == SB_BF16 ? 2 : 4), post, out_dtype,
+                                 stream);
 }
 
 hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row, const int8_t *bq,

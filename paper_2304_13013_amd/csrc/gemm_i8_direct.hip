@@ -61,36 +61,7 @@ SB_DIRECT(gemm_f8d_a5b5_f32, OUT_F32, false, MATH_F8 + 3, false)
 #undef SB_DIRECT
 #undef SB_DIRECT_ENTRY
 
-double rounds(int64_t blocks, int slots) { return (double)((blocks + slots - 1) / slots); }
-
 }  // namespace
-
-// Times in microseconds, fitted to a sweep of 30 products (64..6304 rows, 128..8192 columns, K = 128..8192) on an
-// MI355X; within 15 % on most of them.  k is in stages of 128 bytes.
-double direct_product_time(int64_t M, int64_t N, int64_t K, int *split) {
-    const int ncu = num_compute_units();
-    const double k = (double)((K + 127) / 128);
-    const int64_t blocks32 = ((M + 31) / 32) * (N / 32), blocks64 = ((M + 63) / 64) * (N / 64);
-    const double t32 = 2.0 + rounds(blocks32, ncu) * (0.35 + 0.091 * k);
-    const double t64 = 2.8 + rounds(blocks64, ncu) * (0.3 + 0.2 * k);
-    const double fill = (double)blocks64 / ncu;  // two small workgroups share a compute unit's throughput
-    const double t64h = 2.6 + (0.15 + 0.27 * k) * (fill > 1.0 ? fill : 1.0);
-    *split = t32 <= t64 && t32 <= t64h ? DIRECT_32 : t64 <= t64h ? DIRECT_64 : DIRECT_64H;
-    return *split == DIRECT_32 ? t32 : *split == DIRECT_64 ? t64 : t64h;
-}
-
-// Against the 128x128-tile instance, whose workgroups take 0.61 us per k-tile while they are alone on their compute
-// unit (a chain of LDS stages) and up to a third more when two share it.  Measured, tiles against blocks: 64 x 1024,
-// K = 4096: 22.7 / 4.4 us; 512 x 256, K = 1024: 8.3 / 2.8; 197 x 3072, K = 768: 7.3 / 4.3; 2000 x 768, K = 3072: 18.3 /
-// 11.9; and on the other side of the line 2000 x 3072, K = 768: 9.5 / 15.0; 1000 x 4096, K = 1024: 9.4 / 12.3.
-int direct_split_for(int64_t M, int64_t N, int64_t K) {
-    const int ncu = num_compute_units();
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const double over = tiles > ncu ? (double)(tiles - ncu) / ncu : 0.0;
-    const double tiled = 2.9 + 0.61 * (double)((K + 127) / 128) * (1.0 + 0.35 * over);
-    int split;
-    return direct_product_time(M, N, K, &split) < tiled ? split : DIRECT_NONE;
-}
 
 hipError_t launch_gemm_i8_direct(int split, const GemmI8Args &a, bool post, sb_dtype out_dtype, hipStream_t stream) {
     const bool bf = out_dtype == SB_BF16;

@@ -256,15 +256,8 @@ __device__ __forceinline__ void gemm_i8_direct_body(const GemmI8Args &p) {
     }
 }
 
-// Dispatch (gemm_i8_direct.hip).  split: which of the kernel's splits of the work; the launchers take 0 < M, and
+// Launchers (gemm_i8_direct.hip).  split: which of the kernel's splits of the work (dispatch.h); they take 0 < M, and
 // operand sizes the tiled kernel accepts too.
-enum { DIRECT_NONE = 0, DIRECT_32, DIRECT_64, DIRECT_64H };
-// Estimated time (us) of the best split for a product, and that split.
-double direct_product_time(int64_t M, int64_t N, int64_t K, int *split);
-// The split that beats the 128x128-tile instance, or DIRECT_NONE.
-int direct_split_for(int64_t M, int64_t N, int64_t K);
-// Rows of a product that the 256x256 tiles take (gemm_i8.hip); the rest, if any, is a small product with that split.
-int64_t rows_for_tiles(int64_t M, int64_t N, int64_t K, int *split);
 // The product's rows from `first` on (out_bytes: size of an output element).
 GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes);
 // out_dtype SB_I32_RAW ignores the states; a.state_col != nullptr: row-and-column scales; post: a.bias / a.gamma follow.

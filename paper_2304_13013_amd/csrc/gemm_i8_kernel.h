@@ -42,6 +42,7 @@
 //     operand fragment being the two 16-byte LDS reads that two int8 k-steps would issue.
 //   * The cycle figures quoted above come from s_memtime stamps compiled into a working copy of this kernel.
 #pragma once
+#include "dispatch.h"
 #include "sb_common.h"
 #include <type_traits>
 
@@ -131,9 +132,6 @@ __device__ __forceinline__ bool gemm_tile_of(int wg, int round, int nwg, int til
     *tn = r / group_rows;
     return true;
 }
-
-// Fewer 256x256 tiles than half of the compute units (gemm_i8.hip).
-bool few_tiles(int64_t M, int64_t N);
 
 // Workgroup barrier WITHOUT the memory fence of __syncthreads(): the fence would drain every outstanding
 // global->LDS request (vmcnt(0)) and serialize the pipeline.  Explicit vmcnt / lgkmcnt waits order the LDS traffic.
@@ -683,29 +681,13 @@ __device__ __forceinline__ void gemm_i8_dequant_body(const GemmI8Args &p) {
         gemm_i8_dequant_role<C, OUT, 2 * C::MT_EVEN - C::MT_LOADER, COLSCALE, MATH, POST>(p, wave, C::MT_LOADER * 32);
 }
 
-// Launch geometry shared by the entry points: a persistent grid, a multiple of the XCD count, at most one workgroup
-// per compute unit.  When the tiles make only a few rounds of the full grid and do not fill the last one, the grid is
-// shrunk so that every workgroup gets the same number of tiles (645 tiles: 216 workgroups x 3 instead of 256 x 2.5):
-// the number of rounds is the same, and the kernel being power-bound, fewer active compute units run at a higher
-// clock, which measures 4-10 % faster than a last round that leaves half the GPU idle.  With many rounds the tail is
-// a small share and the full grid measures better.
+// Launch geometry shared by the entry points.
 template <class C>
-inline void gemm_i8_prepare(GemmI8Args &a, int workgroups, int *grid, bool balance = true) {
+inline void gemm_i8_prepare(GemmI8Args &a, int workgroups, int *grid) {
     a.tiles_m = (a.M + C::BM - 1) / C::BM;
     a.tiles_n = (a.N + C::BN - 1) / C::BN;
     if (a.group_m <= 0) a.group_m = 8;
-    int full = workgroups & ~7;
-    if (full < 8) full = 8;
-    int g = full;
-    if (balance) {
-        const long long tiles = (long long)a.tiles_m * a.tiles_n;
-        const long long rounds = (tiles + full - 1) / full;
-        const long long per_round = (tiles + rounds - 1) / rounds;
-        if (rounds <= 4) g = (int)((per_round + 7) & ~7LL);
-        if (g > full) g = full;
-        if (g < 8) g = 8;
-    }
-    *grid = g;
+    *grid = persistent_grid((int64_t)a.tiles_m * a.tiles_n, workgroups);
 }
 
 }  // namespace sb

@@ -147,6 +147,35 @@ def test_tiles_of_a_float8_product(M, N, K):
     assert torch.equal(got, (a.double() @ b.double().t()).float() * (sr * st)[:, None])
 
 
+# A few tokens into a very wide output: 129 tiles in the only, partial row of tiles, so that nothing is left for the tiles
+# if the "last rows" leave them.  Every form of the product.
+@pytest.mark.parametrize("M", [1, 32, 64])
+def test_few_rows_of_a_very_wide_output(oracle, M, N=32832, K=2048):
+    rng = np.random.default_rng(M)
+    a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    b = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
+    sr = (np.abs(rng.standard_normal(M)) + 0.01).astype(np.float32)
+    sc = (np.abs(rng.standard_normal(N)) + 0.01).astype(np.float32)
+    bias, gamma = rng.standard_normal((2, N)).astype(np.float32)
+    dev = [torch.from_numpy(v).to(DEV) for v in (a, sr, b, sc)]
+    st = torch.full((1,), 0.37, device=DEV)
+    acc = host(sb.matmul_int8_dequant(dev[0], None, dev[2], None, out_dtype=torch.int32))
+    np.testing.assert_array_equal(acc, host(dev[0].double() @ dev[2].double().t()).astype(np.int32))
+    ref = oracle.dequantize(acc, sr, np.float32(0.37))
+    ybf = sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st).view(torch.int16)
+    np.testing.assert_array_equal(host(ybf).view(np.uint16), oracle.round_to_bf16(ref))
+    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, torch.from_numpy(bias).to(DEV),
+                                                  torch.from_numpy(gamma).to(DEV), out_dtype=torch.float32)
+    np.testing.assert_array_equal(host(post), oracle.bias_layerscale(ref, bias, gamma))
+    rc = host(sb.matmul_int8_dequant_rc(*dev, out_dtype=torch.float32))
+    np.testing.assert_array_equal(rc, oracle.dequantize_rowcol(acc, sr, sc))
+    vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)  # exact float8 sums, as above
+    a8, b8 = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
+    got = sb.matmul_f8_dequant(a8.to(torch.float8_e4m3fn).view(torch.uint8), 0, dev[1],
+                               b8.to(torch.float8_e4m3fn).view(torch.uint8), 0, st, out_dtype=torch.float32)
+    assert torch.equal(got, (a8.double() @ b8.double().t()).float() * (dev[1] * st)[:, None])
+
+
 # A step whose arrays exceed the last-level cache (28 or 32 million elements: the second pass runs backwards and
 # non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
 # agrees with the binary64 evaluation; ragged counts, so that the last workgroups are partial.
