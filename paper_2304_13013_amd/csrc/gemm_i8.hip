@@ -20,45 +20,6 @@ typedef GemmI8Cfg<128, 2, 4, 4, 1> K128Q;
 // at 300).
 typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> K128S;
 
-#define SB_GEMM_I8_ENTRY(name, CFG, OUT) \
-    __global__ __launch_bounds__(CFG::THREADS) void name(GemmI8Args p) { gemm_i8_dequant_body<CFG, OUT>(p); }
-SB_GEMM_I8_ENTRY(gemm_i8_k128_bf16, K128, OUT_BF16)
-SB_GEMM_I8_ENTRY(gemm_i8_k128_f32, K128, OUT_F32)
-SB_GEMM_I8_ENTRY(gemm_i8_k128_i32, K128, OUT_I32)
-// Two waves per SIMD for the four-wave configuration (two workgroups per compute unit): at most 256 registers per lane.
-#define SB_GEMM_I8_ENTRY_S(name, CFG, OUT)                                                                     \
-    __global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name(GemmI8Args p) { \
-        gemm_i8_dequant_body<CFG, OUT>(p);                                                                     \
-    }
-SB_GEMM_I8_ENTRY_S(gemm_i8_k128s_bf16, K128S, OUT_BF16)
-SB_GEMM_I8_ENTRY_S(gemm_i8_k128s_f32, K128S, OUT_F32)
-SB_GEMM_I8_ENTRY_S(gemm_i8_k128s_i32, K128S, OUT_I32)
-#undef SB_GEMM_I8_ENTRY_S
-#define SB_GEMM_I8_ENTRY_Q(name, CFG, OUT) \
-    __global__ __launch_bounds__(CFG::THREADS) void name(GemmI8Args p) { gemm_i8_dequant_body<CFG, OUT, true>(p); }
-SB_GEMM_I8_ENTRY_Q(gemm_i8q_k128_bf16, K128Q, OUT_BF16)
-SB_GEMM_I8_ENTRY_Q(gemm_i8q_k128_f32, K128Q, OUT_F32)
-#undef SB_GEMM_I8_ENTRY_Q
-#undef SB_GEMM_I8_ENTRY
-// ... and on the small tile, for products with few tiles.
-#define SB_GEMM_I8_ENTRY_QS(name, CFG, OUT)                                                                    \
-    __global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name(GemmI8Args p) { \
-        gemm_i8_dequant_body<CFG, OUT, true>(p);                                                               \
-    }
-SB_GEMM_I8_ENTRY_QS(gemm_i8q_k128s_bf16, K128S, OUT_BF16)
-SB_GEMM_I8_ENTRY_QS(gemm_i8q_k128s_f32, K128S, OUT_F32)
-#undef SB_GEMM_I8_ENTRY_QS
-// Bias and layer-scale after the dequantization: the even wave split (the two vectors take 64 registers in the epilogue).
-#define SB_GEMM_I8_ENTRY_P(name, CFG, OUT)                                                                     \
-    __global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name(GemmI8Args p) { \
-        gemm_i8_dequant_body<CFG, OUT, false, MATH_I8, true>(p);                                               \
-    }
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k128_bf16, K128Q, OUT_BF16)
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k128_f32, K128Q, OUT_F32)
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k128s_bf16, K128S, OUT_BF16)
-SB_GEMM_I8_ENTRY_P(gemm_i8p_k128s_f32, K128S, OUT_F32)
-#undef SB_GEMM_I8_ENTRY_P
-
 template <class C>
 hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI8Args args, hipStream_t stream) {
     if (!attr_set->load(std::memory_order_acquire)) {  // setting it twice (two host threads racing) is harmless
@@ -74,6 +35,39 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     kernel<<<grid, C::THREADS, C::LDS_BYTES, stream>>>(args);
     return hipGetLastError();
 }
+
+// The two kernels of an instance (K a multiple of 128, and _h for K = 64 mod 128) and their launcher.
+#define SB_GEMM_I8(name, CFG, OUT, COLSCALE, POST, ATTR)                                                       \
+    __global__ __launch_bounds__(CFG::THREADS) ATTR void name##_k(GemmI8Args p) {                              \
+        gemm_i8_dequant_body<CFG, OUT, COLSCALE, MATH_I8, POST, false>(p);                                     \
+    }                                                                                                          \
+    __global__ __launch_bounds__(CFG::THREADS) ATTR void name##_h(GemmI8Args p) {                              \
+        gemm_i8_dequant_body<CFG, OUT, COLSCALE, MATH_I8, POST, true>(p);                                      \
+    }                                                                                                          \
+    hipError_t name(const GemmI8Args &args, hipStream_t stream) {                                              \
+        static std::atomic<bool> attr_set[2]; /* zero-initialized */                                           \
+        return args.K % 128 == 0 ? launch<CFG>(name##_k, &attr_set[0], args, stream)                           \
+                                 : launch<CFG>(name##_h, &attr_set[1], args, stream);                          \
+    }
+// Two waves per SIMD for the four-wave configuration (two workgroups per compute unit): at most 256 registers per lane.
+#define SB_TWO_WAVES __attribute__((amdgpu_waves_per_eu(2)))
+SB_GEMM_I8(gemm_i8_k128_bf16, K128, OUT_BF16, false, false, )
+SB_GEMM_I8(gemm_i8_k128_f32, K128, OUT_F32, false, false, )
+SB_GEMM_I8(gemm_i8_k128_i32, K128, OUT_I32, false, false, )
+SB_GEMM_I8(gemm_i8_k128s_bf16, K128S, OUT_BF16, false, false, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8_k128s_f32, K128S, OUT_F32, false, false, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8_k128s_i32, K128S, OUT_I32, false, false, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8q_k128_bf16, K128Q, OUT_BF16, true, false, )
+SB_GEMM_I8(gemm_i8q_k128_f32, K128Q, OUT_F32, true, false, )
+SB_GEMM_I8(gemm_i8q_k128s_bf16, K128S, OUT_BF16, true, false, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8q_k128s_f32, K128S, OUT_F32, true, false, SB_TWO_WAVES)
+// Bias and layer-scale after the dequantization: the even wave split (the two vectors take 64 registers in the epilogue).
+SB_GEMM_I8(gemm_i8p_k128_bf16, K128Q, OUT_BF16, false, true, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8p_k128_f32, K128Q, OUT_F32, false, true, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8p_k128s_bf16, K128S, OUT_BF16, false, true, SB_TWO_WAVES)
+SB_GEMM_I8(gemm_i8p_k128s_f32, K128S, OUT_F32, false, true, SB_TWO_WAVES)
+#undef SB_TWO_WAVES
+#undef SB_GEMM_I8
 
 }  // namespace
 
@@ -103,39 +97,20 @@ GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes) {
 }
 
 // The tiled kernel's instances.
-static hipError_t launch_tiled_post(const GemmI8Args &args, bool bf, hipStream_t stream) {
-    static std::atomic<bool> attr_set[4];  // zero-initialized
-    if (few_tiles(args.M, args.N, num_compute_units()))
-        return bf ? launch<K128S>(gemm_i8p_k128s_bf16, &attr_set[0], args, stream)
-                  : launch<K128S>(gemm_i8p_k128s_f32, &attr_set[1], args, stream);
-    return bf ? launch<K128Q>(gemm_i8p_k128_bf16, &attr_set[2], args, stream)
-              : launch<K128Q>(gemm_i8p_k128_f32, &attr_set[3], args, stream);
-}
-
-static hipError_t launch_tiled_rowcol(const GemmI8Args &args, bool bf, hipStream_t stream) {
-    static std::atomic<bool> attr_set[4];  // zero-initialized
-    // The same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large tiles, 27 us on 300
-    // small ones).
-    if (few_tiles(args.M, args.N, num_compute_units()))
-        return bf ? launch<K128S>(gemm_i8q_k128s_bf16, &attr_set[0], args, stream)
-                  : launch<K128S>(gemm_i8q_k128s_f32, &attr_set[1], args, stream);
-    return bf ? launch<K128Q>(gemm_i8q_k128_bf16, &attr_set[2], args, stream)
-              : launch<K128Q>(gemm_i8q_k128_f32, &attr_set[3], args, stream);
-}
-
-static hipError_t launch_tiled(const GemmI8Args &args, sb_dtype out_dtype, hipStream_t stream) {
-    static std::atomic<bool> attr_set[6];  // zero-initialized
-    const bool few = few_tiles(args.M, args.N, num_compute_units());
+static hipError_t launch_tiled(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
+    const bool few = few_tiles(args.M, args.N, num_compute_units()), bf = out_dtype == SB_BF16;
+    if (post)
+        return few ? (bf ? gemm_i8p_k128s_bf16(args, stream) : gemm_i8p_k128s_f32(args, stream))
+                   : (bf ? gemm_i8p_k128_bf16(args, stream) : gemm_i8p_k128_f32(args, stream));
+    // Row-and-column scales: the same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large
+    // tiles, 27 us on 300 small ones).
+    if (args.state_col != nullptr && out_dtype != SB_I32_RAW)
+        return few ? (bf ? gemm_i8q_k128s_bf16(args, stream) : gemm_i8q_k128s_f32(args, stream))
+                   : (bf ? gemm_i8q_k128_bf16(args, stream) : gemm_i8q_k128_f32(args, stream));
     switch (out_dtype) {
-        case SB_BF16:
-            return few ? launch<K128S>(gemm_i8_k128s_bf16, &attr_set[0], args, stream)
-                       : launch<K128>(gemm_i8_k128_bf16, &attr_set[3], args, stream);
-        case SB_F32:
-            return few ? launch<K128S>(gemm_i8_k128s_f32, &attr_set[1], args, stream)
-                       : launch<K128>(gemm_i8_k128_f32, &attr_set[4], args, stream);
-        default:
-            return few ? launch<K128S>(gemm_i8_k128s_i32, &attr_set[2], args, stream)
-                       : launch<K128>(gemm_i8_k128_i32, &attr_set[5], args, stream);
+        case SB_BF16: return few ? gemm_i8_k128s_bf16(args, stream) : gemm_i8_k128_bf16(args, stream);
+        case SB_F32: return few ? gemm_i8_k128s_f32(args, stream) : gemm_i8_k128_f32(args, stream);
+        default: return few ? gemm_i8_k128s_i32(args, stream) : gemm_i8_k128_i32(args, stream);
     }
 }
 
@@ -145,10 +120,7 @@ static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out
     if (plan.tile_rows > 0) {
         GemmI8Args tiled = args;
         tiled.M = (int)plan.tile_rows;
-        const hipError_t e = post ? launch_tiled_post(tiled, out_dtype == SB_BF16, stream)
-                             : args.state_col != nullptr && out_dtype != SB_I32_RAW
-                                 ? launch_tiled_rowcol(tiled, out_dtype == SB_BF16, stream)
-                                 : launch_tiled(tiled, out_dtype, stream);
+        const hipError_t e = launch_tiled(tiled, post, out_dtype, stream);
         if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
     }
     return launch_gemm_i8_direct(plan.split, rows_from(args, plan.tile_rows, out_dtype == SB_BF16 ? 2 : 4), post, out_dtype,

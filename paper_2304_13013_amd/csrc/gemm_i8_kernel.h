@@ -177,7 +177,11 @@ __device__ __forceinline__ void wait_stage(int later) {
 // The float8 product runs the same pipeline with one MFMA per 64 k-values: an operand fragment is then 32 bytes per
 // lane, fetched by the two 16-byte LDS reads that two consecutive int8 k-steps would issue.  Which 64 k-values a
 // lane's registers hold does not matter as long as both operands use the same assignment, which they do.
-template <class C, int OUT, int MT, bool COLSCALE, int MATH = MATH_I8, bool POST = false>
+//
+// HALF: K = 64 mod 128, so that the last stage is half a stage, zero beyond K (int8 only).  Instances of their own: the
+// choice between two sets of request offsets, made in every stage at run time, takes 0.7 % of the 256x256-tile products
+// and 2-3 % of the 128x128-tile ones, and a branch around the last stage's requests hardly less.
+template <class C, int OUT, int MT, bool COLSCALE, int MATH, bool POST, bool HALF>
 __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const int wave, const int wm0) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
@@ -190,6 +194,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     typedef typename std::conditional<F8, v8i, v4i>::type FragT;
     static_assert(!F8 || (OUT != OUT_I32 && !COLSCALE), "the float8 product has dequantized outputs and a tensor-wise weight state");
     static_assert(!POST || (OUT != OUT_I32 && !COLSCALE && !F8), "bias / layer-scale follow the tensor-wise int8 dequantization");
+    static_assert(!HALF || (!F8 && C::BK == 128), "half a stage is 64 int8 codes");
     static_assert(KKG >= 2 && KKG % 2 == 0, "the register double-buffering alternates per k-step group within a stage");
     constexpr int NSCALE = OUT != OUT_I32 ? MT + (COLSCALE ? C::NT * 4 : 0) : 0;  // per-lane scale loads per tile
     constexpr int NFRAG = MT + C::NT;
@@ -197,7 +202,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wn0 = (wave % C::WAVES_N) * C::WTN;
-    const int KT = (p.K + C::BK - 1) / C::BK;  // K is a multiple of 64: the last stage may be half a stage
+    const int KT = HALF ? (p.K + C::BK - 1) / C::BK : p.K / C::BK;
     const bool loader = wave < C::LOADERS;
 
     // Per-lane byte offset of its MFMA operand chunk inside a 32-row block of a stage, one per k-step.
@@ -215,15 +220,11 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     const bool loads_a = wave * C::RPL < C::BM;
     const int lrow = lane / C::CPR, lpos = lane % C::CPR;
     const int row0_in_tile = (wave * C::RPL) % C::BM;
-    // voff_last: the same for the last k-tile, whose chunks past K (the next row's bytes) are sent out of the buffer's
-    // bounds and read as zero.
-    unsigned voff[C::NVAR], voff_last[C::NVAR];
+    unsigned voff[C::NVAR];
 #pragma unroll
     for (int v = 0; v < C::NVAR; ++v) {
         const int r = v * C::RPS + lrow;  // row within the wave's share, for requests i with i % NVAR == v
-        const int chunk = lpos ^ ((r / C::SWZ_DIV) % C::CPR);
-        voff[v] = (unsigned)(row0_in_tile + lrow) * (unsigned)p.K + (chunk << 4);
-        voff_last[v] = (KT - 1) * C::BK + (chunk << 4) < p.K ? voff[v] : 0xfffffff0u;
+        voff[v] = (unsigned)(row0_in_tile + lrow) * (unsigned)p.K + ((lpos ^ ((r / C::SWZ_DIV) % C::CPR)) << 4);
     }
     const unsigned req_step = (unsigned)C::RPS * (unsigned)p.K;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -235,13 +236,17 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     auto issue_stage = [&](int slot, int kt) {
         unsigned char *dst = smem + slot * C::STAGE_BYTES + wave * C::RPL * C::BK;
         const unsigned soff = tile_soff + (unsigned)kt * C::BK;
-        unsigned off[C::NVAR];
 #pragma unroll
-        for (int v = 0; v < C::NVAR; ++v) off[v] = kt + 1 == KT ? voff_last[v] : voff[v];
-#pragma unroll
-        for (int i = 0; i < C::LPW; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, off[i % C::NVAR],
+        for (int i = 0; i < C::LPW; ++i) {
+            unsigned off = voff[i % C::NVAR];
+            if constexpr (HALF) {
+                // The last k-tile's chunks past K (the next row's bytes) are sent out of the buffer's bounds and read as zero.
+                const int chunk = lpos ^ ((((i % C::NVAR) * C::RPS + lrow) / C::SWZ_DIV) % C::CPR);
+                if (kt + 1 == KT && chunk >= C::CPR / 2) off = 0xfffffff0u;
+            }
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, off,
                                                      soff + (unsigned)i * req_step, 0, 0);
+        }
     };
 
     // MFMA operand fragments, double-buffered in registers.  A k-step group issues its MFMAs in the order
@@ -670,15 +675,15 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
 
 // The kernel body.  It is a __device__ template called from non-template __global__ entry points: a __global__
 // template that uses device-only buffer builtins does not instantiate in the host pass.
-template <class C, int OUT, bool COLSCALE = false, int MATH = MATH_I8, bool POST = false>
+template <class C, int OUT, bool COLSCALE = false, int MATH = MATH_I8, bool POST = false, bool HALF = false>
 __device__ __forceinline__ void gemm_i8_dequant_body(const GemmI8Args &p) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
     if (C::MT_LOADER == C::MT_EVEN)
-        gemm_i8_dequant_role<C, OUT, C::MT_EVEN, COLSCALE, MATH, POST>(p, wave, (wave / C::WAVES_N) * C::WTM);
+        gemm_i8_dequant_role<C, OUT, C::MT_EVEN, COLSCALE, MATH, POST, HALF>(p, wave, (wave / C::WAVES_N) * C::WTM);
     else if (wave < C::LOADERS)
-        gemm_i8_dequant_role<C, OUT, C::MT_LOADER, COLSCALE, MATH, POST>(p, wave, 0);
+        gemm_i8_dequant_role<C, OUT, C::MT_LOADER, COLSCALE, MATH, POST, HALF>(p, wave, 0);
     else
-        gemm_i8_dequant_role<C, OUT, 2 * C::MT_EVEN - C::MT_LOADER, COLSCALE, MATH, POST>(p, wave, C::MT_LOADER * 32);
+        gemm_i8_dequant_role<C, OUT, 2 * C::MT_EVEN - C::MT_LOADER, COLSCALE, MATH, POST, HALF>(p, wave, C::MT_LOADER * 32);
 }
 
 // Launch geometry shared by the entry points.

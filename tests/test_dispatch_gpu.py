@@ -128,11 +128,16 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
     ref = oracle.dequantize(acc, sr, np.float32(0.37))
     ybf = sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st).view(torch.int16)
     np.testing.assert_array_equal(host(ybf).view(np.uint16), oracle.round_to_bf16(ref))
-    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, torch.from_numpy(bias).to(DEV),
-                                                  torch.from_numpy(gamma).to(DEV), out_dtype=torch.float32)
-    np.testing.assert_array_equal(host(post), oracle.bias_layerscale(ref, bias, gamma))
-    rc = host(sb.matmul_int8_dequant_rc(*dev, out_dtype=torch.float32))
-    np.testing.assert_array_equal(rc, oracle.dequantize_rowcol(acc, sr, sc))
+    np.testing.assert_array_equal(host(sb.matmul_int8_dequant(dev[0], dev[1], dev[2], st, out_dtype=torch.float32)), ref)
+    vecs = [torch.from_numpy(v).to(DEV) for v in (bias, gamma)]
+    ref_post, ref_rc = oracle.bias_layerscale(ref, bias, gamma), oracle.dequantize_rowcol(acc, sr, sc)
+    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, *vecs, out_dtype=torch.float32)
+    np.testing.assert_array_equal(host(post), ref_post)
+    np.testing.assert_array_equal(host(sb.matmul_int8_dequant_rc(*dev, out_dtype=torch.float32)), ref_rc)
+    post = sb.matmul_int8_dequant_bias_layerscale(dev[0], dev[1], dev[2], st, *vecs).view(torch.int16)
+    np.testing.assert_array_equal(host(post).view(np.uint16), oracle.round_to_bf16(ref_post))
+    rc = sb.matmul_int8_dequant_rc(*dev).view(torch.int16)
+    np.testing.assert_array_equal(host(rc).view(np.uint16), oracle.round_to_bf16(ref_rc))
 
 
 # Exact sums, as for the small float8 products: last rows, and the small tile with ragged edges.
