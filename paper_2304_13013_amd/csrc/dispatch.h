@@ -14,32 +14,37 @@ inline bool few_tiles(int64_t M, int64_t N, int ncu) {
     return tiles * 2 <= ncu;
 }
 
-// Estimated time (us) of the small-product kernel's best split for a product, and that split.  Fitted to a sweep of 30
-// products (64..6304 rows, 128..8192 columns, K = 128..8192) on an MI355X; within 15 % on most of them.  k is in stages
-// of 128 bytes.
+// Estimated time (us) of the small-product kernel's best split for a product, and that split.  Fitted to 1300 products
+// (1..33000 rows, 64..8192 columns, K = 64..8192; int8 with every scale and output type, float8) on an MI355X: the ratio to
+// the measured time has a standard deviation of 10 % per split, and the split picked is 0.3 % slower than the best one in
+// the mean.  k is in stages of 128 bytes.  The 32x32 split is for outputs whose 64x64 blocks leave compute units idle;
+// beyond one block per compute unit it fetches too much (734 x 1600, K = 8064: 45 us, the 64x64 splits 29.5).
 inline double direct_product_time(int64_t M, int64_t N, int64_t K, int ncu, int *split) {
     const double k = (double)((K + 127) / 128);
     const int64_t blocks32 = ((M + 31) / 32) * (N / 32), blocks64 = ((M + 63) / 64) * (N / 64);
-    const double t32 = 2.0 + (double)((blocks32 + ncu - 1) / ncu) * (0.35 + 0.091 * k);
-    const double t64 = 2.8 + (double)((blocks64 + ncu - 1) / ncu) * (0.3 + 0.2 * k);
-    const double fill = (double)blocks64 / ncu;  // two small workgroups share a compute unit's throughput
-    const double t64h = 2.6 + (0.15 + 0.27 * k) * (fill > 1.0 ? fill : 1.0);
-    *split = t32 <= t64 && t32 <= t64h ? DIRECT_32 : t64 <= t64h ? DIRECT_64 : DIRECT_64H;
+    const int64_t rounds32 = (blocks32 + ncu - 1) / ncu, rounds64 = (blocks64 + ncu - 1) / ncu;
+    const int64_t rounds64h = (blocks64 + 2 * ncu - 1) / (2 * ncu);
+    const double t32 = 1.6 + (double)rounds32 * (0.5 + 0.079 * k);
+    const double t64 = rounds64 <= 1 ? 2.75 + 0.19 * k : (double)rounds64 * (2.45 + 0.24 * k);
+    const double t64h = rounds64 <= 1 ? 2.65 + 0.275 * k : (double)rounds64h * (3.35 + 0.45 * k);
+    *split = rounds64 <= 1 && t32 <= t64 && t32 <= t64h ? DIRECT_32 : t64 <= t64h ? DIRECT_64 : DIRECT_64H;
     return *split == DIRECT_32 ? t32 : *split == DIRECT_64 ? t64 : t64h;
 }
 
-// The split that beats the 128x128-tile instance, or DIRECT_NONE.  That instance's workgroups take 0.61 us per k-tile
-// while they are alone on their compute unit (a chain of LDS stages) and up to a third more when two share it.  Measured,
-// tiles against blocks: 64 x 1024, K = 4096: 22.7 / 4.4 us; 512 x 256, K = 1024: 8.3 / 2.8; 197 x 3072, K = 768: 7.3 /
-// 4.3; 2000 x 768, K = 3072: 18.3 / 11.9; and on the other side of the line 2000 x 3072, K = 768: 9.5 / 15.0; 1000 x 4096,
-// K = 1024: 9.4 / 12.3.
+// The split that beats the 128x128-tile instance, or DIRECT_NONE.  The line is where the 64x64 blocks no longer fit the
+// GPU at once, two per compute unit: over the same products the best split takes 0.15 to 1.04 of the tiles' time up to
+// there (median 0.4) and 0.9 to 2.3 of it past it (median 1.4).  Tiles against blocks: 64 x 1024, K = 4096: 22.7 / 4.4 us;
+// 197 x 3072, K = 768: 7.3 / 4.3; 2000 x 768, K = 3072: 18.3 / 11.9; and on the other side of the line 1137 x 1856,
+// K = 128: 4.4 / 5.6; 7233 x 320, K = 1920: 13.5 / 16.7; 338 x 5760, K = 7552 with bias and layer-scale: 41.6 / 52.7.
 inline int direct_split_for(int64_t M, int64_t N, int64_t K, int ncu) {
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const double over = tiles > ncu ? (double)(tiles - ncu) / ncu : 0.0;
-    const double tiled = 2.9 + 0.61 * (double)((K + 127) / 128) * (1.0 + 0.35 * over);
-    int split;
-    return direct_product_time(M, N, K, ncu, &split) < tiled ? split : DIRECT_NONE;
+    int split = DIRECT_NONE;
+    if (((M + 63) / 64) * (N / 64) <= 2 * (int64_t)ncu) direct_product_time(M, N, K, ncu, &split);
+    return split;
 }
+
+// What a product does besides the contraction: int8 with one weight scale; int8 with column scales or with bias and
+// layer-scale; float8.
+enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
 
 // A product's rows [0, tile_rows) go to the tiled kernel (128x128 tiles if they make few 256x256 ones), the rest to the
 // small-product kernel with `split`; either part may be empty, and split is DIRECT_NONE exactly if the second one is.
@@ -49,22 +54,32 @@ struct ProductPlan {
 };
 
 // When the last, partial row of tiles starts another round of the persistent grid, that round keeps a few workgroups
-// busy with tiles that are mostly past the end: the small-product kernel does those rows in less time than the round
-// takes, if it is estimated below 6 us per 1024 of K.  Measured, one launch against two: 16448 x 1024, K = 4096 (260
-// tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7, K = 1024 28.4 / 23.7; 16448 x 4096, K = 1024 91.3 /
-// 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0; 8200 x 2048, K = 512 18.8 / 17.1.  Where the number of rounds
-// stays (21000 x 800, K = 1536: 41.0 / 45.8) nothing is split off, and neither where the partial row is the only one (fewer
-// than 256 rows of a very wide output): the tiles keep at least one whole row of tiles.
-inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, int ncu) {
+// busy with tiles that are mostly past the end, and the small-product kernel may do those rows in less time.  Measured,
+// one launch against two: 16448 x 1024, K = 4096 (260 tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7,
+// K = 1024 28.4 / 23.7; 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0; 8200 x 2048,
+// K = 512 18.8 / 17.1.  What the round takes, by 900 products: 7 us per 1024 of K and 1 us more if it is the second one;
+// if more come before it, workgroups that finish early start it, and it takes 5.5 us per 1024 of K; 7 with the longer
+// epilogues (K >= 1024); 4 where the stores of full rounds get into each other's way (the plain int8 product, whose waves
+// share the rows 3 : 5, at K < 1024; and four-byte outputs).  One line at 6 us per 1024 of K made 4337 x 8192, K = 1600 67.2 / 72.9 and 19692 x 2496, K = 768
+// 50.8 / 56.2.  Four-byte outputs in several rounds are bound by their stores if there are many or K is small, and gain
+// nothing reliable (52260 x 1088, K = 2624 216 / 231; 32956 x 1024, K = 768 53.2 / 59.8).  Where the number of rounds stays
+// (21000 x 800, K = 1536: 41.0 / 45.8) nothing is split off, and neither where the partial row is the only one (fewer than
+// 256 rows of a very wide output): the tiles keep at least one whole row of tiles.
+inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
     int split = DIRECT_NONE;
     if (few_tiles(M, N, ncu)) {
         split = direct_split_for(M, N, K, ncu);
         return ProductPlan{split == DIRECT_NONE ? M : 0, split};
     }
     const int64_t full = M / 256 * 256, tiles_n = (N + 255) / 256, tiles = full / 256 * tiles_n;
-    const bool same_rounds = (tiles + ncu - 1) / ncu == (tiles + tiles_n + ncu - 1) / ncu;
-    if (full == 0 || full == M || same_rounds) return ProductPlan{M, DIRECT_NONE};
-    if (direct_product_time(M - full, N, K, ncu, &split) < 6.0 / 1024.0 * (double)K) return ProductPlan{full, split};
+    const int64_t rounds = (tiles + ncu - 1) / ncu;
+    if (full == 0 || full == M || (tiles + tiles_n + ncu - 1) / ncu == rounds) return ProductPlan{M, DIRECT_NONE};
+    if (out_bytes > 2 && rounds > 1 && (rounds > 3 || K < 1024)) return ProductPlan{M, DIRECT_NONE};
+    const double k1024 = (double)K / 1024.0;
+    const double later = out_bytes > 2 || (kind == PRODUCT_PLAIN && K < 1024) ? 4.0
+                         : kind == PRODUCT_LONG_EPILOGUE && K >= 1024 ? 7.0 : 5.5;
+    const double round = rounds == 1 ? 1.0 + 7.0 * k1024 : later * k1024;
+    if (direct_product_time(M - full, N, K, ncu, &split) < round) return ProductPlan{full, split};
     return ProductPlan{M, DIRECT_NONE};
 }
 

@@ -43,8 +43,9 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
                     nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
     // Tiles, a small product, or tiles and a small product for the last rows, by the rules of the int8 product.
-    const ProductPlan plan = plan_product(M, N, K, num_compute_units());
-    const GemmI8Args rest = rows_from(args, plan.tile_rows, out_dtype == SB_BF16 ? 2 : 4);
+    const int out_bytes = out_dtype == SB_BF16 ? 2 : 4;
+    const ProductPlan plan = plan_product(M, N, K, PRODUCT_F8, out_bytes, num_compute_units());
+    const GemmI8Args rest = rows_from(args, plan.tile_rows, out_bytes);
     if (plan.tile_rows == 0) return launch_gemm_f8_direct(plan.split, rest, fmt_a, fmt_b, out_dtype, stream);
     typedef void (*Kernel)(GemmI8Args);
     static const Kernel kernels[16] = {

@@ -116,15 +116,16 @@ static hipError_t launch_tiled(const GemmI8Args &args, bool post, sb_dtype out_d
 
 // Tiles, a small product, or tiles and a small product for the last rows.
 static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
-    const ProductPlan plan = plan_product(args.M, args.N, args.K, num_compute_units());
+    const int out_bytes = out_dtype == SB_BF16 ? 2 : 4;
+    const ProductKind kind = post || args.state_col != nullptr ? PRODUCT_LONG_EPILOGUE : PRODUCT_PLAIN;
+    const ProductPlan plan = plan_product(args.M, args.N, args.K, kind, out_bytes, num_compute_units());
     if (plan.tile_rows > 0) {
         GemmI8Args tiled = args;
         tiled.M = (int)plan.tile_rows;
         const hipError_t e = launch_tiled(tiled, post, out_dtype, stream);
         if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
     }
-    return launch_gemm_i8_direct(plan.split, rows_from(args, plan.tile_rows, out_dtype == SB_BF16 ? 2 : 4), post, out_dtype,
-                                 stream);
+    return launch_gemm_i8_direct(plan.split, rows_from(args, plan.tile_rows, out_bytes), post, out_dtype, stream);
 }
 
 hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row, const int8_t *bq,

@@ -8,20 +8,22 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NONE, D32, D64, D64H = range(4)
+PLAIN, LONG_EPILOGUE, F8 = range(3)
 WRAPPER = r"""
 #include "%s"
 extern "C" {
 int few_tiles(long long M, long long N, int ncu) { return sb::few_tiles(M, N, ncu); }
-long long plan_product(long long M, long long N, long long K, int ncu, int *split) {
-    const sb::ProductPlan p = sb::plan_product(M, N, K, ncu);
+long long plan_product(long long M, long long N, long long K, int kind, int out_bytes, int ncu, int *split) {
+    const sb::ProductPlan p = sb::plan_product(M, N, K, (sb::ProductKind)kind, out_bytes, ncu);
     *split = p.split;
     return p.tile_rows;
 }
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
 // Every plan of M = lo..hi (step) must cover each row once: returns the first M whose plan does not, or 0.
-long long bad_plan(long long lo, long long hi, long long step, long long N, long long K, int ncu) {
+long long bad_plan(long long lo, long long hi, long long step, long long N, long long K, int kind, int out_bytes,
+                   int ncu) {
     for (long long M = lo; M <= hi; M += step) {
-        const sb::ProductPlan p = sb::plan_product(M, N, K, ncu);
+        const sb::ProductPlan p = sb::plan_product(M, N, K, (sb::ProductKind)kind, out_bytes, ncu);
         const bool direct = p.split != sb::DIRECT_NONE;
         if (p.split < 0 || p.split > sb::DIRECT_64H || p.tile_rows < 0 || p.tile_rows > M) return M;
         if (direct != (p.tile_rows < M)) return M;                       // rows past the tiles need a split, and only they
@@ -44,10 +46,10 @@ def rules(tmp_path_factory):
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", lib, src])
     rules = ctypes.CDLL(lib)
     rules.few_tiles.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int]
-    rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     rules.plan_product.restype = ctypes.c_longlong
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
-    rules.bad_plan.argtypes = [ctypes.c_longlong] * 5 + [ctypes.c_int]
+    rules.bad_plan.argtypes = [ctypes.c_longlong] * 5 + [ctypes.c_int] * 3
     rules.bad_plan.restype = ctypes.c_longlong
     return rules
 
@@ -59,7 +61,38 @@ def test_every_plan_covers_each_row_once(rules, ncu):
     for N in widths:
         for K in (64, 192, 1088, 1664, 2048, 2688, 5120, 8192, 131072):
             for lo, hi, step in ((1, 1100, 1), (1101, 70000, 251)):
-                assert rules.bad_plan(lo, hi, step, N, K, ncu) == 0, (N, K, ncu)
+                for kind, out_bytes in ((PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (F8, 2)):
+                    assert rules.bad_plan(lo, hi, step, N, K, kind, out_bytes, ncu) == 0, (N, K, kind, out_bytes, ncu)
+
+
+def route(rules, M, N, K, out_bytes=2, kind=PLAIN):
+    """(rows on the tiles, split of the rest) on an MI355X."""
+    split = ctypes.c_int(-1)
+    rows = rules.plan_product(M, N, K, kind, out_bytes, 256, ctypes.byref(split))
+    return rows, split.value
+
+
+# Products near the lines that were slower on the other route (up to 27 %): 64x64 blocks just past two per compute unit
+# stay on the 128x128 tiles, and last rows that cost more than the round they save stay on the 256x256 ones.
+@pytest.mark.parametrize("M,N,K,out_bytes", [(1137, 1856, 128, 2), (1358, 1600, 128, 2), (7233, 320, 1920, 2),
+                                             (12045, 192, 896, 2), (9108, 256, 4864, 4), (338, 5760, 7552, 2),
+                                             (4337, 8192, 1600, 2), (6837, 7232, 1024, 2),
+                                             (19692, 2496, 768, 2), (19484, 2496, 384, 2),
+                                             (35816, 2752, 1280, 4), (52260, 1088, 2624, 4), (32956, 1024, 768, 4)])
+def test_products_that_stay_on_the_tiles(rules, M, N, K, out_bytes):
+    assert route(rules, M, N, K, out_bytes) == (M, NONE)
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 1024, 4096), (197, 3072, 768), (2000, 768, 3072), (1121, 1792, 128)])
+def test_products_that_leave_the_tiles(rules, M, N, K):
+    rows, split = route(rules, M, N, K)
+    assert rows == 0 and split != NONE
+
+
+@pytest.mark.parametrize("M,N,K", [(16448, 1024, 4096), (16448, 4096, 1024), (32896, 5120, 1280), (8200, 2048, 512)])
+def test_last_rows_that_leave_the_tiles(rules, M, N, K):
+    rows, split = route(rules, M, N, K)
+    assert rows == M // 256 * 256 and split != NONE
 
 
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])
