@@ -42,6 +42,15 @@ inline int direct_split_for(int64_t M, int64_t N, int64_t K, int ncu) {
     return split;
 }
 
+// K = 64 mod 128 on the 256x256 tiles: 64-byte k-steps instead of 128-byte ones whose last stage is half zeros.  At
+// K = 64, where that stage is the only one, they are 2 to 4 % faster with every output and scale (17571 x 5440: 45.4 /
+// 50.4 us); and for four-byte outputs beyond the 256 MiB last-level cache, whose stores bound short contractions, 2 to
+// 12 % (K = 192 to 832, 400..900 MB; 1 to 7 % slower up to 200 MB).  Otherwise the 128-byte steps are: 65.3 / 52.0 us at
+// 11237 x 2880, K = 1088.
+inline bool short_k_steps(int64_t M, int64_t N, int64_t K, int out_bytes) {
+    return K == 64 || (out_bytes > 2 && K % 128 != 0 && K < 1024 && M * N * out_bytes > (int64_t)256 << 20);
+}
+
 // What a product does besides the contraction: int8 with one weight scale; int8 with column scales or with bias and
 // layer-scale; float8.
 enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
@@ -56,15 +65,16 @@ struct ProductPlan {
 // When the last, partial row of tiles starts another round of the persistent grid, that round keeps a few workgroups
 // busy with tiles that are mostly past the end, and the small-product kernel may do those rows in less time.  Measured,
 // one launch against two: 16448 x 1024, K = 4096 (260 tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7,
-// K = 1024 28.4 / 23.7; 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0; 8200 x 2048,
-// K = 512 18.8 / 17.1.  What the round takes, by 900 products: 7 us per 1024 of K and 1 us more if it is the second one;
-// if more come before it, workgroups that finish early start it, and it takes 5.5 us per 1024 of K; 7 with the longer
-// epilogues (K >= 1024); 4 where the stores of full rounds get into each other's way (the plain int8 product, whose waves
-// share the rows 3 : 5, at K < 1024; and four-byte outputs).  One line at 6 us per 1024 of K made 4337 x 8192, K = 1600 67.2 / 72.9 and 19692 x 2496, K = 768
-// 50.8 / 56.2.  Four-byte outputs in several rounds are bound by their stores if there are many or K is small, and gain
-// nothing reliable (52260 x 1088, K = 2624 216 / 231; 32956 x 1024, K = 768 53.2 / 59.8).  Where the number of rounds stays
-// (21000 x 800, K = 1536: 41.0 / 45.8) nothing is split off, and neither where the partial row is the only one (fewer than
-// 256 rows of a very wide output): the tiles keep at least one whole row of tiles.
+// K = 1024 28.4 / 23.7; 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0;
+// 8200 x 2048, K = 512 18.8 / 17.1.  What the round takes, by 900 products: 7 us per 1024 of K and 1 us more if it is
+// the second one; if more come before it, workgroups that finish early start it, and it takes 5.5 us per 1024 of K; 7
+// with the longer epilogues (K >= 1024); 4 where the stores of full rounds get into each other's way (the plain int8
+// product, whose waves share the rows 3 : 5, at K < 1024; and four-byte outputs).  One line at 6 us per 1024 of K made
+// 4337 x 8192, K = 1600 67.2 / 72.9 and 19692 x 2496, K = 768 50.8 / 56.2.  Four-byte outputs in several rounds are
+// bound by their stores if there are many or K is small, and gain nothing reliable (52260 x 1088, K = 2624 216 / 231;
+// 32956 x 1024, K = 768 53.2 / 59.8).  Where the number of rounds stays (21000 x 800, K = 1536: 41.0 / 45.8) nothing is
+// split off, and neither where the partial row is the only one (fewer than 256 rows of a very wide output): the tiles
+// keep at least one whole row of tiles.
 inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
     int split = DIRECT_NONE;
     if (few_tiles(M, N, ncu)) {

@@ -29,7 +29,9 @@
 //   * MFMA operand fragments are double-buffered in registers, and the LDS reads of k-step j+1 are issued one at a
 //     time between the MFMAs of k-step j (also across the stage hand-over): an LDS read issued in the shadow of an
 //     MFMA costs no issue time.  The reads are inline asm so that the lgkmcnt waits can be counted; the compiler's
-//     own would drain the queue in front of every MFMA group.
+//     own would drain the queue in front of every MFMA group.  The compiler takes the registers of such a read as
+//     written at once, so an instance that spills (it would store them, and reuse them, before the data lands) must
+//     never run: all are built at zero spills.
 //   * Barriers are bare s_barrier instructions with explicit vmcnt / lgkmcnt waits; __syncthreads() would drain
 //     every outstanding global->LDS request.  The vector-memory counter is one in-order counter for loads and
 //     stores, so every wave keeps books of what it issued after each stage's requests and waits for "at most that

@@ -105,11 +105,12 @@ def test_small_float8_products(M, N, K, fa, fb):
     assert torch.equal(got, want)
 
 
-# The tiled kernel with a last stage of half zeros (K = 64 mod 128) on its large and small tile, and products whose last
-# rows leave the tiles because they would start another round of the grid: 1 row, a tile row less one, a width that is no
-# multiple of the tile; every output type and scale.
+# The tiled kernel with a last stage of half zeros (K = 64 mod 128) on its large and small tile, its instances with 64-byte
+# k-steps (K = 64, and four-byte outputs beyond the last-level cache), and products whose last rows leave the tiles because
+# they would start another round of the grid: 1 row, a tile row less one, a width that is no multiple of the tile; every
+# output type and scale.
 SPLIT = [(11237, 2880, 192), (5000, 1088, 320), (16385, 1024, 1024), (16639, 1024, 1536), (16448, 960, 1216),
-         (32896, 2048, 1088)]
+         (32896, 2048, 1088), (9000, 1088, 64), (16000, 4224, 192)]
 
 
 @pytest.mark.parametrize("M,N,K", SPLIT)
