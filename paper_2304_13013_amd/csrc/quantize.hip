@@ -16,6 +16,7 @@
 // All three kernels are HBM-bound: one 16-byte load per 8 elements, the row (or tile) stays in registers between
 // the absmax and the quantization, codes leave as 8- or 16-byte stores.
 #include "sb_common.h"
+#include <type_traits>
 
 namespace sb {
 namespace {
@@ -136,20 +137,33 @@ __device__ __forceinline__ void absmax_partial_body(const v4u *__restrict__ w, i
 
 // A second matrix with the same number of columns whose rows follow the first one's in the same launch (SwitchBackQ
 // quantizes X and W row-wise in one forward pass; 6304 and 768 rows of 3072: 11.1 + 4.2 us in two launches, 12.1 us in
-// one).  rows == 0: none.
+// one).  A kernel for one matrix takes NoSecondRows: looking for a second one in every workgroup made it 3 to 4 % slower
+// (4583 x 2368: 7.25 / 7.54 us).
 struct SecondRows {
     const v4u *x;
     v2u *q;
     float *state;
-    int64_t rows;
+    int64_t first_rows, rows;  // of the first matrix, of this one
 };
+struct NoSecondRows {};
+
+// Moves the row and the pointers to the second matrix if the row lies past the first one's; false: past both.
+__device__ __forceinline__ bool select_rows(const SecondRows &second, int64_t &row, const v4u *__restrict__ &x,
+                                            v2u *__restrict__ &q, float *__restrict__ &state) {
+    if (row < second.first_rows) return true;
+    row -= second.first_rows;
+    x = second.x;
+    q = second.q;
+    state = second.state;
+    return row < second.rows;
+}
 
 // ---- row-wise: one wavefront per row (cols <= 64*8*NCH) ---------------------------------------------------
-template <int NCH, int CODE>
+template <int NCH, int CODE, class Second>
 __global__ __launch_bounds__(256) void quantize_rowwise_wave_kernel(const v4u *__restrict__ x, int64_t rows,
                                                                     int chunks, v2u *__restrict__ q,
                                                                     float *__restrict__ state, TensorAbsmaxJob job,
-                                                                    SecondRows second) {
+                                                                    Second second) {
     __shared__ unsigned int rider_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, rider_max);
@@ -157,12 +171,11 @@ __global__ __launch_bounds__(256) void quantize_rowwise_wave_kernel(const v4u *_
     }
     const int lane = threadIdx.x & 63;
     int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) {  // uniform per wavefront; the kernel has no block-level barrier
-        row -= rows;
-        if (row >= second.rows) return;
-        x = second.x;
-        q = second.q;
-        state = second.state;
+    // The whole wavefront leaves; the kernel has no block-level barrier.
+    if constexpr (std::is_same<Second, SecondRows>::value) {
+        if (!select_rows(second, row, x, q, state)) return;
+    } else {
+        if (row >= rows) return;
     }
     const v4u *xr = x + row * chunks;
     v4u v[NCH];
@@ -187,23 +200,19 @@ __global__ __launch_bounds__(256) void quantize_rowwise_wave_kernel(const v4u *_
 }
 
 // ---- row-wise: one 256-thread block per row (cols <= 256*8*NCH) ---------------------------------------------
-template <int NCH, int CODE>
+template <int NCH, int CODE, class Second>
 __global__ __launch_bounds__(256) void quantize_rowwise_block_kernel(const v4u *__restrict__ x, int chunks,
                                                                      v2u *__restrict__ q,
                                                                      float *__restrict__ state, TensorAbsmaxJob job,
-                                                                     int64_t rows, SecondRows second) {
+                                                                     Second second) {
     __shared__ unsigned int wave_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, wave_max);
         return;
     }
     int64_t row = blockIdx.x;
-    if (row >= rows) {  // uniform per workgroup; the grid has rows + second.rows of them
-        row -= rows;
-        x = second.x;
-        q = second.q;
-        state = second.state;
-    }
+    // The grid has a workgroup for every row.
+    if constexpr (std::is_same<Second, SecondRows>::value) select_rows(second, row, x, q, state);
     const v4u *xr = x + row * chunks;
     v4u v[NCH];
 #pragma unroll
@@ -230,23 +239,19 @@ __global__ __launch_bounds__(256) void quantize_rowwise_block_kernel(const v4u *
 }
 
 // ---- row-wise: very wide rows, two passes over the row (the second one hits L2) ---------------------------
-template <int CODE>
+template <int CODE, class Second>
 __global__ __launch_bounds__(256) void quantize_rowwise_wide_kernel(const v4u *__restrict__ x, int chunks,
                                                                     v2u *__restrict__ q,
                                                                     float *__restrict__ state, TensorAbsmaxJob job,
-                                                                    int64_t rows, SecondRows second) {
+                                                                    Second second) {
     __shared__ unsigned int wave_max[4];
     if (job.nblocks > 0 && (int)blockIdx.x >= job.first_block) {  // uniform per workgroup
         absmax_partial_body(job.w, job.nchunks, job.partials, (int)blockIdx.x - job.first_block, job.nblocks, wave_max);
         return;
     }
     int64_t row = blockIdx.x;
-    if (row >= rows) {  // uniform per workgroup; the grid has rows + second.rows of them
-        row -= rows;
-        x = second.x;
-        q = second.q;
-        state = second.state;
-    }
+    // The grid has a workgroup for every row.
+    if constexpr (std::is_same<Second, SecondRows>::value) select_rows(second, row, x, q, state);
     const v4u *xr = x + row * chunks;
     unsigned int m = 0;
     for (int c = threadIdx.x; c < chunks; c += 256) m = absmax_of_chunk(m, xr[c]);
@@ -540,23 +545,26 @@ int tensorwise_partial_blocks(int64_t nchunks) {
     return nblocks < 1 ? 1 : nblocks;
 }
 
-template <int CODE>
+inline int64_t rows_of(NoSecondRows) { return 0; }
+inline int64_t rows_of(const SecondRows &second) { return second.rows; }
+
+template <int CODE, class Second = NoSecondRows>
 hipError_t launch_quantize_rowwise_t(const void *x, int64_t rows, int64_t cols, void *q, float *state,
                                      hipStream_t stream, TensorAbsmaxJob job = TensorAbsmaxJob{nullptr, 0, nullptr, 0, 0},
-                                     SecondRows second = SecondRows{nullptr, nullptr, nullptr, 0}) {
+                                     Second second = Second{}) {
     const int chunks = (int)(cols / 8);
     const v4u *xp = static_cast<const v4u *>(x);
     v2u *qp = static_cast<v2u *>(q);
-    const int64_t all_rows = rows + second.rows;
+    const int64_t all_rows = rows + rows_of(second);
     unsigned int wave_grid = (unsigned int)((all_rows + 3) / 4), block_grid = (unsigned int)all_rows;
     // The rider's workgroups follow the rows' in the grid.
     job.first_block = (int)(chunks <= 256 ? wave_grid : block_grid);
     wave_grid += (unsigned int)job.nblocks;
     block_grid += (unsigned int)job.nblocks;
 #define SB_WAVE(N)                                                                                          \
-    quantize_rowwise_wave_kernel<N, CODE><<<wave_grid, 256, 0, stream>>>(xp, rows, chunks, qp, state, job, second)
+    quantize_rowwise_wave_kernel<N, CODE, Second><<<wave_grid, 256, 0, stream>>>(xp, rows, chunks, qp, state, job, second)
 #define SB_BLOCK(N)                                                                                         \
-    quantize_rowwise_block_kernel<N, CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, rows, second)
+    quantize_rowwise_block_kernel<N, CODE, Second><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, second)
     if (chunks <= 64) SB_WAVE(1);
     else if (chunks <= 128) SB_WAVE(2);
     else if (chunks <= 192) SB_WAVE(3);
@@ -566,7 +574,7 @@ hipError_t launch_quantize_rowwise_t(const void *x, int64_t rows, int64_t cols, 
     else if (chunks <= 1024) SB_BLOCK(4);
     else if (chunks <= 1536) SB_BLOCK(6);
     else if (chunks <= 2048) SB_BLOCK(8);
-    else quantize_rowwise_wide_kernel<CODE><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, rows, second);
+    else quantize_rowwise_wide_kernel<CODE, Second><<<block_grid, 256, 0, stream>>>(xp, chunks, qp, state, job, second);
 #undef SB_WAVE
 #undef SB_BLOCK
     return hipGetLastError();
@@ -581,9 +589,9 @@ hipError_t launch_quantize_rowwise(const void *x, int64_t rows, int64_t cols, in
 // Two matrices [rows, cols] and [rows2, cols] in one launch (rows + rows2 > 0; either may be 0).
 hipError_t launch_quantize_rowwise_pair(const void *x, int64_t rows, int8_t *q, float *state, const void *x2,
                                         int64_t rows2, int8_t *q2, float *state2, int64_t cols, hipStream_t stream) {
-    return launch_quantize_rowwise_t<CODE_INT8>(
+    return launch_quantize_rowwise_t<CODE_INT8, SecondRows>(
         x, rows, cols, q, state, stream, TensorAbsmaxJob{nullptr, 0, nullptr, 0, 0},
-        SecondRows{static_cast<const v4u *>(x2), reinterpret_cast<v2u *>(q2), state2, rows2});
+        SecondRows{static_cast<const v4u *>(x2), reinterpret_cast<v2u *>(q2), state2, rows, rows2});
 }
 
 hipError_t launch_quantize_rowwise_f8(const void *x, int64_t rows, int64_t cols, int fmt, uint8_t *codes, float *state,
