@@ -86,7 +86,6 @@ hipError_t launch_stable_adamw_step_multi(const sb_adamw_tensor *table, int n, i
                                           float lambda, float *rms_out, void *ws, hipStream_t stream);
 
 constexpr int kTensorwisePartials = 1024;  // upper bound on blocks of the tensor-wise absmax pass
-constexpr int kAdamwPartials = 2048;  // upper bound on the workgroups of a StableAdamW step
 constexpr int kColwiseRuns = 64;  // upper bound on the row runs of the column-wise absmax pass
 
 }  // namespace sb

@@ -11,24 +11,15 @@
 // All arithmetic is binary32 except the sum, which is binary64 so that its order does not matter at the tolerance of
 // the parity tests.  Each lane handles four consecutive elements per step (16-byte accesses of the binary32 arrays);
 // the count % 4 trailing elements are handled by the first lanes of workgroup 0.
+#include "adamw_rules.h"
 #include "sb_common.h"
 
 namespace sb {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kElementsPerBlock = kThreads * 4 * 4;  // four quads per lane before the grid stride matters
+constexpr int kThreads = kAdamwThreads;
 
-// Both passes are bound by memory.  While all of a step's arrays fit the 256 MiB last-level cache together, plain
-// accesses in one direction serve the second pass (and the next step) from it.  Above that (STREAM) the second pass walks
-// the workgroups backwards, so that it starts at the moments the first pass wrote last, and what only one pass touches
-// (gradient, parameters) is accessed non-temporally, so that it does not push the moments out.  A transformer block's ten
-// tensors, both passes, bf16 / binary32 gradients: width 2048 (0.7 / 0.8 GB) 338 / 356 us plain, 286 / 298 us streaming;
-// width 1280 (275 / 315 MB) 107.7 / 112.6 and 104.8 / 110.7; width 768 (99 / 113 MB) 42.4 / 44.9 and 45.6 / 48.4.
-// (Four quads per lane in flight at once, loads ahead of the partial sums: 6 % slower at width 1280, the same at 768.)
-constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
-bool streams(int64_t elements, bool grad_bf16) { return elements * (12 + (grad_bf16 ? 2 : 4)) > kLastLevelCacheBytes; }
-
+// STREAM: the step's arrays exceed the last-level cache (adamw_streams).
 template <bool STREAM, class T>
 __device__ __forceinline__ T load_once(const T *p) {
     if (STREAM) return __builtin_nontemporal_load(p);
@@ -201,18 +192,11 @@ __global__ __launch_bounds__(kThreads) void adamw_update_multi_kernel(const sb_a
                               rms_out ? rms_out + ti : nullptr, block - t.first_block, red);
 }
 
-int adamw_grid(int64_t count) {
-    int64_t blocks = (count + kElementsPerBlock - 1) / kElementsPerBlock;
-    if (blocks < 1) blocks = 1;
-    if (blocks > kAdamwPartials) blocks = kAdamwPartials;
-    return (int)blocks;
-}
-
 }  // namespace
 
 size_t stable_adamw_workspace_bytes() { return (size_t)kAdamwPartials * sizeof(double); }
 
-int stable_adamw_blocks(int64_t count) { return adamw_grid(count); }
+int stable_adamw_blocks(int64_t count) { return adamw_blocks(count); }
 
 namespace {
 
@@ -237,7 +221,7 @@ template <bool STREAM>
 hipError_t launch_one(float *theta, float *v, float *u, const void *grad, bool grad_bf16, int64_t count, float alpha,
                       float b1_hat, float b2_hat, float omb1, float omb2, float eps, float lambda, float *rms_out,
                       double *partials, hipStream_t stream) {
-    const int grid = adamw_grid(count);
+    const int grid = adamw_blocks(count);
     const float eps2 = eps * eps;
     if (grad_bf16)
         adamw_moments_kernel<true, STREAM><<<grid, kThreads, 0, stream>>>(grad, v, u, count, b1_hat, omb1, b2_hat, omb2, eps2,
@@ -254,12 +238,10 @@ hipError_t launch_one(float *theta, float *v, float *u, const void *grad, bool g
 
 }  // namespace
 
-// The element counts of a batched step live in device memory; its workgroup count bounds their sum from below closely
-// enough (exactly, up to a partial workgroup per tensor, for tensors of up to kAdamwPartials workgroups).
 hipError_t launch_stable_adamw_step_multi(const sb_adamw_tensor *table, int n, int total_blocks, bool grad_bf16,
                                           float alpha, float b1_hat, float b2_hat, float omb1, float omb2, float eps,
                                           float lambda, float *rms_out, void *ws, hipStream_t stream) {
-    const bool stream_arrays = streams((int64_t)total_blocks * kElementsPerBlock, grad_bf16);
+    const bool stream_arrays = adamw_streams(adamw_elements_at_least(total_blocks, n), grad_bf16);
     return (stream_arrays ? launch_multi<true> : launch_multi<false>)(table, n, total_blocks, grad_bf16, alpha, b1_hat,
                                                                       b2_hat, omb1, omb2, eps, lambda, rms_out,
                                                                       static_cast<double *>(ws), stream);
@@ -268,7 +250,7 @@ hipError_t launch_stable_adamw_step_multi(const sb_adamw_tensor *table, int n, i
 hipError_t launch_stable_adamw_step(float *theta, float *v, float *u, const void *grad, bool grad_bf16, int64_t count,
                                     float alpha, float b1_hat, float b2_hat, float omb1, float omb2, float eps,
                                     float lambda, float *rms_out, void *ws, hipStream_t stream) {
-    return (streams(count, grad_bf16) ? launch_one<true> : launch_one<false>)(
+    return (adamw_streams(count, grad_bf16) ? launch_one<true> : launch_one<false>)(
         theta, v, u, grad, grad_bf16, count, alpha, b1_hat, b2_hat, omb1, omb2, eps, lambda, rms_out,
         static_cast<double *>(ws), stream);
 }

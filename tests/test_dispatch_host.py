@@ -1,5 +1,5 @@
-"""The dispatch rules of csrc/dispatch.h, compiled for the host and checked over the range of sizes the calls accept: no
-GPU is needed."""
+"""The size rules of csrc/dispatch.h and csrc/adamw_rules.h, compiled for the host and checked over the range of sizes
+the calls accept: no GPU is needed."""
 import ctypes
 import os
 import subprocess
@@ -10,7 +10,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NONE, D32, D64, D64H = range(4)
 PLAIN, LONG_EPILOGUE, F8 = range(3)
 WRAPPER = r"""
-#include "%s"
+#include "dispatch.h"
+#include "adamw_rules.h"
 extern "C" {
 int few_tiles(long long M, long long N, int ncu) { return sb::few_tiles(M, N, ncu); }
 long long plan_product(long long M, long long N, long long K, int kind, int out_bytes, int ncu, int *split) {
@@ -20,6 +21,9 @@ long long plan_product(long long M, long long N, long long K, int kind, int out_
 }
 int short_k_steps(long long M, long long N, long long K, int out_bytes) { return sb::short_k_steps(M, N, K, out_bytes); }
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
+int adamw_blocks(long long count) { return sb::adamw_blocks(count); }
+long long adamw_elements_at_least(long long blocks, long long n) { return sb::adamw_elements_at_least(blocks, n); }
+int adamw_streams(long long elements, int grad_bf16) { return sb::adamw_streams(elements, grad_bf16); }
 // Every plan of M = lo..hi (step) must cover each row once: returns the first M whose plan does not, or 0.
 long long bad_plan(long long lo, long long hi, long long step, long long N, long long K, int kind, int out_bytes,
                    int ncu) {
@@ -29,7 +33,7 @@ long long bad_plan(long long lo, long long hi, long long step, long long N, long
         if (p.split < 0 || p.split > sb::DIRECT_64H || p.tile_rows < 0 || p.tile_rows > M) return M;
         if (direct != (p.tile_rows < M)) return M;                       // rows past the tiles need a split, and only they
         if (p.tile_rows == 0 && !sb::few_tiles(M, N, ncu)) return M;     // many tiles: never all rows off the tiles
-        if (direct && p.tile_rows %% 256) return M;                      // the tiles that stay are whole
+        if (direct && p.tile_rows % 256) return M;                      // the tiles that stay are whole
         if (p.tile_rows > 0 && sb::persistent_grid((p.tile_rows + 255) / 256 * ((N + 255) / 256), ncu) < 8) return M;
     }
     return 0;
@@ -43,14 +47,19 @@ def rules(tmp_path_factory):
     folder = tmp_path_factory.mktemp("dispatch")
     src, lib = str(folder / "rules.cpp"), str(folder / "rules.so")
     with open(src, "w") as fh:
-        fh.write(WRAPPER % os.path.join(ROOT, "paper_2304_13013_amd", "csrc", "dispatch.h"))
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", lib, src])
+        fh.write(WRAPPER)
+    csrc = os.path.join(ROOT, "paper_2304_13013_amd", "csrc")
+    subprocess.check_call(["g++", "-I", csrc, "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", lib, src])
     rules = ctypes.CDLL(lib)
     rules.few_tiles.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int]
     rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     rules.plan_product.restype = ctypes.c_longlong
     rules.short_k_steps.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    rules.adamw_blocks.argtypes = [ctypes.c_longlong]
+    rules.adamw_elements_at_least.argtypes = [ctypes.c_longlong] * 2
+    rules.adamw_elements_at_least.restype = ctypes.c_longlong
+    rules.adamw_streams.argtypes = [ctypes.c_longlong, ctypes.c_int]
     rules.bad_plan.argtypes = [ctypes.c_longlong] * 5 + [ctypes.c_int] * 3
     rules.bad_plan.restype = ctypes.c_longlong
     return rules
@@ -113,3 +122,18 @@ def test_persistent_grid(rules, slots):
         assert grid % 8 == 0 and 8 <= grid <= slots
         rounds = -(-tiles // slots)
         assert -(-tiles // grid) <= max(rounds, 1)          # a shrunk grid makes no more rounds
+
+
+def block_of(n):
+    return [3 * n * n, n * n, 4 * n * n, 4 * n * n, 3 * n, n, 4 * n, n, n, n]
+
+
+# Batched optimizer steps: sets of many small tensors that fit the last-level cache, transformer blocks on both sides of
+# the line, and the bound for tensors of more than 2048 workgroups, which counts them as 8.4 million elements.
+@pytest.mark.parametrize("counts,streams", [([256] * 5000, False), ([1024] * 5000, False), ([4097] * 4500, False),
+                                            (block_of(768), False), (block_of(1280), True), (block_of(512) * 12, True),
+                                            ([67_108_864], False), ([67_108_864] * 3, True)])
+def test_batched_optimizer_step_streams(rules, counts, streams):
+    at_least = rules.adamw_elements_at_least(sum(rules.adamw_blocks(c) for c in counts), len(counts))
+    assert at_least <= sum(counts)
+    assert rules.adamw_streams(at_least, 1) == streams
