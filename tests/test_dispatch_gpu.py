@@ -59,10 +59,11 @@ def test_colwise_quantizer_row_runs(oracle, rows, cols):
     np.testing.assert_array_equal(host(q_t), qo)
 
 
-# The small-product kernel, all three of its splits: one row, rows and columns past a block's edge, a contraction shorter
-# than one stage, one that leaves waves idle, an odd number of half stages (K = 64 mod 128), and every output and scale.
+# The small-product kernel, all three of its splits, each with whole and half last stages (K = 64 mod 128) and with more
+# stages per wave than the ring holds: one row, rows and columns past a block's edge, a contraction shorter than one stage,
+# one that leaves waves idle, and every output and scale.  (A host test checks which split each size takes.)
 SMALL = [(1, 64, 64), (33, 64, 192), (197, 192, 4096), (64, 1024, 576), (300, 1024, 8192), (197, 3072, 768),
-         (512, 2048, 320), (2000, 768, 768), (1990, 768, 3008)]
+         (512, 2048, 320), (2000, 768, 768), (1990, 768, 3008), (197, 3072, 832), (1000, 1024, 4032), (513, 1984, 2048)]
 
 
 @pytest.mark.parametrize("M,N,K", SMALL)
@@ -90,19 +91,27 @@ def test_small_int8_products(oracle, M, N, K):
 
 
 # Codes 0, +-1/4, +-1/2, +-1: no product is truncated and binary32 holds every partial sum, so the float8 sum is exact.
+SMALL_F8 = [(1, 64, 128), (197, 192, 4096), (300, 1024, 640), (1990, 768, 768), (197, 3072, 768), (1000, 1024, 4096),
+            (2001, 704, 3072)]
+
+
 @pytest.mark.parametrize("fa,fb", [(0, 0), (1, 0), (0, 1), (1, 1)])
-@pytest.mark.parametrize("M,N,K", [(1, 64, 128), (197, 192, 4096), (300, 1024, 640), (1990, 768, 768)])
+@pytest.mark.parametrize("M,N,K", SMALL_F8)
 def test_small_float8_products(M, N, K, fa, fb):
+    check_exact_float8_product(M, N, K, fa, fb)
+
+
+def check_exact_float8_product(M, N, K, fa, fb):
     rng = np.random.default_rng(M + N + K)
     vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)
     a, b = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
     types = (torch.float8_e4m3fn, torch.float8_e5m2)
     sr = torch.rand(M, device=DEV) + 0.5
     st = torch.full((1,), 0.37, device=DEV)
-    got = sb.matmul_f8_dequant(a.to(types[fa]).view(torch.uint8), fa, sr, b.to(types[fb]).view(torch.uint8), fb, st,
-                               out_dtype=torch.float32)
+    args = a.to(types[fa]).view(torch.uint8), fa, sr, b.to(types[fb]).view(torch.uint8), fb, st
     want = (a.double() @ b.double().t()).float() * (sr * st)[:, None]
-    assert torch.equal(got, want)
+    assert torch.equal(sb.matmul_f8_dequant(*args, out_dtype=torch.float32), want)
+    assert torch.equal(sb.matmul_f8_dequant(*args), want.bfloat16())
 
 
 # The tiled kernel with a last stage of half zeros (K = 64 mod 128) on its large and small tile, its instances with 64-byte
@@ -142,15 +151,13 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
 
 
 # Exact sums, as for the small float8 products: last rows, and the small tile with ragged edges.
-@pytest.mark.parametrize("M,N,K", [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2112, 384)])
-def test_tiles_of_a_float8_product(M, N, K):
-    rng = np.random.default_rng(M + N + K)
-    vals = np.array([0.0, 0.25, -0.25, 0.5, -0.5, 1.0, -1.0], np.float32)
-    a, b = (torch.from_numpy(vals[rng.integers(0, 7, size=(r, K))]).to(DEV) for r in (M, N))
-    sr, st = torch.rand(M, device=DEV) + 0.5, torch.full((1,), 0.37, device=DEV)
-    got = sb.matmul_f8_dequant(a.to(torch.float8_e5m2).view(torch.uint8), 1, sr,
-                               b.to(torch.float8_e4m3fn).view(torch.uint8), 0, st, out_dtype=torch.float32)
-    assert torch.equal(got, (a.double() @ b.double().t()).float() * (sr * st)[:, None])
+TILES_F8 = [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2112, 384)]
+
+
+@pytest.mark.parametrize("fa,fb", [(1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K", TILES_F8)
+def test_tiles_of_a_float8_product(M, N, K, fa, fb):
+    check_exact_float8_product(M, N, K, fa, fb)
 
 
 # A few tokens into a very wide output: 129 tiles in the only, partial row of tiles, so that nothing is left for the tiles
@@ -182,8 +189,8 @@ def test_few_rows_of_a_very_wide_output(oracle, M, N=32832, K=2048):
     assert torch.equal(got, (a8.double() @ b8.double().t()).float() * (dev[1] * st)[:, None])
 
 
-# A step whose arrays exceed the last-level cache (28 or 32 million elements: the second pass runs backwards and
-# non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
+# A step whose arrays exceed the last-level cache (24 million elements in four tensors, 20 million in one: 280 to 390 MB;
+# the second pass runs backwards and non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
 # agrees with the binary64 evaluation; ragged counts, so that the last workgroups are partial.
 @pytest.mark.parametrize("grad_dtype", [torch.bfloat16, torch.float32])
 def test_adamw_step_larger_than_the_last_level_cache(grad_dtype):

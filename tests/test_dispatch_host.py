@@ -115,6 +115,36 @@ def test_short_k_steps(rules, M, N, K, out_bytes, short):
     assert rules.short_k_steps(M, N, K, out_bytes) == short
 
 
+def stages_per_wave(K, split):
+    return -(-K // 128) // (2 if split == D64H else 4)
+
+
+# The sizes of the GPU tests reach every split of the small-product kernel and every instance of the tiled one: a retuned
+# rule that empties their coverage fails here.
+def test_sizes_of_the_gpu_tests_reach_every_path(rules):
+    import test_dispatch_gpu as sizes
+    plans = [(K, route(rules, M, N, K)) for M, N, K in sizes.SMALL]
+    assert all(rows == 0 for _, (rows, _) in plans)
+    assert {(split, K % 128) for K, (_, split) in plans} == {(s, h) for s in (D32, D64, D64H) for h in (0, 64)}
+    assert {split for K, (_, split) in plans if stages_per_wave(K, split) > 2} == {D32, D64, D64H}
+    plans = [(K, route(rules, M, N, K, 4, F8)) for M, N, K in sizes.SMALL_F8]
+    assert all(rows == 0 for _, (rows, _) in plans)
+    assert {split for K, (_, split) in plans if stages_per_wave(K, split) > 2} == {D32, D64, D64H}
+    for kind, out_bytes in ((PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (LONG_EPILOGUE, 4)):
+        seen = set()
+        for M, N, K in sizes.SPLIT:
+            rows, split = route(rules, M, N, K, out_bytes, kind)
+            assert rows > 0, (M, N, K)
+            seen.add(("small" if rules.few_tiles(rows, N, 256) else "large",
+                      "short" if rules.short_k_steps(rows, N, K, out_bytes) else "half" if K % 128 else "whole",
+                      split != NONE))
+        assert seen >= {("small", "half", False), ("large", "half", False), ("large", "short", False),
+                        ("large", "whole", True), ("large", "half", True)}, (kind, out_bytes, seen)
+    plans = [(M, rules.few_tiles(M, N, 256), route(rules, M, N, K, 4, F8)) for M, N, K in sizes.TILES_F8]
+    assert {(bool(few), rows < M) for M, few, (rows, _) in plans} == {(True, False), (False, True)}
+    assert all(rows > 0 for _, _, (rows, _) in plans)
+
+
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])
 def test_persistent_grid(rules, slots):
     for tiles in list(range(0, 4 * slots + 20)) + [10 ** 6, 2 ** 31]:
