@@ -196,8 +196,8 @@ int switchback_forward_bias_layerscale(const void *x_bf16, const void *w_bf16, c
  *   state = absmax (binary32), t = 1/state (one correctly rounded divide; zero or overflowing rows give zero codes and
  *   state 0), code = float8cast(fl(x * t)) with round-to-nearest-even onto the format's values, subnormals included;
  *   out[i,j] = (state_row[i] * state_tensor) * sum_k value(aq[i,k]) value(bq[j,k]), the sum accumulated in binary32
- *   by the matrix instruction (order unspecified but deterministic), r_i = fl(state_row[i] * state_tensor) formed
- *   first, output rounded to nearest-even when SB_BF16.
+ *   by the matrix instruction (order unspecified but deterministic; it may depend on M and on the row's place), r_i =
+ *   fl(state_row[i] * state_tensor) formed first, output rounded to nearest-even when SB_BF16.
  * Shapes as for the int8 calls, and additionally K % 128 == 0 (n % 128 == 0 and m % 128 == 0 for the layer calls);
  * out_dtype SB_BF16 or SB_F32.  The layer calls use the int8 layer's sb_saved with its code buffers holding float8
  * bytes (same sizes).  The weight gradient of the variant is switchback_backward_weight (16 bit). */

@@ -1,12 +1,16 @@
-// The product of gemm_i8_kernel.h for few output elements: the same arithmetic and the same results, another split of
-// the work, hand-written for gfx950.
+// The product of gemm_i8_kernel.h for few output elements: the same arithmetic, another split of the work, hand-written
+// for gfx950.  int8 results are the same bits; a float8 sum is formed in up to four pieces instead of one chain.
 //
 // A product with few output tiles is bound by latency, not by matrix instructions: on 128x128 tiles a 197 x 3072
 // output is 48 workgroups for 256 compute units, and each of them walks the contraction as a serial chain of k-tiles
 // whose operands arrive one LDS stage ahead.  Here a workgroup owns a small output block (ROWS x COLS) and its waves
 // split the CONTRACTION: every wave has its own ring of LDS stages, which it alone fills and reads, so nothing waits
 // for another wave until the partial sums meet in LDS at the end.  Integer partial sums are exact, so the bits do not
-// depend on the split; the float8 sums are added in wave order.
+// depend on the split.  The float8 sums are added in wave order, so the bits of a row may depend on whether its product
+// (or its place among the last rows of a large one) takes this kernel; the group sums of the matrix instruction lie on a
+// coarse grid and binary32 mostly holds their sums exactly: over 18 products (64..4000 rows, K = 128..8192, both data
+// families) the error against binary64 is that of the tiled kernel to four digits (5.9e-5 of the result with uniform
+// codes, 8.8e-6 with normal data).
 //
 // The operands go through LDS although no two waves share them: a load straight into the registers of a matrix
 // fragment has neighbouring lanes in different rows, which the address path serves at 17-20 bytes per clock and compute
