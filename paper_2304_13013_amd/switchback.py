@@ -107,9 +107,16 @@ def _check(status):
 # A small layer's pass is bound by the host (host time of forward, backward_input and backward_weight at 64 tokens,
 # 64 -> 64: 16.8 + 13.1 + 10.4 us with Stream and c_void_p objects, 13.1 + 9.9 + 7.4 us without), so the
 # pointers go to ctypes as plain integers and the current stream is asked for its handle without a Stream object.
-def _stream():
-    """Handle of the current stream of the current device."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_getter(torch_c):
+    """A function that returns the handle of the current stream of the current device.  The two private calls are those of
+    torch 2.10; without them it goes through the public Stream object."""
+    raw, device = (getattr(torch_c, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_stream = _stream_getter(torch._C)
 
 
 def _dev(t, dtype, ndim=None):

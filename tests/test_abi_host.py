@@ -228,3 +228,16 @@ def test_a_missing_library_is_an_error_not_a_fallback(monkeypatch):
         sb.load_library()
     with pytest.raises(sb.SwitchBackError):
         sb.workspace_bytes(sb.SB_OP_FORWARD, 8, 64, 64)
+
+
+def test_stream_handle_with_and_without_the_private_torch_calls(monkeypatch):
+    class With:
+        _cuda_getDevice = staticmethod(lambda: 3)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 0x1000 + device)
+
+    class Stream:
+        cuda_stream = 0x2000
+
+    assert sb._stream_getter(With)() == 0x1003
+    monkeypatch.setattr(sb.torch.cuda, "current_stream", Stream)
+    assert sb._stream_getter(object())() == 0x2000

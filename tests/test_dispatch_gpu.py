@@ -30,6 +30,13 @@ def rand_bf16(rng, shape, scale=1.0):
     return I.f32_to_bf16_bits((rng.standard_normal(shape) * scale).astype(np.float32))
 
 
+def test_stream_handle_is_the_current_streams():
+    side = torch.cuda.Stream()
+    assert sb._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert sb._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+
+
 # The rows of W follow those of X in one launch: one wavefront per row (n <= 2048, the boundary inside a workgroup),
 # one workgroup per row, and the two-pass rows (n > 16384); no rows of X at all.
 @pytest.mark.parametrize("b,n,m", [(5, 64, 128), (3, 2048, 64), (2, 2112, 64), (1, 16448, 64), (0, 256, 128)])
