@@ -9,9 +9,9 @@ namespace {
 // The three splits of the work.  D32: 32x32 blocks, four waves, two workgroups per compute unit.  D64: 64x64 blocks, four
 // waves, one workgroup per compute unit: half the operand bytes, for outputs of more than a few hundred 32x32 blocks.
 // D64H: 64x64 blocks, two waves, two workgroups per compute unit: when there are more 64x64 blocks than compute units.
-typedef DirectCfg<32, 32, 4, 2> D32;
-typedef DirectCfg<64, 64, 4, 2> D64;
-typedef DirectCfg<64, 64, 2, 2> D64H;
+typedef DirectCfg<32, 32, 4> D32;
+typedef DirectCfg<64, 64, 4> D64;
+typedef DirectCfg<64, 64, 2> D64H;
 
 template <class C>
 hipError_t launch_direct(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI8Args a, hipStream_t stream) {

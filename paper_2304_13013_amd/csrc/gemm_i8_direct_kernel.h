@@ -24,9 +24,10 @@
 
 namespace sb {
 
-template <int ROWS_, int COLS_, int WAVES_, int STAGES_>
+template <int ROWS_, int COLS_, int WAVES_>
 struct DirectCfg {
-    static constexpr int ROWS = ROWS_, COLS = COLS_, WAVES = WAVES_, STAGES = STAGES_;
+    static constexpr int ROWS = ROWS_, COLS = COLS_, WAVES = WAVES_;
+    static constexpr int STAGES = 2;  // of a wave's ring
     static constexpr int RB = ROWS / 32, CB = COLS / 32, THREADS = 64 * WAVES;
     static constexpr int BK = 128;                          // bytes of k per stage: one cache line per operand row
     static constexpr int STAGE_BYTES = (ROWS + COLS) * BK;  // token rows, then weight rows
@@ -35,7 +36,7 @@ struct DirectCfg {
     static constexpr int WAVE_BYTES = STAGES * STAGE_BYTES;  // a wave's ring; its partial sums follow in the same place
     static constexpr int LDS_BYTES = WAVES * WAVE_BYTES;
     static constexpr int QUADS = ROWS * COLS >= 8 * THREADS ? 2 : 1;  // column quads a lane finishes and stores at once
-    static_assert(ROWS % 32 == 0 && (COLS == 32 || COLS == 64) && STAGES >= 2 && STAGES <= 4, "configuration");
+    static_assert(ROWS % 32 == 0 && (COLS == 32 || COLS == 64), "configuration");
     static_assert(LDS_BYTES <= 160 * 1024 && ROWS * PITCH * 4 <= WAVE_BYTES, "LDS");
     static_assert(REQ * (STAGES - 1) < 64, "vmcnt range");
 };

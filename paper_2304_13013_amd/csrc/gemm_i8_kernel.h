@@ -10,8 +10,9 @@
 //   * 256x256 output tile per workgroup of eight waves, two per SIMD; a wave tile is 64 columns wide and 128 rows
 //     high (96 and 160 with the uneven split below).  A persistent grid (one workgroup per compute unit) walks the
 //     tiles in an order that keeps the workgroups of one XCD (workgroup id % 8) on a compact patch of tiles, so its
-//     L2 sees each operand panel once.  The tile and the wave grid are parameters of GemmI8Cfg; the other instance in
-//     use is 128x128 with four waves, two workgroups per compute unit, for products with few tiles.
+//     L2 sees each operand panel once.  The tile and the wave grid are parameters of GemmI8Cfg; the other instances in
+//     use are 128x128 tiles with four waves, two workgroups per compute unit, for products with few tiles, and 256x256
+//     tiles with 64-byte k-steps for some short contractions.
 //   * Operand tiles go HBM/L2 -> LDS with buffer_load_dwordx4 ... lds (no VGPR staging), STAGES deep.  One wave
 //     instruction fills 1 KiB of LDS linearly, so the bank-conflict-avoiding swizzle is applied on the GLOBAL side:
 //     LDS slot (row, p) holds 16-byte k-chunk p ^ f(row) of that row, f(row) = (row / (256/BK)) % (BK/16).  Rows past
@@ -25,7 +26,8 @@
 //     With LOADERS = 4 only waves 0..3 issue them, all right after the stage hand-over barrier: waves w and w+4
 //     share a SIMD, so while a loader wave is stuck issuing its partner has the matrix pipe to itself, and the
 //     loader runs its MFMAs afterwards.  MT_LOADER = 3 evens out the two chains: the loader computes 3 of the 8
-//     32-row blocks of its wave column, its partner 5.  With LOADERS = 8 every wave issues its share at the hand-over.
+//     32-row blocks of its wave column, its partner 5.  With LOADERS = 8 (the 64-byte k-steps) every wave issues its
+//     share at the hand-over.
 //   * MFMA operand fragments are double-buffered in registers, and the LDS reads of k-step j+1 are issued one at a
 //     time between the MFMAs of k-step j (also across the stage hand-over): an LDS read issued in the shadow of an
 //     MFMA costs no issue time.  The reads are inline asm so that the lgkmcnt waits can be counted; the compiler's
