@@ -158,8 +158,8 @@ def assert_bias_layerscale(got32, got_bf16_bits, acc, srow, sw, bias, gamma, ora
 @pytest.mark.parametrize("which", ["both", "bias", "gamma", "neither"])
 @pytest.mark.parametrize("M,N,K", [(300, 320, 192), (512, 1024, 256), (4096, 2304, 256), (1000, 4160, 320)])
 def test_bias_layerscale_product(oracle, M, N, K, which):
-    """All three kernel instances: 64-byte k-steps (K = 192, 320), the 128x128 tile (8 large tiles), the 256x256 tile
-    over more than one round of a 256-workgroup grid would need > 256 tiles; 144 tiles run one round."""
+    """The small-product kernel (300 x 320 with half a last stage, 512 x 1024), the 256x256 tile (144 tiles, one round) and
+    the 128x128 tile (1000 x 4160, half a last stage)."""
     rng = np.random.default_rng(M + N + K)
     a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
     b = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
@@ -535,9 +535,9 @@ def check_int8_product_whole(oracle, a, b, srow, sw):
 @pytest.mark.parametrize("M,N,K", [(4096, 4608, 128), (4096, 4608, 192), (32896, 1280, 192), (6304, 3072, 768),
                                    (2000, 9280, 320), (6304, 768, 3072), (3000, 1984, 256)])
 def test_int8_product_whole_output_over_several_rounds(oracle, M, N, K):
-    """288 to 645 output tiles on at most 256 workgroups: two to three tiles per workgroup, with both k-step
-    instances (K a multiple of 128, and of 64 only), short and long contractions, ragged M.  The last two shapes have
-    few large tiles (75 and 96) and take the 128x128-tile instance, two workgroups per compute unit, ragged M and N."""
+    """288 to 645 output tiles on at most 256 workgroups: two to three tiles per workgroup, with whole last stages and half
+    ones (K = 64 mod 128), short and long contractions, ragged M.  The last two shapes have few large tiles (75 and 96)
+    and take the 128x128-tile instance, two workgroups per compute unit, ragged M and N."""
     rng = np.random.default_rng(M + 3 * N + 7 * K)
     a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
     b = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
@@ -945,8 +945,8 @@ def test_float8_layer_is_deterministic_and_rejects_unsupported_widths():
 
 
 # ---------------------------------------------------------------------------------------------------------------
-# seeded random shapes: ragged M, every multiple-of-64 width class, all kernel instances (which one runs depends on
-# K % 128 and on the tile count), every output mode, whole outputs
+# seeded random shapes: ragged M, every multiple-of-64 width class, small and tiled products (which one runs depends on
+# the output's size, and the instance on K % 128 and the tile count), every output mode, whole outputs
 # ---------------------------------------------------------------------------------------------------------------
 
 def random_shapes(seed, count, max_m, max_n, max_k):
