@@ -24,6 +24,12 @@ __global__ __launch_bounds__(Small::THREADS) __attribute__((amdgpu_waves_per_eu(
     gemm_bf16_tn_body<Small>(p);
 }
 
+// One item per tile, its token range summed in pieces (Plan).
+__global__ __launch_bounds__(Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16_tn_small_fold_kernel(
+    GemmBf16Args p) {
+    gemm_bf16_tn_body<Small, true>(p);
+}
+
 // out[e] = sum over splits (ascending) of partial[s][e]; four elements per thread.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const v4f *__restrict__ partial, int64_t quads,
                                                             int splits, void *__restrict__ out, int out_bf16) {
@@ -60,10 +66,8 @@ int choose_splits_big(int64_t b, int tiles, int ncu) {
 // second-best count on all of them), in units of one stage of a workgroup that shares its compute unit (1.1 us):
 // every round of the persistent grid costs the stages of an item, at 0.64 of the unit while the round has at most one
 // workgroup per compute unit and rising linearly to the full unit at two; the partial sums are written once and read
-// once per split, plus the output pass, at 2.9 TB/s, by a launch that costs 3 us (2.7 units) besides: without that term
-// 512 tokens of a 256 -> 1024 layer were split in two (7.3 + 2.4 us and the second launch's host time; 7.7 us unsplit,
-// the step 35.2 -> 32.4 us).
-int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n) {
+// once per split, plus the output pass, at 2.9 TB/s, by a launch that costs launch_cost besides.
+int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n, double launch_cost) {
     const int64_t stages = (b + Small::BKT - 1) / Small::BKT;
     const double pass = (double)m * (double)n * 4.0 / (2.9e12 * 1.1e-6);  // one pass over m x n floats, in stage units
     int best = 1;
@@ -71,7 +75,7 @@ int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n) {
     for (int s = 1; s <= MAX_SPLITS; ++s) {
         if ((int64_t)s * Small::BKT * 4 > b && s > 1) break;
         const double per_item = (double)((stages + s - 1) / s);
-        double cost = s > 1 ? (s + 0.5) * pass + 2.7 : 0.0;
+        double cost = s > 1 ? (s + 0.5) * pass + launch_cost : 0.0;
         for (int left = tiles * s; left > 0; left -= 2 * ncu) {
             const int k = left < 2 * ncu ? left : 2 * ncu;
             cost += per_item * (k <= ncu ? 0.64 : 0.64 + 0.36 * (double)(k - ncu) / ncu);
@@ -84,9 +88,17 @@ int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n) {
     return best;
 }
 
+// The launch that adds the partial sums costs 3 us (2.7 units) and its host time: without that term 512 tokens of a 256 ->
+// 1024 layer are split in two (7.3 + 2.4 us; 7.7 us unsplit, the step 35.2 -> 32.4 us).
+constexpr double kReduceLaunchCost = 2.7;
+
+// pieces > 1: one item per tile, summed in as many pieces as the splits that the launch's cost was not worth (two or
+// three): the bits of the split product.  One chain over all tokens is 0.3 to 0.5 us faster (524 x 576 x 704: 7.5 / 8.0 us,
+// split 9.5) but further from the exact sum (512 tokens, 256 -> 1024, binary32 gradient: relative error 0.90e-7 in two
+// pieces, 1.25e-7 in one chain).
 struct Plan {
     bool small;
-    int tiles_m, tiles_n, splits, k_per_split;
+    int tiles_m, tiles_n, splits, k_per_split, pieces, k_per_piece;
 };
 
 // The instance and the split count are functions of the shape alone, so the workspace query and the launch agree.
@@ -98,13 +110,16 @@ Plan plan_of(int64_t b, int64_t n, int64_t m) {
     p.tiles_m = (int)((m + Big::BM - 1) / Big::BM);
     p.tiles_n = (int)((n + Big::BN - 1) / Big::BN);
     p.splits = choose_splits_big(b, p.tiles_m * p.tiles_n, ncu);
+    p.pieces = 1;
     if (p.splits > 1 && stages / p.splits < kShortItemStages) {
         p.small = true;
         p.tiles_m = (int)((m + Small::BM - 1) / Small::BM);
         p.tiles_n = (int)((n + Small::BN - 1) / Small::BN);
-        p.splits = choose_splits_small(b, p.tiles_m * p.tiles_n, ncu, m, n);
+        p.splits = choose_splits_small(b, p.tiles_m * p.tiles_n, ncu, m, n, kReduceLaunchCost);
+        if (p.splits == 1) p.pieces = choose_splits_small(b, p.tiles_m * p.tiles_n, ncu, m, n, 0.0);
     }
     p.k_per_split = (int)((stages + p.splits - 1) / p.splits) * Big::BKT;
+    p.k_per_piece = (int)((stages + p.pieces - 1) / p.pieces) * Big::BKT;
     return p;
 }
 
@@ -126,10 +141,11 @@ size_t gemm_bf16_tn_workspace_bytes(int64_t b, int64_t n, int64_t m) {
 
 hipError_t launch_gemm_bf16_tn(const void *dy, const void *x, int64_t b, int64_t n, int64_t m, void *dw,
                                sb_dtype dw_dtype, void *ws, hipStream_t stream) {
-    static std::atomic<bool> big_set{false}, small_set{false};
+    static std::atomic<bool> big_set{false}, small_set{false}, fold_set{false};
     const Plan plan = plan_of(b, n, m);
-    hipError_t e = plan.small ? set_lds_limit_once<Small>(gemm_bf16_tn_small_kernel, small_set)
-                              : set_lds_limit_once<Big>(gemm_bf16_tn_kernel, big_set);
+    hipError_t e = plan.pieces > 1 ? set_lds_limit_once<Small>(gemm_bf16_tn_small_fold_kernel, fold_set)
+                   : plan.small    ? set_lds_limit_once<Small>(gemm_bf16_tn_small_kernel, small_set)
+                                   : set_lds_limit_once<Big>(gemm_bf16_tn_kernel, big_set);
     if (e != hipSuccess) return e;
     GemmBf16Args a;
     a.dy = static_cast<const unsigned short *>(dy);
@@ -141,6 +157,7 @@ hipError_t launch_gemm_bf16_tn(const void *dy, const void *x, int64_t b, int64_t
     a.tiles_n = plan.tiles_n;
     a.splits = plan.splits;
     a.k_per_split = plan.k_per_split;
+    a.k_per_piece = plan.k_per_piece;
     a.partial = static_cast<float *>(ws);
     a.out = dw;
     a.out_bf16 = dw_dtype == SB_BF16;
@@ -149,7 +166,9 @@ hipError_t launch_gemm_bf16_tn(const void *dy, const void *x, int64_t b, int64_t
     const int per_xcd = (total + 7) / 8, cus_per_xcd = num_compute_units() / 8 > 0 ? num_compute_units() / 8 : 1;
     const int slots_per_xcd = cus_per_xcd * (plan.small ? 2 : 1);
     const int grid = 8 * (per_xcd < slots_per_xcd ? per_xcd : slots_per_xcd);
-    if (plan.small)
+    if (plan.pieces > 1)
+        gemm_bf16_tn_small_fold_kernel<<<grid, Small::THREADS, Small::LDS_BYTES, stream>>>(a);
+    else if (plan.small)
         gemm_bf16_tn_small_kernel<<<grid, Small::THREADS, Small::LDS_BYTES, stream>>>(a);
     else
         gemm_bf16_tn_kernel<<<grid, Big::THREADS, Big::LDS_BYTES, stream>>>(a);

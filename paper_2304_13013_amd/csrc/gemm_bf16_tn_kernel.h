@@ -33,6 +33,7 @@ struct GemmBf16Args {
     int b, n, m;
     int tiles_m, tiles_n, splits, k_per_split;  // k_per_split is a multiple of the stage length
     int out_bf16;
+    int k_per_piece;  // FOLD instances only (splits == 1): tokens per partial sum, a multiple of the stage length
 };
 
 // TILE_ x TILE_ output tile per workgroup of WAVES_M_ x WAVES_N_ waves (wave tile TILE_/WAVES_M_ rows by 64 columns).
@@ -69,7 +70,9 @@ struct GemmBf16Cfg {
 
 // What one wave does: an (MT*32) x 64 part of the workgroup's tile, rows from wm0.  Every role runs the same
 // sequence of barriers.
-template <class C, int MT>
+// FOLD: the token range is one item, but its pieces of k_per_piece tokens are summed on their own and added in token
+// order, in registers: the bits of the split product and its reduction, without the second launch.
+template <class C, int MT, bool FOLD>
 __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const int wave, const int wm0) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
@@ -275,13 +278,47 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
                 }
             }
         };
+        v16f pieces[FOLD ? MT : 1][FOLD ? C::NT : 1];  // sum of the pieces before this one
+        int piece_left = FOLD ? p.k_per_piece / C::BKT : 0;
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < C::NT; ++nt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) pieces[mt][nt][r] = 0.0f;
+        }
+        auto end_piece = [&]() {
+            if constexpr (FOLD) {
+                piece_left = p.k_per_piece / C::BKT;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < C::NT; ++nt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            pieces[mt][nt][r] += acc[mt][nt][r];
+                            acc[mt][nt][r] = 0.0f;
+                        }
+            }
+        };
         if (KT > 0) {
             if (loader) wait_stage<C::LPW, 0>(issued_upto);
             block_barrier();
 #pragma unroll
             for (int i = 0; i < NFRAG; ++i) issue_frag_read(i, 0, 0, 0);
-            for (int kt = 0; kt + 1 < KT; ++kt) k_tile(kt, std::false_type());
+            for (int kt = 0; kt + 1 < KT; ++kt) {
+                k_tile(kt, std::false_type());
+                if (FOLD && --piece_left == 0) end_piece();
+            }
             k_tile(KT - 1, std::true_type());
+            if constexpr (FOLD) {
+                end_piece();
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < C::NT; ++nt) acc[mt][nt] = pieces[mt][nt];
+            }
         }
 
         const int m_base = tm * C::BM + wm0, n_base = tn * C::BN + wn0;
@@ -360,15 +397,15 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
 
 // The kernel body; the __global__ entry that calls it lives next to the launcher (a __global__ template that uses
 // device-only buffer builtins does not instantiate in the host pass).
-template <class C>
+template <class C, bool FOLD = false>
 __device__ __forceinline__ void gemm_bf16_tn_body(const GemmBf16Args &p) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
     if (C::MT_LOADER == C::MT_EVEN)
-        gemm_bf16_tn_role<C, C::MT_EVEN>(p, wave, (wave / C::WAVES_N) * C::WTM);
+        gemm_bf16_tn_role<C, C::MT_EVEN, FOLD>(p, wave, (wave / C::WAVES_N) * C::WTM);
     else if (wave < C::LOADERS)
-        gemm_bf16_tn_role<C, C::MT_LOADER>(p, wave, 0);
+        gemm_bf16_tn_role<C, C::MT_LOADER, FOLD>(p, wave, 0);
     else
-        gemm_bf16_tn_role<C, 2 * C::MT_EVEN - C::MT_LOADER>(p, wave, C::MT_LOADER * 32);
+        gemm_bf16_tn_role<C, 2 * C::MT_EVEN - C::MT_LOADER, FOLD>(p, wave, C::MT_LOADER * 32);
 }
 
 }  // namespace sb

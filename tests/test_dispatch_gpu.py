@@ -220,6 +220,20 @@ def test_few_rows_of_a_very_wide_output(oracle, M, N=32832, K=2048):
     assert torch.equal(got, (a8.double() @ b8.double().t()).float() * (dev[1] * st)[:, None])
 
 
+# Small weight gradients whose reduction launch is not worth its cost still sum the tokens in the pieces of the split they
+# replace, in two or three (the last one ragged): the bits of the gradients over those token ranges, added in order.
+@pytest.mark.parametrize("b,n,m,piece", [(512, 256, 1024, 256), (758, 3264, 256, 384), (641, 384, 2048, 384),
+                                         (1016, 896, 1024, 384)])
+def test_small_weight_gradient_sums_its_pieces(b, n, m, piece):
+    rng = np.random.default_rng(b + n + m)
+    x, dy = to_dev(rand_bf16(rng, (b, n))), to_dev(rand_bf16(rng, (b, m), 0.1))
+    want = torch.zeros(m, n, device=DEV)
+    for lo in range(0, b, piece):
+        want += sb.backward_weight(dy[lo:lo + piece], x[lo:lo + piece], dw_dtype=torch.float32)
+    assert torch.equal(sb.backward_weight(dy, x, dw_dtype=torch.float32), want)
+    assert torch.equal(sb.backward_weight(dy, x), want.bfloat16())
+
+
 # A step whose arrays exceed the last-level cache (24 million elements in four tensors, 20 million in one: 280 to 390 MB;
 # the second pass runs backwards and non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
 # agrees with the binary64 evaluation; ragged counts, so that the last workgroups are partial.
