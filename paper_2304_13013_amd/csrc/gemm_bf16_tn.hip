@@ -89,7 +89,7 @@ int choose_splits_small(int64_t b, int tiles, int ncu, int64_t m, int64_t n, dou
 }
 
 // The launch that adds the partial sums costs 3 us (2.7 units) and its host time: without that term 512 tokens of a 256 ->
-// 1024 layer are split in two (7.3 + 2.4 us; 7.7 us unsplit, the step 35.2 -> 32.4 us).
+// 1024 layer are split in two (7.3 + 2.4 us; 8.2 us unsplit, the step 35.2 -> 32.4 us).
 constexpr double kReduceLaunchCost = 2.7;
 
 // pieces > 1: one item per tile, summed in as many pieces as the splits that the launch's cost was not worth (two or
