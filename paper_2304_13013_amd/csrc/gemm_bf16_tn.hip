@@ -1,33 +1,35 @@
 // Host-side dispatch of the bf16 weight-gradient GEMM (kernel: gemm_bf16_tn_kernel.h) and its split-K reduction.
-#include "gemm_bf16_tn_kernel.h"
+#include "gemm_bf16_tn_wide_kernel.h"
 
 #include <atomic>
 
 namespace sb {
 namespace {
 
-// Two 64-token stages, four loader waves; a loader wave computes 3 of the 8 row blocks of its wave column, its SIMD
-// partner 5 (with the tile walk below this measures 0-7 % faster than the even split on all four ViT-H shapes).
-typedef GemmBf16Cfg<2, 4, 3> Big;
-// 128 x 128 tiles, four waves (all load), two workgroups per compute unit: for weight gradients that the large tile
-// could only spread over the GPU by cutting the token range into many short pieces, where the start and end of an item
-// weigh more than the doubled operand traffic (ViT-B/16 sized layers: 10-29 % faster; within 5 % of the large tile at
-// equal fill, slower on every ViT-L and ViT-H layer but ViT-L's 1024 x 1024 projection).
-typedef GemmBf16Cfg<2, 4, 2, 64, 128, 2, 2> Small;
-static_assert(Big::BKT == Small::BKT, "the split lengths below are in stages of either instance");
+// 256 x 256 tiles, four waves of 128 x 128.
+typedef WideCfg Big;
+// 128 x 128 tiles, two workgroups per compute unit: for weight gradients that the large tile could only spread over the GPU
+// by cutting the token range into many short pieces, where the start and end of an item weigh more than the doubled
+// operand traffic.
+typedef GemmBf16Cfg Small;
+static_assert(Big::UNIT == Small::BKT, "the split lengths below are in pairs of stages of one, stages of the other");
 constexpr int MAX_SPLITS = 16;
 constexpr int kShortItemStages = 32;  // below this many stages per work item the large tile loses to the small one
 
-__global__ __launch_bounds__(Big::THREADS) void gemm_bf16_tn_kernel(GemmBf16Args p) { gemm_bf16_tn_body<Big>(p); }
+// One wave per SIMD: all 512 registers are a lane's.
+__global__ __launch_bounds__(Big::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_tn_kernel(
+    GemmBf16Args p) {
+    gemm_bf16_tn_wide_body(p);
+}
 __global__ __launch_bounds__(Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16_tn_small_kernel(
     GemmBf16Args p) {
-    gemm_bf16_tn_body<Small>(p);
+    gemm_bf16_tn_body<false>(p);
 }
 
 // One item per tile, its token range summed in pieces (Plan).
 __global__ __launch_bounds__(Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16_tn_small_fold_kernel(
     GemmBf16Args p) {
-    gemm_bf16_tn_body<Small, true>(p);
+    gemm_bf16_tn_body<true>(p);
 }
 
 // out[e] = sum over splits (ascending) of partial[s][e]; four elements per thread.
@@ -49,7 +51,7 @@ int choose_splits_big(int64_t b, int tiles, int ncu) {
     int best = 1;
     double best_score = -1.0;
     for (int s = 1; s <= MAX_SPLITS; ++s) {
-        if ((int64_t)s * Big::BKT * 4 > b && s > 1) break;
+        if ((int64_t)s * Big::UNIT * 4 > b && s > 1) break;
         const int blocks = tiles * s;
         const int rounds = (blocks + ncu - 1) / ncu;
         const double score = (double)blocks / (rounds * ncu) - 0.015 * s;
@@ -104,22 +106,26 @@ struct Plan {
 // The instance and the split count are functions of the shape alone, so the workspace query and the launch agree.
 Plan plan_of(int64_t b, int64_t n, int64_t m) {
     const int ncu = num_compute_units();
-    const int64_t stages = (b + Big::BKT - 1) / Big::BKT;
+    const int64_t stages = (b + Big::UNIT - 1) / Big::UNIT;
     Plan p;
     p.small = false;
     p.tiles_m = (int)((m + Big::BM - 1) / Big::BM);
     p.tiles_n = (int)((n + Big::BN - 1) / Big::BN);
     p.splits = choose_splits_big(b, p.tiles_m * p.tiles_n, ncu);
     p.pieces = 1;
-    if (p.splits > 1 && stages / p.splits < kShortItemStages) {
+    if (stages == 0 || (p.splits > 1 && stages / p.splits < kShortItemStages)) {  // the large tile has no empty items
         p.small = true;
         p.tiles_m = (int)((m + Small::BM - 1) / Small::BM);
         p.tiles_n = (int)((n + Small::BN - 1) / Small::BN);
         p.splits = choose_splits_small(b, p.tiles_m * p.tiles_n, ncu, m, n, kReduceLaunchCost);
         if (p.splits == 1) p.pieces = choose_splits_small(b, p.tiles_m * p.tiles_n, ncu, m, n, 0.0);
     }
-    p.k_per_split = (int)((stages + p.splits - 1) / p.splits) * Big::BKT;
-    p.k_per_piece = (int)((stages + p.pieces - 1) / p.pieces) * Big::BKT;
+    if (!p.small) {  // whole stages: the last split may have become empty
+        const int64_t per_split = (stages + p.splits - 1) / p.splits;
+        p.splits = (int)((stages + per_split - 1) / per_split);
+    }
+    p.k_per_split = (int)((stages + p.splits - 1) / p.splits) * Big::UNIT;
+    p.k_per_piece = (int)((stages + p.pieces - 1) / p.pieces) * Big::UNIT;
     return p;
 }
 

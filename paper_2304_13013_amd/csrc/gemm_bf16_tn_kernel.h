@@ -9,10 +9,10 @@
 // i/4+8 and i/4+12, so with lane r addressing token r/4 and columns 4*(r%4).. a lane receives one column at four
 // consecutive tokens; two such reads make the 8-token operand of v_mfma_f32_32x32x16_bf16.
 //
-// Pipeline, wave roles and barriers are those of the int8 kernel (gemm_i8_kernel.h): 256x256 tile, 8 waves with
-// 128x64 wave tiles, two LDS stages of 64 tokens, four loader waves, fragment reads issued between the MFMAs of
-// the preceding k-step, bare s_barrier with counted waits.  A second instance has 128x128 tiles and four waves with
-// 64x64 wave tiles, two workgroups per compute unit.
+// This kernel: 128x128 tiles, four waves of 64x64, two workgroups per compute unit, for weight gradients with few tiles
+// and short token ranges.  Pipeline and barriers are those of the int8 kernel (gemm_i8_kernel.h): two LDS stages of 64
+// tokens, fragment reads issued between the MFMAs of the preceding k-step, bare s_barrier with counted waits.  Long
+// ranges run gemm_bf16_tn_wide_kernel.h.
 // The X-side tile is the MFMA's first operand and the dY-side tile its second, so a lane owns one dW row.
 //
 // The contraction is long (b ~ 32k) and the output small, so work items are (split, tile) pairs (split-K); they are
@@ -36,44 +36,35 @@ struct GemmBf16Args {
     int k_per_piece;  // FOLD instances only (splits == 1): tokens per partial sum, a multiple of the stage length
 };
 
-// TILE_ x TILE_ output tile per workgroup of WAVES_M_ x WAVES_N_ waves (wave tile TILE_/WAVES_M_ rows by 64 columns).
-// The default is the 256 x 256 tile of eight waves, one workgroup per compute unit.  The 128 x 128 tile of four waves
-// takes 80 KiB of LDS, so two workgroups share a compute unit; it moves twice the operand bytes per multiply-add and
-// serves weight gradients with too few large tiles to fill the GPU without many splits.
-template <int STAGES_ = 2, int LOADERS_ = 4, int MT_LOADER_ = 4, int BKT_ = 64, int TILE_ = 256, int WAVES_M_ = 2,
-          int WAVES_N_ = 4>
+// 80 KiB of LDS, so two workgroups share a compute unit; all four waves load.
 struct GemmBf16Cfg {
-    static constexpr int BM = TILE_, BN = TILE_, BKT = BKT_;  // dW rows (dY columns), dW columns (X columns), tokens/stage
-    static constexpr int PITCH = TILE_ * 2;                   // bytes of one token row of an operand tile in LDS
+    static constexpr int BM = 128, BN = 128, BKT = 64;        // dW rows (dY columns), dW columns (X columns), tokens/stage
+    static constexpr int PITCH = BM * 2;                      // bytes of one token row of an operand tile in LDS
     static constexpr int CHUNKS = PITCH / 16;                 // 16-byte column chunks per token row
     static constexpr int ROWS_PER_REQ = 1024 / PITCH;         // token rows one 1 KiB request fills
-    static constexpr int NVOFF = 4 / ROWS_PER_REQ;            // distinct (token % 4) swizzles among a wave's requests
     static constexpr int REQ_OP = BKT / ROWS_PER_REQ;         // 1 KiB requests per operand tile
-    static constexpr int STAGES = STAGES_, LOADERS = LOADERS_;
-    static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, NWAVES = WAVES_M * WAVES_N, THREADS = NWAVES * 64;
-    static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N, NT = WTN / 32;
-    static constexpr int MT_EVEN = WTM / 32;                  // 32-row MFMA blocks per wave tile when all waves get the same
-    static constexpr int MT_LOADER = MT_LOADER_;  // 32-row MFMA blocks of a loader wave's tile; when < MT_EVEN its SIMD partner
-                                                  // (wave + 4) takes the other 2 * MT_EVEN - MT_LOADER blocks of the wave column
+    static constexpr int STAGES = 2;
+    static constexpr int WAVES_M = 2, WAVES_N = 2, NWAVES = WAVES_M * WAVES_N, THREADS = NWAVES * 64;
+    static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N, MT = WTM / 32, NT = WTN / 32;
     static constexpr int KK = BKT / 16;                       // MFMA k-steps (16 tokens) per stage
     static constexpr int OP_BYTES = BKT * PITCH;              // one operand tile: BKT token rows
     static constexpr int STAGE_BYTES = 2 * OP_BYTES;          // dY tile then X tile
-    static constexpr int LPW = STAGE_BYTES / 1024 / LOADERS;  // 1 KiB requests (of one operand) per loader wave
+    static constexpr int LPW = STAGE_BYTES / 1024 / NWAVES;   // 1 KiB requests (of one operand) per wave
     static constexpr int EPI_WAVE_BYTES = 32 * WTN * 2, EPI_PIECES = WTN * 2 / 16;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + NWAVES * EPI_WAVE_BYTES;
-    static_assert(STAGES >= 2 && LDS_BYTES <= 160 * 1024 && (LOADERS == 4 || LOADERS == 8) && LOADERS <= NWAVES, "configuration");
-    static_assert((TILE_ == 256 || TILE_ == 128) && NT == 2 && MT_EVEN >= 2 && MT_EVEN <= 4, "tile");
-    static_assert(MT_LOADER == MT_EVEN || (LOADERS == 4 && NWAVES == 8 && WAVES_M == 2 && MT_LOADER == 3), "uneven split");
-    static_assert((BKT == 64 || BKT == 32) && LPW % NVOFF == 0 && REQ_OP % LPW == 0, "stage length");
-    static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
+    static_assert(LDS_BYTES <= 80 * 1024 && ROWS_PER_REQ == 4 && MT == 2 && NT == 2 && REQ_OP % LPW == 0, "configuration");
 };
 
-// What one wave does: an (MT*32) x 64 part of the workgroup's tile, rows from wm0.  Every role runs the same
-// sequence of barriers.
 // FOLD: the token range is one item, but its pieces of k_per_piece tokens are summed on their own and added in token
 // order, in registers: the bits of the split product and its reduction, without the second launch.
-template <class C, int MT, bool FOLD>
-__device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const int wave, const int wm0) {
+// (A __device__ function: a __global__ template that uses device-only buffer builtins does not instantiate in the host
+// pass; the __global__ entries live next to the launcher.)
+template <bool FOLD>
+__device__ __forceinline__ void gemm_bf16_tn_body(const GemmBf16Args &p) {
+    typedef GemmBf16Cfg C;
+    constexpr int MT = C::MT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
+    const int wm0 = (wave / C::WAVES_N) * C::WTM;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
     constexpr int S = C::STAGES;
@@ -82,17 +73,14 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
     const int wn0 = (wave % C::WAVES_N) * C::WTN;
     const int frow = lane & 31, fhalf = lane >> 5;
 
-    // Loader role (see the int8 kernel for why only LOADERS waves issue requests, all right after a hand-over).
-    // Request i of loader wave w fills 1 KiB = ROWS_PER_REQ consecutive token rows of one operand tile, the
+    // Request i of wave w fills 1 KiB = ROWS_PER_REQ consecutive token rows of one operand tile, the
     // ((w*LPW + i) % REQ_OP)-th such group; the first REQ_OP requests of a stage load dY, the rest X, so a wave loads
     // one operand only.  LDS slot (token, p) holds 16-byte column chunk p ^ ((token & 3) << 2): token rows are a
     // multiple of 256 bytes apart, so without it the four token rows one transposing read touches would all fall into
     // the same 64-byte bank window.  A lane's byte offset is
-    //   voff[i % NVOFF] (per lane: its token row of the group, its swizzled chunk) + i * req_step + item_soff
-    //   + kt * stage_step.
+    //   voff (per lane: its token row of the group, its swizzled chunk) + i * req_step + item_soff + kt * stage_step.
     // Columns past the operand's width (partial tiles) read the next token row or, at the very end, zeros from the
     // bounds check; they only feed results that are never stored.
-    const bool loader = wave < C::LOADERS;
     const bool loads_dy = wave * C::LPW < C::REQ_OP;
     const unsigned ld = loads_dy ? p.m : p.n;  // row length of the operand this wave loads
     // The bounds check of the buffer resource (num_records in bytes) turns token rows past b into zeros.
@@ -100,10 +88,7 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
         (void *)(loads_dy ? p.dy : p.x), 0, (unsigned)((size_t)p.b * ld * 2), 0x00020000);
     const int l_tok = lane / C::CHUNKS, l_pos = lane % C::CHUNKS;  // token row of the request, 16-byte chunk of it
     const int tok0 = ((wave * C::LPW) % C::REQ_OP) * C::ROWS_PER_REQ;  // first token row of the wave's share within a stage
-    unsigned voff[C::NVOFF];
-#pragma unroll
-    for (int v = 0; v < C::NVOFF; ++v)
-        voff[v] = ((unsigned)l_tok * ld + ((l_pos ^ (((C::ROWS_PER_REQ * v + l_tok) & 3) << 2)) << 3)) * 2;
+    const unsigned voff = ((unsigned)l_tok * ld + ((l_pos ^ (l_tok << 2)) << 3)) * 2;
     const unsigned req_step = (unsigned)C::ROWS_PER_REQ * 2 * ld, stage_step = (unsigned)C::BKT * 2 * ld;
     unsigned item_soff = 0;
     auto set_item_sources = [&](int tm, int tn, int k_begin) {
@@ -114,8 +99,8 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
         const unsigned soff = item_soff + (unsigned)kt * stage_step;
 #pragma unroll
         for (int i = 0; i < C::LPW; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, voff[i % C::NVOFF],
-                                                     soff + (unsigned)i * req_step, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + i * 1024), 16, voff, soff + (unsigned)i * req_step,
+                                                     0, 0);
     };
 
     // Fragment reads.  Lane l: 16-lane group g = l/16 covers columns 16*(g%2).. of the 32-column block and token
@@ -146,10 +131,8 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
         asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(4 * C::PITCH));
         return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3));
     };
-    // Fragment schedule of the int8 kernel: a k-step group issues its MFMAs in the order (g0,x0) (g0,x1) (g1,x0) ...
-    // and reads the next group's fragments in the order x0 g0 x1 g1 g2 g3, one fragment (two transposing reads) after
-    // each of its first six MFMAs.
-    static_assert(C::NT == 2, "fragment schedule below is written for MT x 2 MFMA blocks per wave");
+    // Fragment schedule of the int8 kernel: a k-step group issues its MFMAs in the order (g0,x0) (g0,x1) (g1,x0) (g1,x1)
+    // and reads the next group's fragments in the order x0 g0 x1 g1, one fragment (two transposing reads) after each.
     constexpr int NFRAG = MT + C::NT;
     auto issue_frag_read = [&](int i, int buf, int kt, int kk) {
         const unsigned base = lds_base + (kt % S) * C::STAGE_BYTES + kk * (16 * C::PITCH);
@@ -157,10 +140,7 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
             case 0: xf[buf][0] = read_pair(base + xoff[0]); break;
             case 1: gf[buf][0] = read_pair(base + goff[0]); break;
             case 2: xf[buf][1] = read_pair(base + xoff[1]); break;
-            case 3: gf[buf][1] = read_pair(base + goff[1]); break;
-            case 4: gf[buf][2 % MT] = read_pair(base + goff[2 % MT]); break;
-            case 5: gf[buf][3 % MT] = read_pair(base + goff[3 % MT]); break;
-            default: gf[buf][4 % MT] = read_pair(base + goff[4 % MT]); break;
+            default: gf[buf][1] = read_pair(base + goff[1]); break;
         }
     };
     auto pin_frag = [&](int i, int buf) {
@@ -168,10 +148,7 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
             case 0: asm volatile("" : "+v"(xf[buf][0])); break;
             case 1: asm volatile("" : "+v"(gf[buf][0])); break;
             case 2: asm volatile("" : "+v"(xf[buf][1])); break;
-            case 3: asm volatile("" : "+v"(gf[buf][1])); break;
-            case 4: asm volatile("" : "+v"(gf[buf][2 % MT])); break;
-            case 5: asm volatile("" : "+v"(gf[buf][3 % MT])); break;
-            default: asm volatile("" : "+v"(gf[buf][4 % MT])); break;
+            default: asm volatile("" : "+v"(gf[buf][1])); break;
         }
     };
     // At most n fragment reads (two LDS reads each) outstanding.
@@ -221,11 +198,9 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
     if (have) {
         KT = stages_of(split);
         set_item_sources(tm, tn, split * p.k_per_split);
-        if (loader) {
 #pragma unroll
-            for (int s = 0; s < S; ++s)
-                if (s < KT) issue_stage(s);
-        }
+        for (int s = 0; s < S; ++s)
+            if (s < KT) issue_stage(s);
     }
 
     for (int round = 0; have; ++round) {
@@ -250,10 +225,10 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
                 if (handed_over) {
                     // Stage hand-over (see the int8 kernel): this wave's reads of stage kt are retired, stage kt+1
                     // has landed, the freed stage may be refilled.
-                    if (loader) wait_stage<C::LPW, 0>(issued_upto - (kt + 1));
+                    wait_stage<C::LPW, 0>(issued_upto - (kt + 1));
                     wait_lds_reads();
                     block_barrier();
-                    if (loader && kt + S < KT) issue_stage(kt + S);
+                    if (kt + S < KT) issue_stage(kt + S);
                     issued_upto = min(KT - 1, kt + S);
                 }
                 const int cur = kk & 1, nxt = (kk + 1) & 1;
@@ -303,7 +278,7 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
             }
         };
         if (KT > 0) {
-            if (loader) wait_stage<C::LPW, 0>(issued_upto);
+            wait_stage<C::LPW, 0>(issued_upto);
             block_barrier();
 #pragma unroll
             for (int i = 0; i < NFRAG; ++i) issue_frag_read(i, 0, 0, 0);
@@ -333,11 +308,9 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
         if (have) {
             nKT = stages_of(nsplit);
             set_item_sources(ntm, ntn, nsplit * p.k_per_split);
-            if (loader) {
 #pragma unroll
-                for (int s = 0; s < S; ++s)
-                    if (s < nKT) issue_stage(s);
-            }
+            for (int s = 0; s < S; ++s)
+                if (s < nKT) issue_stage(s);
         }
 
         if (p.splits == 1 && p.out_bf16) {
@@ -393,19 +366,6 @@ __device__ __forceinline__ void gemm_bf16_tn_role(const GemmBf16Args &p, const i
         split = nsplit;
         KT = nKT;
     }
-}
-
-// The kernel body; the __global__ entry that calls it lives next to the launcher (a __global__ template that uses
-// device-only buffer builtins does not instantiate in the host pass).
-template <class C, bool FOLD = false>
-__device__ __forceinline__ void gemm_bf16_tn_body(const GemmBf16Args &p) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
-    if (C::MT_LOADER == C::MT_EVEN)
-        gemm_bf16_tn_role<C, C::MT_EVEN, FOLD>(p, wave, (wave / C::WAVES_N) * C::WTM);
-    else if (wave < C::LOADERS)
-        gemm_bf16_tn_role<C, C::MT_LOADER, FOLD>(p, wave, 0);
-    else
-        gemm_bf16_tn_role<C, 2 * C::MT_EVEN - C::MT_LOADER, FOLD>(p, wave, C::MT_LOADER * 32);
 }
 
 }  // namespace sb

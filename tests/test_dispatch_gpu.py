@@ -234,6 +234,22 @@ def test_small_weight_gradient_sums_its_pieces(b, n, m, piece):
     assert torch.equal(sb.backward_weight(dy, x), want.bfloat16())
 
 
+# The 256x256 tiles of the weight gradient: fewer tokens than a stage, one short of a stage and one past it, one past a pair
+# of stages, a second item per workgroup (289 tiles), tiles that are partial in both directions.  Every element; a binary32
+# result is at most a product of 2^-24 and the additions of a chain from the exact sum, in units of the sum of magnitudes
+# (the matrix instruction adds 16 products or more at a time).
+@pytest.mark.parametrize("b,n,m", [(1, 64, 64), (31, 192, 320), (33, 256, 256), (65, 320, 448), (127, 512, 64),
+                                   (200, 64, 576), (140, 4352, 4288)])
+def test_weight_gradient_large_tiles(oracle, b, n, m):
+    rng = np.random.default_rng(b + n + m)
+    dyb, xb = rand_bf16(rng, (b, m), 0.1), rand_bf16(rng, (b, n))
+    dw32 = sb.backward_weight(to_dev(dyb), to_dev(xb), dw_dtype=torch.float32)
+    dwbf = sb.backward_weight(to_dev(dyb), to_dev(xb))
+    magnitude = oracle.weight_grad(dyb & 0x7fff, xb & 0x7fff)
+    assert np.all(np.abs(host(dw32) - oracle.weight_grad(dyb, xb)) <= (b / 16 + 16) * 2.0 ** -23 * magnitude)
+    assert torch.equal(dwbf, dw32.bfloat16())
+
+
 # A step whose arrays exceed the last-level cache (24 million elements in four tensors, 20 million in one: 280 to 390 MB;
 # the second pass runs backwards and non-temporally) computes what each tensor's own step does, bit for bit, and the single-tensor form of the same rule
 # agrees with the binary64 evaluation; ragged counts, so that the last workgroups are partial.
