@@ -42,15 +42,6 @@ inline int direct_split_for(int64_t M, int64_t N, int64_t K, int ncu) {
     return split;
 }
 
-// K = 64 mod 128 on the 256x256 tiles: 64-byte k-steps instead of 128-byte ones whose last stage is half zeros.  At
-// K = 64, where that stage is the only one, they are 2 to 4 % faster with every output and scale (17571 x 5440: 45.4 /
-// 50.4 us); and for four-byte outputs beyond the 256 MiB last-level cache, whose stores bound short contractions, 2 to
-// 12 % (K = 192 to 832, 400..900 MB; 1 to 7 % slower up to 200 MB).  Otherwise the 128-byte steps are: 65.3 / 52.0 us at
-// 11237 x 2880, K = 1088.
-inline bool short_k_steps(int64_t M, int64_t N, int64_t K, int out_bytes) {
-    return K == 64 || (out_bytes > 2 && K % 128 != 0 && K < 1024 && M * N * out_bytes > (int64_t)256 << 20);
-}
-
 // What a product does besides the contraction: int8 with one weight scale; int8 with column scales or with bias and
 // layer-scale; float8.
 enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };

@@ -1,23 +1,16 @@
-// Host-side dispatch of the int8 GEMM with dequantizing epilogue (kernel: gemm_i8_kernel.h).
+// Host-side dispatch of the int8 GEMM with dequantizing epilogue (kernels: gemm_i8_wide_kernel.h for 256x256 tiles,
+// gemm_i8_kernel.h for 128x128 ones).
 #include "gemm_i8_direct_kernel.h"
+#include "gemm_i8_wide_kernel.h"
 
 #include <atomic>
 
 namespace sb {
 namespace {
 
-// 128-byte k-steps (whole cache lines per row; two LDS stages plus the epilogue patch = 160 KiB): four loader waves with
-// a 3-block wave tile, their SIMD partners take 5 blocks (see the kernel header).  An odd multiple of 64 ends in a stage
-// whose second half reads as zero.
-typedef GemmI8Cfg<128, 2, 4, 3, 1> K128;
-// 64-byte k-steps, four stages, every wave loading: short contractions of an odd multiple of 64 (short_k_steps).
-typedef GemmI8Cfg<64, 4, 8, 4, 1> K64;
-// Row-and-column scales (SwitchBackQ): the 32 column states a lane keeps need the registers of the even split.
-typedef GemmI8Cfg<128, 2, 4, 4, 1> K128Q;
 // Products with few output tiles (ViT-B/16's 768-wide outputs make 75 tiles of 256x256 for 256 compute units):
 // 128x128 tiles, four waves, two workgroups per compute unit.  Twice the operand bytes per multiply-add, so it loses
-// to the large tile as soon as that one fills the GPU (measured: 26 against 33 us at 75 large tiles, 26 against 24 us
-// at 300).
+// to the large tile as soon as that one fills the GPU.
 typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> K128S;
 
 template <class C>
@@ -29,8 +22,8 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
         attr_set->store(true, std::memory_order_release);
     }
     int grid = 0;
-    // Workgroups that fit a compute unit at once: its 160 KiB of LDS decide (registers allow two waves per SIMD).
-    constexpr int per_cu = C::LDS_BYTES * 2 <= 160 * 1024 && C::NWAVES == 4 ? 2 : 1;
+    // Workgroups that fit a compute unit at once: its 160 KiB of LDS decide (the 128x128 tile's registers allow two).
+    constexpr int per_cu = C::LDS_BYTES * 2 <= 160 * 1024 ? 2 : 1;
     gemm_i8_prepare<C>(args, num_compute_units() * per_cu, &grid);
     kernel<<<grid, C::THREADS, C::LDS_BYTES, stream>>>(args);
     return hipGetLastError();
@@ -40,21 +33,20 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     __global__ __launch_bounds__(CFG::THREADS) ATTR void name(GemmI8Args p) {            \
         gemm_i8_dequant_body<CFG, OUT, COLSCALE, MATH_I8, POST, HALF>(p);                \
     }
-// The kernels of an instance and their launcher: K a multiple of 128 (_k), K = 64 mod 128 (_h) and, on the large tile,
-// 64-byte k-steps (_64).
-#define SB_LARGE(name, CFG, HALFCFG, OUT, COLSCALE, POST, ATTR)                           \
-    SB_KERNEL(name##_k, CFG, OUT, COLSCALE, POST, false, ATTR)                            \
-    SB_KERNEL(name##_h, HALFCFG, OUT, COLSCALE, POST, true, ATTR)                         \
-    SB_KERNEL(name##_64, K64, OUT, COLSCALE, POST, false, ATTR)                           \
+// The kernel of a large-tile instance (one wave per SIMD: all 512 registers are a lane's) and its launcher.
+#define SB_LARGE(name, OUT, COLSCALE, POST)                                               \
+    __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_w( \
+        GemmI8Args p) {                                                                   \
+        gemm_i8_wide_body<OUT, COLSCALE, MATH_I8, POST>(p);                               \
+    }                                                                                     \
     hipError_t name(const GemmI8Args &args, hipStream_t stream) {                         \
-        static std::atomic<bool> attr_set[3]; /* zero-initialized */                      \
-        if (short_k_steps(args.M, args.N, args.K, OUT == OUT_BF16 ? 2 : 4))               \
-            return launch<K64>(name##_64, &attr_set[0], args, stream);                    \
-        if (args.K % 128) return launch<HALFCFG>(name##_h, &attr_set[1], args, stream);   \
-        return launch<CFG>(name##_k, &attr_set[2], args, stream);                         \
+        typedef WideI8Cfg<MATH_I8, COLSCALE, POST> C;                                     \
+        static std::atomic<bool> attr_set; /* zero-initialized */                         \
+        return launch<C>(name##_w, &attr_set, args, stream);                              \
     }
 // Two waves per SIMD for the four-wave configuration (two workgroups per compute unit): at most 256 registers per lane.
 #define SB_TWO_WAVES __attribute__((amdgpu_waves_per_eu(2)))
+// A small-tile instance: K a multiple of 128 (_k) and K = 64 mod 128 (_h).
 #define SB_SMALL(name, OUT, COLSCALE, POST)                                               \
     SB_KERNEL(name##_k, K128S, OUT, COLSCALE, POST, false, SB_TWO_WAVES)                  \
     SB_KERNEL(name##_h, K128S, OUT, COLSCALE, POST, true, SB_TWO_WAVES)                   \
@@ -63,17 +55,13 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
         if (args.K % 128) return launch<K128S>(name##_h, &attr_set[0], args, stream);     \
         return launch<K128S>(name##_k, &attr_set[1], args, stream);                       \
     }
-SB_LARGE(gemm_i8_k128_bf16, K128, K128, OUT_BF16, false, false, )
-// Four-byte outputs of K = 64 mod 128 take the even split: their stores go out from the registers, all at once, and the
-// wave with five row blocks ends last (outputs of 400..700 MB, K = 192, against the 64-byte steps: 8 to 17 % slower on the
-// 3/5 split, 26861 x 6208 180 / 154 us; 1 % on the even one).
-SB_LARGE(gemm_i8_k128_f32, K128, K128Q, OUT_F32, false, false, )
-SB_LARGE(gemm_i8_k128_i32, K128, K128Q, OUT_I32, false, false, )
-SB_LARGE(gemm_i8q_k128_bf16, K128Q, K128Q, OUT_BF16, true, false, )
-SB_LARGE(gemm_i8q_k128_f32, K128Q, K128Q, OUT_F32, true, false, )
-// Bias and layer-scale after the dequantization: the even wave split (the two vectors take 64 registers in the epilogue).
-SB_LARGE(gemm_i8p_k128_bf16, K128Q, K128Q, OUT_BF16, false, true, SB_TWO_WAVES)
-SB_LARGE(gemm_i8p_k128_f32, K128Q, K128Q, OUT_F32, false, true, SB_TWO_WAVES)
+SB_LARGE(gemm_i8_k128_bf16, OUT_BF16, false, false)
+SB_LARGE(gemm_i8_k128_f32, OUT_F32, false, false)
+SB_LARGE(gemm_i8_k128_i32, OUT_I32, false, false)
+SB_LARGE(gemm_i8q_k128_bf16, OUT_BF16, true, false)
+SB_LARGE(gemm_i8q_k128_f32, OUT_F32, true, false)
+SB_LARGE(gemm_i8p_k128_bf16, OUT_BF16, false, true)
+SB_LARGE(gemm_i8p_k128_f32, OUT_F32, false, true)
 SB_SMALL(gemm_i8_k128s_bf16, OUT_BF16, false, false)
 SB_SMALL(gemm_i8_k128s_f32, OUT_F32, false, false)
 SB_SMALL(gemm_i8_k128s_i32, OUT_I32, false, false)

@@ -122,10 +122,9 @@ def check_exact_float8_product(M, N, K, fa, fb):
     assert torch.equal(sb.matmul_f8_dequant(*args), want.bfloat16())
 
 
-# The tiled kernel with a last stage of half zeros (K = 64 mod 128) on its large and small tile, its instances with 64-byte
-# k-steps (K = 64, and four-byte outputs beyond the last-level cache), and products whose last rows leave the tiles because
-# they would start another round of the grid: 1 row, a tile row less one, a width that is no multiple of the tile; every
-# output type and scale.
+# The tiled kernels with a last stage of half zeros (K = 64 mod 128; K = 64, where it is the only one), and products whose
+# last rows leave the tiles because they would start another round of the grid: 1 row, a tile row less one, a width that is
+# no multiple of the tile; every output type and scale.
 SPLIT = [(11237, 2880, 192), (5000, 1088, 320), (16385, 1024, 1024), (16639, 1024, 1536), (16448, 960, 1216),
          (32896, 2048, 1088), (9000, 1088, 64), (16000, 4224, 192)]
 
@@ -156,6 +155,14 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
     np.testing.assert_array_equal(host(post).view(np.uint16), oracle.round_to_bf16(ref_post))
     rc = sb.matmul_int8_dequant_rc(*dev).view(torch.int16)
     np.testing.assert_array_equal(host(rc).view(np.uint16), oracle.round_to_bf16(ref_rc))
+
+
+# 256x256 tiles: a single column of partial tiles, tiles of one stage and of half a one (several tiles are under way at once,
+# five rounds of them), of two and of three, partial in both directions.
+@pytest.mark.parametrize("M,N,K", [(33000, 64, 64), (33000, 2304, 64), (8449, 1088, 128), (17000, 2240, 192),
+                                   (16700, 2112, 320)])
+def test_large_tiles(oracle, M, N, K):
+    test_half_stages_and_last_rows(oracle, M, N, K)
 
 
 # Exact sums, as for the small float8 products: last rows, and the small tile with ragged edges.

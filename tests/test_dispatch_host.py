@@ -19,7 +19,6 @@ long long plan_product(long long M, long long N, long long K, int kind, int out_
     *split = p.split;
     return p.tile_rows;
 }
-int short_k_steps(long long M, long long N, long long K, int out_bytes) { return sb::short_k_steps(M, N, K, out_bytes); }
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
 int adamw_blocks(long long count) { return sb::adamw_blocks(count); }
 long long adamw_elements_at_least(long long blocks, long long n) { return sb::adamw_elements_at_least(blocks, n); }
@@ -54,7 +53,6 @@ def rules(tmp_path_factory):
     rules.few_tiles.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int]
     rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     rules.plan_product.restype = ctypes.c_longlong
-    rules.short_k_steps.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
     rules.adamw_blocks.argtypes = [ctypes.c_longlong]
     rules.adamw_elements_at_least.argtypes = [ctypes.c_longlong] * 2
@@ -106,15 +104,6 @@ def test_last_rows_that_leave_the_tiles(rules, M, N, K):
     assert rows == M // 256 * 256 and split != NONE
 
 
-# Products with an odd multiple of 64 that the 64-byte k-steps run faster (2 to 12 %), and some that they do not.
-@pytest.mark.parametrize("M,N,K,out_bytes,short", [(17571, 5440, 64, 2, 1), (20375, 8064, 64, 4, 1),
-                                                   (30863, 6016, 448, 4, 1), (27072, 6464, 320, 4, 1),
-                                                   (26861, 6208, 192, 2, 0), (8520, 1024, 448, 4, 0),
-                                                   (30863, 6016, 512, 4, 0), (30863, 6016, 1088, 4, 0)])
-def test_short_k_steps(rules, M, N, K, out_bytes, short):
-    assert rules.short_k_steps(M, N, K, out_bytes) == short
-
-
 def stages_per_wave(K, split):
     return -(-K // 128) // (2 if split == D64H else 4)
 
@@ -136,7 +125,7 @@ def test_sizes_of_the_gpu_tests_reach_every_path(rules):
             rows, split = route(rules, M, N, K, out_bytes, kind)
             assert rows > 0, (M, N, K)
             seen.add(("small" if rules.few_tiles(rows, N, 256) else "large",
-                      "short" if rules.short_k_steps(rows, N, K, out_bytes) else "half" if K % 128 else "whole",
+                      "short" if K == 64 else "half" if K % 128 else "whole",
                       split != NONE))
         assert seen >= {("small", "half", False), ("large", "half", False), ("large", "short", False),
                         ("large", "whole", True), ("large", "half", True)}, (kind, out_bytes, seen)
