@@ -1,27 +1,25 @@
-// Host-side dispatch of the 8-bit float GEMM with dequantizing epilogue (the float8 variant of SwitchBack; kernel:
-// gemm_i8_kernel.h with the float8 arithmetic selected).
+// Host-side dispatch of the 8-bit float GEMM with dequantizing epilogue (the float8 variant of SwitchBack; kernels:
+// gemm_i8_wide_kernel.h and gemm_i8_kernel.h with the float8 arithmetic selected).
 #include "gemm_i8_direct_kernel.h"
+#include "gemm_i8_wide_kernel.h"
 
 #include <atomic>
 
 namespace sb {
 namespace {
 
-// 128-byte k-steps, two stages, four loader waves, even 4/4 split of the wave column: a float8 operand fragment is
-// 8 registers, so the 5-block wave tile of the int8 kernel's uneven split does not fit the register file.
-typedef GemmI8Cfg<128, 2, 4, 4, 1> F8Cfg;
-
-// 128x128 tiles, four waves, two workgroups per compute unit: products with few large tiles, the same line as for the
-// int8 product (6304 x 768, K = 3072: 34.0 us on 75 large tiles, 26.8 us on 300 small ones).
-typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> F8Small;
+typedef WideI8Cfg<MATH_F8, false, false> F8Cfg;
+// Products with few large tiles, the same line as for the int8 product.
+typedef GemmI8Cfg F8Small;
 
 #define SB_GEMM_F8_ENTRY(name, OUT, FW, FX)                                                                \
-    __global__ __launch_bounds__(F8Cfg::THREADS) void name(GemmI8Args p) {                                \
-        gemm_i8_dequant_body<F8Cfg, OUT, false, MATH_F8 + 2 * FW + FX>(p);                                 \
+    __global__ __launch_bounds__(F8Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void name(     \
+        GemmI8Args p) {                                                                                    \
+        gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false>(p);                                    \
     }                                                                                                      \
     __global__ __launch_bounds__(F8Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name##_s(  \
         GemmI8Args p) {                                                                                    \
-        gemm_i8_dequant_body<F8Small, OUT, false, MATH_F8 + 2 * FW + FX>(p);                               \
+        gemm_i8_dequant_body<OUT, false, MATH_F8 + 2 * FW + FX>(p);                                        \
     }
 // name suffix: format of the token-side operand a, then of the weight-side operand b (4 = E4M3, 5 = E5M2)
 SB_GEMM_F8_ENTRY(gemm_f8_a4b4_bf16, OUT_BF16, 0, 0)

@@ -8,11 +8,9 @@
 namespace sb {
 namespace {
 
-// Products with few output tiles (ViT-B/16's 768-wide outputs make 75 tiles of 256x256 for 256 compute units):
-// 128x128 tiles, four waves, two workgroups per compute unit.  Twice the operand bytes per multiply-add, so it loses
-// to the large tile as soon as that one fills the GPU.
-typedef GemmI8Cfg<128, 2, 4, 2, 1, 128, 128, 2, 2> K128S;
-
+// 128x128 tiles are for products with few output tiles (ViT-B/16's 768-wide outputs make 75 tiles of 256x256 for 256
+// compute units).  Twice the operand bytes per multiply-add, so they lose to the large tile as soon as that one fills the
+// GPU.
 template <class C>
 hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI8Args args, hipStream_t stream) {
     if (!attr_set->load(std::memory_order_acquire)) {  // setting it twice (two host threads racing) is harmless
@@ -29,10 +27,6 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     return hipGetLastError();
 }
 
-#define SB_KERNEL(name, CFG, OUT, COLSCALE, POST, HALF, ATTR)                             \
-    __global__ __launch_bounds__(CFG::THREADS) ATTR void name(GemmI8Args p) {            \
-        gemm_i8_dequant_body<CFG, OUT, COLSCALE, MATH_I8, POST, HALF>(p);                \
-    }
 // The kernel of a large-tile instance (one wave per SIMD: all 512 registers are a lane's) and its launcher.
 #define SB_LARGE(name, OUT, COLSCALE, POST)                                               \
     __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_w( \
@@ -44,16 +38,20 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
         static std::atomic<bool> attr_set; /* zero-initialized */                         \
         return launch<C>(name##_w, &attr_set, args, stream);                              \
     }
-// Two waves per SIMD for the four-wave configuration (two workgroups per compute unit): at most 256 registers per lane.
-#define SB_TWO_WAVES __attribute__((amdgpu_waves_per_eu(2)))
-// A small-tile instance: K a multiple of 128 (_k) and K = 64 mod 128 (_h).
+// A small-tile instance: K a multiple of 128 (_k) and K = 64 mod 128 (_h).  Two waves per SIMD (two workgroups per compute
+// unit): at most 256 registers a lane.
+#define SB_SMALL_KERNEL(name, OUT, COLSCALE, POST, HALF)                                  \
+    __global__ __launch_bounds__(GemmI8Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name( \
+        GemmI8Args p) {                                                                   \
+        gemm_i8_dequant_body<OUT, COLSCALE, MATH_I8, POST, HALF>(p);                      \
+    }
 #define SB_SMALL(name, OUT, COLSCALE, POST)                                               \
-    SB_KERNEL(name##_k, K128S, OUT, COLSCALE, POST, false, SB_TWO_WAVES)                  \
-    SB_KERNEL(name##_h, K128S, OUT, COLSCALE, POST, true, SB_TWO_WAVES)                   \
+    SB_SMALL_KERNEL(name##_k, OUT, COLSCALE, POST, false)                                 \
+    SB_SMALL_KERNEL(name##_h, OUT, COLSCALE, POST, true)                                  \
     hipError_t name(const GemmI8Args &args, hipStream_t stream) {                         \
         static std::atomic<bool> attr_set[2]; /* zero-initialized */                      \
-        if (args.K % 128) return launch<K128S>(name##_h, &attr_set[0], args, stream);     \
-        return launch<K128S>(name##_k, &attr_set[1], args, stream);                       \
+        if (args.K % 128) return launch<GemmI8Cfg>(name##_h, &attr_set[0], args, stream); \
+        return launch<GemmI8Cfg>(name##_k, &attr_set[1], args, stream);                   \
     }
 SB_LARGE(gemm_i8_k128_bf16, OUT_BF16, false, false)
 SB_LARGE(gemm_i8_k128_f32, OUT_F32, false, false)
@@ -70,9 +68,8 @@ SB_SMALL(gemm_i8q_k128s_f32, OUT_F32, true, false)
 SB_SMALL(gemm_i8p_k128s_bf16, OUT_BF16, false, true)
 SB_SMALL(gemm_i8p_k128s_f32, OUT_F32, false, true)
 #undef SB_SMALL
-#undef SB_TWO_WAVES
+#undef SB_SMALL_KERNEL
 #undef SB_LARGE
-#undef SB_KERNEL
 
 }  // namespace
 

@@ -3,31 +3,22 @@
 //
 //   out[i,j] = (state_tensor/127^2 * state_row[i]) * sum_k aq[i,k] * bq[j,k]        aq [M,K], bq [N,K], K contiguous
 //
-// Design
+// This kernel: 128x128 output tiles, for products with too few 256x256 tiles to fill the GPU (those run
+// gemm_i8_wide_kernel.h).  Four waves of 64x64, 80 KiB of LDS and at most 256 registers a lane, so two workgroups share a
+// compute unit, one wave of each per SIMD: they drift apart, and the epilogue of one runs under the matrix instructions of the
+// other.
 //   * v_mfma_i32_32x32x32_i8.  The weight-side tile (bq rows) is the MFMA's first operand and the token-side
 //     tile (aq rows) its second, so a lane ends up owning ONE output row (lane % 32) and, per accumulator quad,
 //     four consecutive output columns: one row scale per lane, and packed bf16x4 leaves each quad.
-//   * 256x256 output tile per workgroup of eight waves, two per SIMD; a wave tile is 64 columns wide and 128 rows
-//     high (96 and 160 with the uneven split below).  A persistent grid (one workgroup per compute unit) walks the
-//     tiles in an order that keeps the workgroups of one XCD (workgroup id % 8) on a compact patch of tiles, so its
-//     L2 sees each operand panel once.  The tile and the wave grid are parameters of GemmI8Cfg; the other instances in
-//     use are 128x128 tiles with four waves, two workgroups per compute unit, for products with few tiles, and 256x256
-//     tiles with 64-byte k-steps for some short contractions.
-//   * Operand tiles go HBM/L2 -> LDS with buffer_load_dwordx4 ... lds (no VGPR staging), STAGES deep.  One wave
-//     instruction fills 1 KiB of LDS linearly, so the bank-conflict-avoiding swizzle is applied on the GLOBAL side:
-//     LDS slot (row, p) holds 16-byte k-chunk p ^ f(row) of that row, f(row) = (row / (256/BK)) % (BK/16).  Rows past
-//     M (or N) lie beyond the buffer's num_records and read as zero; they only feed accumulators that are never
-//     stored.
-//   * One continuous stage pipeline: the stage ring runs across tile boundaries.  The load cursor stays STAGES
-//     stages ahead of the MFMAs, so a new tile's first stages are requested during the last k-tiles of the tile
-//     before it, and the epilogue needs no barrier of its own.
-//   * Wave roles.  A 1 KiB request occupies the CU's address/data path for ~18 cycles and the wave that issues it
-//     stalls meanwhile, MFMAs included; the 64 requests of a 64 KiB stage cost ~1200 cycles however they are dealt.
-//     With LOADERS = 4 only waves 0..3 issue them, all right after the stage hand-over barrier: waves w and w+4
-//     share a SIMD, so while a loader wave is stuck issuing its partner has the matrix pipe to itself, and the
-//     loader runs its MFMAs afterwards.  MT_LOADER = 3 evens out the two chains: the loader computes 3 of the 8
-//     32-row blocks of its wave column, its partner 5.  With LOADERS = 8 (the 64-byte k-steps) every wave issues its
-//     share at the hand-over.
+//   * A persistent grid walks the tiles in an order that keeps the workgroups of one XCD (workgroup id % 8) on a compact
+//     patch of tiles, so its L2 sees each operand panel once.
+//   * Operand tiles go HBM/L2 -> LDS with buffer_load_dwordx4 ... lds (no VGPR staging), two stages of 128 bytes of k.  One
+//     wave instruction fills 1 KiB of LDS linearly, so the bank-conflict-avoiding swizzle is applied on the GLOBAL side:
+//     LDS slot (row, p) holds 16-byte k-chunk p ^ f(row) of that row, f(row) = (row / 2) % 8.  Rows past M (or N) lie
+//     beyond the buffer's num_records and read as zero; they only feed accumulators that are never stored.
+//   * One continuous stage pipeline: the load cursor stays two stages ahead of the MFMAs, across tile boundaries, so a new
+//     tile's first stages are requested during the last k-tiles of the tile before it, and the epilogue needs no barrier of
+//     its own.
 //   * MFMA operand fragments are double-buffered in registers, and the LDS reads of k-step j+1 are issued one at a
 //     time between the MFMAs of k-step j (also across the stage hand-over): an LDS read issued in the shadow of an
 //     MFMA costs no issue time.  The reads are inline asm so that the lgkmcnt waits can be counted; the compiler's
@@ -44,7 +35,6 @@
 //     32-row blocks of the wave tile: the patch reads of one block are in flight while the next block is converted.
 //   * The same pipeline serves the float8 product (MATH_F8): one v_mfma_f32_32x32x64_f8f6f4 per 64 k-values, an
 //     operand fragment being the two 16-byte LDS reads that two int8 k-steps would issue.
-//   * The cycle figures quoted above come from s_memtime stamps compiled into a working copy of this kernel.
 #pragma once
 #include "dispatch.h"
 #include "sb_common.h"
@@ -58,46 +48,27 @@ enum { OUT_BF16 = 0, OUT_F32 = 1, OUT_I32 = 2 };
 // v_mfma_f32_32x32x64_f8f6f4 with binary32 accumulators, scale state_tensor (the codes already lie in [-1, 1]).
 enum { MATH_I8 = 0, MATH_F8 = 4 };
 
-// BM_ x BN_ output tile per workgroup of WAVES_M_ x WAVES_N_ waves; a wave tile is BM_/WAVES_M_ rows by 64 columns.
-// The default is the 256x256 tile of eight waves (two per SIMD, one workgroup per compute unit).  The 128x128 tile of
-// four waves needs 80 KiB of LDS and 256 registers per lane, so two workgroups share a compute unit, one wave of each
-// per SIMD: they drift apart, and the epilogue of one runs under the matrix instructions of the other.  It moves twice
-// the operand bytes per multiply-add, which is why it only serves products with too few 256x256 tiles to fill the GPU.
-template <int BK_, int STAGES_, int LOADERS_, int MT_LOADER_ = 4, int STORE_NT_ = 0, int BM_ = 256, int BN_ = 256,
-          int WAVES_M_ = 2, int WAVES_N_ = 4>
 struct GemmI8Cfg {
-    static constexpr int STORE_NT = STORE_NT_;  // 1: non-temporal output stores (the output should not evict operand panels from L2)
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
-    static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, NWAVES = WAVES_M * WAVES_N, THREADS = NWAVES * 64;
-    static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile: 128 x 64 in the default configuration
-    static constexpr int NT = WTN / 32;                           // 32-column MFMA blocks per wave tile
-    static constexpr int MT_EVEN = WTM / 32;                      // 32-row MFMA blocks per wave tile when all waves get the same
-    static constexpr int MT_LOADER = MT_LOADER_;  // 32-row MFMA blocks of a loader wave's tile; when < MT_EVEN its SIMD partner
-                                                  // (wave + 4) takes the other 2 * MT_EVEN - MT_LOADER blocks of the wave column
+    static constexpr int BM = 128, BN = 128, BK = 128, STAGES = 2;
+    static constexpr int WAVES_M = 2, WAVES_N = 2, NWAVES = WAVES_M * WAVES_N, THREADS = NWAVES * 64;
+    static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
+    static constexpr int MT = WTM / 32, NT = WTN / 32;            // 32x32 MFMA blocks per wave tile
     static constexpr int KK = BK / 32;                            // MFMA k-steps per stage
     static constexpr int CPR = BK / 16;                           // 16-byte chunks per tile row
     static constexpr int RPS = 1024 / BK;                         // tile rows per 1 KiB request
     static constexpr int SWZ_DIV = 256 / BK;                      // rows that share one 256-byte bank window
     static constexpr int STAGE_BYTES = (BM + BN) * BK;
-    static constexpr int LOADERS = LOADERS_;                      // waves 0..LOADERS-1 issue the global->LDS requests
-    static constexpr int RPL = (BM + BN) / LOADERS;               // stage rows per loader wave
-    static constexpr int LPW = RPL / RPS;                         // requests per loader wave per stage
-    static constexpr int NVAR = CPR * SWZ_DIV > RPS ? CPR * SWZ_DIV / RPS : 1;  // distinct swizzles among a wave's requests
+    static constexpr int RPL = (BM + BN) / NWAVES;                // stage rows each wave loads
+    static constexpr int LPW = RPL / RPS;                         // requests per wave and stage
+    static constexpr int NVAR = CPR * SWZ_DIV / RPS;              // distinct swizzles among a wave's requests
     static constexpr int EPI_PIECES = WTN * 2 / 16;               // 16-byte pieces per row of the epilogue patch
     static constexpr int EPI_WAVE_BYTES = 32 * WTN * 2;           // 32 rows of bf16 per wave
     static constexpr int STORES_PER_BLOCK = EPI_WAVE_BYTES / 1024;  // 16-byte global stores per lane per 32-row block
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + NWAVES * EPI_WAVE_BYTES;
-    static constexpr int MT_MAX = MT_LOADER < MT_EVEN ? 2 * MT_EVEN - MT_LOADER : MT_EVEN;  // largest wave tile, in blocks
-    static_assert(BK == 64 || BK == 128, "BK");
-    static_assert(STAGES >= 2 && STAGES <= 4, "STAGES");
-    static_assert(BM % (32 * WAVES_M) == 0 && (NWAVES == 4 || NWAVES == 8), "wave grid");
-    static_assert(NT == 2 && MT_LOADER >= 2 && MT_LOADER <= MT_EVEN && MT_EVEN <= 4,
-                  "the fragment schedule is written for MT x 2 MFMA blocks per wave");
-    static_assert((LOADERS == 4 || LOADERS == 8) && LOADERS <= NWAVES && BM % RPL == 0 && LPW % NVAR == 0, "loader split");
-    static_assert(MT_LOADER == MT_EVEN || (LOADERS == 4 && NWAVES == 8 && WAVES_M == 2),
-                  "an uneven split pairs a loader wave with the non-loading wave below it in the same wave column");
-    static_assert(LPW * (STAGES - 1) + MT_MAX * STORES_PER_BLOCK + MT_MAX < 64, "vmcnt range");
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    static_assert(MT == 2 && NT == 2, "the fragment schedule is written for 2 x 2 MFMA blocks per wave");
+    static_assert(BM % RPL == 0 && LPW % NVAR == 0, "request split");
+    static_assert(LPW * (STAGES - 1) + MT * STORES_PER_BLOCK + MT < 64, "vmcnt range");
+    static_assert(LDS_BYTES <= 80 * 1024, "LDS");
 };
 
 struct GemmI8Args {
@@ -171,22 +142,26 @@ __device__ __forceinline__ void wait_stage(int later) {
 }
 
 
-// What one wave does: an (MT*32) x 64 part of the workgroup's tile, rows from wm0.  Every role runs the same
-// sequence of barriers.
 // COLSCALE: out[i,j] = (float)acc * fl(state_row[i] * fl(state_col[j] / 127^2)) instead of the tensor-wise scale.
 // POST: the dequantized value y continues through the linear layer's bias and the block's layer-scale before it is
 // stored: fl(y + bias[j]) if p.bias is given, then fl(gamma[j] * that) if p.gamma is given.  The two vectors are
-// fetched at the start of the epilogue (64 more registers there, so these instances use the even wave split).
+// fetched at the start of the epilogue.
 //
 // The float8 product runs the same pipeline with one MFMA per 64 k-values: an operand fragment is then 32 bytes per
 // lane, fetched by the two 16-byte LDS reads that two consecutive int8 k-steps would issue.  Which 64 k-values a
 // lane's registers hold does not matter as long as both operands use the same assignment, which they do.
 //
 // HALF: K = 64 mod 128, so that the last stage is half a stage, zero beyond K (int8 only).  Instances of their own: the
-// choice between two sets of request offsets, made in every stage at run time, takes 0.7 % of the 256x256-tile products
-// and 2-3 % of the 128x128-tile ones, and a branch around the last stage's requests hardly less.
-template <class C, int OUT, int MT, bool COLSCALE, int MATH, bool POST, bool HALF>
-__device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const int wave, const int wm0) {
+// choice between two sets of request offsets, made in every stage at run time, takes 2-3 %, and a branch around the last
+// stage's requests hardly less.
+// (A __device__ template called from non-template __global__ entry points: a __global__ template that uses device-only
+// buffer builtins does not instantiate in the host pass.)
+template <int OUT, bool COLSCALE = false, int MATH = MATH_I8, bool POST = false, bool HALF = false>
+__device__ __forceinline__ void gemm_i8_dequant_body(const GemmI8Args &p) {
+    typedef GemmI8Cfg C;
+    constexpr int MT = C::MT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
+    const int wm0 = (wave / C::WAVES_N) * C::WTM;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
     constexpr int S = C::STAGES;
@@ -198,7 +173,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     typedef typename std::conditional<F8, v8i, v4i>::type FragT;
     static_assert(!F8 || (OUT != OUT_I32 && !COLSCALE), "the float8 product has dequantized outputs and a tensor-wise weight state");
     static_assert(!POST || (OUT != OUT_I32 && !COLSCALE && !F8), "bias / layer-scale follow the tensor-wise int8 dequantization");
-    static_assert(!HALF || (!F8 && C::BK == 128), "half a stage is 64 int8 codes");
+    static_assert(!HALF || !F8, "half a stage is 64 int8 codes");
     static_assert(KKG >= 2 && KKG % 2 == 0, "the register double-buffering alternates per k-step group within a stage");
     constexpr int NSCALE = OUT != OUT_I32 ? MT + (COLSCALE ? C::NT * 4 : 0) : 0;  // per-lane scale loads per tile
     constexpr int NFRAG = MT + C::NT;
@@ -207,7 +182,6 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wn0 = (wave % C::WAVES_N) * C::WTN;
     const int KT = HALF ? (p.K + C::BK - 1) / C::BK : p.K / C::BK;
-    const bool loader = wave < C::LOADERS;
 
     // Per-lane byte offset of its MFMA operand chunk inside a 32-row block of a stage, one per k-step.
     const int frow = lane & 31, fhalf = lane >> 5;
@@ -216,7 +190,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
 #pragma unroll
     for (int kk = 0; kk < C::KK; ++kk) frag_off[kk] = frow * C::BK + (((kk * 2 + fhalf) ^ fswz) << 4);
 
-    // Loader role: wave w < LOADERS fills stage rows [w*RPL, (w+1)*RPL), request i of it the RPS rows from
+    // Wave w fills stage rows [w*RPL, (w+1)*RPL), request i of it the RPS rows from
     // w*RPL + i*RPS; they all belong to one operand.  A lane's byte offset into that operand is
     //   (tile row 0 + row in tile) * K + chunk * 16 + k-tile * BK
     // = voff[i % NVAR] (per lane, fixed) + i*RPS*K + tile_soff + kt*BK (scalars): the swizzled chunk depends on i
@@ -254,8 +228,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     };
 
     // MFMA operand fragments, double-buffered in registers.  A k-step group issues its MFMAs in the order
-    // (x0,w0) (x0,w1) (x1,w0) (x1,w1) ... and reads the NEXT group's fragments in the order w0 x0 w1 x1 x2 x3 ..., one
-    // read after each of its first MT+2 MFMAs.
+    // (x0,w0) (x0,w1) (x1,w0) (x1,w1) and reads the NEXT group's fragments in the order w0 x0 w1 x1, one read after each.
     FragT xf[2][MT], wf[2][C::NT];
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
     static_assert((C::BM + C::BN) * C::BK <= 65536, "fragment offsets must fit the 16-bit ds offset field");
@@ -278,10 +251,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
             case 0: wf[buf][0] = read(std::integral_constant<int, 0>(), w_off); break;
             case 1: xf[buf][0] = read(std::integral_constant<int, 0>(), x_off); break;
             case 2: wf[buf][1] = read(std::integral_constant<int, 32 * C::BK>(), w_off); break;
-            case 3: xf[buf][1] = read(std::integral_constant<int, 32 * C::BK>(), x_off); break;
-            case 4: xf[buf][2 % MT] = read(std::integral_constant<int, 64 * C::BK>(), x_off); break;
-            case 5: xf[buf][3 % MT] = read(std::integral_constant<int, 96 * C::BK>(), x_off); break;
-            default: xf[buf][4 % MT] = read(std::integral_constant<int, 128 * C::BK>(), x_off); break;
+            default: xf[buf][1] = read(std::integral_constant<int, 32 * C::BK>(), x_off); break;
         }
     };
     // Ties the register of the i-th fragment read to the wait that precedes this call.
@@ -290,10 +260,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
             case 0: asm volatile("" : "+v"(wf[buf][0])); break;
             case 1: asm volatile("" : "+v"(xf[buf][0])); break;
             case 2: asm volatile("" : "+v"(wf[buf][1])); break;
-            case 3: asm volatile("" : "+v"(xf[buf][1])); break;
-            case 4: asm volatile("" : "+v"(xf[buf][2 % MT])); break;
-            case 5: asm volatile("" : "+v"(xf[buf][3 % MT])); break;
-            default: asm volatile("" : "+v"(xf[buf][4 % MT])); break;
+            default: asm volatile("" : "+v"(xf[buf][1])); break;
         }
     };
     // n counts fragments; the counter counts reads.
@@ -368,8 +335,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     };
 
     // ---- Load cursor: runs STAGES stages ahead of the MFMAs, across segment boundaries, so a new tile's first
-    // stages are requested during the last k-tiles of the one before it.  Every wave advances the cursor; only the
-    // loader waves issue.
+    // stages are requested during the last k-tiles of the one before it.
     Seg ls;
     int l_idx = 0, l_g = 0;  // segment being loaded; global count of stages requested so far (stage g lives in slot g % S)
     bool l_have = segment_of(0, ls);
@@ -378,12 +344,10 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
     auto issue_next = [&]() {
         if (!l_have) return;
         const int slot = l_g % S;
-        if (loader) {
-            issue_stage(slot, l_kt);
-            note_vmem(C::LPW);
+        issue_stage(slot, l_kt);
+        note_vmem(C::LPW);
 #pragma unroll
-            for (int i = 0; i < S; ++i) younger[i] = slot == i ? 0 : younger[i];
-        }
+        for (int i = 0; i < S; ++i) younger[i] = slot == i ? 0 : younger[i];
         ++l_g;
         if (++l_kt == ls.ke) {
             l_have = segment_of(++l_idx, ls);
@@ -440,7 +404,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
             // (Re)start of the fragment pipeline: the very first stage, or the stage after a segment that ended
             // without a hand-over.  Nobody has waited for this stage yet, and the slot of the stage before it (if
             // any) has not been refilled.
-            if (loader) wait_slot_landed(g % S);
+            wait_slot_landed(g % S);
             wait_lds_reads();
             block_barrier();
             if (l_g < g + S) issue_next();
@@ -465,7 +429,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
                     // Hand-over: the fragments of this last k-step of the stage are in (or on their way to)
                     // registers.  Retire this wave's LDS reads, make sure the next stage has landed, then refill
                     // the freed slot.
-                    if (loader) wait_slot_landed(next_slot);
+                    wait_slot_landed(next_slot);
                     wait_lds_reads();
                     block_barrier();
                     issue_next();
@@ -621,7 +585,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
                     for (int j = 0; j < C::STORES_PER_BLOCK; ++j) {
                         const unsigned soff =
                             (unsigned)((m_base + mt * 32 + j * (64 / C::EPI_PIECES)) * p.N + n_base) * 2;
-                        __builtin_amdgcn_raw_buffer_store_b128(val[j], rsrc_out, epi_voff, soff, C::STORE_NT ? 2 : 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(val[j], rsrc_out, epi_voff, soff, 2);
                     }
                 } else {
 #pragma unroll
@@ -632,8 +596,7 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
                         const unsigned soff =
                             (unsigned)((m_base + mt * 32 + j * (64 / C::EPI_PIECES)) * p.N + n_base) * 2;
                         if (gr < p.M && gc < p.N)
-                            __builtin_amdgcn_raw_buffer_store_b128(val[j], rsrc_out, epi_voff, soff,
-                                                                   C::STORE_NT ? 2 : 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(val[j], rsrc_out, epi_voff, soff, 2);
                     }
                 }
                 if (mt + 1 < MT) write_patch();
@@ -675,19 +638,6 @@ __device__ __forceinline__ void gemm_i8_dequant_role(const GemmI8Args &p, const 
         cs = ns;
         have = next_have;
     }
-}
-
-// The kernel body.  It is a __device__ template called from non-template __global__ entry points: a __global__
-// template that uses device-only buffer builtins does not instantiate in the host pass.
-template <class C, int OUT, bool COLSCALE = false, int MATH = MATH_I8, bool POST = false, bool HALF = false>
-__device__ __forceinline__ void gemm_i8_dequant_body(const GemmI8Args &p) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
-    if (C::MT_LOADER == C::MT_EVEN)
-        gemm_i8_dequant_role<C, OUT, C::MT_EVEN, COLSCALE, MATH, POST, HALF>(p, wave, (wave / C::WAVES_N) * C::WTM);
-    else if (wave < C::LOADERS)
-        gemm_i8_dequant_role<C, OUT, C::MT_LOADER, COLSCALE, MATH, POST, HALF>(p, wave, 0);
-    else
-        gemm_i8_dequant_role<C, OUT, 2 * C::MT_EVEN - C::MT_LOADER, COLSCALE, MATH, POST, HALF>(p, wave, C::MT_LOADER * 32);
 }
 
 // Launch geometry shared by the entry points.
