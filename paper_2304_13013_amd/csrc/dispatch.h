@@ -31,59 +31,6 @@ inline double direct_product_time(int64_t M, int64_t N, int64_t K, int ncu, int 
     return *split == DIRECT_32 ? t32 : *split == DIRECT_64 ? t64 : t64h;
 }
 
-// The split that beats the 128x128-tile instance, or DIRECT_NONE.  The line is where the 64x64 blocks no longer fit the
-// GPU at once, two per compute unit: over the same products the best split takes 0.15 to 1.04 of the tiles' time up to
-// there (median 0.4) and 0.9 to 2.3 of it past it (median 1.4).  Tiles against blocks: 64 x 1024, K = 4096: 22.7 / 4.4 us;
-// 197 x 3072, K = 768: 7.3 / 4.3; 2000 x 768, K = 3072: 18.3 / 11.9; and on the other side of the line 1137 x 1856,
-// K = 128: 4.4 / 5.6; 7233 x 320, K = 1920: 13.5 / 16.7; 338 x 5760, K = 7552 with bias and layer-scale: 41.6 / 52.7.
-inline int direct_split_for(int64_t M, int64_t N, int64_t K, int ncu) {
-    int split = DIRECT_NONE;
-    if (((M + 63) / 64) * (N / 64) <= 2 * (int64_t)ncu) direct_product_time(M, N, K, ncu, &split);
-    return split;
-}
-
-// What a product does besides the contraction: int8 with one weight scale; int8 with column scales or with bias and
-// layer-scale; float8.
-enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
-
-// A product's rows [0, tile_rows) go to the tiled kernel (128x128 tiles if they make few 256x256 ones), the rest to the
-// small-product kernel with `split`; either part may be empty, and split is DIRECT_NONE exactly if the second one is.
-struct ProductPlan {
-    int64_t tile_rows;
-    int split;
-};
-
-// When the last, partial row of tiles starts another round of the persistent grid, that round keeps a few workgroups
-// busy with tiles that are mostly past the end, and the small-product kernel may do those rows in less time.  Measured,
-// one launch against two: 16448 x 1024, K = 4096 (260 tiles, 64 rows split off) 87.4 / 62.1 us, K = 3072 72.0 / 51.7,
-// K = 1024 28.4 / 23.7; 16448 x 4096, K = 1024 91.3 / 80.3; 32896 x 5120, K = 1280 (128 rows) 248.5 / 205.0;
-// 8200 x 2048, K = 512 18.8 / 17.1.  What the round takes, by 900 products: 7 us per 1024 of K and 1 us more if it is
-// the second one; if more come before it, workgroups that finish early start it, and it takes 5.5 us per 1024 of K; 7
-// with the longer epilogues (K >= 1024); 4 where the stores of full rounds get into each other's way (the plain int8
-// product, whose waves share the rows 3 : 5, at K < 1024; and four-byte outputs).  One line at 6 us per 1024 of K made
-// 4337 x 8192, K = 1600 67.2 / 72.9 and 19692 x 2496, K = 768 50.8 / 56.2.  Four-byte outputs in several rounds are
-// bound by their stores if there are many or K is small, and gain nothing reliable (52260 x 1088, K = 2624 216 / 231;
-// 32956 x 1024, K = 768 53.2 / 59.8).  Where the number of rounds stays (21000 x 800, K = 1536: 41.0 / 45.8) nothing is
-// split off, and neither where the partial row is the only one (fewer than 256 rows of a very wide output): the tiles
-// keep at least one whole row of tiles.
-inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
-    int split = DIRECT_NONE;
-    if (few_tiles(M, N, ncu)) {
-        split = direct_split_for(M, N, K, ncu);
-        return ProductPlan{split == DIRECT_NONE ? M : 0, split};
-    }
-    const int64_t full = M / 256 * 256, tiles_n = (N + 255) / 256, tiles = full / 256 * tiles_n;
-    const int64_t rounds = (tiles + ncu - 1) / ncu;
-    if (full == 0 || full == M || (tiles + tiles_n + ncu - 1) / ncu == rounds) return ProductPlan{M, DIRECT_NONE};
-    if (out_bytes > 2 && rounds > 1 && (rounds > 3 || K < 1024)) return ProductPlan{M, DIRECT_NONE};
-    const double k1024 = (double)K / 1024.0;
-    const double later = out_bytes > 2 || (kind == PRODUCT_PLAIN && K < 1024) ? 4.0
-                         : kind == PRODUCT_LONG_EPILOGUE && K >= 1024 ? 7.0 : 5.5;
-    const double round = rounds == 1 ? 1.0 + 7.0 * k1024 : later * k1024;
-    if (direct_product_time(M - full, N, K, ncu, &split) < round) return ProductPlan{full, split};
-    return ProductPlan{M, DIRECT_NONE};
-}
-
 // Workgroups of the tiled kernel's persistent grid: a multiple of the XCD count, at most `slots` (what the GPU holds at
 // once).  When the tiles make only a few rounds of the full grid and do not fill the last one, the grid is shrunk so that
 // every workgroup gets the same number of tiles (645 tiles: 216 workgroups x 3 instead of 256 x 2.5): the number of
@@ -99,6 +46,124 @@ inline int persistent_grid(int64_t tiles, int slots) {
     const int64_t per_round = (tiles + rounds - 1) / rounds;
     const int grid = (int)((per_round + 7) & ~7LL);
     return grid > full ? full : grid < 8 ? 8 : grid;
+}
+
+// What a product does besides the contraction: int8 with one weight scale; int8 with column scales or with bias and
+// layer-scale; float8.
+enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
+
+// The tiled kernels: 128x128 (gemm_i8_kernel.h, two workgroups per compute unit), 256x128 and 256x256
+// (gemm_i8_wide_kernel.h).
+enum TileKind { TILES_128 = 0, TILES_256X128, TILES_256, TILE_KINDS };
+
+// Estimated time (us) of a product on tiles.  With r rounds of the persistent grid (of the XCD with most tiles), k stages of
+// 128 bytes and enough tiles for f rounds of a full grid:
+//   launch + r * boundary + k * (r * stage + f * stage_f) + store * megabytes of output
+// fitted to 1200 products (100..40000 rows, 64..8192 columns, K = 128..8192; every output and scale) on an MI355X.  The
+// ratio to the measured time has a standard deviation of 4 to 6 % (7 to 10 % for four-byte outputs); the tile
+// picked is 0.3 to 0.7 % slower than the best one in the mean.
+inline double tiled_product_time(TileKind tile, int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes,
+                                 int ncu) {
+    struct Fit {
+        double launch, boundary, stage, stage_f, store;
+    };
+    static const Fit fits[4][TILE_KINDS] = {
+        // 128x128, 256x128, 256x256: int8; int8 with the longer epilogues; float8; four-byte outputs
+        {{2.29, 1.36, 0.541, 0.502, 0.055}, {2.79, 1.56, 0.548, 0.274, 0.013}, {2.84, 2.72, 0.971, 0.484, 0.034}},
+        {{2.02, 2.28, 0.534, 0.496, 0.089}, {2.82, 2.18, 0.536, 0.267, 0.011}, {2.39, 4.41, 0.954, 0.500, 0.008}},
+        {{1.74, 1.60, 0.537, 0.368, 0.056}, {2.07, 2.18, 0.473, 0.242, 0.072}, {1.54, 3.66, 0.851, 0.444, 0.034}},
+        {{4.11, 0.00, 0.549, 0.506, 0.172}, {5.23, 0.87, 0.533, 0.330, 0.111}, {6.30, 2.09, 0.936, 0.571, 0.106}}};
+    const Fit &fit = fits[out_bytes > 2 ? 3 : (int)kind][tile];
+    const int bm = tile == TILES_128 ? 128 : 256, bn = tile == TILES_256 ? 256 : 128;
+    const int slots = tile == TILES_128 ? 2 * ncu : ncu;
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), per_xcd = persistent_grid(tiles, slots) / 8;
+    const double rounds = (double)(((tiles + 7) / 8 + per_xcd - 1) / per_xcd);
+    const double k = (double)((K + 127) / 128 > 1 || tile != TILES_256X128 ? (K + 127) / 128 : 2);
+    return fit.launch + rounds * fit.boundary + k * (rounds * fit.stage + (double)tiles / slots * fit.stage_f) +
+           fit.store * 1e-6 * (double)M * (double)N * out_bytes;
+}
+
+// The tile with the smallest estimate; the 128x128 ones on equal terms, up to 3 % (the wider ones lose 7 % on a narrow miss
+// at worst: 2382 x 1280, K = 2752, binary32 21.4 us against 23.5, where they win 4 % in the mean).
+inline double best_tiles(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu, TileKind *tile) {
+    double best = 0.97 * tiled_product_time(TILES_128, M, N, K, kind, out_bytes, ncu);
+    *tile = TILES_128;
+    for (int i = TILES_128 + 1; i < TILE_KINDS; ++i) {
+        const double t = tiled_product_time((TileKind)i, M, N, K, kind, out_bytes, ncu);
+        if (t < best) {
+            best = t;
+            *tile = (TileKind)i;
+        }
+    }
+    return best;
+}
+
+// A product's rows [0, first_rows) go to `first` tiles, [first_rows, tile_rows) to `second` ones, the rest to the
+// small-product kernel with `split`.  Any of the three parts may be empty; split is DIRECT_NONE exactly if the last one is.
+struct ProductPlan {
+    int64_t first_rows, tile_rows;
+    TileKind first, second;
+    int split;
+};
+
+// The whole product on the small-product kernel: while its 64x64 blocks fit the GPU at once, two per compute unit, and few
+// 256x256 tiles; 0.15 to 1.04 of the 128x128 tiles' time up to there and 0.9 to 2.3 of it past it.  64 x 1024, K = 4096:
+// 4.4 us against 22.7; 197 x 3072, K = 768: 4.3 / 7.3; 2000 x 768, K = 3072: 11.9 / 18.3; on the other side of the line
+// 1137 x 1856, K = 128: 5.6 / 4.4; 7233 x 320, K = 1920: 16.7 / 13.5; 338 x 5760, K = 7552 with bias and layer-scale: 52.7 /
+// 41.6.  Long contractions of many blocks are bound by their operands' way from L2, 12.5 TB/s, and run on tiles if those
+// save a tenth by the estimates (5431 x 384, K = 6784, float8: 39.0 us on 510 blocks, 31.8 on 256x128 tiles; 190 x 8128, K =
+// 8128: 52.9 / 42.2).
+//
+// Otherwise the fastest of the tiles by the estimates, or 256x256 tiles for the whole rows of them that fill whole rounds of
+// the grid and another kernel for the rows that would start the next round:
+//   LAST ROWS.  The last, partial row of tiles starts another round, which keeps a few workgroups busy with tiles that are
+//   mostly past the end; the small-product kernel may do those rows in less time.  16448 x 1024, K = 4096 (64 rows split off)
+//   80.6 / 62.6 us; 16448 x 4096, K = 1024 91.3 / 80.3 (eight-wave tiles).  What the round takes, by 900 products: 7 us per
+//   1024 of K and 1 us more if it is the second one; if more come before it, workgroups that finish early start it, and it
+//   takes 5.5 us per 1024 of K; 7 with the longer epilogues (K >= 1024); 4 where the stores of full rounds get into each
+//   other's way (the plain int8 product at K < 1024, and four-byte outputs).  Four-byte outputs in several rounds are bound by
+//   their stores if there are many or K is small, and gain nothing reliable.  Where the number of rounds stays nothing is
+//   split off, and neither where the partial row is the only one (fewer than 256 rows of a very wide output).
+//   WHOLE ROUNDS.  More than a partial row is left: other tiles do those rows.  It has to save 5 % by the estimates.
+// Against one kernel for all rows and the 128x128 and 256x256 tiles alone, 1200 products of all kinds run 4 to 8 % faster in
+// the mean (256x128 tiles and whole rounds: 6304 x 768, K = 3072 24.2 / 20.4 us; 8000 x 1024, K = 4096 37.0 / 30.5;
+// 11237 x 2880, K = 1088 44.4 / 37.7; 30000 x 1280, K = 4096 153 / 137).
+inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
+    ProductPlan plan{0, M, TILES_256, TILES_256, DIRECT_NONE};
+    int split = DIRECT_NONE;
+    double best = best_tiles(M, N, K, kind, out_bytes, ncu, &plan.second);
+    if (few_tiles(M, N, ncu)) {
+        const int64_t blocks = ((M + 63) / 64) * (N / 64);
+        if (blocks > 2 * (int64_t)ncu) return plan;
+        const double latency = direct_product_time(M, N, K, ncu, &split), traffic = (double)(blocks * 128 * K) / 12.5e6;
+        if (best < 0.9 * (latency > traffic ? latency : traffic)) return plan;
+        plan.tile_rows = 0;
+        plan.split = split;
+        return plan;
+    }
+    const int64_t full = M / 256, tiles_n = (N + 255) / 256, rounds = (full * tiles_n + ncu - 1) / ncu;
+    // LAST ROWS
+    if (full > 0 && M % 256 != 0 && ((full + 1) * tiles_n + ncu - 1) / ncu != rounds &&
+        (out_bytes == 2 || rounds == 1 || (rounds <= 3 && K >= 1024))) {
+        const double k1024 = (double)K / 1024.0;
+        const double later = out_bytes > 2 || (kind == PRODUCT_PLAIN && K < 1024) ? 4.0
+                             : kind == PRODUCT_LONG_EPILOGUE && K >= 1024 ? 7.0 : 5.5;
+        const double rest = direct_product_time(M - full * 256, N, K, ncu, &split);
+        const double t = tiled_product_time(TILES_256, full * 256, N, K, kind, out_bytes, ncu) + rest;
+        if (rest < (rounds == 1 ? 1.0 + 7.0 * k1024 : later * k1024) && t < 1.05 * best) {
+            best = t < best ? t : best;
+            plan = ProductPlan{full * 256, full * 256, TILES_256, TILES_256, split};
+        }
+    }
+    // WHOLE ROUNDS
+    const int64_t whole = full * tiles_n / ncu * ncu / tiles_n;  // rows of tiles in whole rounds
+    if (whole > 0 && whole < full) {
+        TileKind rest;
+        const double t = tiled_product_time(TILES_256, whole * 256, N, K, kind, out_bytes, ncu) +
+                         best_tiles(M - whole * 256, N, K, kind, out_bytes, ncu, &rest);
+        if (t < 0.95 * best) plan = ProductPlan{whole * 256, M, TILES_256, rest, DIRECT_NONE};
+    }
+    return plan;
 }
 
 }  // namespace sb

@@ -9,6 +9,7 @@ namespace sb {
 namespace {
 
 typedef WideI8Cfg<MATH_F8, false, false> F8Cfg;
+typedef WideI8Cfg<MATH_F8, false, false, 128> F8Narrow;
 // Products with few large tiles, the same line as for the int8 product.
 typedef GemmI8Cfg F8Small;
 
@@ -16,6 +17,10 @@ typedef GemmI8Cfg F8Small;
     __global__ __launch_bounds__(F8Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void name(     \
         GemmI8Args p) {                                                                                    \
         gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false>(p);                                    \
+    }                                                                                                      \
+    __global__ __launch_bounds__(F8Narrow::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_n( \
+        GemmI8Args p) {                                                                                    \
+        gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false, 128>(p);                               \
     }                                                                                                      \
     __global__ __launch_bounds__(F8Small::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void name##_s(  \
         GemmI8Args p) {                                                                                    \
@@ -32,6 +37,41 @@ SB_GEMM_F8_ENTRY(gemm_f8_a5b5_bf16, OUT_BF16, 1, 1)
 SB_GEMM_F8_ENTRY(gemm_f8_a5b5_f32, OUT_F32, 1, 1)
 #undef SB_GEMM_F8_ENTRY
 
+// The instance for a tile, a pair of formats and an output type (`which`, in the order of the entries above).
+hipError_t launch_tiled(TileKind tile, int which, GemmI8Args args, hipStream_t stream) {
+    typedef void (*Kernel)(GemmI8Args);
+    static const Kernel kernels[TILE_KINDS][8] = {
+        {gemm_f8_a4b4_bf16_s, gemm_f8_a4b4_f32_s, gemm_f8_a5b4_bf16_s, gemm_f8_a5b4_f32_s, gemm_f8_a4b5_bf16_s,
+         gemm_f8_a4b5_f32_s, gemm_f8_a5b5_bf16_s, gemm_f8_a5b5_f32_s},
+        {gemm_f8_a4b4_bf16_n, gemm_f8_a4b4_f32_n, gemm_f8_a5b4_bf16_n, gemm_f8_a5b4_f32_n, gemm_f8_a4b5_bf16_n,
+         gemm_f8_a4b5_f32_n, gemm_f8_a5b5_bf16_n, gemm_f8_a5b5_f32_n},
+        {gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32, gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32,
+         gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32}};
+    static std::atomic<bool> attr_set[TILE_KINDS][8];  // zero-initialized; a racing second set is harmless
+    const Kernel kernel = kernels[tile][which];
+    int grid = 0, threads = 0, lds = 0;
+    auto shape = [&](auto config, int per_cu) {
+        typedef decltype(config) C;
+        gemm_i8_prepare<C>(args, per_cu * num_compute_units(), &grid);
+        threads = C::THREADS;
+        lds = C::LDS_BYTES;
+    };
+    if (tile == TILES_128)
+        shape(F8Small(), 2);
+    else if (tile == TILES_256X128)
+        shape(F8Narrow(), 1);
+    else
+        shape(F8Cfg(), 1);
+    if (!attr_set[tile][which].load(std::memory_order_acquire)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        attr_set[tile][which].store(true, std::memory_order_release);
+    }
+    kernel<<<grid, threads, lds, stream>>>(args);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *state_row, const uint8_t *bq, int fmt_b,
@@ -40,38 +80,20 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     if (M == 0 || N == 0) return hipSuccess;
     GemmI8Args args{reinterpret_cast<const int8_t *>(aq), reinterpret_cast<const int8_t *>(bq), state_row, state_tensor,
                     nullptr, out, (int)M, (int)N, (int)K, 0, 0, 8, nullptr, nullptr};
-    // Tiles, a small product, or tiles and a small product for the last rows, by the rules of the int8 product.
     const int out_bytes = out_dtype == SB_BF16 ? 2 : 4;
     const ProductPlan plan = plan_product(M, N, K, PRODUCT_F8, out_bytes, num_compute_units());
-    const GemmI8Args rest = rows_from(args, plan.tile_rows, out_bytes);
-    if (plan.tile_rows == 0) return launch_gemm_f8_direct(plan.split, rest, fmt_a, fmt_b, out_dtype, stream);
-    typedef void (*Kernel)(GemmI8Args);
-    static const Kernel kernels[16] = {
-        gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32, gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32,
-        gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32, gemm_f8_a4b4_bf16_s, gemm_f8_a4b4_f32_s, gemm_f8_a5b4_bf16_s,
-        gemm_f8_a5b4_f32_s, gemm_f8_a4b5_bf16_s, gemm_f8_a4b5_f32_s, gemm_f8_a5b5_bf16_s, gemm_f8_a5b5_f32_s};
-    static std::atomic<bool> attr_set[16];  // zero-initialized; a racing second set is harmless
-    const bool small = few_tiles(M, N, num_compute_units());
-    const int which = (small ? 8 : 0) + (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
-    const int lds = small ? F8Small::LDS_BYTES : F8Cfg::LDS_BYTES;
-    if (!attr_set[which].load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[which]),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const int which = (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
+    if (plan.first_rows > 0) {
+        const hipError_t e = launch_tiled(plan.first, which, rows_of(args, 0, plan.first_rows, out_bytes), stream);
         if (e != hipSuccess) return e;
-        attr_set[which].store(true, std::memory_order_release);
     }
-    int grid = 0;
-    args.M = (int)plan.tile_rows;
-    if (small) {
-        gemm_i8_prepare<F8Small>(args, 2 * num_compute_units(), &grid);
-        kernels[which]<<<grid, F8Small::THREADS, lds, stream>>>(args);
-    } else {
-        gemm_i8_prepare<F8Cfg>(args, num_compute_units(), &grid);
-        kernels[which]<<<grid, F8Cfg::THREADS, lds, stream>>>(args);
+    if (plan.tile_rows > plan.first_rows) {
+        const hipError_t e =
+            launch_tiled(plan.second, which, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), stream);
+        if (e != hipSuccess) return e;
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
-    return launch_gemm_f8_direct(plan.split, rest, fmt_a, fmt_b, out_dtype, stream);
+    if (plan.split == DIRECT_NONE) return hipSuccess;
+    return launch_gemm_f8_direct(plan.split, rows_of(args, plan.tile_rows, M, out_bytes), fmt_a, fmt_b, out_dtype, stream);
 }
 
 }  // namespace sb

@@ -27,16 +27,22 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     return hipGetLastError();
 }
 
-// The kernel of a large-tile instance (one wave per SIMD: all 512 registers are a lane's) and its launcher.
-#define SB_LARGE(name, OUT, COLSCALE, POST)                                               \
-    __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_w( \
+// The kernels of a form on 256x256 (_w) and 256x128 tiles (_w128) and their launcher.  One wave per SIMD: all 512 registers
+// are a lane's.
+#define SB_WIDE_KERNEL(name, OUT, COLSCALE, POST, BN)                                     \
+    __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void name( \
         GemmI8Args p) {                                                                   \
-        gemm_i8_wide_body<OUT, COLSCALE, MATH_I8, POST>(p);                               \
-    }                                                                                     \
-    hipError_t name(const GemmI8Args &args, hipStream_t stream) {                         \
-        typedef WideI8Cfg<MATH_I8, COLSCALE, POST> C;                                     \
-        static std::atomic<bool> attr_set; /* zero-initialized */                         \
-        return launch<C>(name##_w, &attr_set, args, stream);                              \
+        gemm_i8_wide_body<OUT, COLSCALE, MATH_I8, POST, BN>(p);                           \
+    }
+#define SB_WIDE(name, OUT, COLSCALE, POST)                                                \
+    SB_WIDE_KERNEL(name##_w, OUT, COLSCALE, POST, 256)                                    \
+    SB_WIDE_KERNEL(name##_w128, OUT, COLSCALE, POST, 128)                                 \
+    hipError_t name(bool narrow, const GemmI8Args &args, hipStream_t stream) {            \
+        typedef WideI8Cfg<MATH_I8, COLSCALE, POST, 256> C;                                \
+        typedef WideI8Cfg<MATH_I8, COLSCALE, POST, 128> C128;                             \
+        static std::atomic<bool> attr_set[2]; /* zero-initialized */                      \
+        return narrow ? launch<C128>(name##_w128, &attr_set[0], args, stream)             \
+                      : launch<C>(name##_w, &attr_set[1], args, stream);                  \
     }
 // A small-tile instance: K a multiple of 128 (_k) and K = 64 mod 128 (_h).  Two waves per SIMD (two workgroups per compute
 // unit): at most 256 registers a lane.
@@ -53,13 +59,13 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
         if (args.K % 128) return launch<GemmI8Cfg>(name##_h, &attr_set[0], args, stream); \
         return launch<GemmI8Cfg>(name##_k, &attr_set[1], args, stream);                   \
     }
-SB_LARGE(gemm_i8_k128_bf16, OUT_BF16, false, false)
-SB_LARGE(gemm_i8_k128_f32, OUT_F32, false, false)
-SB_LARGE(gemm_i8_k128_i32, OUT_I32, false, false)
-SB_LARGE(gemm_i8q_k128_bf16, OUT_BF16, true, false)
-SB_LARGE(gemm_i8q_k128_f32, OUT_F32, true, false)
-SB_LARGE(gemm_i8p_k128_bf16, OUT_BF16, false, true)
-SB_LARGE(gemm_i8p_k128_f32, OUT_F32, false, true)
+SB_WIDE(gemm_i8_k128_bf16, OUT_BF16, false, false)
+SB_WIDE(gemm_i8_k128_f32, OUT_F32, false, false)
+SB_WIDE(gemm_i8_k128_i32, OUT_I32, false, false)
+SB_WIDE(gemm_i8q_k128_bf16, OUT_BF16, true, false)
+SB_WIDE(gemm_i8q_k128_f32, OUT_F32, true, false)
+SB_WIDE(gemm_i8p_k128_bf16, OUT_BF16, false, true)
+SB_WIDE(gemm_i8p_k128_f32, OUT_F32, false, true)
 SB_SMALL(gemm_i8_k128s_bf16, OUT_BF16, false, false)
 SB_SMALL(gemm_i8_k128s_f32, OUT_F32, false, false)
 SB_SMALL(gemm_i8_k128s_i32, OUT_I32, false, false)
@@ -69,7 +75,8 @@ SB_SMALL(gemm_i8p_k128s_bf16, OUT_BF16, false, true)
 SB_SMALL(gemm_i8p_k128s_f32, OUT_F32, false, true)
 #undef SB_SMALL
 #undef SB_SMALL_KERNEL
-#undef SB_LARGE
+#undef SB_WIDE
+#undef SB_WIDE_KERNEL
 
 }  // namespace
 
@@ -89,45 +96,46 @@ int num_compute_units() {
     return n;
 }
 
-GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes) {
+GemmI8Args rows_of(const GemmI8Args &a, int64_t first, int64_t end, size_t out_bytes) {
     GemmI8Args r = a;
     r.a += (size_t)first * (size_t)a.K;
     if (r.state_row != nullptr) r.state_row += first;
     r.out = static_cast<char *>(a.out) + (size_t)first * (size_t)a.N * out_bytes;
-    r.M = a.M - (int)first;
+    r.M = (int)(end - first);
     return r;
 }
 
-// The tiled kernel's instances.
-static hipError_t launch_tiled(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
-    const bool few = few_tiles(args.M, args.N, num_compute_units()), bf = out_dtype == SB_BF16;
+// The tiled kernels' instances.
+static hipError_t launch_tiled(TileKind tile, const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
+    const bool small = tile == TILES_128, narrow = tile == TILES_256X128, bf = out_dtype == SB_BF16;
     if (post)
-        return few ? (bf ? gemm_i8p_k128s_bf16(args, stream) : gemm_i8p_k128s_f32(args, stream))
-                   : (bf ? gemm_i8p_k128_bf16(args, stream) : gemm_i8p_k128_f32(args, stream));
-    // Row-and-column scales: the same line as for the tensor-wise product (6304 x 768 outputs, K = 3072: 37 us on 75 large
-    // tiles, 27 us on 300 small ones).
+        return small ? (bf ? gemm_i8p_k128s_bf16(args, stream) : gemm_i8p_k128s_f32(args, stream))
+                     : (bf ? gemm_i8p_k128_bf16(narrow, args, stream) : gemm_i8p_k128_f32(narrow, args, stream));
     if (args.state_col != nullptr && out_dtype != SB_I32_RAW)
-        return few ? (bf ? gemm_i8q_k128s_bf16(args, stream) : gemm_i8q_k128s_f32(args, stream))
-                   : (bf ? gemm_i8q_k128_bf16(args, stream) : gemm_i8q_k128_f32(args, stream));
+        return small ? (bf ? gemm_i8q_k128s_bf16(args, stream) : gemm_i8q_k128s_f32(args, stream))
+                     : (bf ? gemm_i8q_k128_bf16(narrow, args, stream) : gemm_i8q_k128_f32(narrow, args, stream));
     switch (out_dtype) {
-        case SB_BF16: return few ? gemm_i8_k128s_bf16(args, stream) : gemm_i8_k128_bf16(args, stream);
-        case SB_F32: return few ? gemm_i8_k128s_f32(args, stream) : gemm_i8_k128_f32(args, stream);
-        default: return few ? gemm_i8_k128s_i32(args, stream) : gemm_i8_k128_i32(args, stream);
+        case SB_BF16: return small ? gemm_i8_k128s_bf16(args, stream) : gemm_i8_k128_bf16(narrow, args, stream);
+        case SB_F32: return small ? gemm_i8_k128s_f32(args, stream) : gemm_i8_k128_f32(narrow, args, stream);
+        default: return small ? gemm_i8_k128s_i32(args, stream) : gemm_i8_k128_i32(narrow, args, stream);
     }
 }
 
-// Tiles, a small product, or tiles and a small product for the last rows.
 static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out_dtype, hipStream_t stream) {
     const int out_bytes = out_dtype == SB_BF16 ? 2 : 4;
     const ProductKind kind = post || args.state_col != nullptr ? PRODUCT_LONG_EPILOGUE : PRODUCT_PLAIN;
     const ProductPlan plan = plan_product(args.M, args.N, args.K, kind, out_bytes, num_compute_units());
-    if (plan.tile_rows > 0) {
-        GemmI8Args tiled = args;
-        tiled.M = (int)plan.tile_rows;
-        const hipError_t e = launch_tiled(tiled, post, out_dtype, stream);
-        if (e != hipSuccess || plan.split == DIRECT_NONE) return e;
+    if (plan.first_rows > 0) {
+        const hipError_t e = launch_tiled(plan.first, rows_of(args, 0, plan.first_rows, out_bytes), post, out_dtype, stream);
+        if (e != hipSuccess) return e;
     }
-    return launch_gemm_i8_direct(plan.split, rows_from(args, plan.tile_rows, out_bytes), post, out_dtype, stream);
+    if (plan.tile_rows > plan.first_rows) {
+        const hipError_t e = launch_tiled(plan.second, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), post,
+                                          out_dtype, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (plan.split == DIRECT_NONE) return hipSuccess;
+    return launch_gemm_i8_direct(plan.split, rows_of(args, plan.tile_rows, args.M, out_bytes), post, out_dtype, stream);
 }
 
 hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row, const int8_t *bq,

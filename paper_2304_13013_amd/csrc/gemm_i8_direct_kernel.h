@@ -263,8 +263,8 @@ __device__ __forceinline__ void gemm_i8_direct_body(const GemmI8Args &p) {
 
 // Launchers (gemm_i8_direct.hip).  split: which of the kernel's splits of the work (dispatch.h); they take 0 < M, and
 // operand sizes the tiled kernel accepts too.
-// The product's rows from `first` on (out_bytes: size of an output element).
-GemmI8Args rows_from(const GemmI8Args &a, int64_t first, size_t out_bytes);
+// The product's rows [first, end) (out_bytes: size of an output element).
+GemmI8Args rows_of(const GemmI8Args &a, int64_t first, int64_t end, size_t out_bytes);
 // out_dtype SB_I32_RAW ignores the states; a.state_col != nullptr: row-and-column scales; post: a.bias / a.gamma follow.
 hipError_t launch_gemm_i8_direct(int split, const GemmI8Args &a, bool post, sb_dtype out_dtype, hipStream_t stream);
 hipError_t launch_gemm_f8_direct(int split, const GemmI8Args &a, int fmt_a, int fmt_b, sb_dtype out_dtype,

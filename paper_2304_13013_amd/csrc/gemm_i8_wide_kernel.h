@@ -19,10 +19,16 @@
 //     the start of the second half, hands it over, and the 16 requests per wave of the stage after the next go out during that
 //     half, one per four instructions (16 per 32 or 48 of them: 4 to 10 % slower; spread over both halves: the same).
 //   * The epilogue of a tile is interleaved with the first half stage of the next one: a block's accumulators are read
-//     just before the instruction that starts them again from zero, and converted in its shadow and the next ones'.
+//     just before the instruction that starts them again from zero, and converted in its shadow and the next ones'.  The last
+//     tile's epilogue follows its own last instructions at a distance (3588 x 2560, K = 128: 7.8 -> 7.4 us).
 //     Results go through a wave-private LDS patch (padded rows) and leave as 16-byte non-temporal stores in row segments of
 //     256 (float8: 128) bytes.
 //   * Row states, column states, bias and layer-scale of a tile are requested into LDS with its first stage.
+// 256x128 tiles (waves of 128x64, half the accumulators) are for products whose 256x256 tiles do not fill the GPU or fill its
+// last round badly.  A stage is 48 KiB and three fit; its requests are spread over two half stages, and land a stage later.
+// Against 128x128 tiles, two workgroups per compute unit (us): 6304 x 768, K = 3072 24.2 -> 20.4; 8000 x 1024, K = 4096 37.0
+// -> 30.5; against 256x256 tiles: 6304 x 3072, K = 768 21.7 -> 20.3; 11237 x 2880, K = 1088 43.5 -> 37.3.
+//
 // All loops count on a constant number of vector-memory operations: past the last tile the requests go on with an empty
 // buffer resource, rows past the end lie beyond the output's resource and columns past the end are sent there.
 //
@@ -63,52 +69,57 @@ __device__ __forceinline__ void keep_out_of_agprs() {
                  "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255");
 }
 
-template <int MATH, bool COLSCALE, bool POST>
+template <int MATH, bool COLSCALE, bool POST, int BN_ = 256>
 struct WideI8Cfg {
     static constexpr bool F8 = MATH >= MATH_F8;
-    static constexpr int BM = 256, BN = 256, BK = 128, STAGES = 2, THREADS = 256;
-    static constexpr int WT = 128;                       // wave tile
-    static constexpr int OP_BYTES = 256 * BK, STAGE_BYTES = 2 * OP_BYTES;  // token-side tile, then weight-side tile
-    static constexpr int LPW = STAGE_BYTES / 1024 / 4;   // 1 KiB requests per wave and stage
-    static constexpr int BLK = F8 ? 32 : 16, NB = WT / BLK;  // matrix instruction blocks of a wave tile
+    static constexpr int BM = 256, BN = BN_, BK = 128, THREADS = 256;
+    static constexpr int STAGES = BN == 256 ? 2 : 3;
+    static constexpr int WTM = 128, WTN = BN / 2;        // wave tile
+    static constexpr int A_BYTES = BM * BK, STAGE_BYTES = (BM + BN) * BK;  // token-side tile, then weight-side tile
+    static constexpr int REQ_A = BM / 32, REQ_B = BN / 32, LPW = REQ_A + REQ_B;  // 1 KiB requests per wave and stage
+    static constexpr int BLK = F8 ? 32 : 16, NBM = WTM / BLK, NBN = WTN / BLK;  // matrix instruction blocks of a wave tile
     static constexpr int QUADS = F8 ? 4 : 1;             // accumulator quads of a block, eight columns apart
-    static constexpr int SLOTS = NB * NB;                // matrix instructions per half stage
-    static constexpr int NREADS = 16;                    // fragment reads per wave and half stage
-    // Patch that transposes the bf16 results of one block row (half a block row with 32-row blocks), padded rows.
-    static constexpr int PATCH_COLS = F8 ? 64 : 128, PATCH_PITCH = PATCH_COLS * 2 + 16;
-    static constexpr int PATCH_BYTES = BLK * PATCH_PITCH;
-    // Vectors of a tile in LDS (256 floats each), and the tiles they are kept for: the load cursor runs up to three
-    // stages ahead of the epilogue that reads them, so with tiles of one stage they need four places.
-    static constexpr int NVEC = 1 + COLSCALE + 2 * POST, RING = 4;
+    static constexpr int SLOTS = NBM * NBN;              // matrix instructions per half stage
+    static constexpr int RPF = F8 ? 2 : 1;               // 16-byte reads per fragment
+    static constexpr int NREADS = (NBM + NBN) * RPF;     // fragment reads per wave and half stage
+    // Requests of a stage that go out during the second half of the stage STAGES before it; the others follow during the
+    // next first half.
+    static constexpr int REQ_2ND = BN == 256 ? LPW : LPW / 2;
+    // Patch that transposes the bf16 results of one block row (part of one with 32-row blocks), padded rows.
+    static constexpr int PATCH_COLS = F8 ? WTN / 2 : WTN, PATCH_PITCH = PATCH_COLS * 2 + 16;
+    static constexpr int PATCH_BYTES = BLK * PATCH_PITCH, PATCH_SLOTS = PATCH_COLS / BLK;
+    static constexpr int PPR = PATCH_COLS / 8, PATCH_READS = BLK * PPR / 64;  // 16-byte pieces per row; reads of a patch
+    // Vectors of a tile in LDS (a float per row or column), and the tiles they are kept for.  A new tile's vectors are
+    // requested up to STAGES + 1 stages ahead of its first epilogue, and what they overwrite must have been read before the
+    // last barrier: with tiles of at least MIN_KT stages this many places do.
+    static constexpr int MIN_KT = BN == 256 ? 1 : 2, RING = BN == 256 ? 4 : 3;
     static constexpr int VEC_AT = STAGES * STAGE_BYTES + 4 * PATCH_BYTES;
-    static constexpr int LDS_BYTES = VEC_AT + NVEC * RING * 1024;
+    static constexpr int VEC_BYTES = BM * 4 + (COLSCALE + 2 * POST) * BN * 4;
+    static constexpr int LDS_BYTES = VEC_AT + RING * VEC_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-template <int OUT, bool COLSCALE, int MATH, bool POST>
+template <int OUT, bool COLSCALE, int MATH, bool POST, int BN = 256>
 __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
-    typedef WideI8Cfg<MATH, COLSCALE, POST> C;
-    constexpr int S = C::STAGES, NB = C::NB;
+    typedef WideI8Cfg<MATH, COLSCALE, POST, BN> C;
+    constexpr int S = C::STAGES, NBM = C::NBM, NBN = C::NBN, RPF = C::RPF;
     constexpr bool F8 = C::F8;
     constexpr int FMT_X = MATH & 1, FMT_W = (MATH >> 1) & 1;
     typedef typename std::conditional<F8, float, int>::type AccE;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: what derives from it is scalar
     const int lane = threadIdx.x & 63;
-    const int wm0 = (wave >> 1) * C::WT, wn0 = (wave & 1) * C::WT;
+    const int wm0 = (wave >> 1) * C::WTM, wn0 = (wave & 1) * C::WTN;
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    // Stages of a tile; K = 64 mod 128 ends in half a stage of zeros.
-    const int KT = (p.K + C::BK - 1) / C::BK;
+    // Stages of a tile; K = 64 mod 128 ends in half a stage of zeros, and a stage of zeros follows if that makes too few.
+    const int KT = max((p.K + C::BK - 1) / C::BK, C::MIN_KT);
+    const int zero_stages = KT - (p.K + C::BK - 1) / C::BK;
     const bool half_last = !F8 && p.K % C::BK != 0;
 
-    // ---- Requests.  Waves 0 and 1 load the token side (a), 2 and 3 the weight side (b).  Rows past M (or N) read as zero
-    // through the bounds check.
-    const bool loads_a = wave < 2;
-    void *const operand = (void *)(loads_a ? p.a : p.b);
-    const unsigned row0 = (wave & 1) * 128;
-    // Request i fills rows row0 + 8i .. + 7 of the operand's tile; LDS slot (row, p) holds 16-byte chunk p ^ f(row), f = the
-    // row's lowest three bits (16-row blocks) or the three above the lowest (32-row blocks).
+    // ---- Requests.  Every wave loads a quarter of the token side's rows (a) and of the weight side's (b), eight rows a
+    // request; LDS slot (row, p) holds 16-byte chunk p ^ f(row), f = the row's lowest three bits (16-row blocks) or the three
+    // above the lowest (32-row blocks).  Rows past M (or N) read as zero through the bounds check.
     const int l_row = lane >> 3;
     unsigned voff[2];
 #pragma unroll
@@ -129,38 +140,49 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
         t.have = gemm_tile_of(blockIdx.x, round, gridDim.x, p.tiles_m, p.tiles_n, p.group_m, &t.tm, &t.tn);
         return t;
     };
-    // Load cursor: two stages ahead of the matrix instructions, across tiles.
+    // Load cursor: STAGES stages ahead of the matrix instructions, across tiles.
     int l_round = 0, l_left = 0, l_ring = C::RING - 1;
-    unsigned l_soff = 0, l_bytes = 0;  // offset of the next stage; size of the operand, 0 past the last tile
-    auto request_vec = [&](const float *src, int which, int first, int count) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, (unsigned)count * 4, 0x00020000),
-            (lds_void *)(smem + C::VEC_AT + (which * C::RING + l_ring) * 1024 + wave * 256), 4, lane * 4,
-            (unsigned)(first + wave * 64) * 4, 0, 0);
+    unsigned l_a = 0, l_b = 0;              // offsets of the next stage in the operands
+    unsigned l_a_bytes = 0, l_b_bytes = 0;  // sizes of the operands, 0 past the last tile
+    auto request_vec = [&](const float *src, int at, int first, int count, int n) {  // n of src's floats from `first`
+        if (wave * 64 < n)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, (unsigned)count * 4, 0x00020000),
+                (lds_void *)(smem + C::VEC_AT + l_ring * C::VEC_BYTES + at + wave * 256), 4, lane * 4,
+                (unsigned)(first + wave * 64) * 4, 0, 0);
     };
     auto next_tile_sources = [&]() {
         const Tile t = tile_of(l_round++);
         l_left = t.have ? KT : 1 << 30;
-        l_bytes = t.have ? (unsigned)(loads_a ? p.M : p.N) * (unsigned)p.K : 0;
-        l_soff = ((unsigned)(loads_a ? t.tm : t.tn) * 256 + row0) * (unsigned)p.K;
+        l_a_bytes = t.have ? (unsigned)p.M * (unsigned)p.K : 0;
+        l_b_bytes = t.have ? (unsigned)p.N * (unsigned)p.K : 0;
+        l_a = (unsigned)(t.tm * C::BM + wave * (C::BM / 4)) * (unsigned)p.K;
+        l_b = (unsigned)(t.tn * C::BN + wave * (C::BN / 4)) * (unsigned)p.K;
         l_ring = l_ring + 1 == C::RING ? 0 : l_ring + 1;
         if (t.have && OUT != OUT_I32) {
-            request_vec(p.state_row, 0, t.tm * C::BM, p.M);
-            if (COLSCALE) request_vec(p.state_col, 1, t.tn * C::BN, p.N);
-            if (POST && p.bias != nullptr) request_vec(p.bias, 1, t.tn * C::BN, p.N);
-            if (POST && p.gamma != nullptr) request_vec(p.gamma, 2, t.tn * C::BN, p.N);
+            request_vec(p.state_row, 0, t.tm * C::BM, p.M, C::BM);
+            if (COLSCALE) request_vec(p.state_col, C::BM * 4, t.tn * C::BN, p.N, C::BN);
+            if (POST && p.bias != nullptr) request_vec(p.bias, C::BM * 4, t.tn * C::BN, p.N, C::BN);
+            if (POST && p.gamma != nullptr) request_vec(p.gamma, C::BM * 4 + C::BN * 4, t.tn * C::BN, p.N, C::BN);
         }
     };
     auto issue_req = [&](int slot, int i) {
+        const bool is_a = i < C::REQ_A;
+        const int r = is_a ? i : i - C::REQ_A;
+        unsigned char *dst = smem + slot * C::STAGE_BYTES +
+                             (is_a ? wave * C::REQ_A * 1024 : C::A_BYTES + wave * C::REQ_B * 1024) + r * 1024;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            __builtin_amdgcn_make_buffer_rsrc(operand, 0, l_bytes, 0x00020000),
-            (lds_void *)(smem + slot * C::STAGE_BYTES + (wave * C::LPW + i) * 1024), 16,
-            half_last && l_left == 1 ? voff_half : voff[F8 ? i & 1 : 0],
-            l_soff + (unsigned)i * req_step, 0, 0);
+            __builtin_amdgcn_make_buffer_rsrc((void *)(is_a ? p.a : p.b), 0, is_a ? l_a_bytes : l_b_bytes, 0x00020000),
+            (lds_void *)dst, 16, half_last && l_left == 1 + zero_stages ? voff_half : voff[F8 ? r & 1 : 0],
+            (is_a ? l_a : l_b) + (unsigned)r * req_step, 0, 0);
     };
     auto advance = [&]() {
-        l_soff += C::BK;
-        if (--l_left == 0) next_tile_sources();
+        l_a += C::BK;
+        l_b += C::BK;
+        if (--l_left == 0)
+            next_tile_sources();
+        else if (C::MIN_KT > 1 && l_left <= zero_stages)
+            l_a_bytes = l_b_bytes = 0;
     };
     next_tile_sources();
 #pragma unroll
@@ -173,16 +195,17 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     // ---- Fragments: 16 (float8: 32) bytes of one row a lane.  Which bytes of k a lane holds does not matter as long as both
     // operands agree.
     typedef v4i Half;
-    constexpr int RPF = F8 ? 2 : 1;  // 16-byte reads per fragment
     const int f_r = lane & (C::BLK - 1), f_g = lane / C::BLK;
     // Chunk h * 4 + f_g (int8) or h * 4 + 2 * f_g and the one after it (float8) of row f_r, for half h of the stage.
     const unsigned f_off = f_r * C::BK + (F8 ? ((f_g * 2) ^ ((f_r >> 1) & 7)) << 4 : (f_g ^ (f_r & 7)) << 4);
-    const unsigned x_lane = lds_base + wm0 * C::BK + f_off, w_lane = lds_base + C::OP_BYTES + wn0 * C::BK + f_off;
-    Half xf[2][NB][RPF], wf[2][NB][RPF];
+    const unsigned x_lane = lds_base + wm0 * C::BK + f_off, w_lane = lds_base + C::A_BYTES + wn0 * C::BK + f_off;
+    Half xf[2][NBM][RPF], wf[2][NBN][RPF];
     auto issue_read = [&](int i, int buf, int slot) {  // of half `buf` of the stage in `slot`, into register buffer buf
         constexpr int STEP = C::BLK * C::BK;
-        const int f = i / (2 * RPF), h = i % RPF;
-        const bool is_x = (i / RPF) & 1;
+        // Fragments in the order w0 x0 w1 x1 ..., then the token side's others.
+        const int n = i / RPF, h = i % RPF;
+        const bool is_x = n < 2 * NBN ? n & 1 : true;
+        const int f = n < 2 * NBN ? n >> 1 : n - NBN;
         const unsigned at = ((is_x ? x_lane : w_lane) ^ (buf << 6 | h << 4)) + slot * C::STAGE_BYTES;
         Half &dst = is_x ? xf[buf][f][h] : wf[buf][f][h];
         switch (f) {
@@ -198,12 +221,12 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     };
     auto pin_frags = [&](int buf) {
 #pragma unroll
-        for (int f = 0; f < NB; ++f)
+        for (int h = 0; h < RPF; ++h) {
 #pragma unroll
-            for (int h = 0; h < RPF; ++h) {
-                asm volatile("" : "+v"(xf[buf][f][h]));
-                asm volatile("" : "+v"(wf[buf][f][h]));
-            }
+            for (int f = 0; f < NBM; ++f) asm volatile("" : "+v"(xf[buf][f][h]));
+#pragma unroll
+            for (int f = 0; f < NBN; ++f) asm volatile("" : "+v"(wf[buf][f][h]));
+        }
     };
 
     float tensor_scale = 0.0f;
@@ -215,13 +238,13 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
 #pragma unroll
     for (int i = 0; i < C::NREADS; ++i) issue_read(i, 0, 0);
 
-    int g = 0;
-    bool slack = false;
+    int slot = 0;   // of the stage in work
+    int slack = 0;  // hand-overs whose wait may leave an epilogue's stores outstanding
 
     // ---- Epilogue of the tile that has just been finished.  Bias and layer-scale that are absent become -0 and 1, which
     // change no value.
-    float rscale[NB];
-    v4f scol[COLSCALE || POST ? NB : 1], sgam[POST ? NB : 1];
+    float rscale[NBM];
+    v4f scol[COLSCALE || POST ? NBN : 1], sgam[POST ? NBN : 1];
     __amdgpu_buffer_rsrc_t rsrc_out;
     unsigned o_voff = 0;
     int cols_in = 0, n_out = p.N;
@@ -229,37 +252,37 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     constexpr int OB = OUT == OUT_BF16 ? 2 : 4;
     const unsigned patch = lds_base + S * C::STAGE_BYTES + wave * C::PATCH_BYTES;
     const unsigned patch_w = patch + f_r * C::PATCH_PITCH + f_g * 8;
-    constexpr int PPR = C::PATCH_COLS / 8;  // 16-byte pieces per patch row
+    constexpr int PPR = C::PPR;
     const unsigned patch_r = patch + (lane / PPR) * C::PATCH_PITCH + (lane % PPR) * 16;
 
     auto epi_begin = [&](const Tile &t, int ring) {
-        const unsigned vec = lds_base + C::VEC_AT + ring * 1024;
+        const unsigned vec = lds_base + C::VEC_AT + ring * C::VEC_BYTES;
         if (OUT != OUT_I32) {
             const unsigned at = vec + (wm0 + f_r) * 4;
 #pragma unroll
-            for (int a = 0; a < NB; ++a)
+            for (int a = 0; a < NBM; ++a)
                 asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(rscale[a]) : "v"(at), "n"(a * C::BLK * 4));
         }
         if (COLSCALE || POST) {
-            const unsigned at = vec + C::RING * 1024 + (wn0 + 4 * f_g) * 4;
+            const unsigned at = vec + C::BM * 4 + (wn0 + 4 * f_g) * 4;
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NBN; ++b)
                 asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(scol[b]) : "v"(at), "n"(b * 64));
             if (POST)
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(sgam[b]) : "v"(at + C::RING * 1024), "n"(b * 64));
+                for (int b = 0; b < NBN; ++b)
+                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(sgam[b]) : "v"(at + C::BN * 4), "n"(b * 64));
         }
         wait_lds_reads();
         if (OUT != OUT_I32) {
 #pragma unroll
-            for (int a = 0; a < NB; ++a) asm volatile("" : "+v"(rscale[a]));
+            for (int a = 0; a < NBM; ++a) asm volatile("" : "+v"(rscale[a]));
 #pragma unroll
-            for (int a = 0; a < NB; ++a) rscale[a] = COLSCALE ? rscale[a] : rscale[a] * tensor_scale;
+            for (int a = 0; a < NBM; ++a) rscale[a] = COLSCALE ? rscale[a] : rscale[a] * tensor_scale;
         }
         if (COLSCALE || POST)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
+            for (int b = 0; b < NBN; ++b) {
                 asm volatile("" : "+v"(scol[b]));
                 if (POST) asm volatile("" : "+v"(sgam[b]));
 #pragma unroll
@@ -270,7 +293,7 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
                 }
             }
         const int m_base = t.tm * C::BM + wm0, n_base = t.tn * C::BN + wn0;
-        const unsigned rows_in = __builtin_amdgcn_readfirstlane(min(max(p.M - m_base, 0), C::WT));
+        const unsigned rows_in = __builtin_amdgcn_readfirstlane(min(max(p.M - m_base, 0), C::WTM));
         cols_in = p.N - n_base;
         n_out = p.N;
         asm volatile("" : "+s"(n_out));
@@ -283,7 +306,7 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
         else
             o_voff = (unsigned)((lane_e & (C::BLK - 1)) * p.N + (lane_e / C::BLK) * 4) * 4;
     };
-    v4u val[4];
+    v4u val[C::PATCH_READS];
     // Quad q of block (a, b): x are its accumulators.
     auto epi_quad = [&](int a, int b, int q, const AccE *x) {
         if (OUT == OUT_I32) {
@@ -312,100 +335,123 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     };
     auto epi_read_patch = [&]() {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < C::PATCH_READS; ++j)
             asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(val[j]) : "v"(patch_r), "n"(j * (64 / PPR) * C::PATCH_PITCH));
     };
     auto epi_store_patch = [&](int a, int col0) {  // after a wait
         const unsigned at = (lane % PPR) * 8 + col0 < cols_in ? o_voff : NOWHERE;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < C::PATCH_READS; ++j) {
             asm volatile("" : "+v"(val[j]));
             __builtin_amdgcn_raw_buffer_store_b128(val[j], rsrc_out, at,
                                                    (unsigned)((a * C::BLK + j * (64 / PPR)) * n_out + col0) * 2, 2);
         }
     };
-    constexpr int PATCH_SLOTS = C::PATCH_COLS / C::BLK;  // blocks of a patch
+    constexpr int PATCH_SLOTS = C::PATCH_SLOTS;  // blocks of a patch
+    // Stores of an epilogue, per lane, that follow its last request (four-byte int8 results are stored block by block, from the
+    // first one on, which has its share of the requests).
+    constexpr int STORES = (OUT == OUT_BF16 ? C::WTM * C::WTN / 512 : C::WTM * C::WTN / 256) -
+                           (OUT != OUT_BF16 && !F8 ? C::LPW - C::REQ_2ND : 0);
 
     // Half a stage: NORMAL; the FIRST of a tile, which starts the accumulators from zero; the same with the epilogue of the
-    // tile before; the epilogue alone.  cur: which half, and its register buffer.
-    enum { NORMAL, FIRST, FIRST_EPI, DRAIN };
+    // tile before; the LAST of the workgroup, with its tile's own epilogue.  cur: which half, and its register buffer.
+    enum { NORMAL, FIRST, FIRST_EPI, LAST };
     auto period = [&](auto cur_c, auto kind_c) __attribute__((always_inline)) {
         constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1, kind = decltype(kind_c)::value;
-        constexpr bool epi = kind == FIRST_EPI || kind == DRAIN, mm = kind != DRAIN;
-        const int slot = g & (S - 1), next_slot = cur ? slot ^ 1 : slot;
+        constexpr bool epi = kind == FIRST_EPI || kind == LAST, more = kind != LAST;  // more: another half stage follows
+        // The epilogue of a block in the LAST half stage comes this many instructions after its last one: a result is there
+        // 11 (float8: 19) wait states after its instruction, and nobody but these distances sees to it.
+        constexpr int LAG = kind == LAST ? (F8 ? 2 : 4) : 0;
+        const int next_slot = !cur ? slot : slot + 1 == S ? 0 : slot + 1, prev_slot = slot == 0 ? S - 1 : slot - 1;
         keep_out_of_agprs();
-        if (mm) {
-            if (cur) {  // the next stage has landed; behind it are at most the stores of an epilogue half a stage ago
-                if (!slack) {
-                    wait_vmcnt<0>();
-                } else {
-                    slack = false;
-                    wait_vmcnt<OUT == OUT_BF16 ? 32 : 63>();
-                }
+        if (cur && more) {
+            // The next stage has landed.  Behind it are the requests of the STAGES - 2 stages after it and the stores of an
+            // epilogue in one of the STAGES - 1 first halves before.
+            constexpr int later = (S - 2) * C::LPW, with_stores = later + STORES < 63 ? later + STORES : 63;
+            if (slack == 0) {
+                wait_vmcnt<later>();
+            } else {
+                --slack;
+                wait_vmcnt<with_stores>();
             }
-            wait_lds_reads();
-            if (cur) block_barrier();
-            pin_frags(cur);
         }
+        wait_lds_reads();
+        if (cur && more) block_barrier();
+        pin_frags(cur);
 #pragma unroll
-        for (int idx = 0; idx < C::SLOTS; ++idx) {
-            const int a = idx / NB, b = !F8 && !epi && (a & 1) ? NB - 1 - idx % NB : idx % NB;
-            if (epi && OUT == OUT_BF16 && idx >= PATCH_SLOTS && idx % PATCH_SLOTS == (F8 ? 1 : 3)) {
-                // The patch reads of the blocks before these have landed: behind them are at least the writes of one (float8)
-                // or three blocks (and some fragment reads).
-                wait_lgkmcnt<F8 ? 4 : 3>();
-                const int last = idx / PATCH_SLOTS * PATCH_SLOTS - 1;
-                epi_store_patch(last / NB, last % NB / PATCH_SLOTS * C::PATCH_COLS);
-            }
+        for (int idx = 0; idx < C::SLOTS + LAG; ++idx) {
             constexpr int NACC = F8 ? 16 : 4;
-            const int r0 = (a * NB + b) * NACC;  // first accumulator of the block
+            const int a = idx / NBN, b = !F8 && !epi && (a & 1) ? NBN - 1 - idx % NBN : idx % NBN;
+            const int r0 = (a * NBN + b) * NACC;  // first accumulator of the block
+            const int e = idx - LAG, ea = e / NBN, eb = e % NBN;  // block whose epilogue it is
             AccE x[NACC];
-            if (epi)
+            auto read_block = [&]() {
 #pragma unroll
-                for (int e = 0; e < NACC; ++e) asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x[e]) : "n"(r0 + e));
-            if (mm) {
+                for (int i = 0; i < NACC; ++i) asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x[i]) : "n"(e * NACC + i));
+            };
+            auto store_patch_before = [&](int behind) {  // its reads have landed, at least `behind` operations are behind them
+                if (behind == 3) wait_lgkmcnt<3>(); else if (behind == 2) wait_lgkmcnt<2>(); else wait_lgkmcnt<0>();
+                const int last = e / PATCH_SLOTS * PATCH_SLOTS - 1;
+                epi_store_patch(last / NBN, last % NBN / PATCH_SLOTS * C::PATCH_COLS);
+            };
+            if (kind == FIRST_EPI) read_block();
+            if (idx < C::SLOTS) {
                 if constexpr (F8) {
                     const v8i w8 = __builtin_shufflevector(wf[cur][b][0], wf[cur][b][RPF - 1], 0, 1, 2, 3, 4, 5, 6, 7);
                     const v8i x8 = __builtin_shufflevector(xf[cur][a][0], xf[cur][a][RPF - 1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    if constexpr (kind == NORMAL)
+                    if constexpr (kind == NORMAL || kind == LAST)
                         asm volatile("v_mfma_f32_32x32x64_f8f6f4 a[%0:%1], %2, %3, a[%0:%1] cbsz:%4 blgp:%5" ::"n"(r0), "n"(r0 + 15), "v"(w8), "v"(x8), "n"(FMT_W), "n"(FMT_X));
                     else
                         asm volatile("v_mfma_f32_32x32x64_f8f6f4 a[%0:%1], %2, %3, 0 cbsz:%4 blgp:%5" ::"n"(r0), "n"(r0 + 15), "v"(w8), "v"(x8), "n"(FMT_W), "n"(FMT_X));
                 } else {
-                    if constexpr (kind == NORMAL)
+                    if constexpr (kind == NORMAL || kind == LAST)
                         asm volatile("v_mfma_i32_16x16x64_i8 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(r0), "n"(r0 + 3), "v"(wf[cur][b][0]), "v"(xf[cur][a][0]));
                     else
                         asm volatile("v_mfma_i32_16x16x64_i8 a[%0:%1], %2, %3, 0" ::"n"(r0), "n"(r0 + 3), "v"(wf[cur][b][0]), "v"(xf[cur][a][0]));
                 }
-                
-                
+            }
+            if constexpr (more) {
+                // Fragment reads: the first ones with the fifth int8 instruction, so that all land before the half stage ends.
+                constexpr int RD = C::SLOTS / C::NREADS - (BN == 256 ? 1 : 0);
                 if constexpr (F8) {
 #pragma unroll
                     for (int i = 2 * idx; i < 2 * idx + 2; ++i)
                         if (i < C::NREADS) issue_read(i, nxt, next_slot);
-                } else if (idx >= 4 && (idx - 4) % 3 == 0 && (idx - 4) / 3 < C::NREADS) {
-                    issue_read((idx - 4) / 3, nxt, next_slot);
+                } else if (idx >= 4 && (idx - 4) % RD == 0 && (idx - 4) / RD < C::NREADS) {
+                    issue_read((idx - 4) / RD, nxt, next_slot);
                 }
-
-                constexpr int RQ = C::SLOTS / C::LPW;
-                if (cur && idx % RQ == RQ / 2) issue_req(slot, idx / RQ);
-            }
-            if (epi) {
+                // Requests.
+                constexpr int N2 = C::REQ_2ND, N1 = C::LPW - N2;
+                if constexpr (cur == 1) {
+                    constexpr int RQ = C::SLOTS / N2;
+                    if (idx % RQ == RQ / 2 && idx / RQ < N2) issue_req(slot, idx / RQ);
+                } else if constexpr (N1 > 0 && kind != FIRST) {
+                    constexpr int RQ = epi ? 1 : C::SLOTS / N1, PER = epi && F8 ? N1 : 1;
 #pragma unroll
-                for (int q = 0; q < C::QUADS; ++q) epi_quad(a, b, q, x);
-                if (OUT == OUT_BF16 && (idx + 1) % PATCH_SLOTS == 0) epi_read_patch();
+                    for (int i = idx / RQ * PER; i < (idx / RQ + 1) * PER; ++i)
+                        if (idx % RQ == RQ / 2 && i < N1) issue_req(prev_slot, N2 + i);
+                }
+            }
+            if (epi && e >= 0) {
+                // A patch is stored after its reads have travelled for a while: behind them are the writes of three int8 blocks,
+                // or (float8, right after the matrix instruction) two fragment reads while there are any.
+                const bool store = OUT == OUT_BF16 && e >= PATCH_SLOTS && e % PATCH_SLOTS == (F8 ? 0 : 3);
+                if (store && F8) store_patch_before(more && 2 * idx + 2 <= C::NREADS ? 2 : 0);
+                if (store && !F8) store_patch_before(3);
+                if (kind == LAST) read_block();
+#pragma unroll
+                for (int q = 0; q < C::QUADS; ++q) epi_quad(ea, eb, q, x);
+                if (OUT == OUT_BF16 && (e + 1) % PATCH_SLOTS == 0) epi_read_patch();
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         if (epi && OUT == OUT_BF16) {
             wait_lds_reads();
-            epi_store_patch(NB - 1, C::WT - C::PATCH_COLS);
+            epi_store_patch(NBM - 1, C::WTN - C::PATCH_COLS);
         }
-        if (cur) {
-            advance();
-            ++g;
-        }
-        if (epi) slack = true;
+        if (C::REQ_2ND == C::LPW ? cur == 1 && more : cur == 0 && (kind == NORMAL || kind == FIRST_EPI)) advance();
+        if (cur) slot = next_slot;
+        if (epi) slack = S - 1;
         keep_out_of_agprs();
     };
     typedef std::integral_constant<int, 0> I0;
@@ -413,9 +459,9 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     typedef std::integral_constant<int, NORMAL> KNormal;
     typedef std::integral_constant<int, FIRST> KFirst;
     typedef std::integral_constant<int, FIRST_EPI> KFirstEpi;
-    typedef std::integral_constant<int, DRAIN> KDrain;
+    typedef std::integral_constant<int, LAST> KLast;
 
-    Tile t = tile_of(0), prev = t;
+    Tile t = tile_of(0);
     if (!t.have) {
         wait_vmcnt<0>();
         wait_lds_reads();
@@ -424,22 +470,21 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     int ring = 0;
     period(I0(), KFirst());
     for (int round = 1;; ++round) {
-        period(I1(), KNormal());
         for (int kt = 1; kt < KT; ++kt) {
-            period(I0(), KNormal());
             period(I1(), KNormal());
+            period(I0(), KNormal());
         }
-        prev = t;
-        t = tile_of(round);
-        epi_begin(prev, ring);
+        const Tile next = tile_of(round);
+        if (!next.have) break;
+        period(I1(), KNormal());
+        epi_begin(t, ring);
         ring = ring + 1 == C::RING ? 0 : ring + 1;
-        if (!t.have) break;
+        t = next;
         period(I0(), KFirstEpi());
     }
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    period(I0(), KDrain());
-    wait_vmcnt<0>();
-    wait_lds_reads();
+    epi_begin(t, ring);
+    period(I1(), KLast());
+    wait_vmcnt<0>();  // the requests past the end write LDS
 }
 
 }  // namespace sb

@@ -165,12 +165,25 @@ def test_large_tiles(oracle, M, N, K):
     test_half_stages_and_last_rows(oracle, M, N, K)
 
 
-# Exact sums, as for the small float8 products: last rows, and the small tile with ragged edges.
+# 256x128 tiles: a contraction shorter than the two stages they make of it (with the longer epilogues), half a last stage,
+# one tile and several per workgroup, partial in both directions; and the same rows on two kinds of tiles, split after whole
+# rounds of the grid.  (A host test checks which tiles each size takes.)
+NARROW = [(34462, 384, 64), (34462, 384, 128), (4048, 1984, 192), (6304, 832, 1088), (11237, 2880, 192),
+          (12345, 3328, 384), (22069, 2240, 2048)]
+
+
+@pytest.mark.parametrize("M,N,K", NARROW)
+def test_narrow_tiles_and_whole_rounds(oracle, M, N, K):
+    test_half_stages_and_last_rows(oracle, M, N, K)
+
+
+# Exact sums, as for the small float8 products: last rows, the small tile with ragged edges, 256x128 tiles, whole rounds.
 TILES_F8 = [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2112, 384)]
+NARROW_F8 = [(6304, 768, 3072), (5431, 960, 4096), (22069, 1472, 384)]
 
 
 @pytest.mark.parametrize("fa,fb", [(1, 0), (0, 0)])
-@pytest.mark.parametrize("M,N,K", TILES_F8)
+@pytest.mark.parametrize("M,N,K", TILES_F8 + NARROW_F8)
 def test_tiles_of_a_float8_product(M, N, K, fa, fb):
     check_exact_float8_product(M, N, K, fa, fb)
 

@@ -19,6 +19,13 @@ long long plan_product(long long M, long long N, long long K, int kind, int out_
     *split = p.split;
     return p.tile_rows;
 }
+// Rows [0, result) on the first kind of tiles, the others on the second one.
+long long plan_tiles(long long M, long long N, long long K, int kind, int out_bytes, int ncu, int *first, int *second) {
+    const sb::ProductPlan p = sb::plan_product(M, N, K, (sb::ProductKind)kind, out_bytes, ncu);
+    *first = p.first;
+    *second = p.second;
+    return p.first_rows;
+}
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
 int adamw_blocks(long long count) { return sb::adamw_blocks(count); }
 long long adamw_elements_at_least(long long blocks, long long n) { return sb::adamw_elements_at_least(blocks, n); }
@@ -33,6 +40,7 @@ long long bad_plan(long long lo, long long hi, long long step, long long N, long
         if (direct != (p.tile_rows < M)) return M;                       // rows past the tiles need a split, and only they
         if (p.tile_rows == 0 && !sb::few_tiles(M, N, ncu)) return M;     // many tiles: never all rows off the tiles
         if (direct && p.tile_rows % 256) return M;                      // the tiles that stay are whole
+        if (p.first_rows < 0 || p.first_rows > p.tile_rows || p.first_rows % 256) return M;
         if (p.tile_rows > 0 && sb::persistent_grid((p.tile_rows + 255) / 256 * ((N + 255) / 256), ncu) < 8) return M;
     }
     return 0;
@@ -53,6 +61,8 @@ def rules(tmp_path_factory):
     rules.few_tiles.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int]
     rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     rules.plan_product.restype = ctypes.c_longlong
+    rules.plan_tiles.argtypes = rules.plan_product.argtypes + [ctypes.POINTER(ctypes.c_int)]
+    rules.plan_tiles.restype = ctypes.c_longlong
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
     rules.adamw_blocks.argtypes = [ctypes.c_longlong]
     rules.adamw_elements_at_least.argtypes = [ctypes.c_longlong] * 2
@@ -132,6 +142,32 @@ def test_sizes_of_the_gpu_tests_reach_every_path(rules):
     plans = [(M, rules.few_tiles(M, N, 256), route(rules, M, N, K, 4, F8)) for M, N, K in sizes.TILES_F8]
     assert {(bool(few), rows < M) for M, few, (rows, _) in plans} == {(True, False), (False, True)}
     assert all(rows > 0 for _, _, (rows, _) in plans)
+
+
+TILES_128, TILES_256X128, TILES_256 = range(3)
+
+
+def tiles(rules, M, N, K, kind, out_bytes):
+    """(rows on the first tiles, their kind or None, kind of the others or None) on an MI355X."""
+    first, second = ctypes.c_int(-1), ctypes.c_int(-1)
+    rows = rules.plan_tiles(M, N, K, kind, out_bytes, 256, ctypes.byref(first), ctypes.byref(second))
+    return rows, first.value if rows else None, second.value if rows < route(rules, M, N, K, out_bytes, kind)[0] else None
+
+
+def test_sizes_of_the_gpu_tests_reach_every_tile(rules):
+    import test_dispatch_gpu as sizes
+    for kind, out_bytes in ((PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (LONG_EPILOGUE, 4)):
+        plans = [(M, N, K, *tiles(rules, M, N, K, kind, out_bytes)) for M, N, K in sizes.NARROW]
+        narrow = {("half" if K % 128 else "whole", -(-M // 256) * -(-N // 128) > 256)
+                  for M, N, K, rows, _, second in plans if rows == 0 and second == TILES_256X128}
+        assert {("half", True), ("whole", True)} <= narrow, (kind, out_bytes, plans)
+        if (kind, out_bytes) == (LONG_EPILOGUE, 2):
+            assert {K for _, _, K, _, _, second in plans if second == TILES_256X128} >= {64, 128}
+        if out_bytes == 2:
+            assert any(rows and second is not None for *_, rows, _, second in plans), plans
+    assert {second for M, N, K in sizes.NARROW_F8 for second in tiles(rules, M, N, K, F8, 2)[1:]} >= {
+        TILES_256X128, TILES_256}
+    assert any(rows and second is not None for rows, _, second in (tiles(rules, M, N, K, F8, 2) for M, N, K in sizes.NARROW_F8))
 
 
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])
