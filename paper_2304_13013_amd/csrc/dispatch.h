@@ -1,4 +1,4 @@
-// Which kernels an int8 or float8 product of a given size runs: host arithmetic alone (no HIP in this file), so that the
+// Which kernels a product or a weight gradient of a given size runs: host arithmetic alone (no HIP in this file), so that the
 // rules can be compiled and checked over their whole range without a GPU.
 #pragma once
 #include <stdint.h>
@@ -162,6 +162,103 @@ inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kin
         const double t = tiled_product_time(TILES_256, whole * 256, N, K, kind, out_bytes, ncu) +
                          best_tiles(M - whole * 256, N, K, kind, out_bytes, ncu, &rest);
         if (t < 0.95 * best) plan = ProductPlan{whole * 256, M, TILES_256, rest, DIRECT_NONE};
+    }
+    return plan;
+}
+
+// ---- Weight gradient of b tokens, dW [m, n]: 256x256 tiles (gemm_bf16_tn_wide_kernel.h) or 128x128 ones, two workgroups
+// per compute unit (gemm_bf16_tn_kernel.h), and into how many items the token range of a tile is split.
+
+enum { DW_STAGE = 64 };  // tokens; every token range but the last is whole stages
+
+// Pieces that the tokens of a tile are summed in, at least: long chains of binary32 additions lose precision (512 tokens,
+// 256 -> 1024: relative error 0.90e-7 in two pieces, 1.25e-7 in one; 16448 tokens, 1024 -> 3072, 3.5e-7 in five pieces, twice
+// that in one).  As many as once were the fastest splits, of 256x256 tiles where they leave 32 stages each (whole rounds of
+// the GPU with as few as that takes), else of 128x128 ones (in units of a stage, 1.1 us: the stages of an item, at 0.64 of
+// the unit while a compute unit has one workgroup; the partial sums at 2.9 TB/s and 2.7 for the launch that adds them, which
+// does not count where it is what keeps the range whole).
+inline int least_pieces(int64_t b, int64_t n, int64_t m, int ncu) {
+    const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;
+    const int64_t tiles = ((m + 255) / 256) * ((n + 255) / 256), small_tiles = ((m + 127) / 128) * ((n + 127) / 128);
+    int best = 1;
+    double best_score = -1.0;
+    for (int s = 1; s <= 16 && (s == 1 || (int64_t)s * DW_STAGE * 4 <= b); ++s) {
+        const int64_t items = tiles * s, rounds = (items + ncu - 1) / ncu;
+        const double score = (double)items / (double)(rounds * ncu) - 0.015 * s;
+        if (score > best_score) {
+            best_score = score;
+            best = s;
+        }
+    }
+    if (best == 1 || stages / best >= 32) return best;
+    const double pass = (double)m * (double)n * 4.0 / (2.9e12 * 1.1e-6);
+    for (double launch = 2.7; launch >= 0.0; launch -= 2.7) {
+        double best_cost = 0.0;
+        for (int s = 1; s <= 16 && (s == 1 || (int64_t)s * DW_STAGE * 4 <= b); ++s) {
+            double cost = s > 1 ? (s + 0.5) * pass + launch : 0.0;
+            for (int64_t left = small_tiles * s; left > 0; left -= 2 * ncu) {
+                const int64_t k = left < 2 * ncu ? left : 2 * ncu;
+                cost += (double)((stages + s - 1) / s) * (k <= ncu ? 0.64 : 0.64 + 0.36 * (double)(k - ncu) / ncu);
+            }
+            if (s == 1 || cost < best_cost) {
+                best_cost = cost;
+                best = s;
+            }
+        }
+        if (best > 1) break;
+    }
+    return best;
+}
+
+// splits > 1: partial sums and a launch that adds them.  pieces > 1 (128x128 tiles, one item per tile): the pieces are summed
+// in registers, to the bits of the split product.  No split of the 256x256 tiles is empty.
+struct WeightGradPlan {
+    bool small;
+    int splits, stages_per_split, pieces, stages_per_piece;
+};
+
+// Estimated time (us).  r rounds of the grid, enough items for f full grids, k stages per item, w the compute units' second
+// workgroups over all rounds (small tiles), MB megabytes of binary32 result:
+//   256x256: 1.3 + 4.45 r + k (0.995 r + 0.341 f);  128x128: 2.8 + k (0.465 r + 0.072 w + 0.434 f);  both 0.09 to 0.17 MB
+//   split: 6.6 + 0.02 s + 0.23 s MB;  3.7 + 0.07 s + 0.31 s MB
+// fitted to 5900 launches of 1000 weight gradients (100..34000 tokens, widths 128..8192, 1 to 96 splits): the ratio to the
+// measured time has a standard deviation of 5 and 9 %.
+inline double weight_gradient_time(bool small, int64_t b, int64_t n, int64_t m, int s, int ncu) {
+    const int side = small ? 128 : 256, slots = small ? 2 * ncu : ncu;
+    const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;
+    const double k = (double)((stages + s - 1) / s), mb = (double)m * (double)n * 4e-6;
+    const int64_t items = ((m + side - 1) / side) * ((n + side - 1) / side) * s, rounds = (items + slots - 1) / slots;
+    const double full = (double)items / slots;
+    if (!small)
+        return 1.32 + 4.45 * rounds + k * (0.995 * rounds + 0.341 * full) + 0.087 * mb +
+               (s > 1 ? 6.62 + (0.017 + 0.232 * mb) * s : 0.0);
+    const int64_t last = items - (rounds - 1) * slots;
+    const double second = (double)(rounds - 1) + (last > ncu ? (double)(last - ncu) / ncu : 0.0);
+    return 2.84 + k * (0.465 * rounds + 0.072 * second + 0.434 * full) + 0.17 * mb +
+           (s > 1 ? 3.71 + (0.07 + 0.314 * mb) * s : 0.0);
+}
+
+// The fastest by the estimates that sums in least_pieces or more; the split that the pieces are of, unless another saves 6 %
+// (what looks 3 % better loses 5 to 13 % in one of ten: 23446 tokens, 576 -> 1792 66.6 against 75.6 us).  Measured against that
+// split always (us): 28030 tokens, 320 -> 192 405 / 25; 5214 tokens, 256 -> 448 81 / 14; 197 tokens, 768 -> 3072 9.8 / 5.6; 0.73
+// of the time in the mean over 400 weight gradients.
+inline WeightGradPlan plan_weight_gradient(int64_t b, int64_t n, int64_t m, int ncu) {
+    const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;
+    const int least = least_pieces(b, n, m, ncu);
+    const bool long_items = least == 1 || stages / least >= 32;
+    WeightGradPlan plan{true, 1, (int)stages, least, (int)((stages + least - 1) / least)};
+    double best = weight_gradient_time(true, b, n, m, 1, ncu) + (least > 1 ? 0.3 : 0.0);
+    for (int i = 0; i < 2 && stages > 0; ++i) {
+        const bool small = i == 0;
+        const int most = small ? 64 : 16, shortest = small ? 4 : 6;  // splits; stages of one, if there are more than `least`
+        for (int s = least; s <= most && (s == least || stages / s >= shortest); ++s) {
+            if (small && s == 1) continue;
+            const double t = weight_gradient_time(small, b, n, m, s, ncu) * (s == least && small != long_items ? 0.94 : 1.0);
+            if (t >= best) continue;
+            const int64_t per_split = (stages + s - 1) / s;
+            best = t;
+            plan = WeightGradPlan{small, (int)((stages + per_split - 1) / per_split), (int)per_split, 1, (int)per_split};
+        }
     }
     return plan;
 }

@@ -254,13 +254,17 @@ def test_small_weight_gradient_sums_its_pieces(b, n, m, piece):
     assert torch.equal(sb.backward_weight(dy, x), want.bfloat16())
 
 
-# The 256x256 tiles of the weight gradient: fewer tokens than a stage, one short of a stage and one past it, one past a pair
-# of stages, a second item per workgroup (289 tiles), tiles that are partial in both directions.  Every element; a binary32
-# result is at most a product of 2^-24 and the additions of a chain from the exact sum, in units of the sum of magnitudes
-# (the matrix instruction adds 16 products or more at a time).
-@pytest.mark.parametrize("b,n,m", [(1, 64, 64), (31, 192, 320), (33, 256, 256), (65, 320, 448), (127, 512, 64),
-                                   (200, 64, 576), (140, 4352, 4288)])
-def test_weight_gradient_large_tiles(oracle, b, n, m):
+# Weight gradients on 256x256 tiles without a split: one token past a pair of 32-token stages, one short of a stage and one
+# past it, whole ones, a second item per workgroup (342 tiles), tiles that are partial in both directions; on 128x128 tiles:
+# one token, more splits than a reduction step adds at once (40 pieces of 11 stages, the last one ragged).  Every element; a
+# binary32 result is at most the additions of a chain from the exact sum, in units of the sum of magnitudes (the matrix
+# instruction adds 16 products or more at a time).
+LARGE_DW = [(65, 1344, 5952), (95, 1344, 5952), (97, 1344, 5952), (64, 1600, 5056), (64, 4544, 4736)]
+SMALL_DW = [(1, 64, 64), (200, 64, 576), (28030, 320, 192)]
+
+
+@pytest.mark.parametrize("b,n,m", LARGE_DW + SMALL_DW)
+def test_weight_gradient_tiles(oracle, b, n, m):
     rng = np.random.default_rng(b + n + m)
     dyb, xb = rand_bf16(rng, (b, m), 0.1), rand_bf16(rng, (b, n))
     dw32 = sb.backward_weight(to_dev(dyb), to_dev(xb), dw_dtype=torch.float32)

@@ -26,6 +26,12 @@ long long plan_tiles(long long M, long long N, long long K, int kind, int out_by
     *second = p.second;
     return p.first_rows;
 }
+int plan_weight_gradient(long long b, long long n, long long m, int ncu, int *out) {
+    const sb::WeightGradPlan p = sb::plan_weight_gradient(b, n, m, ncu);
+    out[0] = p.splits, out[1] = p.stages_per_split, out[2] = p.pieces, out[3] = p.stages_per_piece;
+    out[4] = sb::least_pieces(b, n, m, ncu);
+    return p.small;
+}
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
 int adamw_blocks(long long count) { return sb::adamw_blocks(count); }
 long long adamw_elements_at_least(long long blocks, long long n) { return sb::adamw_elements_at_least(blocks, n); }
@@ -168,6 +174,37 @@ def test_sizes_of_the_gpu_tests_reach_every_tile(rules):
     assert {second for M, N, K in sizes.NARROW_F8 for second in tiles(rules, M, N, K, F8, 2)[1:]} >= {
         TILES_256X128, TILES_256}
     assert any(rows and second is not None for rows, _, second in (tiles(rules, M, N, K, F8, 2) for M, N, K in sizes.NARROW_F8))
+
+
+def weight_gradient(rules, b, n, m, ncu=256):
+    out = (ctypes.c_int * 5)()
+    small = rules.plan_weight_gradient(ctypes.c_longlong(b), ctypes.c_longlong(n), ctypes.c_longlong(m), ncu, out)
+    return (bool(small), *out)
+
+
+# Every token is in one split and one piece, no split is empty, and no chain is longer than the fewest pieces allowed make it.
+@pytest.mark.parametrize("ncu", [256, 64, 8])
+def test_weight_gradient_plans_cover_every_token_once(rules, ncu):
+    widths = [64, 192, 320, 768, 1088, 2880, 5120, 16384, 131072]
+    for b in list(range(0, 700, 13)) + [1024, 4097, 6304, 16448, 28030, 32896, 1048319]:
+        stages = -(-b // 64)
+        for n in widths:
+            for m in widths:
+                small, splits, per_split, pieces, per_piece, least = weight_gradient(rules, b, n, m, ncu)
+                assert 1 <= splits <= 64 and 1 <= least <= 16 and (splits == 1 or pieces == 1)
+                assert splits * per_split >= stages and (splits == 1 or (splits - 1) * per_split < stages), (b, n, m)
+                assert pieces == 1 or (small and splits == 1 and pieces * per_piece >= stages), (b, n, m)
+                assert min(per_split, per_piece) <= -(-stages // least), (b, n, m)
+                assert small or stages > 0, "an empty range has no item on the large tiles"
+
+
+def test_sizes_of_the_gpu_tests_reach_both_weight_gradients(rules):
+    import test_dispatch_gpu as sizes
+    assert all(weight_gradient(rules, *s)[:2] == (False, 1) for s in sizes.LARGE_DW)
+    assert any(-(-n // 256) * -(-m // 256) > 256 for _, n, m in sizes.LARGE_DW)
+    assert all(weight_gradient(rules, *s)[0] for s in sizes.SMALL_DW)
+    assert max(weight_gradient(rules, *s)[1] for s in sizes.SMALL_DW) > 16
+    assert weight_gradient(rules, 8637, 1920, 1984)[:2] == (False, 4)
 
 
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])
