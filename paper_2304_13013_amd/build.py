@@ -1,11 +1,14 @@
-"""Builds libswitchback.so (the gfx950 HIP kernels + C ABI) in-tree with hipcc."""
+"""Builds libswitchback.so (the gfx950 HIP kernels + C ABI) in-tree with hipcc, and its Python side with g++."""
+import importlib.util
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libswitchback.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["quantize.hip", "gemm_i8.hip", "gemm_i8_direct.hip", "gemm_f8.hip", "gemm_bf16_tn.hip", "stable_adamw.hip", "switchback_api.hip",
            "ceilings.hip"]
 
@@ -22,8 +25,32 @@ def _hipcc():
     raise RuntimeError("hipcc not found")
 
 
+def _torch_dir():
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def _compile_binding():
+    """csrc/binding.cpp: host code against torch's headers, no kernels."""
+    torch_dir, obj = _torch_dir(), os.path.join(HERE, "_build", "binding.o")
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-isystem", os.path.join(torch_dir, "include"),
+                          "-I", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj],
+                         capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for binding.cpp:\n%s" % res.stderr)
+    return obj
+
+
+def _link_binding(obj):
+    """Next to the library, which it finds by its own place."""
+    res = subprocess.run(["g++", "-shared", "-o", BINDING, obj, "-L", HERE, "-lswitchback",
+                          "-L", os.path.join(_torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+                          "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link of the Python binding failed:\n%s" % res.stderr)
+
+
 def build(verbose=False):
-    """Compile every kernel source for gfx950 and link the shared library.  Always recompiles."""
+    """Compile every kernel source for gfx950, link the shared library and the Python binding.  Always recompiles."""
     out_dir = os.path.join(HERE, "_build")
     os.makedirs(out_dir, exist_ok=True)
     hipcc = _hipcc()
@@ -39,11 +66,13 @@ def build(verbose=False):
         return obj
 
     with ThreadPoolExecutor(max_workers=4) as ex:
+        binding = ex.submit(_compile_binding)
         objs = list(ex.map(compile_one, SOURCES))
     res = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                          capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (res.stdout, res.stderr))
+    _link_binding(binding.result())
     return LIB
 
 

@@ -98,15 +98,37 @@ def load_library():
     return lib
 
 
+_native = None
+
+
+def _entries():
+    """The entry points as built-in functions (csrc/binding.cpp).  Raises if the library has not been built."""
+    return _native if _native is not None and _lib is not None else _bind()
+
+
+def _bind():
+    global _native, _dev, _out
+    load_library()
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise SwitchBackError("the Python binding of libswitchback is not built: %s" % e)
+    _binding.general_forms(_dev_general, _out_general)
+    _native, _dev, _out = _binding, _binding.dev, _binding.out
+    return _native
+
+
 def _check(status):
     if status != 0:
         raise SwitchBackError("libswitchback: %s (status %d)"
                               % (load_library().switchback_status_string(status).decode(), status))
 
 
-# A small layer's pass is bound by the host (host time of forward, backward_input and backward_weight at 64 tokens,
-# 64 -> 64: 16.8 + 13.1 + 10.4 us with Stream and c_void_p objects, 13.1 + 9.9 + 7.4 us without), so the
-# pointers go to ctypes as plain integers and the current stream is asked for its handle without a Stream object.
+# A small layer's pass is bound by the host, so the current stream is asked for its handle without a Stream object, the
+# pointers are plain integers, and the calls and the checks of their tensors are built-in functions (host time of forward,
+# backward_input and backward_weight at 64 tokens, 64 -> 64, of which the launches take 9, 6 and 3 us: 16.8 + 13.1 + 10.4 us
+# with Stream and c_void_p objects, 11.1 + 8.4 + 6.3 through ctypes with plain integers, 9.0 + 7.1 + 4.9 built in; a fresh
+# output 1.75 and 1.13 us).
 def _stream_getter(torch_c):
     """A function that returns the handle of the current stream of the current device.  The two private calls are those of
     torch 2.10; without them it goes through the public Stream object."""
@@ -119,7 +141,7 @@ def _stream_getter(torch_c):
 _stream = _stream_getter(torch._C)
 
 
-def _dev(t, dtype, ndim=None):
+def _dev_general(t, dtype, ndim=None):
     """Device address of a contiguous GPU tensor of this type (and rank)."""
     if not t.is_cuda:
         raise SwitchBackError("tensors must live on the GPU")
@@ -133,7 +155,7 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
-def _out(t, shape, dtype, device, name):
+def _out_general(t, shape, dtype, device, name):
     """A fresh output tensor, or the caller's after checking that it has exactly the shape the kernels will write."""
     if t is None:
         return torch.empty(tuple(shape), dtype=dtype, device=device)
@@ -141,6 +163,9 @@ def _out(t, shape, dtype, device, name):
         raise SwitchBackError("%s must be a %s tensor of shape %s, got %s %s"
                               % (name, dtype, tuple(shape), t.dtype, tuple(t.shape)))
     return t
+
+
+_dev, _out = _dev_general, _out_general  # until the first call binds the built-in forms, which hand on what is not plain
 
 
 def _check_bufs(bufs, b, n, m):
@@ -166,7 +191,7 @@ def _workspace(op, b, n, m, device):
 
 def quantize_rowwise(x, q=None, state=None):
     """Q_row(x), state_row(x) for a bf16 [rows, cols] tensor -> (int8 [rows, cols], f32 [rows])."""
-    lib = load_library()
+    lib = _entries()
     rows, cols = x.shape
     q = _out(q, (rows, cols), torch.int8, x.device, "q")
     state = _out(state, (rows,), torch.float32, x.device, "state")
@@ -178,7 +203,7 @@ def quantize_rowwise(x, q=None, state=None):
 
 def dequantize_rowwise(q, state, out=None):
     """Row-wise dequantization of SwitchBackM: bf16 [rows, cols] = q * state / 127."""
-    lib = load_library()
+    lib = _entries()
     rows, cols = q.shape
     out = _out(out, (rows, cols), torch.bfloat16, q.device, "out")
     _out(state, (rows,), torch.float32, q.device, "state")
@@ -189,7 +214,7 @@ def dequantize_rowwise(q, state, out=None):
 
 def quantize_tensorwise(w, q=None, q_t=None, state=None, ws=None, transpose=True):
     """Q_tensor(w), Q_tensor(w)^T, state_tensor(w) for a bf16 [rows, cols] tensor."""
-    lib = load_library()
+    lib = _entries()
     rows, cols = w.shape
     q = _out(q, (rows, cols), torch.int8, w.device, "q")
     if transpose or q_t is not None:
@@ -206,7 +231,7 @@ def quantize_tensorwise(w, q=None, q_t=None, state=None, ws=None, transpose=True
 def matmul_int8_dequant(aq, state_row, bq, state_tensor, out_dtype=torch.bfloat16, out=None):
     """out[i,j] = state_tensor/127^2 * state_row[i] * sum_k aq[i,k] bq[j,k]; int32 accumulators if out_dtype is
     torch.int32 (the states may then be None)."""
-    lib = load_library()
+    lib = _entries()
     M, K = aq.shape
     N = bq.shape[0]
     if bq.shape[1] != K:
@@ -239,7 +264,7 @@ class LayerBuffers:
 
 def forward(x, w, bufs=None, y=None, y_dtype=torch.bfloat16):
     """Algorithm 1 forward.  Returns (y [b,m], bufs); bufs holds xq, state_x, wq, wq_t, state_w."""
-    lib = load_library()
+    lib = _entries()
     b, n = x.shape
     m = w.shape[0]
     if w.shape[1] != n:
@@ -248,7 +273,7 @@ def forward(x, w, bufs=None, y=None, y_dtype=torch.bfloat16):
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                  _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.byref(bufs.saved),
+                                  _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved),
                                   _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
@@ -265,7 +290,7 @@ def matmul_int8_dequant_bias_layerscale(aq, state_row, bq, state_tensor, bias=No
                                         out_dtype=torch.bfloat16, out=None):
     """out[i,j] = gamma[j] * (state_tensor/127^2 * state_row[i] * sum_k aq[i,k] bq[j,k] + bias[j]); bias, gamma f32 [N]
     or None."""
-    lib = load_library()
+    lib = _entries()
     M, K = aq.shape
     N = bq.shape[0]
     if bq.shape[1] != K:
@@ -281,7 +306,7 @@ def matmul_int8_dequant_bias_layerscale(aq, state_row, bq, state_tensor, bias=No
 
 def forward_bias_layerscale(x, w, bias=None, gamma=None, bufs=None, y=None, y_dtype=torch.bfloat16):
     """Algorithm 1 forward with the layer's bias and the block's layer-scale in the epilogue: gamma * (X W^T + bias)."""
-    lib = load_library()
+    lib = _entries()
     b, n = x.shape
     m = w.shape[0]
     if w.shape[1] != n:
@@ -291,7 +316,7 @@ def forward_bias_layerscale(x, w, bias=None, gamma=None, bufs=None, y=None, y_dt
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_bias_layerscale(
         _dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), _vec(bias, m, x.device, "bias"),
-        _vec(gamma, m, x.device, "gamma"), b, n, m, _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.byref(bufs.saved),
+        _vec(gamma, m, x.device, "gamma"), b, n, m, _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved),
         _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
@@ -299,7 +324,7 @@ def forward_bias_layerscale(x, w, bias=None, gamma=None, bufs=None, y=None, y_dt
 def forward_static(x, w, bufs, y=None, y_dtype=torch.bfloat16):
     """switchback_forward_static: Algorithm 1 forward without a workspace (the library's own per-GPU scratch array
     holds the tensor-wise partial maxima); the call itself allocates nothing when bufs and y are given."""
-    lib = load_library()
+    lib = _entries()
     b, n = x.shape
     m = w.shape[0]
     if w.shape[1] != n:
@@ -307,18 +332,18 @@ def forward_static(x, w, bufs, y=None, y_dtype=torch.bfloat16):
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_static(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                         _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.byref(bufs.saved), _stream()))
+                                         _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved), _stream()))
     return y, bufs
 
 
 def backward_input(dy, bufs, dx=None, dx_dtype=torch.bfloat16):
     """Algorithm 1 input gradient.  Returns dx [b,n]; fills bufs.gq and bufs.state_g."""
-    lib = load_library()
+    lib = _entries()
     b, m = dy.shape
     n = bufs.n
     _check_bufs(bufs, b, n, m)
     dx = _out(dx, (b, n), dx_dtype, dy.device, "dx")
-    _check(lib.switchback_backward_input(_dev(dy, torch.bfloat16, 2), ctypes.byref(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_input(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
                                          _dev(dx, dx_dtype, 2), _SB_DTYPE[dx_dtype], _ptr(bufs.gq),
                                          _ptr(bufs.state_g), _stream()))
     return dx
@@ -326,7 +351,7 @@ def backward_input(dy, bufs, dx=None, dx_dtype=torch.bfloat16):
 
 def backward_weight(dy, x, bufs=None, dw=None, dw_dtype=torch.bfloat16):
     """Algorithm 1 weight gradient dW = dY^T X (bf16 operands, binary32 accumulation).  Returns dw [m,n]."""
-    lib = load_library()
+    lib = _entries()
     b, m = dy.shape
     n = x.shape[1]
     if x.shape[0] != b:
@@ -344,13 +369,13 @@ def backward_weight(dy, x, bufs=None, dw=None, dw_dtype=torch.bfloat16):
 def backward_weight_m(dy, bufs, x_hat=None, dw=None, dw_dtype=torch.bfloat16):
     """SwitchBackM weight gradient: X is rebuilt from bufs.xq / bufs.state_x (filled by forward) into x_hat, then
     dW = dY^T X^.  Returns (dw [m,n], x_hat [b,n])."""
-    lib = load_library()
+    lib = _entries()
     b, m = dy.shape
     n = bufs.n
     _check_bufs(bufs, b, n, m)
     x_hat = _out(x_hat, (b, n), torch.bfloat16, dy.device, "x_hat")
     dw = _out(dw, (m, n), dw_dtype, dy.device, "dw")
-    _check(lib.switchback_backward_weight_m(_dev(dy, torch.bfloat16, 2), ctypes.byref(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_weight_m(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
                                             _dev(x_hat, torch.bfloat16, 2), _dev(dw, dw_dtype, 2),
                                             _SB_DTYPE[dw_dtype], _ptr(bufs.ws_dw), bufs.ws_dw.numel(), _stream()))
     return dw, x_hat
@@ -360,7 +385,7 @@ def backward_weight_m(dy, bufs, x_hat=None, dw=None, dw_dtype=torch.bfloat16):
 
 def quantize_colwise_transpose(w, q_t=None, state=None, ws=None):
     """One absmax per column of w [rows, cols]; returns (q_t int8 [cols, rows], state f32 [cols])."""
-    lib = load_library()
+    lib = _entries()
     rows, cols = w.shape
     q_t = _out(q_t, (cols, rows), torch.int8, w.device, "q_t")
     state = _out(state, (cols,), torch.float32, w.device, "state")
@@ -372,7 +397,7 @@ def quantize_colwise_transpose(w, q_t=None, state=None, ws=None):
 
 def matmul_int8_dequant_rc(aq, state_a, bq, state_b, out_dtype=torch.bfloat16, out=None):
     """out[i,j] = state_a[i] * state_b[j] / 127^2 * sum_k aq[i,k] bq[j,k]."""
-    lib = load_library()
+    lib = _entries()
     M, K = aq.shape
     N = bq.shape[0]
     if bq.shape[1] != K:
@@ -401,7 +426,7 @@ class LayerBuffersQ:
 
 def forward_q(x, w, bufs=None, y=None, y_dtype=torch.bfloat16):
     """SwitchBackQ forward.  Returns (y [b,m], bufs)."""
-    lib = load_library()
+    lib = _entries()
     b, n = x.shape
     m = w.shape[0]
     if w.shape[1] != n:
@@ -417,7 +442,7 @@ def forward_q(x, w, bufs=None, y=None, y_dtype=torch.bfloat16):
 
 def backward_input_q(dy, w, bufs, dx=None, dx_dtype=torch.bfloat16):
     """SwitchBackQ input gradient.  Returns dx [b,n]; fills bufs.gq, state_g, wq_t, state_w_col."""
-    lib = load_library()
+    lib = _entries()
     b, m = dy.shape
     n = w.shape[1]
     if w.shape[0] != m:
@@ -453,7 +478,7 @@ def stable_adamw_step(theta, v, u, grad, alpha, beta1, beta2, eps, lam, t, rms_o
 # ---- float8 SwitchBack: the same layer with float8cast(x / absmax) as the quantizer; codes are uint8 tensors ------
 
 def quantize_rowwise_f8(x, fmt, codes=None, state=None):
-    lib = load_library()
+    lib = _entries()
     rows, cols = x.shape
     codes = _out(codes, (rows, cols), torch.uint8, x.device, "codes")
     state = _out(state, (rows,), torch.float32, x.device, "state")
@@ -463,7 +488,7 @@ def quantize_rowwise_f8(x, fmt, codes=None, state=None):
 
 
 def quantize_tensorwise_f8(w, fmt, codes=None, codes_t=None, state=None, ws=None):
-    lib = load_library()
+    lib = _entries()
     rows, cols = w.shape
     codes = _out(codes, (rows, cols), torch.uint8, w.device, "codes")
     codes_t = _out(codes_t, (cols, rows), torch.uint8, w.device, "codes_t")
@@ -476,7 +501,7 @@ def quantize_tensorwise_f8(w, fmt, codes=None, codes_t=None, state=None, ws=None
 
 
 def matmul_f8_dequant(aq, fmt_a, state_row, bq, fmt_b, state_tensor, out=None, out_dtype=torch.bfloat16):
-    lib = load_library()
+    lib = _entries()
     M, K = aq.shape
     N = bq.shape[0]
     if bq.shape[1] != K:
@@ -492,7 +517,7 @@ def matmul_f8_dequant(aq, fmt_a, state_row, bq, fmt_b, state_tensor, out=None, o
 
 def forward_f8(x, w, bufs=None, y=None, y_dtype=torch.bfloat16, fmt_x=SB_E4M3, fmt_w=SB_E4M3):
     """float8 SwitchBack forward.  Returns (y [b,m], bufs); bufs (a LayerBuffers) then holds float8 bytes."""
-    lib = load_library()
+    lib = _entries()
     b, n = x.shape
     m = w.shape[0]
     if w.shape[1] != n:
@@ -501,19 +526,19 @@ def forward_f8(x, w, bufs=None, y=None, y_dtype=torch.bfloat16, fmt_x=SB_E4M3, f
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_f8(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                     _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.byref(bufs.saved), fmt_x, fmt_w,
+                                     _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved), fmt_x, fmt_w,
                                      _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
 
 def backward_input_f8(dy, bufs, dx=None, dx_dtype=torch.bfloat16, fmt_g=SB_E5M2, fmt_w=SB_E4M3):
     """float8 SwitchBack input gradient.  Returns dx [b,n]; fills bufs.gq (float8 bytes) and bufs.state_g."""
-    lib = load_library()
+    lib = _entries()
     b, m = dy.shape
     n = bufs.n
     _check_bufs(bufs, b, n, m)
     dx = _out(dx, (b, n), dx_dtype, dy.device, "dx")
-    _check(lib.switchback_backward_input_f8(_dev(dy, torch.bfloat16, 2), ctypes.byref(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_input_f8(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
                                             _dev(dx, dx_dtype, 2), _SB_DTYPE[dx_dtype], _ptr(bufs.gq),
                                             _ptr(bufs.state_g), fmt_g, fmt_w, _stream()))
     return dx
@@ -585,7 +610,7 @@ class AdamwPlan:
 
 def stable_adamw_step_multi(plan, alpha, beta1, beta2, eps, lam, t):
     """One StableAdamW step for every tensor of the plan (two launches in total).  Returns plan.rms [n]."""
-    lib = load_library()
+    lib = _entries()
     _check(lib.switchback_stable_adamw_step_multi(_ptr(plan.table), plan.n, plan.total_blocks,
                                                   _SB_DTYPE[plan.grad_dtype], alpha, beta1, beta2, eps, lam, t,
                                                   _ptr(plan.rms), _ptr(plan.ws), plan.ws.numel(), _stream()))

@@ -241,3 +241,18 @@ def test_stream_handle_with_and_without_the_private_torch_calls(monkeypatch):
     assert sb._stream_getter(With)() == 0x1003
     monkeypatch.setattr(sb.torch.cuda, "current_stream", Stream)
     assert sb._stream_getter(object())() == 0x2000
+
+
+def test_builtin_entries_refuse_what_ctypes_refused():
+    """The built-in entry points convert their arguments as the ctypes declarations of the same functions do."""
+    lib, native = sb.load_library(), sb._entries()
+    for args in ((None, -1, 0, None, None, None), (None, 0, 8, None, None, None), (16, 1, 7, 16, 16, 0), (8, 1, 8, 16, 16, 0),
+                 (None, True, 7, None, None, None), (None, -(2 ** 64) - 1, 8, None, None, None)):
+        assert native.switchback_quantize_rowwise(*args) == lib.switchback_quantize_rowwise(*args), args
+    for args in ((None, 1.0, 8, None, None, None), (1.5, 1, 8, None, None, None), (None, None, 8, None, None, None)):
+        for f in (native.switchback_quantize_rowwise, lib.switchback_quantize_rowwise):
+            with pytest.raises(ctypes.ArgumentError):
+                f(*args)
+    for f in (native.switchback_quantize_rowwise, lib.switchback_quantize_rowwise):
+        with pytest.raises(TypeError):
+            f(None, 1)

@@ -303,3 +303,34 @@ def test_adamw_step_larger_than_the_last_level_cache(grad_dtype):
     assert abs(rms.item() - want_rms.item()) <= 2e-6 * want_rms.item()
     for got, ref in zip(big[:3], want):  # a handful of binary32 roundings (2^-24 each) of the tensor's values
         assert (got.double() - ref).norm() <= 4 * 2.0 ** -24 * ref.norm()
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("case", ["plain", "view", "parameter", "subclass", "transposed", "wrong dtype", "host", "rank",
+                                  "function mode", "empty", "lazy negation"])
+def test_builtin_tensor_checks_agree_with_the_general_ones(case):
+    """The built-in forms of the two checks answer and refuse as the Python ones that they stand for."""
+    base = torch.arange(64 * 64, device=DEV, dtype=torch.float32).view(64, 64)
+    t = {"view": base[8:], "parameter": torch.nn.Parameter(base), "subclass": base.as_subclass(_Sub), "transposed": base.t(),
+         "wrong dtype": base.bfloat16(), "host": base.cpu(), "rank": base.view(-1), "empty": base[:0],
+         "lazy negation": torch._neg_view(base)}.get(case, base)
+    sb._entries()
+
+    def answer(f, *args):
+        try:
+            return f(*args)
+        except sb.SwitchBackError as e:
+            return str(e)
+
+    mode = torch.overrides.BaseTorchFunctionMode() if case == "function mode" else torch.no_grad()
+    with mode:
+        assert answer(sb._dev, t, torch.float32, 2) == answer(sb._dev_general, t, torch.float32, 2)
+        assert answer(sb._dev, t, torch.float32) == answer(sb._dev_general, t, torch.float32)
+        a, g = (answer(f, t, (64, 64), torch.float32, t.device, "y") for f in (sb._out, sb._out_general))
+        assert a is g or a == g
+        fresh, want = (f(None, (3, 5), t.dtype, t.device, "y") for f in (sb._out, sb._out_general))
+    assert (fresh.shape, fresh.dtype, fresh.device, fresh.stride(), type(fresh), fresh.requires_grad) == (
+        want.shape, want.dtype, want.device, want.stride(), type(want), want.requires_grad)
