@@ -84,9 +84,11 @@ inline double tiled_product_time(TileKind tile, int64_t M, int64_t N, int64_t K,
 }
 
 // The tile with the smallest estimate; the 128x128 ones on equal terms, up to 3 % (the wider ones lose 7 % on a narrow miss
-// at worst: 2382 x 1280, K = 2752, binary32 21.4 us against 23.5, where they win 4 % in the mean).
+// at worst: 2382 x 1280, K = 2752, binary32 21.4 us against 23.5, where they win 4 % in the mean).  Not for a single stage
+// and two-byte outputs, where a narrow miss goes the other way (6251 x 1408, K = 128: 8.1 us on 128x128 tiles, 7.3 on 256x256
+// ones; 24576 x 320: 8.0 and 7.1; four-byte outputs 39081 x 832 28.0 and 30.8).
 inline double best_tiles(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu, TileKind *tile) {
-    double best = 0.97 * tiled_product_time(TILES_128, M, N, K, kind, out_bytes, ncu);
+    double best = (K > 128 || out_bytes > 2 ? 0.97 : 1.0) * tiled_product_time(TILES_128, M, N, K, kind, out_bytes, ncu);
     *tile = TILES_128;
     for (int i = TILES_128 + 1; i < TILE_KINDS; ++i) {
         const double t = tiled_product_time((TileKind)i, M, N, K, kind, out_bytes, ncu);
