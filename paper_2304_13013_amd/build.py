@@ -29,24 +29,17 @@ def _torch_dir():
     return os.path.dirname(importlib.util.find_spec("torch").origin)
 
 
-def _compile_binding():
-    """csrc/binding.cpp: host code against torch's headers, no kernels."""
-    torch_dir, obj = _torch_dir(), os.path.join(HERE, "_build", "binding.o")
-    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-isystem", os.path.join(torch_dir, "include"),
-                          "-I", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj],
+def _build_binding():
+    """csrc/binding.cpp: host code against torch's headers, no kernels.  It is handed the library's entry points when it is
+    bound, and links none."""
+    torch_dir = _torch_dir()
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                          "-isystem", os.path.join(torch_dir, "include"), "-I", sysconfig.get_paths()["include"],
+                          os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
+                          "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"],
                          capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed for binding.cpp:\n%s" % res.stderr)
-    return obj
-
-
-def _link_binding(obj):
-    """Next to the library, which it finds by its own place."""
-    res = subprocess.run(["g++", "-shared", "-o", BINDING, obj, "-L", HERE, "-lswitchback",
-                          "-L", os.path.join(_torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
-                          "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("link of the Python binding failed:\n%s" % res.stderr)
 
 
 def build(verbose=False):
@@ -66,13 +59,13 @@ def build(verbose=False):
         return obj
 
     with ThreadPoolExecutor(max_workers=4) as ex:
-        binding = ex.submit(_compile_binding)
+        binding = ex.submit(_build_binding)
         objs = list(ex.map(compile_one, SOURCES))
     res = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                          capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (res.stdout, res.stderr))
-    _link_binding(binding.result())
+    binding.result()
     return LIB
 
 

@@ -1,7 +1,11 @@
 // Python side of the C ABI: the calls themselves and the two checks that every call makes of its tensors, as built-in
 // functions.  A small layer's pass is bound by the host: each of its launches takes 3 us, and what Python and ctypes add
-// to a call is of the same size.  The general forms of the checks stay in Python: whatever is not a plain tensor that
-// passes (subclasses, function modes, wrong types and shapes) goes to those, which raise or answer as they always did.
+// to a call is of the same size.  The general forms of the checks stay in Python: whatever is not a
+// plain tensor that passes (subclasses, function modes, wrong types and shapes) goes to those, which raise or answer as they
+// always did.
+//
+// The module links no library of kernels: bind() gets the addresses of one that is loaded, and returns functions that carry
+// them, so two libraries may be bound side by side.
 #include <Python.h>
 
 #include <ATen/Functions.h>
@@ -10,6 +14,7 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <new>
 #include <tuple>
 #include <type_traits>
 #include <utility>
@@ -18,8 +23,6 @@
 
 namespace {
 
-PyObject *general_dev, *general_out;  // the Python functions, set once by general_forms()
-
 struct WithoutGil {  // other Python threads run meanwhile
     PyThreadState *state = PyEval_SaveThread();
     ~WithoutGil() { PyEval_RestoreThread(state); }
@@ -27,16 +30,30 @@ struct WithoutGil {  // other Python threads run meanwhile
 
 bool plain(PyObject *o) { return THPVariable_CheckExact(o) && !at::impl::torch_function_mode_enabled(); }
 
-PyObject *call_general(PyObject *f, PyObject *const *args, Py_ssize_t nargs) {
-    if (f == nullptr) {
-        PyErr_SetString(PyExc_RuntimeError, "general_forms() has not been called");
-        return nullptr;
+struct Entry {
+    void *address;
+    PyObject *general;  // the ctypes function
+};
+// What bind() was given: the self of every function that it returns.
+struct Bound {
+    PyObject *dev = nullptr, *out = nullptr;  // the checks in Python
+    PyObject *saved_type = nullptr;           // ctypes structure of sb_saved
+    Entry entries[32] = {};
+    ~Bound() {
+        Py_XDECREF(dev);
+        Py_XDECREF(out);
+        Py_XDECREF(saved_type);
+        for (Entry &e : entries) Py_XDECREF(e.general);
     }
+};
+Bound *bound(PyObject *self) { return static_cast<Bound *>(PyCapsule_GetPointer(self, nullptr)); }
+
+PyObject *call_general(PyObject *f, PyObject *const *args, Py_ssize_t nargs) {
     return PyObject_Vectorcall(f, args, (size_t)nargs, nullptr);
 }
 
 // dev(t, dtype, ndim=None): device address of a contiguous GPU tensor of this type (and rank).
-PyObject *dev(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
+PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
     if ((nargs == 2 || nargs == 3) && plain(args[0]) && THPDtype_Check(args[1])) try {
             const at::Tensor &t = THPVariable_Unpack(args[0]);
             const bool any_rank = nargs == 2 || args[2] == Py_None;
@@ -47,11 +64,11 @@ PyObject *dev(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
         } catch (...) {
             PyErr_Clear();
         }
-    return call_general(general_dev, args, nargs);
+    return call_general(bound(self)->dev, args, nargs);
 }
 
 // out(t, shape, dtype, device, name): a fresh output tensor, or the caller's if it has exactly this shape and type.
-PyObject *out(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
+PyObject *out(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
     constexpr Py_ssize_t MAX_RANK = 2;
     if (nargs == 5 && PyTuple_CheckExact(args[1]) && PyTuple_GET_SIZE(args[1]) <= MAX_RANK && THPDtype_Check(args[2]) &&
         THPDevice_Check(args[3])) {
@@ -89,25 +106,24 @@ PyObject *out(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
                 PyErr_Clear();
             }
     }
-    return call_general(general_out, args, nargs);
+    return call_general(bound(self)->out, args, nargs);
 }
 
-PyObject *general_forms(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
-    if (nargs != 2) {
-        PyErr_SetString(PyExc_TypeError, "general_forms(dev, out)");
-        return nullptr;
-    }
-    Py_INCREF(args[0]);
-    Py_INCREF(args[1]);
-    Py_XSETREF(general_dev, args[0]);
-    Py_XSETREF(general_out, args[1]);
-    Py_RETURN_NONE;
-}
-
-// What ctypes takes for these C types: integers (an address is one) modulo the type's range, None for a null pointer.
+// What ctypes takes for these C types: integers (an address is one) modulo the type's range, None for a null pointer, the
+// structure itself for a pointer to it.
 template <class T>
-bool convert(PyObject *o, T &v) {
-    if constexpr (std::is_pointer<T>::value) {
+bool convert(PyObject *o, T &v, PyObject *saved_type) {
+    if constexpr (std::is_same<T, const sb_saved *>::value) {
+        Py_buffer view;
+        if (o == Py_None) {
+            v = nullptr;
+        } else if (reinterpret_cast<PyObject *>(Py_TYPE(o)) != saved_type || PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
+            return false;
+        } else {  // the caller's reference keeps it
+            v = static_cast<T>(view.buf);
+            PyBuffer_Release(&view);
+        }
+    } else if constexpr (std::is_pointer<T>::value) {
         if (o != Py_None && !PyLong_Check(o)) return false;
         v = o == Py_None ? nullptr : reinterpret_cast<T>((uintptr_t)PyLong_AsUnsignedLongLongMask(o));
     } else if constexpr (std::is_floating_point<T>::value) {
@@ -129,19 +145,20 @@ PyObject *refused(Py_ssize_t i) {
 }
 
 // One entry of the C ABI, its argument types taken from its declaration.
-template <auto F, class... A, size_t... I>
-PyObject *call_entry(int (*)(A...), PyObject *const *args, Py_ssize_t nargs, std::index_sequence<I...>) {
+template <class... A, size_t... I>
+PyObject *call_entry(int (*)(A...), const Entry &e, PyObject *saved_type, PyObject *const *args, Py_ssize_t nargs,
+                     std::index_sequence<I...>) {
     if (nargs != (Py_ssize_t)sizeof...(A)) {
         PyErr_Format(PyExc_TypeError, "this function takes %zu arguments (%zd given)", sizeof...(A), nargs);
         return nullptr;
     }
     std::tuple<A...> v{};
     Py_ssize_t bad = -1;
-    if (!((convert(args[I], std::get<I>(v)) || (bad = (Py_ssize_t)I, false)) && ...)) return refused(bad);
+    if (!((convert(args[I], std::get<I>(v), saved_type) || (bad = (Py_ssize_t)I, false)) && ...)) return refused(bad);
     int status;
     {
         WithoutGil released;
-        status = F(std::get<I>(v)...);
+        status = reinterpret_cast<int (*)(A...)>(e.address)(std::get<I>(v)...);
     }
     return PyLong_FromLong(status);
 }
@@ -149,38 +166,81 @@ template <class... A>
 constexpr std::index_sequence_for<A...> indices_of(int (*)(A...)) {
     return {};
 }
-template <auto F>
-PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
-    return call_entry<F>(F, args, nargs, decltype(indices_of(F)){});
+template <size_t INDEX, class F>
+PyObject *entry(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    Bound *b = bound(self);
+    return call_entry((F) nullptr, b->entries[INDEX], b->saved_type, args, nargs, decltype(indices_of((F) nullptr)){});
 }
 
 #define SB_METHOD(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
-#define SB_ENTRY(name) SB_METHOD("switchback_" #name, &entry<&switchback_##name>)
-PyMethodDef methods[] = {SB_METHOD("dev", &dev),
-                         SB_METHOD("out", &out),
-                         SB_METHOD("general_forms", &general_forms),
-                         SB_ENTRY(quantize_rowwise),
-                         SB_ENTRY(dequantize_rowwise),
-                         SB_ENTRY(quantize_tensorwise),
-                         SB_ENTRY(matmul_int8_dequant),
-                         SB_ENTRY(matmul_int8_dequant_bias_layerscale),
-                         SB_ENTRY(forward),
-                         SB_ENTRY(forward_bias_layerscale),
-                         SB_ENTRY(forward_static),
-                         SB_ENTRY(backward_input),
-                         SB_ENTRY(backward_weight),
-                         SB_ENTRY(backward_weight_m),
-                         SB_ENTRY(quantize_colwise_transpose),
-                         SB_ENTRY(matmul_int8_dequant_rc),
-                         SB_ENTRY(forward_q),
-                         SB_ENTRY(backward_input_q),
-                         SB_ENTRY(quantize_rowwise_f8),
-                         SB_ENTRY(quantize_tensorwise_f8),
-                         SB_ENTRY(matmul_f8_dequant),
-                         SB_ENTRY(forward_f8),
-                         SB_ENTRY(backward_input_f8),
-                         SB_ENTRY(stable_adamw_step_multi),
-                         {nullptr, nullptr, 0, nullptr}};
+#define SB_ENTRY(name) SB_METHOD("switchback_" #name, (&entry<__COUNTER__ - FIRST, decltype(&switchback_##name)>))
+constexpr size_t CHECKS = 2, FIRST = __COUNTER__ + 1;
+PyMethodDef bound_methods[] = {SB_METHOD("dev", &dev),
+                               SB_METHOD("out", &out),
+                               SB_ENTRY(quantize_rowwise),
+                               SB_ENTRY(dequantize_rowwise),
+                               SB_ENTRY(quantize_tensorwise),
+                               SB_ENTRY(matmul_int8_dequant),
+                               SB_ENTRY(matmul_int8_dequant_bias_layerscale),
+                               SB_ENTRY(forward),
+                               SB_ENTRY(forward_bias_layerscale),
+                               SB_ENTRY(forward_static),
+                               SB_ENTRY(backward_input),
+                               SB_ENTRY(backward_weight),
+                               SB_ENTRY(backward_weight_m),
+                               SB_ENTRY(quantize_colwise_transpose),
+                               SB_ENTRY(matmul_int8_dequant_rc),
+                               SB_ENTRY(forward_q),
+                               SB_ENTRY(backward_input_q),
+                               SB_ENTRY(quantize_rowwise_f8),
+                               SB_ENTRY(quantize_tensorwise_f8),
+                               SB_ENTRY(matmul_f8_dequant),
+                               SB_ENTRY(forward_f8),
+                               SB_ENTRY(backward_input_f8),
+                               SB_ENTRY(stable_adamw_step_multi)};
+constexpr size_t ENTRIES = sizeof(bound_methods) / sizeof(bound_methods[0]) - CHECKS;
+
+// bind(dev, out, saved_type, entry) -> {name: built-in function}: the general forms of the checks, the ctypes structure of
+// sb_saved, and a function that gives an entry's address and ctypes function by name.
+PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
+    if (nargs != 4) {
+        PyErr_SetString(PyExc_TypeError, "bind(dev, out, saved_type, entry)");
+        return nullptr;
+    }
+    static_assert(ENTRIES <= sizeof(Bound::entries) / sizeof(Entry), "entries");
+    Bound *b = new (std::nothrow) Bound;
+    PyObject *self = b == nullptr ? PyErr_NoMemory() : PyCapsule_New(b, nullptr, [](PyObject *c) { delete bound(c); });
+    if (self == nullptr) {
+        delete b;
+        return nullptr;
+    }
+    for (Py_ssize_t i = 0; i < 3; ++i) Py_INCREF(args[i]);
+    b->dev = args[0], b->out = args[1], b->saved_type = args[2];
+    PyObject *functions = PyDict_New();
+    bool ok = functions != nullptr;
+    for (size_t i = 0; ok && i < CHECKS + ENTRIES; ++i) {
+        if (i >= CHECKS) {
+            PyObject *pair = PyObject_CallFunction(args[3], "s", bound_methods[i].ml_name);
+            unsigned long long address = 0;
+            Entry e{nullptr, nullptr};
+            ok = pair != nullptr && PyArg_ParseTuple(pair, "KO", &address, &e.general);
+            if (ok) {
+                e.address = reinterpret_cast<void *>((uintptr_t)address);
+                Py_INCREF(e.general);
+                b->entries[i - CHECKS] = e;
+            }
+            Py_XDECREF(pair);
+        }
+        PyObject *f = ok ? PyCFunction_New(&bound_methods[i], self) : nullptr;
+        ok = f != nullptr && PyDict_SetItemString(functions, bound_methods[i].ml_name, f) == 0;
+        Py_XDECREF(f);
+    }
+    Py_DECREF(self);
+    if (!ok) Py_CLEAR(functions);
+    return functions;
+}
+
+PyMethodDef methods[] = {SB_METHOD("bind", &bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -8,6 +8,7 @@ backward_weight (Algorithm 1 of arxiv 2304.13013: X [b,n], W [m,n], Y/dY [b,m]).
 """
 import ctypes
 import os
+import types
 
 import torch
 
@@ -98,23 +99,28 @@ def load_library():
     return lib
 
 
-_native = None
+_native = _bound_to = None
 
 
 def _entries():
     """The entry points as built-in functions (csrc/binding.cpp).  Raises if the library has not been built."""
-    return _native if _native is not None and _lib is not None else _bind()
+    return _native if _native is not None and _bound_to is _lib else _bind()
 
 
 def _bind():
-    global _native, _dev, _out
-    load_library()
+    global _native, _bound_to, _dev, _out
+    lib = load_library()
     try:
         from . import _binding
     except ImportError as e:
         raise SwitchBackError("the Python binding of libswitchback is not built: %s" % e)
-    _binding.general_forms(_dev_general, _out_general)
-    _native, _dev, _out = _binding, _binding.dev, _binding.out
+
+    def entry(name):
+        f = getattr(lib, name)
+        return ctypes.cast(f, ctypes.c_void_p).value, f
+    _native = types.SimpleNamespace(**_binding.bind(_dev_general, _out_general, SbSaved, entry))
+    _dev, _out = _native.dev, _native.out
+    _bound_to = lib
     return _native
 
 
@@ -165,7 +171,7 @@ def _out_general(t, shape, dtype, device, name):
     return t
 
 
-_dev, _out = _dev_general, _out_general  # until the first call binds the built-in forms, which hand on what is not plain
+_dev, _out = _dev_general, _out_general  # until _bind() puts the built-in forms here, which hand on what is not plain
 
 
 def _check_bufs(bufs, b, n, m):
@@ -273,7 +279,7 @@ def forward(x, w, bufs=None, y=None, y_dtype=torch.bfloat16):
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                  _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved),
+                                  _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], bufs.saved,
                                   _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
@@ -316,7 +322,7 @@ def forward_bias_layerscale(x, w, bias=None, gamma=None, bufs=None, y=None, y_dt
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_bias_layerscale(
         _dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), _vec(bias, m, x.device, "bias"),
-        _vec(gamma, m, x.device, "gamma"), b, n, m, _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved),
+        _vec(gamma, m, x.device, "gamma"), b, n, m, _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], bufs.saved,
         _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
@@ -332,7 +338,7 @@ def forward_static(x, w, bufs, y=None, y_dtype=torch.bfloat16):
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_static(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                         _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved), _stream()))
+                                         _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], bufs.saved, _stream()))
     return y, bufs
 
 
@@ -343,7 +349,7 @@ def backward_input(dy, bufs, dx=None, dx_dtype=torch.bfloat16):
     n = bufs.n
     _check_bufs(bufs, b, n, m)
     dx = _out(dx, (b, n), dx_dtype, dy.device, "dx")
-    _check(lib.switchback_backward_input(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_input(_dev(dy, torch.bfloat16, 2), bufs.saved, b, n, m,
                                          _dev(dx, dx_dtype, 2), _SB_DTYPE[dx_dtype], _ptr(bufs.gq),
                                          _ptr(bufs.state_g), _stream()))
     return dx
@@ -375,7 +381,7 @@ def backward_weight_m(dy, bufs, x_hat=None, dw=None, dw_dtype=torch.bfloat16):
     _check_bufs(bufs, b, n, m)
     x_hat = _out(x_hat, (b, n), torch.bfloat16, dy.device, "x_hat")
     dw = _out(dw, (m, n), dw_dtype, dy.device, "dw")
-    _check(lib.switchback_backward_weight_m(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_weight_m(_dev(dy, torch.bfloat16, 2), bufs.saved, b, n, m,
                                             _dev(x_hat, torch.bfloat16, 2), _dev(dw, dw_dtype, 2),
                                             _SB_DTYPE[dw_dtype], _ptr(bufs.ws_dw), bufs.ws_dw.numel(), _stream()))
     return dw, x_hat
@@ -526,7 +532,7 @@ def forward_f8(x, w, bufs=None, y=None, y_dtype=torch.bfloat16, fmt_x=SB_E4M3, f
     _check_bufs(bufs, b, n, m)
     y = _out(y, (b, m), y_dtype, x.device, "y")
     _check(lib.switchback_forward_f8(_dev(x, torch.bfloat16, 2), _dev(w, torch.bfloat16, 2), b, n, m,
-                                     _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], ctypes.addressof(bufs.saved), fmt_x, fmt_w,
+                                     _dev(y, y_dtype, 2), _SB_DTYPE[y_dtype], bufs.saved, fmt_x, fmt_w,
                                      _ptr(bufs.ws_fwd), bufs.ws_fwd.numel(), _stream()))
     return y, bufs
 
@@ -538,7 +544,7 @@ def backward_input_f8(dy, bufs, dx=None, dx_dtype=torch.bfloat16, fmt_g=SB_E5M2,
     n = bufs.n
     _check_bufs(bufs, b, n, m)
     dx = _out(dx, (b, n), dx_dtype, dy.device, "dx")
-    _check(lib.switchback_backward_input_f8(_dev(dy, torch.bfloat16, 2), ctypes.addressof(bufs.saved), b, n, m,
+    _check(lib.switchback_backward_input_f8(_dev(dy, torch.bfloat16, 2), bufs.saved, b, n, m,
                                             _dev(dx, dx_dtype, 2), _SB_DTYPE[dx_dtype], _ptr(bufs.gq),
                                             _ptr(bufs.state_g), fmt_g, fmt_w, _stream()))
     return dx

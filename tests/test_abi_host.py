@@ -3,6 +3,7 @@ declares, sizes workspaces, and rejects bad arguments before any kernel launch."
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -256,3 +257,18 @@ def test_builtin_entries_refuse_what_ctypes_refused():
     for f in (native.switchback_quantize_rowwise, lib.switchback_quantize_rowwise):
         with pytest.raises(TypeError):
             f(None, 1)
+
+
+def test_builtin_entries_call_the_library_that_is_loaded(tmp_path, monkeypatch):
+    """A library loaded from another place (LIB_PATH) is the one that the built-in entry points call."""
+    stub = tmp_path / "stub.c"
+    stub.write_text("".join("int %s(void) { return 77; }\n" % name for name in declared_functions()))
+    path = str(tmp_path / "libstub.so")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", path, str(stub)])
+    before = sb._entries()
+    with monkeypatch.context() as m:
+        m.setattr(sb, "LIB_PATH", path)
+        m.setattr(sb, "_lib", None)
+        assert sb._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 77
+        assert before.switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
+    assert sb._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
