@@ -1,8 +1,8 @@
 // Python side of the C ABI: the calls themselves and the two checks that every call makes of its tensors, as built-in
 // functions.  A small layer's pass is bound by the host: each of its launches takes 3 us, and what Python and ctypes add
-// to a call is of the same size.  The general forms of the checks stay in Python: whatever is not a
-// plain tensor that passes (subclasses, function modes, wrong types and shapes) goes to those, which raise or answer as they
-// always did.
+// to a call is of the same size.  The general forms stay in Python (the checks) and ctypes (the calls): whatever is not a
+// plain tensor that passes (subclasses, function modes, wrong types and shapes) or not a plain argument (ctypes objects,
+// wrong types and numbers of them) goes to those, which raise or answer as they always did.
 //
 // The module links no library of kernels: bind() gets the addresses of one that is loaded, and returns functions that carry
 // them, so two libraries may be bound side by side.
@@ -56,10 +56,11 @@ PyObject *call_general(PyObject *f, PyObject *const *args, Py_ssize_t nargs) {
 PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
     if ((nargs == 2 || nargs == 3) && plain(args[0]) && THPDtype_Check(args[1])) try {
             const at::Tensor &t = THPVariable_Unpack(args[0]);
+            int overflow = 0;
             const bool any_rank = nargs == 2 || args[2] == Py_None;
             if (t.is_cuda() && t.has_storage() && !t.is_conj() && !t.is_neg() && !t._is_zerotensor() &&
                 t.layout() == at::kStrided && t.scalar_type() == reinterpret_cast<THPDtype *>(args[1])->scalar_type &&
-                t.is_contiguous() && (any_rank || (PyLong_CheckExact(args[2]) && t.dim() == PyLong_AsLong(args[2]))))
+                t.is_contiguous() && (any_rank || (PyLong_CheckExact(args[2]) && t.dim() == PyLong_AsLongAndOverflow(args[2], &overflow))))
                 return PyLong_FromVoidPtr(t.data_ptr());
         } catch (...) {
             PyErr_Clear();
@@ -127,6 +128,7 @@ bool convert(PyObject *o, T &v, PyObject *saved_type) {
         if (o != Py_None && !PyLong_Check(o)) return false;
         v = o == Py_None ? nullptr : reinterpret_cast<T>((uintptr_t)PyLong_AsUnsignedLongLongMask(o));
     } else if constexpr (std::is_floating_point<T>::value) {
+        if (!PyFloat_Check(o) && !PyLong_Check(o)) return false;
         v = (T)PyFloat_AsDouble(o);
     } else {
         if (!PyLong_Check(o)) return false;
@@ -135,26 +137,15 @@ bool convert(PyObject *o, T &v, PyObject *saved_type) {
     return !PyErr_Occurred();
 }
 
-PyObject *refused(Py_ssize_t i) {
-    PyErr_Clear();
-    PyObject *m = PyImport_ImportModule("ctypes"), *e = m != nullptr ? PyObject_GetAttrString(m, "ArgumentError") : nullptr;
-    if (e != nullptr) PyErr_Format(e, "argument %zd: wrong type", i + 1);
-    Py_XDECREF(e);
-    Py_XDECREF(m);
-    return nullptr;
-}
-
 // One entry of the C ABI, its argument types taken from its declaration.
 template <class... A, size_t... I>
 PyObject *call_entry(int (*)(A...), const Entry &e, PyObject *saved_type, PyObject *const *args, Py_ssize_t nargs,
                      std::index_sequence<I...>) {
-    if (nargs != (Py_ssize_t)sizeof...(A)) {
-        PyErr_Format(PyExc_TypeError, "this function takes %zu arguments (%zd given)", sizeof...(A), nargs);
-        return nullptr;
-    }
     std::tuple<A...> v{};
-    Py_ssize_t bad = -1;
-    if (!((convert(args[I], std::get<I>(v), saved_type) || (bad = (Py_ssize_t)I, false)) && ...)) return refused(bad);
+    if (nargs != (Py_ssize_t)sizeof...(A) || !(convert(args[I], std::get<I>(v), saved_type) && ...)) {
+        PyErr_Clear();
+        return call_general(e.general, args, nargs);
+    }
     int status;
     {
         WithoutGil released;

@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
 from paper_2304_13013_amd import switchback as sb
@@ -257,6 +258,20 @@ def test_builtin_entries_refuse_what_ctypes_refused():
     for f in (native.switchback_quantize_rowwise, lib.switchback_quantize_rowwise):
         with pytest.raises(TypeError):
             f(None, 1)
+    number = type("Number", (), {"_as_parameter_": 8})()
+    for args in ((None, ctypes.c_int64(0), 8, None, None, None), (ctypes.c_void_p(16), 1, 7, 16, 16, 0), (None, 0, number, None, None, None)):
+        assert native.switchback_quantize_rowwise(*args) == lib.switchback_quantize_rowwise(*args), args
+    for alpha in (1, 1e-3, ctypes.c_float(1e-3), np.float32(1e-3), np.float64(2.0)):
+        for f in (native.switchback_stable_adamw_step_multi, lib.switchback_stable_adamw_step_multi):
+            assert f(None, 0, 0, 0, alpha, 0.9, 0.98, 1e-6, 0.2, 1, None, None, 0, None) == 0, alpha
+    saved = sb.LayerBuffers(8, 64, 128, "cpu").saved
+    for s in (None, saved, ctypes.byref(saved), ctypes.pointer(saved)):
+        for f in (native.switchback_backward_input, lib.switchback_backward_input):
+            assert f(None, s, 0, 64, 64, None, 0, None, None, None) == (1 if s is None else 0)
+    for f in (native.switchback_backward_input, lib.switchback_backward_input):
+        for s in (16, b"0" * 40, (ctypes.c_void_p * 5)()):
+            with pytest.raises(ctypes.ArgumentError):
+                f(None, s, 0, 64, 64, None, 0, None, None, None)
 
 
 def test_builtin_entries_call_the_library_that_is_loaded(tmp_path, monkeypatch):
