@@ -1,6 +1,7 @@
 """Builds libswitchback.so (the gfx950 HIP kernels + C ABI) in-tree with hipcc, and its Python side with g++."""
 import importlib.util
 import os
+import re
 import subprocess
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
@@ -8,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libswitchback.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))  # of this Python alone
 SOURCES = ["quantize.hip", "gemm_i8.hip", "gemm_i8_direct.hip", "gemm_f8.hip", "gemm_bf16_tn.hip", "stable_adamw.hip", "switchback_api.hip",
            "ceilings.hip"]
 
@@ -29,11 +30,18 @@ def _torch_dir():
     return os.path.dirname(importlib.util.find_spec("torch").origin)
 
 
+def _torch_build():
+    """The torch that the binding is compiled against, as switchback.py names the one that it runs with."""
+    with open(os.path.join(_torch_dir(), "version.py")) as fh:
+        text = fh.read()
+    return " ".join(re.search(r"^%s = '([^']*)'" % name, text, re.M).group(1) for name in ("__version__", "git_version"))
+
+
 def _build_binding():
     """csrc/binding.cpp: host code against torch's headers, no kernels.  It is handed the library's entry points when it is
     bound, and links none."""
     torch_dir = _torch_dir()
-    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DSB_BUILT_FOR=\"%s\"" % _torch_build(),
                           "-isystem", os.path.join(torch_dir, "include"), "-I", sysconfig.get_paths()["include"],
                           os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
                           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"],

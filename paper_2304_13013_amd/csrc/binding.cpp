@@ -4,8 +4,9 @@
 // plain tensor that passes (subclasses, function modes, wrong types and shapes) or not a plain argument (ctypes objects,
 // wrong types and numbers of them) goes to those, which raise or answer as they always did.
 //
-// The module links no library of kernels: bind() gets the addresses of one that is loaded, and returns functions that carry
-// them, so two libraries may be bound side by side.
+// The tensor checks read tensors through the headers of the torch that this file is compiled against, so the module says
+// which one that is (built_for), and the caller uses it with no other.  It links no library of kernels: bind() gets the
+// addresses of one that is loaded, and returns functions that carry them, so two libraries may be bound side by side.
 #include <Python.h>
 
 #include <ATen/Functions.h>
@@ -236,4 +237,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__binding() {
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", SB_BUILT_FOR) != 0) Py_CLEAR(m);
+    return m;
+}

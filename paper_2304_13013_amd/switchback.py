@@ -7,7 +7,9 @@ Names follow the C ABI: quantize_rowwise, quantize_tensorwise, matmul_int8_dequa
 backward_weight (Algorithm 1 of arxiv 2304.13013: X [b,n], W [m,n], Y/dY [b,m]).
 """
 import ctypes
+import importlib.util
 import os
+import sysconfig
 import types
 
 import torch
@@ -103,23 +105,35 @@ _native = _bound_to = None
 
 
 def _entries():
-    """The entry points as built-in functions (csrc/binding.cpp).  Raises if the library has not been built."""
+    """The entry points, as built-in functions (csrc/binding.cpp) where those fit this Python and this torch, else through
+    ctypes.  Raises if the library has not been built."""
     return _native if _native is not None and _bound_to is _lib else _bind()
+
+
+def _load_binding():
+    """The built-in functions' module, or None: it reads tensors through the headers of the torch that it was compiled
+    against, and is used with no other."""
+    path = os.path.join(_HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
+    try:
+        spec = importlib.util.spec_from_file_location("_binding", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError:
+        return None
+    return module if module.built_for == "%s %s" % (torch.__version__, torch.version.git_version) else None
 
 
 def _bind():
     global _native, _bound_to, _dev, _out
-    lib = load_library()
-    try:
-        from . import _binding
-    except ImportError as e:
-        raise SwitchBackError("the Python binding of libswitchback is not built: %s" % e)
-
-    def entry(name):
-        f = getattr(lib, name)
-        return ctypes.cast(f, ctypes.c_void_p).value, f
-    _native = types.SimpleNamespace(**_binding.bind(_dev_general, _out_general, SbSaved, entry))
-    _dev, _out = _native.dev, _native.out
+    lib, binding = load_library(), _load_binding()
+    if binding is None:
+        _native, _dev, _out = lib, _dev_general, _out_general
+    else:
+        def entry(name):
+            f = getattr(lib, name)
+            return ctypes.cast(f, ctypes.c_void_p).value, f
+        _native = types.SimpleNamespace(**binding.bind(_dev_general, _out_general, SbSaved, entry))
+        _dev, _out = _native.dev, _native.out
     _bound_to = lib
     return _native
 

@@ -287,3 +287,35 @@ def test_builtin_entries_call_the_library_that_is_loaded(tmp_path, monkeypatch):
         assert sb._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 77
         assert before.switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
     assert sb._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
+
+
+def test_another_torch_runs_through_ctypes(monkeypatch):
+    """The built-in forms read tensors as the torch that they were compiled against lays them out: with another one, and
+    where there is no binding for this Python, the calls go through ctypes."""
+    import torch
+    import sysconfig
+    sb._entries()
+    assert sb._dev is not sb._dev_general, "the binding is built for this torch"
+    for change in (lambda m: m.setattr(torch.version, "git_version", "another"), lambda m: m.setattr(torch, "__version__", "1.0"),
+                   lambda m: m.setattr(sysconfig, "get_config_var", lambda name: ".another-python.so")):
+        with monkeypatch.context() as m:
+            for name in ("_native", "_bound_to", "_dev", "_out"):
+                m.setattr(sb, name, getattr(sb, name))
+            change(m)
+            sb._bind()
+            assert sb._entries() is sb.load_library() and (sb._dev, sb._out) == (sb._dev_general, sb._out_general)
+            saved = sb.LayerBuffers(8, 64, 128, "cpu").saved
+            assert sb._entries().switchback_backward_input(None, saved, 0, 64, 64, None, 0, None, None, None) == 0
+            with pytest.raises(sb.SwitchBackError, match="live on the GPU"):
+                sb.quantize_rowwise(torch.zeros(4, 64, dtype=torch.bfloat16))
+    assert sb._dev is not sb._dev_general
+
+
+def test_module_loaded_by_its_path():
+    """switchback.py needs no package around it."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("switchback_by_path", os.path.join(ROOT, "paper_2304_13013_amd", "switchback.py"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
+    assert sb._entries().dev is sb._dev

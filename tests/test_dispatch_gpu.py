@@ -329,8 +329,32 @@ def test_builtin_tensor_checks_agree_with_the_general_ones(case):
     with mode:
         assert answer(sb._dev, t, torch.float32, 2) == answer(sb._dev_general, t, torch.float32, 2)
         assert answer(sb._dev, t, torch.float32) == answer(sb._dev_general, t, torch.float32)
+        assert answer(sb._dev, t, torch.float32, 2 ** 70) == answer(sb._dev_general, t, torch.float32, 2 ** 70)
         a, g = (answer(f, t, (64, 64), torch.float32, t.device, "y") for f in (sb._out, sb._out_general))
         assert a is g or a == g
         fresh, want = (f(None, (3, 5), t.dtype, t.device, "y") for f in (sb._out, sb._out_general))
     assert (fresh.shape, fresh.dtype, fresh.device, fresh.stride(), type(fresh), fresh.requires_grad) == (
         want.shape, want.dtype, want.device, want.stride(), type(want), want.requires_grad)
+
+
+def test_ctypes_path_computes_the_same(monkeypatch, b=100, n=192, m=128):
+    """The calls through ctypes, which another torch than the binding's takes: every entry point with an sb_saved, and one without."""
+    rng = np.random.default_rng(5)
+    x, w, dy = to_dev(rand_bf16(rng, (b, n))), to_dev(rand_bf16(rng, (m, n), n ** -0.5)), to_dev(rand_bf16(rng, (b, m), 0.1))
+
+    def everything():
+        y, bufs = sb.forward(x, w)
+        out = [y, sb.backward_input(dy, bufs), *sb.backward_weight_m(dy, bufs), sb.backward_weight(dy, x, bufs),
+               sb.forward_static(x, w, bufs)[0], sb.forward_bias_layerscale(x, w, bufs=bufs)[0], *sb.quantize_rowwise(x)]
+        x8, w8 = x[:, :128].contiguous(), w[:, :128].contiguous()
+        y8, bufs8 = sb.forward_f8(x8, w8)
+        return out + [y8, sb.backward_input_f8(dy, bufs8)]
+
+    built_in = everything()
+    assert sb._dev is not sb._dev_general
+    for name in ("_native", "_bound_to", "_dev", "_out"):
+        monkeypatch.setattr(sb, name, getattr(sb, name))
+    monkeypatch.setattr(sb, "_load_binding", lambda: None)
+    sb._bind()
+    assert sb._dev is sb._dev_general
+    assert all(torch.equal(a, c) for a, c in zip(built_in, everything(), strict=True))
