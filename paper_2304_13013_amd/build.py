@@ -2,8 +2,10 @@
 import importlib.util
 import os
 import re
+import shutil
 import subprocess
 import sysconfig
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -50,6 +52,25 @@ def _build_binding():
         raise RuntimeError("g++ failed for binding.cpp:\n%s" % res.stderr)
 
 
+def check_kernels(asm):
+    """Faults of a source's device assembly that no test shows reliably, as a list of texts.  The matrix-product kernels load
+    LDS and memory from inline assembly, into registers that the compiler takes as written at once: a register that is spilled
+    while its load is on the way is stored too early, and an address in it faults.  Four-wave kernels name their accumulators
+    in the assembly text: a value of the compiler's in an accumulation register would be overwritten."""
+    faults = []
+    for entry in re.split(r"^ {2}- ", asm[asm.rfind("amdhsa.kernels:"):], flags=re.M):
+        fields = dict(re.findall(r"^ +\.(name|vgpr_spill_count|sgpr_spill_count|private_segment_fixed_size): +(\S+)", entry, re.M))
+        faults += ["%s: %s %s" % (fields.get("name"), key, value) for key, value in fields.items()
+                   if key in ("vgpr_spill_count", "private_segment_fixed_size") and value != "0"]
+    for name, body in re.findall(r"^(\w+):(?: [^\n]*)?\n(.*?)^\.Lfunc_end", asm, re.M | re.S):
+        if not re.search(r"v_mfma_\w+ a\[\d+:\d+\], v\S+ v\S+ 0", body):  # an accumulator named in the text, cleared
+            continue
+        code = re.sub(r";;#ASMSTART\n.*?;;#ASMEND", "", body, flags=re.S)
+        faults += ["%s: %s" % (name, line.strip()) for line in code.splitlines()
+                   if re.search(r"\ba\d+\b|\ba\[", line.split(";")[0])]
+    return faults
+
+
 def build(verbose=False):
     """Compile every kernel source for gfx950, link the shared library and the Python binding.  Always recompiles."""
     out_dir = os.path.join(HERE, "_build")
@@ -58,10 +79,17 @@ def build(verbose=False):
 
     def compile_one(src):
         obj = os.path.join(out_dir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-        res = subprocess.run(cmd, capture_output=True, text=True)
-        if res.returncode != 0:
-            raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, res.stdout, res.stderr))
+        with tempfile.TemporaryDirectory() as temps:
+            res = subprocess.run([hipcc, *HIPCC_FLAGS, "-save-temps=obj", "-c", os.path.join(CSRC, src), "-o",
+                                  os.path.join(temps, "source.o")], capture_output=True, text=True)
+            if res.returncode != 0:
+                raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, res.stdout, res.stderr))
+            asm, = (f for f in os.listdir(temps) if f.endswith("gfx950.s"))
+            with open(os.path.join(temps, asm)) as fh:
+                faults = check_kernels(fh.read())
+            if faults:
+                raise RuntimeError("%s: kernels that must not run:\n%s" % (src, "\n".join(faults[:20])))
+            shutil.move(os.path.join(temps, "source.o"), obj)
         if verbose and res.stderr.strip():
             print(res.stderr)
         return obj

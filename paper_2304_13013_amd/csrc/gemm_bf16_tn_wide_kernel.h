@@ -17,8 +17,7 @@
 // The loop keeps a constant number of requests in flight, so its one wait per period is a constant: past the last stage
 // of a workgroup the requests go on with an empty buffer resource (zeros from the bounds check, no memory traffic).
 // The matrix instructions are inline asm: their accumulators have to stay in AGPRs, and no fragment may be moved while
-// its asm read is in flight (an instance that spills or copies fragments must never run; this one takes 256 + 168
-// registers and does neither).
+// its asm read is in flight (an instance that spills must never run, and the build refuses one).
 //
 // 32896 tokens, 1280 -> 5120: 395 -> 351 us with the reduction of its five splits (eight waves of 128x64 before; 1.09 ->
 // 1.23 PFLOP/s); 16384 tokens, 4096 -> 16384: 1630 -> 1515 us (1.45 PFLOP/s; all-zero operands 1420 -> 1185); 16448

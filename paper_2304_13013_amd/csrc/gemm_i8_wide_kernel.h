@@ -33,8 +33,7 @@
 // buffer resource, rows past the end lie beyond the output's resource and columns past the end are sent there.
 //
 // Accumulators, fragment reads and matrix instructions are inline asm.  No fragment may be moved while its read is in
-// flight: an instance that spills must never run (all are built without; float8 and bias / layer-scale take the most
-// registers, 256 + 224).
+// flight: an instance that spills must never run, and the build refuses one, as it does a value of the compiler's in an AGPR.
 //
 // Measured against eight waves of 128x64 with two in-row bursts of requests per stage (us, codes of normal data):
 //   32896 x 5120, K = 1280: 207 -> 185 (2.34 POP/s); 32896 x 1280, K = 5120: 183 -> 170; 16384 x 4096, K = 16384: 870 ->
