@@ -157,10 +157,17 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
     np.testing.assert_array_equal(host(rc).view(np.uint16), oracle.round_to_bf16(ref_rc))
 
 
-# 256x256 tiles: a single column of partial tiles, tiles of one stage and of half a one (several tiles are under way at once,
-# five rounds of them), of two and of three, partial in both directions.
-@pytest.mark.parametrize("M,N,K", [(33000, 64, 64), (33000, 2304, 64), (8449, 1088, 128), (17000, 2240, 192),
-                                   (16700, 2112, 320)])
+# 256x256 tiles, with every output and scale: one, two and three stages a tile, the last one whole or half, two and three tiles
+# per workgroup, partial in both directions.  At these lengths the epilogue of a tile stands in the first half stage of the
+# next one, right before its hand-over.
+LARGE = [(16385, 1472, 64), (8449, 2880, 128), (20011, 2240, 192), (14000, 3264, 256), (12345, 2240, 320), (12345, 2240, 384)]
+# 128x128 tiles: the same for a single stage, two and five; one tile per workgroup and more than fit the GPU at once.
+SMALL_TILES = [(3000, 704, 64), (33000, 320, 128), (3000, 704, 192), (3000, 704, 256), (3000, 704, 576), (3000, 704, 640)]
+
+
+# The other sizes: a single column of partial tiles (128x128), and short contractions on whichever tile the output takes.
+@pytest.mark.parametrize("M,N,K", LARGE + SMALL_TILES + [(33000, 64, 64), (33000, 2304, 64), (8449, 1088, 128), (17000, 2240, 192),
+                                                         (16700, 2112, 320)])
 def test_large_tiles(oracle, M, N, K):
     test_half_stages_and_last_rows(oracle, M, N, K)
 
@@ -180,6 +187,18 @@ def test_narrow_tiles_and_whole_rounds(oracle, M, N, K):
 # Exact sums, as for the small float8 products: last rows, the small tile with ragged edges, 256x128 tiles, whole rounds.
 TILES_F8 = [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2112, 384)]
 NARROW_F8 = [(6304, 768, 3072), (5431, 960, 4096), (22069, 1472, 384)]
+
+
+# Every pair of formats on each tile: 256x256 with one stage a tile and with two, 256x128, 128x128 with one stage and with more
+# tiles than fit the GPU at once; partial in both directions.
+FORMATS_F8 = {"256": [(8449, 2880, 128), (14000, 3264, 256)], "256x128": [(5431, 960, 4096)],
+              "128": [(3000, 704, 128), (33000, 320, 256)]}
+
+
+@pytest.mark.parametrize("fa,fb", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K", sum(FORMATS_F8.values(), []))
+def test_formats_on_every_tile_of_a_float8_product(M, N, K, fa, fb):
+    check_exact_float8_product(M, N, K, fa, fb)
 
 
 @pytest.mark.parametrize("fa,fb", [(1, 0), (0, 0)])
@@ -271,6 +290,22 @@ def test_weight_gradient_tiles(oracle, b, n, m):
     dwbf = sb.backward_weight(to_dev(dyb), to_dev(xb))
     magnitude = oracle.weight_grad(dyb & 0x7fff, xb & 0x7fff)
     assert np.all(np.abs(host(dw32) - oracle.weight_grad(dyb, xb)) <= (b / 16 + 16) * 2.0 ** -23 * magnitude)
+    assert torch.equal(dwbf, dw32.bfloat16())
+
+
+# A second item per workgroup on the 128x128 tiles (969 to 1008 tiles on 512 places): without a split, and with the tokens of a
+# tile summed in seven pieces, which start over with the next item.  Bound as above.
+MANY_SMALL_DW = [(70, 2624, 6080), (303, 2368, 6464), (14434, 3136, 4928)]
+
+
+@pytest.mark.parametrize("b,n,m", MANY_SMALL_DW)
+def test_weight_gradient_small_tiles_with_a_second_item(b, n, m):
+    rng = np.random.default_rng(b + n + m)
+    dy, x = to_dev(rand_bf16(rng, (b, m), 0.1)), to_dev(rand_bf16(rng, (b, n)))
+    dw32, dwbf = sb.backward_weight(dy, x, dw_dtype=torch.float32), sb.backward_weight(dy, x)
+    dy_t, x = dy.double().t().contiguous(), x.double()
+    bound = (b / 16 + 16) * 2.0 ** -23 * (dy_t.abs() @ x.abs())
+    assert bool(((dw32 - dy_t @ x).abs() <= bound).all())
     assert torch.equal(dwbf, dw32.bfloat16())
 
 

@@ -9,6 +9,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NONE, D32, D64, D64H = range(4)
 PLAIN, LONG_EPILOGUE, F8 = range(3)
+FORMS = [(PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (LONG_EPILOGUE, 4)]  # of the int8 product: epilogue, bytes of an output
 WRAPPER = r"""
 #include "dispatch.h"
 #include "adamw_rules.h"
@@ -135,19 +136,13 @@ def test_sizes_of_the_gpu_tests_reach_every_path(rules):
     plans = [(K, route(rules, M, N, K, 4, F8)) for M, N, K in sizes.SMALL_F8]
     assert all(rows == 0 for _, (rows, _) in plans)
     assert {split for K, (_, split) in plans if stages_per_wave(K, split) > 2} == {D32, D64, D64H}
-    for kind, out_bytes in ((PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (LONG_EPILOGUE, 4)):
-        seen = set()
-        for M, N, K in sizes.SPLIT:
-            rows, split = route(rules, M, N, K, out_bytes, kind)
-            assert rows > 0, (M, N, K)
-            seen.add(("small" if rules.few_tiles(rows, N, 256) else "large",
-                      "short" if K == 64 else "half" if K % 128 else "whole",
-                      split != NONE))
-        assert seen >= {("small", "half", False), ("large", "half", False), ("large", "short", False),
-                        ("large", "whole", True), ("large", "half", True)}, (kind, out_bytes, seen)
-    plans = [(M, rules.few_tiles(M, N, 256), route(rules, M, N, K, 4, F8)) for M, N, K in sizes.TILES_F8]
-    assert {(bool(few), rows < M) for M, few, (rows, _) in plans} == {(True, False), (False, True)}
-    assert all(rows > 0 for _, _, (rows, _) in plans)
+    for kind, out_bytes in FORMS:  # last rows split off, with whole and half last stages
+        plans = [(K, *route(rules, M, N, K, out_bytes, kind)) for M, N, K in sizes.SPLIT]
+        assert all(rows > 0 for _, rows, _ in plans)
+        assert {K % 128 for K, _, split in plans if split != NONE} == {0, 64}, (kind, out_bytes, plans)
+    for out_bytes in (2, 4):
+        plans = [(M, *route(rules, M, N, K, out_bytes, F8)) for M, N, K in sizes.TILES_F8]
+        assert all(rows > 0 for _, rows, _ in plans) and {rows < M for M, rows, _ in plans} == {True, False}
 
 
 TILES_128, TILES_256X128, TILES_256 = range(3)
@@ -160,9 +155,27 @@ def tiles(rules, M, N, K, kind, out_bytes):
     return rows, first.value if rows else None, second.value if rows < route(rules, M, N, K, out_bytes, kind)[0] else None
 
 
+def only(rules, tile, M, N, K, kind, out_bytes):
+    """Whether the whole product runs on this one kind of tiles."""
+    return tiles(rules, M, N, K, kind, out_bytes) == (0, None, tile) and route(rules, M, N, K, out_bytes, kind) == (M, NONE)
+
+
 def test_sizes_of_the_gpu_tests_reach_every_tile(rules):
     import test_dispatch_gpu as sizes
-    for kind, out_bytes in ((PLAIN, 2), (PLAIN, 4), (LONG_EPILOGUE, 2), (LONG_EPILOGUE, 4)):
+    for form in FORMS:  # each listed size runs what its list is named for, whichever the output and scale
+        assert all(only(rules, TILES_256, *s, *form) for s in sizes.LARGE), form
+        assert all(only(rules, TILES_128, *s, *form) for s in sizes.SMALL_TILES), form
+    for out_bytes in (2, 4):
+        for name, tile in (("256", TILES_256), ("256x128", TILES_256X128), ("128", TILES_128)):
+            assert all(only(rules, tile, *s, F8, out_bytes) for s in sizes.FORMATS_F8[name]), (name, out_bytes)
+    stages = lambda listed: {(-(-K // 128), K % 128) for _, _, K in listed}
+    assert stages(sizes.LARGE) >= {(s, h) for s in (1, 2, 3) for h in (0, 64)}
+    assert stages(sizes.SMALL_TILES) >= {(s, h) for s in (1, 2, 5) for h in (0, 64)}
+    assert {-(-M // 256) * -(-N // 256) // 256 for M, N, _ in sizes.LARGE} == {1, 2}  # whole rounds before the last one
+    assert any(-(-M // 128) * -(-N // 128) > 512 for M, N, _ in sizes.SMALL_TILES)
+    assert all(M % 256 and N % 256 for M, N, _ in sizes.LARGE)
+    assert all(-(-M // 256) * -(-N // 256) > 256 for M, N, _ in sizes.FORMATS_F8["256"])
+    for kind, out_bytes in FORMS:
         plans = [(M, N, K, *tiles(rules, M, N, K, kind, out_bytes)) for M, N, K in sizes.NARROW]
         narrow = {("half" if K % 128 else "whole", -(-M // 256) * -(-N // 128) > 256)
                   for M, N, K, rows, _, second in plans if rows == 0 and second == TILES_256X128}
@@ -205,6 +218,9 @@ def test_sizes_of_the_gpu_tests_reach_both_weight_gradients(rules):
     assert all(weight_gradient(rules, *s)[0] for s in sizes.SMALL_DW)
     assert max(weight_gradient(rules, *s)[1] for s in sizes.SMALL_DW) > 16
     assert weight_gradient(rules, 8637, 1920, 1984)[:2] == (False, 4)
+    plans = [(-(-n // 128) * -(-m // 128), *weight_gradient(rules, b, n, m)) for b, n, m in sizes.MANY_SMALL_DW]
+    assert all(items > 512 and small and splits == 1 for items, small, splits, *_ in plans)
+    assert {pieces for _, _, _, _, pieces, *_ in plans} == {1, 7}
 
 
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])

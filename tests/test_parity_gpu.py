@@ -587,9 +587,9 @@ def test_layer_whole_output(oracle, config, layer, with_dw):
 
 @pytest.mark.parametrize("b,n,m", [(256, 4352, 4352), (1500, 2304, 2816), (4000, 1280, 1280)])
 def test_weight_gradient_whole_output_over_several_rounds(oracle, b, n, m):
-    """More work items than workgroups, so workgroups of the persistent grid take a second item: 289 large tiles
-    without a split of the token range; 198 and 100 small tiles (the instance for short work items) with one.  dW
-    compared with the oracle on every element."""
+    """289 large tiles without a split of the token range, so workgroups of the persistent grid take a second item; 396
+    small tiles (the instance for short work items) without a split, and 100 of them in three token ranges.  dW compared
+    with the oracle on every element."""
     rng = np.random.default_rng(b + n + m)
     dyb, xb = rand_bf16(rng, (b, m), 0.1), rand_bf16(rng, (b, n))
     dy, x = to_dev(dyb), to_dev(xb)
