@@ -230,6 +230,28 @@ def test_float8_rows_on_both_sides_of_a_split(oracle, fa, M=16448, N=1024, K=102
     assert err[1] <= 1.02 * err[0], err
 
 
+# The same for contractions of three to 64 stages, on codes of layer data: neither the pieces nor the one chain is further from
+# binary64 than the other (the products inside an instruction lose far more than the additions between them).
+CHAIN_ROWS, CHAIN_LAST, CHAIN_COLS, CHAIN_K = 16384, 256, 1024, [384, 1024, 4096, 8192]
+
+
+@pytest.mark.parametrize("fa", [0, 1])
+@pytest.mark.parametrize("K", CHAIN_K)
+def test_float8_sums_in_one_chain_and_in_pieces(K, fa):
+    gen = torch.Generator(device=DEV).manual_seed(K + fa)
+    x = torch.randn(CHAIN_ROWS, K, generator=gen, device=DEV).bfloat16()
+    w = (torch.randn(CHAIN_COLS, K, generator=gen, device=DEV) / K ** 0.5).bfloat16()
+    a, sr = sb.quantize_rowwise_f8(x, fa)
+    b, _, st = sb.quantize_tensorwise_f8(w, 0)
+    some = slice(0, CHAIN_LAST)
+    chain = sb.matmul_f8_dequant(a, fa, sr, b, 0, st, out_dtype=torch.float32)[some]
+    pieces = sb.matmul_f8_dequant(a[some].contiguous(), fa, sr[some].contiguous(), b, 0, st, out_dtype=torch.float32)
+    values = a[some].view((torch.float8_e4m3fn, torch.float8_e5m2)[fa]).double()
+    exact = values @ b.view(torch.float8_e4m3fn).double().t().contiguous() * sr[some].double()[:, None] * st.double()
+    err = [(y.double() - exact).norm() for y in (chain, pieces)]
+    assert abs(err[0] - err[1]) <= 0.02 * err[1], err  # 262144 outputs: the ratio scatters by about 0.2 %
+
+
 # A few tokens into a very wide output: 129 tiles in the only, partial row of tiles, so that nothing is left for the tiles
 # if the "last rows" leave them.  Every form of the product.
 @pytest.mark.parametrize("M", [1, 32, 64])

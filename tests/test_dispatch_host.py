@@ -145,6 +145,13 @@ def test_sizes_of_the_gpu_tests_reach_every_path(rules):
         assert all(rows > 0 for _, rows, _ in plans) and {rows < M for M, rows, _ in plans} == {True, False}
 
 
+def test_sizes_of_the_float8_error_test_take_both_routes(rules):
+    import test_dispatch_gpu as sizes
+    for K in sizes.CHAIN_K:
+        assert route(rules, sizes.CHAIN_ROWS, sizes.CHAIN_COLS, K, 4, F8) == (sizes.CHAIN_ROWS, NONE)
+        assert route(rules, sizes.CHAIN_LAST, sizes.CHAIN_COLS, K, 4, F8)[0] == 0
+
+
 TILES_128, TILES_256X128, TILES_256 = range(3)
 
 
