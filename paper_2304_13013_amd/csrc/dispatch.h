@@ -112,9 +112,10 @@ struct ProductPlan {
 // 256x256 tiles; 0.15 to 1.04 of the 128x128 tiles' time up to there and 0.9 to 2.3 of it past it.  64 x 1024, K = 4096:
 // 4.4 us against 22.7; 197 x 3072, K = 768: 4.3 / 7.3; 2000 x 768, K = 3072: 11.9 / 18.3; on the other side of the line
 // 1137 x 1856, K = 128: 5.6 / 4.4; 7233 x 320, K = 1920: 16.7 / 13.5; 338 x 5760, K = 7552 with bias and layer-scale: 52.7 /
-// 41.6.  Long contractions of many blocks are bound by their operands' way from L2, 12.5 TB/s, and run on tiles if those
-// save a tenth by the estimates (5431 x 384, K = 6784, float8: 39.0 us on 510 blocks, 31.8 on 256x128 tiles; 190 x 8128, K =
-// 8128: 52.9 / 42.2).
+// 41.6.  Long contractions of nearly that many blocks are bound by their operands' way from L2 (12.5 TB/s assumed, 11.4
+// measured with float8 at K = 6784) and run on tiles if those save a tenth by the estimates.  Those are cautious: it takes
+// float8, two-byte outputs and K above 8192.  Below, the blocks are slower by up to a fifth (us, blocks / 256x128 tiles: 5431 x
+// 384, K = 6784, float8 39.0 / 31.8; 190 x 8128, K = 8128 52.9 / 42.2).
 //
 // Otherwise the fastest of the tiles by the estimates, or 256x256 tiles for the whole rows of them that fill whole rounds of
 // the grid and another kernel for the rows that would start the next round:

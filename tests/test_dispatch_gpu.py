@@ -230,9 +230,9 @@ def test_float8_rows_on_both_sides_of_a_split(oracle, fa, M=16448, N=1024, K=102
     assert err[1] <= 1.02 * err[0], err
 
 
-# The same for contractions of three to 64 stages, on codes of layer data: neither the pieces nor the one chain is further from
+# The same for contractions of three to 256 stages, on codes of layer data: neither the pieces nor the one chain is further from
 # binary64 than the other (the products inside an instruction lose far more than the additions between them).
-CHAIN_ROWS, CHAIN_LAST, CHAIN_COLS, CHAIN_K = 16384, 256, 1024, [384, 1024, 4096, 8192]
+CHAIN_ROWS, CHAIN_LAST, CHAIN_COLS, CHAIN_K = 16384, 256, 1024, [384, 1024, 4096, 8192, 32768]
 
 
 @pytest.mark.parametrize("fa", [0, 1])
