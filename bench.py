@@ -267,17 +267,17 @@ def main():
 
     # ---- measured ceilings (outside the timed region): what this GPU sustains for code that does nothing but issue
     # matrix instructions from registers, on the workload's own operand values (the clock the GPU holds under load
-    # depends on how many operand bits toggle), and for a plain copy.  Eight waves
-    # per workgroup, two per SIMD; four workgroups per compute unit in a row so that a launch lasts several ms.
+    # depends on how many operand bits toggle), and for a plain copy.  The instructions and the register fragments of
+    # the product kernels, one wave per SIMD; eight workgroups per compute unit in a row so that a launch lasts several ms.
     def ceiling(kind, a, b_, reps=3):
-        wgs, iters = 4 * torch.cuda.get_device_properties(dev).multi_processor_count, 2000
-        sink = torch.empty(wgs * 8 * 64, dtype=torch.float32, device=dev)
-        sb.ceiling_mfma(kind, a, b_, wgs, 8, iters, sink)
+        wgs, iters = 8 * torch.cuda.get_device_properties(dev).multi_processor_count, 500
+        sink = torch.empty(wgs * 4 * 64, dtype=torch.float32, device=dev)
+        sb.ceiling_mfma(kind, a, b_, wgs, 4, iters, sink)
         torch.cuda.synchronize()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(reps):
-            work, _ = sb.ceiling_mfma(kind, a, b_, wgs, 8, iters, sink)
+            work, _ = sb.ceiling_mfma(kind, a, b_, wgs, 4, iters, sink)
         e1.record()
         torch.cuda.synchronize()
         return work * reps / e0.elapsed_time(e1) / 1e9

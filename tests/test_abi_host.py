@@ -319,3 +319,15 @@ def test_module_loaded_by_its_path():
     spec.loader.exec_module(module)
     assert module._entries().switchback_quantize_rowwise(None, 0, 8, None, None, None) == 0
     assert sb._entries().dev is sb._dev
+
+
+def test_ceiling_loops_issue_the_instructions_of_the_product_kernels():
+    csrc = os.path.join(ROOT, "paper_2304_13013_amd", "csrc")
+
+    def instructions(*names):
+        return {i for name in names for i in re.findall(r'"(v_mfma_\w+)', open(os.path.join(csrc, name)).read())}
+
+    products = instructions("gemm_i8_wide_kernel.h", "gemm_bf16_tn_wide_kernel.h")
+    assert len(products) == 3 and instructions("ceilings.hip") == products
+    with open(os.path.join(ROOT, "include", "switchback_ceilings.h")) as fh:
+        assert set(re.findall(r"v_mfma_\w+", fh.read())) == products

@@ -1060,3 +1060,13 @@ def test_products_are_repeatable_at_full_size(config, layer):
         y8b.fill_(1.0)
         sb.matmul_f8_dequant(u8(bufs.xq), sb.SB_E4M3, bufs.state_x, u8(bufs.wq), sb.SB_E4M3, bufs.state_w, out=y8b)
         assert torch.equal(y8b, y8), "float8 repetition %d differs" % rep
+
+
+# Operands of ones: every accumulator holds its number of multiply-adds, so the lanes' sums add up to half the operations (all
+# of them whole numbers below 2^24).  The buffers are shorter than what the waves read from them together.
+@pytest.mark.parametrize("kind,one,code", [(0, torch.int8, 1), (1, torch.bfloat16, 0x3f80), (2, torch.uint8, 0x38)])
+@pytest.mark.parametrize("waves", [4, 8])
+def test_ceiling_loops_count_their_operations(kind, one, code, waves):
+    ones = torch.full((6144,), code, dtype=torch.int16 if kind == 1 else one, device=DEV).view(one)
+    ops, sink = sb.ceiling_mfma(kind, ones[:4096].contiguous(), ones, 3, waves, 2)
+    assert sink.numel() == 3 * waves * 64 and 2 * sink.double().sum().item() == ops
