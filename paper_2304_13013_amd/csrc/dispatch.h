@@ -226,37 +226,52 @@ struct WeightGradPlan {
 //   split: 6.6 + 0.02 s + 0.23 s MB;  3.7 + 0.07 s + 0.31 s MB
 // fitted to 5900 launches of 1000 weight gradients (100..34000 tokens, widths 128..8192, 1 to 96 splits): the ratio to the
 // measured time has a standard deviation of 5 and 9 %.
-inline double weight_gradient_time(bool small, int64_t b, int64_t n, int64_t m, int s, int ncu) {
-    const int side = small ? 128 : 256, slots = small ? 2 * ncu : ncu;
-    const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;
-    const double k = (double)((stages + s - 1) / s), mb = (double)m * (double)n * 4e-6;
-    const int64_t items = ((m + side - 1) / side) * ((n + side - 1) / side) * s, rounds = (items + slots - 1) / slots;
-    const double full = (double)items / slots;
-    if (!small)
-        return 1.32 + 4.45 * rounds + k * (0.995 * rounds + 0.341 * full) + 0.087 * mb +
-               (s > 1 ? 6.62 + (0.017 + 0.232 * mb) * s : 0.0);
-    const int64_t last = items - (rounds - 1) * slots;
-    const double second = (double)(rounds - 1) + (last > ncu ? (double)(last - ncu) / ncu : 0.0);
-    return 2.84 + k * (0.465 * rounds + 0.072 * second + 0.434 * full) + 0.17 * mb +
-           (s > 1 ? 3.71 + (0.07 + 0.314 * mb) * s : 0.0);
-}
+// Int: 32 bits where the sizes allow it (all that the calls take): a plan divides whole numbers up to 78 times over, on the host
+// and in every call (with the stop below 1.4 -> 0.2 us at 16448 tokens, 1024 -> 3072, 1.7 -> 0.8 at 28030, 320 -> 192).
+template <class Int>
+struct WeightGradTime {
+    Int side, slots, ncu, stages, tiles;
+    double mb;
+    WeightGradTime(bool small, int64_t b, int64_t n, int64_t m, int ncu)
+        : side(small ? 128 : 256), slots(small ? 2 * ncu : ncu), ncu(ncu), stages((Int)((b + DW_STAGE - 1) / DW_STAGE)),
+          tiles((Int)((m + side - 1) / side) * (Int)((n + side - 1) / side)), mb((double)m * (double)n * 4e-6) {}
+    double of(Int s) const {
+        const Int items = tiles * s, rounds = (items + slots - 1) / slots;
+        const double k = (double)((stages + s - 1) / s), full = (double)items / slots;
+        if (side == 256)
+            return 1.32 + 4.45 * rounds + k * (0.995 * rounds + 0.341 * full) + 0.087 * mb +
+                   (s > 1 ? 6.62 + (0.017 + 0.232 * mb) * s : 0.0);
+        const Int last = items - (rounds - 1) * slots;
+        const double second = (double)(rounds - 1) + (last > ncu ? (double)(last - ncu) / ncu : 0.0);
+        return 2.84 + k * (0.465 * rounds + 0.072 * second + 0.434 * full) + 0.17 * mb +
+               (s > 1 ? 3.71 + (0.07 + 0.314 * mb) * s : 0.0);
+    }
+    // No larger than of(s) or any of(s' > s): the work of a full GPU and the cost of the partial sums.
+    double at_least(int s) const {
+        const double work = (double)stages * tiles / slots;
+        return side == 256 ? (0.995 + 0.341) * work + (0.017 + 0.232 * mb) * s : (0.465 + 0.434) * work + (0.07 + 0.314 * mb) * s;
+    }
+};
 
 // The fastest by the estimates that sums in least_pieces or more; the split that the pieces are of, unless another saves 6 %
 // (what looks 3 % better loses 5 to 13 % in one of ten: 23446 tokens, 576 -> 1792 66.6 against 75.6 us).  Measured against that
 // split always (us): 28030 tokens, 320 -> 192 405 / 25; 5214 tokens, 256 -> 448 81 / 14; 197 tokens, 768 -> 3072 9.8 / 5.6; 0.73
 // of the time in the mean over 400 weight gradients.
-inline WeightGradPlan plan_weight_gradient(int64_t b, int64_t n, int64_t m, int ncu) {
+template <class Int>
+inline WeightGradPlan plan_weight_gradient_in(int64_t b, int64_t n, int64_t m, int ncu) {
     const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;
     const int least = least_pieces(b, n, m, ncu);
     const bool long_items = least == 1 || stages / least >= 32;
     WeightGradPlan plan{true, 1, (int)stages, least, (int)((stages + least - 1) / least)};
-    double best = weight_gradient_time(true, b, n, m, 1, ncu) + (least > 1 ? 0.3 : 0.0);
+    double best = WeightGradTime<Int>(true, b, n, m, ncu).of(1) + (least > 1 ? 0.3 : 0.0);
     for (int i = 0; i < 2 && stages > 0; ++i) {
         const bool small = i == 0;
         const int most = small ? 64 : 16, shortest = small ? 4 : 6;  // splits; stages of one, if there are more than `least`
-        for (int s = least; s <= most && (s == least || stages / s >= shortest); ++s) {
+        const WeightGradTime<Int> time(small, b, n, m, ncu);
+        for (int s = least; s <= most && (s == least || stages >= s * shortest); ++s) {
             if (small && s == 1) continue;
-            const double t = weight_gradient_time(small, b, n, m, s, ncu) * (s == least && small != long_items ? 0.94 : 1.0);
+            if (s > least && time.at_least(s) > best) break;
+            const double t = time.of(s) * (s == least && small != long_items ? 0.94 : 1.0);
             if (t >= best) continue;
             const int64_t per_split = (stages + s - 1) / s;
             best = t;
@@ -264,6 +279,10 @@ inline WeightGradPlan plan_weight_gradient(int64_t b, int64_t n, int64_t m, int 
         }
     }
     return plan;
+}
+inline WeightGradPlan plan_weight_gradient(int64_t b, int64_t n, int64_t m, int ncu) {
+    const bool narrow = b <= (int64_t)1 << 30 && n <= (int64_t)1 << 18 && m <= (int64_t)1 << 18;  // 64 splits of 2^22 tiles
+    return narrow ? plan_weight_gradient_in<int32_t>(b, n, m, ncu) : plan_weight_gradient_in<int64_t>(b, n, m, ncu);
 }
 
 }  // namespace sb

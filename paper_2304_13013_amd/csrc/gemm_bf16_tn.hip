@@ -47,9 +47,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const v4f *__restric
         static_cast<v4f *>(out)[i] = s;
 }
 
-// The plan is a function of the shape alone, so the workspace query and the launch agree.
-WeightGradPlan plan_of(int64_t b, int64_t n, int64_t m) { return plan_weight_gradient(b, n, m, num_compute_units()); }
-
 template <class C>
 hipError_t set_lds_limit_once(void (*kernel)(GemmBf16Args), std::atomic<bool> &done) {
     if (done.load(std::memory_order_acquire)) return hipSuccess;  // a second set by a racing host thread is harmless
@@ -61,15 +58,18 @@ hipError_t set_lds_limit_once(void (*kernel)(GemmBf16Args), std::atomic<bool> &d
 
 }  // namespace
 
-size_t gemm_bf16_tn_workspace_bytes(int64_t b, int64_t n, int64_t m) {
-    const int s = plan_of(b, n, m).splits;
-    return s > 1 ? (size_t)s * (size_t)m * (size_t)n * sizeof(float) : 0;
+// The plan is a function of the shape alone, so the workspace query and the launch agree.
+WeightGradPlan plan_gemm_bf16_tn(int64_t b, int64_t n, int64_t m) {
+    return plan_weight_gradient(b, n, m, num_compute_units());
 }
 
-hipError_t launch_gemm_bf16_tn(const void *dy, const void *x, int64_t b, int64_t n, int64_t m, void *dw,
+size_t gemm_bf16_tn_workspace_bytes(const WeightGradPlan &plan, int64_t n, int64_t m) {
+    return plan.splits > 1 ? (size_t)plan.splits * (size_t)m * (size_t)n * sizeof(float) : 0;
+}
+
+hipError_t launch_gemm_bf16_tn(const WeightGradPlan &plan, const void *dy, const void *x, int64_t b, int64_t n, int64_t m, void *dw,
                                sb_dtype dw_dtype, void *ws, hipStream_t stream) {
     static std::atomic<bool> big_set{false}, small_set{false}, fold_set{false};
-    const WeightGradPlan plan = plan_of(b, n, m);
     hipError_t e = plan.pieces > 1 ? set_lds_limit_once<Small>(gemm_bf16_tn_small_fold_kernel, fold_set)
                    : plan.small    ? set_lds_limit_once<Small>(gemm_bf16_tn_small_kernel, small_set)
                                    : set_lds_limit_once<Big>(gemm_bf16_tn_kernel, big_set);

@@ -70,8 +70,11 @@ hipError_t launch_gemm_i8_dequant_post(const int8_t *aq, const float *state_row,
 hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *state_row, const uint8_t *bq, int fmt_b,
                                   const float *state_tensor, int64_t M, int64_t N, int64_t K, void *out,
                                   sb_dtype out_dtype, hipStream_t stream);
-size_t gemm_bf16_tn_workspace_bytes(int64_t b, int64_t n, int64_t m);
-hipError_t launch_gemm_bf16_tn(const void *dy, const void *x, int64_t b, int64_t n, int64_t m, void *dw,
+// The weight gradient's plan (dispatch.h) is made once per call: its workspace is checked and its kernels are launched by it.
+struct WeightGradPlan;
+WeightGradPlan plan_gemm_bf16_tn(int64_t b, int64_t n, int64_t m);
+size_t gemm_bf16_tn_workspace_bytes(const WeightGradPlan &plan, int64_t n, int64_t m);
+hipError_t launch_gemm_bf16_tn(const WeightGradPlan &plan, const void *dy, const void *x, int64_t b, int64_t n, int64_t m, void *dw,
                                sb_dtype dw_dtype, void *ws, hipStream_t stream);
 
 size_t stable_adamw_workspace_bytes();

@@ -1,5 +1,6 @@
 // C ABI of libswitchback: argument validation and the kernel sequence of each pass of Algorithm 1
 // (arxiv 2304.13013).  Every step runs in the HIP kernels of this library; nothing here touches tensor data.
+#include "dispatch.h"
 #include "sb_common.h"
 
 #include <atomic>
@@ -45,6 +46,12 @@ int layer_shape_status(int64_t b, int64_t n, int64_t m) {
     // bf16 operands of the weight gradient are the largest.
     if ((b + 256) * n * 2 >= (int64_t)1 << 32 || (b + 256) * m * 2 >= (int64_t)1 << 32) return SB_UNSUPPORTED_SHAPE;
     return SB_OK;
+}
+
+int weight_gradient_workspace_status(const sb::WeightGradPlan &plan, int64_t n, int64_t m, const void *ws, size_t ws_bytes) {
+    const size_t need = sb::gemm_bf16_tn_workspace_bytes(plan, n, m);
+    if (need > 0 && (ws == nullptr || !aligned16(ws))) return SB_INVALID_ARG;
+    return ws_bytes < need ? SB_WORKSPACE_TOO_SMALL : SB_OK;
 }
 
 int from_hip(hipError_t e) { return e == hipSuccess ? SB_OK : SB_HIP_ERROR; }
@@ -214,11 +221,11 @@ int switchback_backward_weight(const void *dy_bf16, const void *x_bf16, int64_t 
     if (st != SB_OK) return st;
     if (dw_dtype != SB_BF16 && dw_dtype != SB_F32) return SB_INVALID_ARG;
     if (!ok_ptr(dw) || (b > 0 && (!ok_ptr(dy_bf16) || !ok_ptr(x_bf16)))) return SB_INVALID_ARG;
-    const size_t need = switchback_workspace_bytes(SB_OP_BACKWARD_WEIGHT, b, n, m);
-    if (need > 0 && (ws == nullptr || !aligned16(ws))) return SB_INVALID_ARG;
-    if (ws_bytes < need) return SB_WORKSPACE_TOO_SMALL;
+    const sb::WeightGradPlan plan = sb::plan_gemm_bf16_tn(b, n, m);
+    st = weight_gradient_workspace_status(plan, n, m, ws, ws_bytes);
+    if (st != SB_OK) return st;
     // Algorithm 1, backward: W_gradient = 16-bit matmul of dY^T and X (b == 0 gives an all-zero gradient).
-    return from_hip(sb::launch_gemm_bf16_tn(dy_bf16, x_bf16, b, n, m, dw, dw_dtype, ws,
+    return from_hip(sb::launch_gemm_bf16_tn(plan, dy_bf16, x_bf16, b, n, m, dw, dw_dtype, ws,
                                             static_cast<hipStream_t>(stream)));
 }
 
@@ -229,19 +236,18 @@ int switchback_backward_weight_m(const void *dy_bf16, const sb_saved *saved, int
     if (st != SB_OK) return st;
     if (saved == nullptr) return SB_INVALID_ARG;
     if (b > 0 && (!ok_ptr(saved->xq) || saved->state_x == nullptr || !ok_ptr(x_hat_bf16))) return SB_INVALID_ARG;
-    // SwitchBackM backward: X = row-wise dequantize(X_int8, state_X), then the 16-bit matmul of Algorithm 1.  The
-    // weight-gradient call validates the remaining arguments before anything is enqueued.
     if (dw_dtype != SB_BF16 && dw_dtype != SB_F32) return SB_INVALID_ARG;
     if (!ok_ptr(dw) || (b > 0 && !ok_ptr(dy_bf16))) return SB_INVALID_ARG;
-    const size_t need = switchback_workspace_bytes(SB_OP_BACKWARD_WEIGHT, b, n, m);
-    if (need > 0 && (ws == nullptr || !aligned16(ws))) return SB_INVALID_ARG;
-    if (ws_bytes < need) return SB_WORKSPACE_TOO_SMALL;
+    const sb::WeightGradPlan plan = sb::plan_gemm_bf16_tn(b, n, m);
+    st = weight_gradient_workspace_status(plan, n, m, ws, ws_bytes);
+    if (st != SB_OK) return st;
+    // SwitchBackM backward: X = row-wise dequantize(X_int8, state_X), then the 16-bit matmul of Algorithm 1.
+    hipStream_t s = static_cast<hipStream_t>(stream);
     if (b > 0) {
-        hipError_t e = sb::launch_dequantize_rowwise(saved->xq, saved->state_x, b, n, x_hat_bf16,
-                                                     static_cast<hipStream_t>(stream));
+        hipError_t e = sb::launch_dequantize_rowwise(saved->xq, saved->state_x, b, n, x_hat_bf16, s);
         if (e != hipSuccess) return SB_HIP_ERROR;
     }
-    return switchback_backward_weight(dy_bf16, x_hat_bf16, b, n, m, dw, dw_dtype, ws, ws_bytes, stream);
+    return from_hip(sb::launch_gemm_bf16_tn(plan, dy_bf16, x_hat_bf16, b, n, m, dw, dw_dtype, ws, s));
 }
 
 int switchback_quantize_colwise_transpose(const void *w_bf16, int64_t rows, int64_t cols, int8_t *q_t, float *state,
@@ -443,7 +449,7 @@ size_t switchback_workspace_bytes(int op, int64_t b, int64_t n, int64_t m) {
         case SB_OP_BACKWARD_INPUT: return 0;
         case SB_OP_BACKWARD_WEIGHT:
             if (b < 0 || n <= 0 || m <= 0) return 0;
-            return sb::gemm_bf16_tn_workspace_bytes(b, n, m);
+            return sb::gemm_bf16_tn_workspace_bytes(sb::plan_gemm_bf16_tn(b, n, m), n, m);
         case SB_OP_QUANTIZE_COLWISE:  // w is [m, n]
             if (n <= 0 || m <= 0) return 0;
             return sb::quantize_colwise_workspace_bytes(m, n);
