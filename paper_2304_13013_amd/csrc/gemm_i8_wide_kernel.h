@@ -302,35 +302,53 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
         asm volatile("" : "+v"(lane_e));
         if (OUT == OUT_BF16)
             o_voff = (unsigned)((lane_e / PPR) * p.N + (lane_e % PPR) * 8) * 2;
+        else if (F8)
+            o_voff = (unsigned)((lane_e & 15) * p.N + (lane_e >> 4 & 1) * 8 + (lane_e >> 5) * 4) * 4;
         else
             o_voff = (unsigned)((lane_e & (C::BLK - 1)) * p.N + (lane_e / C::BLK) * 4) * 4;
     };
     v4u val[C::PATCH_READS];
-    // Quad q of block (a, b): x are its accumulators.
-    auto epi_quad = [&](int a, int b, int q, const AccE *x) {
-        if (OUT == OUT_I32) {
-            v4u v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(unsigned, x[4 * q + e]);
-            const unsigned at = b * C::BLK < cols_in ? o_voff : NOWHERE;
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_out, at, (unsigned)(a * C::BLK * n_out + b * C::BLK + q * 8) * 4, 0);
-            return;
-        }
+    // Quad q of block (a, b), dequantized: x are the block's accumulators.
+    auto epi_value = [&](int a, int b, int q, const AccE *x) -> v4f {
         v4f y;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             y[e] = (float)x[4 * q + e] * (COLSCALE ? rscale[a] * scol[b][e] : rscale[a]);
             if (POST) y[e] = sgam[b][e] * (y[e] + scol[b][e]);
         }
-        if (OUT == OUT_F32) {
-            const unsigned at = b * C::BLK < cols_in ? o_voff : NOWHERE;
+        return y;
+    };
+    auto epi_quad = [&](int a, int b, int q, const AccE *x) {
+        const unsigned at = b * C::BLK < cols_in ? o_voff : NOWHERE;
+        if (OUT == OUT_I32) {
+            v4u v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(unsigned, x[4 * q + e]);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_out, at, (unsigned)(a * C::BLK * n_out + b * C::BLK + q * 8) * 4, 0);
+        } else if (OUT == OUT_F32 && !F8) {
+            const v4f y = epi_value(a, b, q, x);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, y), rsrc_out, at,
                                                    (unsigned)(a * C::BLK * n_out + b * C::BLK + q * 8) * 4, 0);
-            return;
+        } else if (OUT == OUT_F32) {
+            // A quad is 32 bytes of each of 32 rows; two of them, exchanged between groups of 16 lanes, are 64 bytes of 16 rows
+            // each, as the int8 blocks store them (rows a power of two apart lose most by 32-byte pieces: 8127 x 1024, K = 768 26.1
+            // -> 16.4 us; 3584 x 8192, K = 256 51.8 -> 35.7).
+            if (q & 1) return;
+            v4f y0 = epi_value(a, b, q, x), y1 = epi_value(a, b, q + 1, x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(y0[e]), __float_as_uint(y1[e]), false, false);
+                y0[e] = __uint_as_float(s[0]);
+                y1[e] = __uint_as_float(s[1]);
+            }
+            const unsigned soff = (unsigned)(a * C::BLK * n_out + b * C::BLK + q * 8) * 4;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, y0), rsrc_out, at, soff, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, y1), rsrc_out, at, soff + 16u * n_out * 4, 0);
+        } else {
+            const v2u pk = __builtin_bit_cast(v2u, __builtin_convertvector(epi_value(a, b, q, x), v4bf));
+            const int col = (b * C::BLK) % C::PATCH_COLS + q * 8;
+            asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(patch_w), "v"(pk), "n"(col * 2));
         }
-        const v2u pk = __builtin_bit_cast(v2u, __builtin_convertvector(y, v4bf));
-        const int col = (b * C::BLK) % C::PATCH_COLS + q * 8;
-        asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(patch_w), "v"(pk), "n"(col * 2));
     };
     auto epi_read_patch = [&]() {
 #pragma unroll
