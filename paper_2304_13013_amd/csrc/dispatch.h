@@ -56,39 +56,43 @@ enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
 // (gemm_i8_wide_kernel.h).
 enum TileKind { TILES_128 = 0, TILES_256X128, TILES_256, TILE_KINDS };
 
-// Estimated time (us) of a product on tiles.  With r rounds of the persistent grid (of the XCD with most tiles), k stages of
-// 128 bytes and enough tiles for f rounds of a full grid:
-//   launch + r * boundary + k * (r * stage + f * stage_f) + store * megabytes of output
-// fitted to 1200 products (100..40000 rows, 64..8192 columns, K = 128..8192; every output and scale) on an MI355X.  The
-// ratio to the measured time has a standard deviation of 4 to 6 % (7 to 10 % for four-byte outputs); the tile
-// picked is 0.3 to 0.7 % slower than the best one in the mean.
+// Estimated time (us) of a product on tiles.  With r rounds of the persistent grid (of the XCD with most tiles), u tiles on
+// the compute unit that gets most (2 r where two workgroups share one), k stages of 128 bytes and enough tiles for f rounds of
+// a full grid:
+//   launch + r * boundary + u * boundary_u + k * (r * stage + f * stage_f + u * stage_u) + store * megabytes of output
+// Two-byte outputs fitted to 1200 products (100..40000 rows, 64..8192 columns, K = 128..8192; every output and scale) on an
+// MI355X: the ratio to the measured time has a standard deviation of 4 to 6 %, the tile picked is 0.3 to 0.7 % slower than the
+// best one in the mean.  Four-byte ones, whose stores weigh as much as the product of a short contraction, to 7000 and (float8)
+// 6000 products within 30 % of the best tile: picked / best 1.003 (1.016 without u: 34752 x 192, K = 384 makes 532 tiles of
+// 128x128, two on a few compute units' both workgroups, 17.6 us, 14.0 on 256x256 ones).
 inline double tiled_product_time(TileKind tile, int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes,
                                  int ncu) {
     struct Fit {
-        double launch, boundary, stage, stage_f, store;
+        double launch, boundary, stage, stage_f, store, boundary_u, stage_u;
     };
-    static const Fit fits[4][TILE_KINDS] = {
-        // 128x128, 256x128, 256x256: int8; int8 with the longer epilogues; float8; four-byte outputs
-        {{2.29, 1.36, 0.541, 0.502, 0.055}, {2.79, 1.56, 0.548, 0.274, 0.013}, {2.84, 2.72, 0.971, 0.484, 0.034}},
-        {{2.02, 2.28, 0.534, 0.496, 0.089}, {2.82, 2.18, 0.536, 0.267, 0.011}, {2.39, 4.41, 0.954, 0.500, 0.008}},
-        {{1.74, 1.60, 0.537, 0.368, 0.056}, {2.07, 2.18, 0.473, 0.242, 0.072}, {1.54, 3.66, 0.851, 0.444, 0.034}},
-        {{4.11, 0.00, 0.549, 0.506, 0.172}, {5.23, 0.87, 0.533, 0.330, 0.111}, {6.30, 2.09, 0.936, 0.571, 0.106}}};
-    const Fit &fit = fits[out_bytes > 2 ? 3 : (int)kind][tile];
+    static const Fit fits[5][TILE_KINDS] = {
+        // 128x128, 256x128, 256x256: int8; int8 with the longer epilogues; float8; four-byte outputs, int8 and float8
+        {{2.29, 1.36, 0.541, 0.502, 0.055, 0, 0}, {2.79, 1.56, 0.548, 0.274, 0.013, 0, 0}, {2.84, 2.72, 0.971, 0.484, 0.034, 0, 0}},
+        {{2.02, 2.28, 0.534, 0.496, 0.089, 0, 0}, {2.82, 2.18, 0.536, 0.267, 0.011, 0, 0}, {2.39, 4.41, 0.954, 0.500, 0.008, 0, 0}},
+        {{1.74, 1.60, 0.537, 0.368, 0.056, 0, 0}, {2.07, 2.18, 0.473, 0.242, 0.072, 0, 0}, {1.54, 3.66, 0.851, 0.444, 0.034, 0, 0}},
+        {{3.80, 0, 0.339, 0.489, 0.036, 1.90, 0.119}, {4.60, 3.60, 0.426, 0.465, 0.012, 0, 0}, {5.15, 6.61, 0.780, 0.807, 0.016, 0, 0}},
+        {{3.47, 0, 0.399, 0.432, 0.028, 2.12, 0.056}, {4.54, 3.65, 0.367, 0.459, 0.015, 0, 0}, {4.88, 6.79, 0.641, 0.844, 0.018, 0, 0}}};
+    const Fit &fit = fits[out_bytes == 2 ? (int)kind : kind == PRODUCT_F8 ? 4 : 3][tile];
     const int bm = tile == TILES_128 ? 128 : 256, bn = tile == TILES_256 ? 256 : 128;
     const int slots = tile == TILES_128 ? 2 * ncu : ncu;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), per_xcd = persistent_grid(tiles, slots) / 8;
-    const double rounds = (double)(((tiles + 7) / 8 + per_xcd - 1) / per_xcd);
+    const double rounds = (double)(((tiles + 7) / 8 + per_xcd - 1) / per_xcd), unit = per_xcd * 8 > ncu ? 2 * rounds : rounds;
     const double k = (double)((K + 127) / 128 > 1 || tile != TILES_256X128 ? (K + 127) / 128 : 2);
-    return fit.launch + rounds * fit.boundary + k * (rounds * fit.stage + (double)tiles / slots * fit.stage_f) +
+    return fit.launch + rounds * fit.boundary + unit * fit.boundary_u +
+           k * (rounds * fit.stage + (double)tiles / slots * fit.stage_f + unit * fit.stage_u) +
            fit.store * 1e-6 * (double)M * (double)N * out_bytes;
 }
 
-// The tile with the smallest estimate; the 128x128 ones on equal terms, up to 3 % (the wider ones lose 7 % on a narrow miss
-// at worst: 2382 x 1280, K = 2752, binary32 21.4 us against 23.5, where they win 4 % in the mean).  Not for a single stage
-// and two-byte outputs, where a narrow miss goes the other way (6251 x 1408, K = 128: 8.1 us on 128x128 tiles, 7.3 on 256x256
-// ones; 24576 x 320: 8.0 and 7.1; four-byte outputs 39081 x 832 28.0 and 30.8).
+// The tile with the smallest estimate; the 128x128 ones on equal terms, up to 3 % with two-byte outputs (the wider ones lose 7
+// % on a narrow miss at worst, where they win 4 % in the mean).  Not for a single stage, where a narrow miss goes the other way
+// (6251 x 1408, K = 128: 8.1 us on 128x128 tiles, 7.3 on 256x256 ones; 24576 x 320: 8.0 and 7.1).
 inline double best_tiles(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu, TileKind *tile) {
-    double best = (K > 128 || out_bytes > 2 ? 0.97 : 1.0) * tiled_product_time(TILES_128, M, N, K, kind, out_bytes, ncu);
+    double best = (K > 128 && out_bytes == 2 ? 0.97 : 1.0) * tiled_product_time(TILES_128, M, N, K, kind, out_bytes, ncu);
     *tile = TILES_128;
     for (int i = TILES_128 + 1; i < TILE_KINDS; ++i) {
         const double t = tiled_product_time((TileKind)i, M, N, K, kind, out_bytes, ncu);

@@ -189,10 +189,10 @@ TILES_F8 = [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2
 NARROW_F8 = [(6304, 768, 3072), (5431, 960, 4096), (22069, 1472, 384)]
 
 
-# Every pair of formats on each tile: 256x256 with one stage a tile and with two, 256x128, 128x128 with one stage and with more
+# Every pair of formats on each tile: 256x256 with one stage a tile and with two, 256x128, 128x128 with one stage, also with more
 # tiles than fit the GPU at once; partial in both directions.
 FORMATS_F8 = {"256": [(8449, 2880, 128), (14000, 3264, 256)], "256x128": [(5431, 960, 4096)],
-              "128": [(3000, 704, 128), (33000, 320, 256)]}
+              "128": [(3000, 704, 128), (33000, 320, 128)]}
 
 
 @pytest.mark.parametrize("fa,fb", [(0, 0), (1, 0), (0, 1), (1, 1)])
