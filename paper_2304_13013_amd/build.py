@@ -54,21 +54,82 @@ def _build_binding():
 
 def check_kernels(asm):
     """Faults of a source's device assembly that no test shows reliably, as a list of texts.  The matrix-product kernels load
-    LDS and memory from inline assembly, into registers that the compiler takes as written at once: a register that is spilled
-    while its load is on the way is stored too early, and an address in it faults.  Four-wave kernels name their accumulators
-    in the assembly text: a value of the compiler's in an accumulation register would be overwritten."""
+    LDS and memory from inline assembly, into registers that the compiler takes as written at once: a register that is spilled,
+    copied or reused while its load is on the way holds something else, and an address in it faults.  Four-wave kernels name
+    their accumulators in the assembly text: a value of the compiler's in an accumulation register would be overwritten."""
     faults = []
     for entry in re.split(r"^ {2}- ", asm[asm.rfind("amdhsa.kernels:"):], flags=re.M):
-        fields = dict(re.findall(r"^ +\.(name|vgpr_spill_count|sgpr_spill_count|private_segment_fixed_size): +(\S+)", entry, re.M))
+        fields = dict(re.findall(r"^ +\.(name|vgpr_spill_count|private_segment_fixed_size): +(\S+)", entry, re.M))
         faults += ["%s: %s %s" % (fields.get("name"), key, value) for key, value in fields.items()
-                   if key in ("vgpr_spill_count", "private_segment_fixed_size") and value != "0"]
+                   if key != "name" and value != "0"]
     for name, body in re.findall(r"^(\w+):(?: [^\n]*)?\n(.*?)^\.Lfunc_end", asm, re.M | re.S):
-        if not re.search(r"v_mfma_\w+ a\[\d+:\d+\], v\S+ v\S+ 0", body):  # an accumulator named in the text, cleared
-            continue
-        code = re.sub(r";;#ASMSTART\n.*?;;#ASMEND", "", body, flags=re.S)
-        faults += ["%s: %s" % (name, line.strip()) for line in code.splitlines()
-                   if re.search(r"\ba\d+\b|\ba\[", line.split(";")[0])]
+        faults += ["%s: %s (before its LDS read has landed)" % (name, line) for line in _early_uses(body)]
+        if re.search(r"v_mfma_\w+ a\[\d+:\d+\], v\S+ v\S+ 0", body):  # an accumulator named in the text, cleared
+            code = re.sub(r";;#ASMSTART\n.*?;;#ASMEND", "", body, flags=re.S)
+            faults += ["%s: %s" % (name, line.strip()) for line in code.splitlines()
+                       if re.search(r"\ba\d+\b|\ba\[", line.split(";")[0])]
     return faults
+
+
+def _early_uses(body):
+    """Instructions of a kernel that touch a register whose LDS read has not been waited for, on any way through it."""
+    def registers(text):  # a bit each
+        mask = 0
+        for first, last, single in re.findall(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b", text):
+            mask |= 1 << int(single) if single else (1 << int(last) + 1) - (1 << int(first))
+        return mask
+
+    # Blocks of steps: touch registers; wait until at most so many LDS operations are on the way; start one that will write
+    # these registers (none: a write, a scalar load); go to a label, and perhaps on; end.
+    blocks, labels = [[]], {}
+    for line in body.splitlines():
+        line = line.split(";")[0].strip()
+        label = re.match(r"(\.LBB\w+):$", line)
+        if label:
+            labels[label.group(1)] = len(blocks)
+            blocks.append([])
+        if not line or line[0] == "." or line[-1] == ":":
+            continue
+        op, _, rest = line.partition(" ")
+        steps = blocks[-1]
+        if op == "s_waitcnt":
+            count = re.search(r"lgkmcnt\((\d+)\)", rest)
+            if count:
+                steps.append(("wait", int(count.group(1)), line))
+        elif op in ("s_branch", "s_endpgm") or op.startswith("s_cbranch"):
+            steps.append((op, rest.strip(), line))
+        else:
+            touched = registers(rest)
+            if touched:
+                steps.append(("touch", touched, line))
+            if op.startswith("ds_read"):
+                steps.append(("start", registers(rest.split(",")[0]), line))
+            elif op.startswith(("ds_", "s_load", "s_buffer_load")):
+                steps.append(("start", 0, line))
+    found, seen, todo = {}, set(), [(0, ())]
+    while todo:
+        state = todo.pop()
+        if state in seen or state[0] >= len(blocks):
+            continue
+        seen.add(state)
+        index, flying = state
+        for kind, what, line in blocks[index]:
+            if kind == "touch":
+                if any(what & f for f in flying):
+                    found[line] = True
+            elif kind == "wait":
+                flying = flying[len(flying) - what:] if 0 < what <= len(flying) else flying if what else ()
+            elif kind == "start":
+                flying += (what,)
+            elif kind == "s_endpgm":
+                break
+            else:
+                todo.append((labels[what], flying))
+                if kind == "s_branch":
+                    break
+        else:
+            todo.append((index + 1, flying))
+    return list(found)
 
 
 def build(verbose=False):

@@ -505,6 +505,9 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
         return;
     }
     int ring = 0;
+    // The paths below keep the fragments in registers of their own: no copy to those before the reads have landed.
+    wait_lds_reads();
+    pin_frags(0);
     if constexpr (S == 2 && !POST) {  // both fragment buffers and bias and layer-scale do not fit the registers
         if (only_stage) {
 #pragma unroll

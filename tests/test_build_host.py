@@ -1,4 +1,5 @@
-"""What the build refuses: kernels whose registers the compiler has spilled, or whose named accumulators it uses itself."""
+"""What the build refuses: kernels whose registers the compiler has spilled, whose named accumulators it uses itself, or that
+touch a register before its LDS read has landed."""
 import subprocess
 
 import pytest
@@ -29,12 +30,27 @@ extern "C" __global__ __launch_bounds__(64) void named(v4i *p, int *q) {
     q[threadIdx.x] = r;
 }
 """
+# A fragment read that is waited for before its use, or (second form) used on one of two ways without a wait.
+READ = HEAD + """
+extern "C" __global__ __launch_bounds__(64) void read(int *p, int n) {
+    __shared__ int s[64];
+    s[threadIdx.x] = p[threadIdx.x];
+    __syncthreads();
+    int v;
+    asm volatile("ds_read_b32 %%0, %%1" : "=v"(v) : "v"((unsigned)(threadIdx.x ^ 1) * 4));
+    if (n > 0) __builtin_amdgcn_s_waitcnt(0xc07f);
+    %s
+    asm volatile("v_add_u32 %%0, %%0, %%0" : "+v"(v));
+    p[threadIdx.x] = v;
+}
+"""
 
 
 @pytest.mark.parametrize("source,fault", [(LIVE % 256, None), (LIVE % 64, "vgpr_spill_count"), (NAMED % "", None),
-                                          (NAMED % 'asm volatile("; %0" ::"a"(q[threadIdx.x]));', " a")],
-                         ids=["fits", "spills", "named", "used"])
-def test_build_refuses_spills_and_used_accumulators(tmp_path, source, fault):
+                                          (NAMED % 'asm volatile("; %0" ::"a"(q[threadIdx.x]));', " a"),
+                                          (READ % "__builtin_amdgcn_s_waitcnt(0xc07f);", None), (READ % "", "landed")],
+                         ids=["fits", "spills", "named", "used", "waited", "early"])
+def test_build_refuses_kernels_that_must_not_run(tmp_path, source, fault):
     src, asm = tmp_path / "k.hip", tmp_path / "k.s"
     src.write_text(source.replace("%%", "%"))
     subprocess.run([build._hipcc(), *build.HIPCC_FLAGS, "-S", "--offload-device-only", str(src), "-o", str(asm)], check=True,
