@@ -104,11 +104,11 @@ inline double best_tiles(int64_t M, int64_t N, int64_t K, ProductKind kind, int 
     return best;
 }
 
-// A product's rows [0, first_rows) go to `first` tiles, [first_rows, tile_rows) to `second` ones, the rest to the
-// small-product kernel with `split`.  Any of the three parts may be empty; split is DIRECT_NONE exactly if the last one is.
+// A product's rows [0, first_rows) go to 256x256 tiles, [first_rows, tile_rows) to `rest` ones, the others to the small-product
+// kernel with `split`.  Any of the three parts may be empty; split is DIRECT_NONE exactly if the last one is.
 struct ProductPlan {
     int64_t first_rows, tile_rows;
-    TileKind first, second;
+    TileKind rest;
     int split;
 };
 
@@ -136,9 +136,9 @@ struct ProductPlan {
 // the mean (256x128 tiles and whole rounds: 6304 x 768, K = 3072 24.2 / 20.4 us; 8000 x 1024, K = 4096 37.0 / 30.5;
 // 11237 x 2880, K = 1088 44.4 / 37.7; 30000 x 1280, K = 4096 153 / 137).
 inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
-    ProductPlan plan{0, M, TILES_256, TILES_256, DIRECT_NONE};
+    ProductPlan plan{0, M, TILES_256, DIRECT_NONE};
     int split = DIRECT_NONE;
-    double best = best_tiles(M, N, K, kind, out_bytes, ncu, &plan.second);
+    double best = best_tiles(M, N, K, kind, out_bytes, ncu, &plan.rest);
     if (few_tiles(M, N, ncu)) {
         const int64_t blocks = ((M + 63) / 64) * (N / 64);
         if (blocks > 2 * (int64_t)ncu) return plan;
@@ -159,7 +159,7 @@ inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kin
         const double t = tiled_product_time(TILES_256, full * 256, N, K, kind, out_bytes, ncu) + rest;
         if (rest < (rounds == 1 ? 1.0 + 7.0 * k1024 : later * k1024) && t < 1.05 * best) {
             best = t < best ? t : best;
-            plan = ProductPlan{full * 256, full * 256, TILES_256, TILES_256, split};
+            plan = ProductPlan{full * 256, full * 256, TILES_256, split};
         }
     }
     // WHOLE ROUNDS
@@ -168,7 +168,7 @@ inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kin
         TileKind rest;
         const double t = tiled_product_time(TILES_256, whole * 256, N, K, kind, out_bytes, ncu) +
                          best_tiles(M - whole * 256, N, K, kind, out_bytes, ncu, &rest);
-        if (t < 0.95 * best) plan = ProductPlan{whole * 256, M, TILES_256, rest, DIRECT_NONE};
+        if (t < 0.95 * best) plan = ProductPlan{whole * 256, M, rest, DIRECT_NONE};
     }
     return plan;
 }

@@ -225,7 +225,7 @@ __device__ __forceinline__ void gemm_bf16_tn_body(const GemmBf16Args &p) {
                 if (handed_over) {
                     // Stage hand-over (see the int8 kernel): this wave's reads of stage kt are retired, stage kt+1
                     // has landed, the freed stage may be refilled.
-                    wait_stage<C::LPW, 0>(issued_upto - (kt + 1));
+                    wait_stage<C::LPW>(issued_upto - (kt + 1));
                     wait_lds_reads();
                     block_barrier();
                     if (kt + S < KT) issue_stage(kt + S);
@@ -278,7 +278,7 @@ __device__ __forceinline__ void gemm_bf16_tn_body(const GemmBf16Args &p) {
             }
         };
         if (KT > 0) {
-            wait_stage<C::LPW, 0>(issued_upto);
+            wait_stage<C::LPW>(issued_upto);
             block_barrier();
 #pragma unroll
             for (int i = 0; i < NFRAG; ++i) issue_frag_read(i, 0, 0, 0);

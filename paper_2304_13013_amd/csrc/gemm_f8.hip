@@ -1,5 +1,5 @@
 // Host-side dispatch of the 8-bit float GEMM with dequantizing epilogue (the float8 variant of SwitchBack; kernels:
-// gemm_i8_wide_kernel.h and gemm_i8_kernel.h with the float8 arithmetic selected).
+// gemm_i8_wide_kernel.h, gemm_i8_kernel.h and gemm_i8_direct_kernel.h with the float8 arithmetic selected; dispatch.h picks).
 #include "gemm_i8_direct_kernel.h"
 #include "gemm_i8_wide_kernel.h"
 
@@ -10,7 +10,6 @@ namespace {
 
 typedef WideI8Cfg<MATH_F8, false, false> F8Cfg;
 typedef WideI8Cfg<MATH_F8, false, false, 128> F8Narrow;
-// Products with few large tiles, the same line as for the int8 product.
 typedef GemmI8Cfg F8Small;
 
 #define SB_GEMM_F8_ENTRY(name, OUT, FW, FX)                                                                \
@@ -84,12 +83,12 @@ hipError_t launch_gemm_f8_dequant(const uint8_t *aq, int fmt_a, const float *sta
     const ProductPlan plan = plan_product(M, N, K, PRODUCT_F8, out_bytes, num_compute_units());
     const int which = (fmt_b ? 4 : 0) + (fmt_a ? 2 : 0) + (out_dtype == SB_BF16 ? 0 : 1);
     if (plan.first_rows > 0) {
-        const hipError_t e = launch_tiled(plan.first, which, rows_of(args, 0, plan.first_rows, out_bytes), stream);
+        const hipError_t e = launch_tiled(TILES_256, which, rows_of(args, 0, plan.first_rows, out_bytes), stream);
         if (e != hipSuccess) return e;
     }
     if (plan.tile_rows > plan.first_rows) {
         const hipError_t e =
-            launch_tiled(plan.second, which, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), stream);
+            launch_tiled(plan.rest, which, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), stream);
         if (e != hipSuccess) return e;
     }
     if (plan.split == DIRECT_NONE) return hipSuccess;

@@ -1,5 +1,5 @@
-// Host-side dispatch of the int8 GEMM with dequantizing epilogue (kernels: gemm_i8_wide_kernel.h for 256x256 tiles,
-// gemm_i8_kernel.h for 128x128 ones).
+// Host-side dispatch of the int8 GEMM with dequantizing epilogue (kernels: gemm_i8_wide_kernel.h for 256x256 and 256x128 tiles,
+// gemm_i8_kernel.h for 128x128 ones, gemm_i8_direct_kernel.h for small products and last rows; dispatch.h picks).
 #include "gemm_i8_direct_kernel.h"
 #include "gemm_i8_wide_kernel.h"
 
@@ -8,9 +8,6 @@
 namespace sb {
 namespace {
 
-// 128x128 tiles are for products with few output tiles (ViT-B/16's 768-wide outputs make 75 tiles of 256x256 for 256
-// compute units).  Twice the operand bytes per multiply-add, so they lose to the large tile as soon as that one fills the
-// GPU.
 template <class C>
 hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI8Args args, hipStream_t stream) {
     if (!attr_set->load(std::memory_order_acquire)) {  // setting it twice (two host threads racing) is harmless
@@ -126,11 +123,11 @@ static hipError_t launch_product(const GemmI8Args &args, bool post, sb_dtype out
     const ProductKind kind = post || args.state_col != nullptr ? PRODUCT_LONG_EPILOGUE : PRODUCT_PLAIN;
     const ProductPlan plan = plan_product(args.M, args.N, args.K, kind, out_bytes, num_compute_units());
     if (plan.first_rows > 0) {
-        const hipError_t e = launch_tiled(plan.first, rows_of(args, 0, plan.first_rows, out_bytes), post, out_dtype, stream);
+        const hipError_t e = launch_tiled(TILES_256, rows_of(args, 0, plan.first_rows, out_bytes), post, out_dtype, stream);
         if (e != hipSuccess) return e;
     }
     if (plan.tile_rows > plan.first_rows) {
-        const hipError_t e = launch_tiled(plan.second, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), post,
+        const hipError_t e = launch_tiled(plan.rest, rows_of(args, plan.first_rows, plan.tile_rows, out_bytes), post,
                                           out_dtype, stream);
         if (e != hipSuccess) return e;
     }

@@ -160,7 +160,7 @@ __device__ __forceinline__ void gemm_i8_direct_body(const GemmI8Args &p) {
         if (i < n) issue(i);
     for (int i = 0; i < n; ++i) {
         const int slot = i % C::STAGES;
-        wait_stage<C::REQ, 0>(min(C::STAGES - 1, n - 1 - i));  // the requests of a wave retire in order
+        wait_stage<C::REQ>(min(C::STAGES - 1, n - 1 - i));  // the requests of a wave retire in order
         __builtin_amdgcn_sched_barrier(0);
         read_group(0, slot, 0);
 #pragma unroll

@@ -127,18 +127,13 @@ __device__ __forceinline__ void wait_lgkmcnt() {
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Wait until at most `later` stages (LPW requests each) plus EXTRA other vector-memory operations remain
-// outstanding.  Counts that do not fit the 6-bit counter are clamped, which only makes the wait stricter.
-template <int LPW, int EXTRA>
+// Wait until at most `later` stages (0 or 1, LPW requests each) remain outstanding.
+template <int LPW>
 __device__ __forceinline__ void wait_stage(int later) {
-    constexpr int c0 = EXTRA < 63 ? EXTRA : 63, c1 = LPW + EXTRA < 63 ? LPW + EXTRA : 63;
-    constexpr int c2 = 2 * LPW + EXTRA < 63 ? 2 * LPW + EXTRA : 63, c3 = 3 * LPW + EXTRA < 63 ? 3 * LPW + EXTRA : 63;
-    switch (later) {
-        case 0: wait_vmcnt<c0>(); break;
-        case 1: wait_vmcnt<c1>(); break;
-        case 2: wait_vmcnt<c2>(); break;
-        default: wait_vmcnt<c3>(); break;
-    }
+    if (later == 0)
+        wait_vmcnt<0>();
+    else
+        wait_vmcnt<LPW>();
 }
 
 

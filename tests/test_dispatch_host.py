@@ -20,11 +20,10 @@ long long plan_product(long long M, long long N, long long K, int kind, int out_
     *split = p.split;
     return p.tile_rows;
 }
-// Rows [0, result) on the first kind of tiles, the others on the second one.
-long long plan_tiles(long long M, long long N, long long K, int kind, int out_bytes, int ncu, int *first, int *second) {
+// Rows [0, result) on 256x256 tiles, the others on `rest` ones.
+long long plan_tiles(long long M, long long N, long long K, int kind, int out_bytes, int ncu, int *rest) {
     const sb::ProductPlan p = sb::plan_product(M, N, K, (sb::ProductKind)kind, out_bytes, ncu);
-    *first = p.first;
-    *second = p.second;
+    *rest = p.rest;
     return p.first_rows;
 }
 int plan_weight_gradient(long long b, long long n, long long m, int ncu, int *out) {
@@ -68,7 +67,7 @@ def rules(tmp_path_factory):
     rules.few_tiles.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int]
     rules.plan_product.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     rules.plan_product.restype = ctypes.c_longlong
-    rules.plan_tiles.argtypes = rules.plan_product.argtypes + [ctypes.POINTER(ctypes.c_int)]
+    rules.plan_tiles.argtypes = rules.plan_product.argtypes
     rules.plan_tiles.restype = ctypes.c_longlong
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
     rules.adamw_blocks.argtypes = [ctypes.c_longlong]
@@ -156,10 +155,10 @@ TILES_128, TILES_256X128, TILES_256 = range(3)
 
 
 def tiles(rules, M, N, K, kind, out_bytes):
-    """(rows on the first tiles, their kind or None, kind of the others or None) on an MI355X."""
-    first, second = ctypes.c_int(-1), ctypes.c_int(-1)
-    rows = rules.plan_tiles(M, N, K, kind, out_bytes, 256, ctypes.byref(first), ctypes.byref(second))
-    return rows, first.value if rows else None, second.value if rows < route(rules, M, N, K, out_bytes, kind)[0] else None
+    """(rows on the first tiles, TILES_256 or None, kind of the others or None) on an MI355X."""
+    rest = ctypes.c_int(-1)
+    rows = rules.plan_tiles(M, N, K, kind, out_bytes, 256, ctypes.byref(rest))
+    return rows, TILES_256 if rows else None, rest.value if rows < route(rules, M, N, K, out_bytes, kind)[0] else None
 
 
 def only(rules, tile, M, N, K, kind, out_bytes):
@@ -194,6 +193,15 @@ def test_sizes_of_the_gpu_tests_reach_every_tile(rules):
     assert {second for M, N, K in sizes.NARROW_F8 for second in tiles(rules, M, N, K, F8, 2)[1:]} >= {
         TILES_256X128, TILES_256}
     assert any(rows and second is not None for rows, _, second in (tiles(rules, M, N, K, F8, 2) for M, N, K in sizes.NARROW_F8))
+
+
+# Four-byte outputs just past one round of 128x128 tiles, where a compute unit gets four of them, and just up to it.
+@pytest.mark.parametrize("M,N,K,kind,tile", [(34752, 192, 384, PLAIN, TILES_256), (4455, 2048, 64, PLAIN, TILES_256),
+                                             (35776, 192, 640, PLAIN, TILES_256), (5014, 2048, 256, F8, TILES_256),
+                                             (6890, 1280, 384, F8, TILES_256), (25074, 192, 128, PLAIN, TILES_128),
+                                             (16000, 320, 128, F8, TILES_128)])
+def test_tiles_of_four_byte_outputs(rules, M, N, K, kind, tile):
+    assert only(rules, tile, M, N, K, kind, 4)
 
 
 def weight_gradient(rules, b, n, m, ncu=256):
