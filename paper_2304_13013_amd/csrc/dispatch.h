@@ -56,6 +56,11 @@ enum ProductKind { PRODUCT_PLAIN = 0, PRODUCT_LONG_EPILOGUE, PRODUCT_F8 };
 // (gemm_i8_wide_kernel.h).
 enum TileKind { TILES_128 = 0, TILES_256X128, TILES_256, TILE_KINDS };
 
+// 256x256 tiles of a single stage, one per workgroup at most: they have instances of their own (gemm_i8_wide_kernel.h).
+inline bool one_stage(int64_t M, int64_t N, int64_t K, int ncu) {
+    return K <= 128 && ((M + 255) / 256) * ((N + 255) / 256) <= (ncu & ~7);
+}
+
 // Estimated time (us) of a product on tiles.  With r rounds of the persistent grid (of the XCD with most tiles), u tiles on
 // the compute unit that gets most (2 r where two workgroups share one), k stages of 128 bytes and enough tiles for f rounds of
 // a full grid:

@@ -17,6 +17,10 @@ typedef GemmI8Cfg F8Small;
         GemmI8Args p) {                                                                                    \
         gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false>(p);                                    \
     }                                                                                                      \
+    __global__ __launch_bounds__(F8Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_1( \
+        GemmI8Args p) {                                                                                    \
+        gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false, 256, true>(p);                         \
+    }                                                                                                      \
     __global__ __launch_bounds__(F8Narrow::THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void name##_n( \
         GemmI8Args p) {                                                                                    \
         gemm_i8_wide_body<OUT, false, MATH_F8 + 2 * FW + FX, false, 128>(p);                               \
@@ -36,18 +40,22 @@ SB_GEMM_F8_ENTRY(gemm_f8_a5b5_bf16, OUT_BF16, 1, 1)
 SB_GEMM_F8_ENTRY(gemm_f8_a5b5_f32, OUT_F32, 1, 1)
 #undef SB_GEMM_F8_ENTRY
 
-// The instance for a tile, a pair of formats and an output type (`which`, in the order of the entries above).
+// The instance for a tile (256x256 ones: with or without further stages), a pair of formats and an output type (`which`, in the
+// order of the entries above).
 hipError_t launch_tiled(TileKind tile, int which, GemmI8Args args, hipStream_t stream) {
     typedef void (*Kernel)(GemmI8Args);
-    static const Kernel kernels[TILE_KINDS][8] = {
+    static const Kernel kernels[TILE_KINDS + 1][8] = {
         {gemm_f8_a4b4_bf16_s, gemm_f8_a4b4_f32_s, gemm_f8_a5b4_bf16_s, gemm_f8_a5b4_f32_s, gemm_f8_a4b5_bf16_s,
          gemm_f8_a4b5_f32_s, gemm_f8_a5b5_bf16_s, gemm_f8_a5b5_f32_s},
         {gemm_f8_a4b4_bf16_n, gemm_f8_a4b4_f32_n, gemm_f8_a5b4_bf16_n, gemm_f8_a5b4_f32_n, gemm_f8_a4b5_bf16_n,
          gemm_f8_a4b5_f32_n, gemm_f8_a5b5_bf16_n, gemm_f8_a5b5_f32_n},
         {gemm_f8_a4b4_bf16, gemm_f8_a4b4_f32, gemm_f8_a5b4_bf16, gemm_f8_a5b4_f32, gemm_f8_a4b5_bf16, gemm_f8_a4b5_f32,
-         gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32}};
-    static std::atomic<bool> attr_set[TILE_KINDS][8];  // zero-initialized; a racing second set is harmless
-    const Kernel kernel = kernels[tile][which];
+         gemm_f8_a5b5_bf16, gemm_f8_a5b5_f32},
+        {gemm_f8_a4b4_bf16_1, gemm_f8_a4b4_f32_1, gemm_f8_a5b4_bf16_1, gemm_f8_a5b4_f32_1, gemm_f8_a4b5_bf16_1,
+         gemm_f8_a4b5_f32_1, gemm_f8_a5b5_bf16_1, gemm_f8_a5b5_f32_1}};
+    static std::atomic<bool> attr_set[TILE_KINDS + 1][8];  // zero-initialized; a racing second set is harmless
+    const int row = tile == TILES_256 && one_stage(args.M, args.N, args.K, num_compute_units()) ? (int)TILE_KINDS : (int)tile;
+    const Kernel kernel = kernels[row][which];
     int grid = 0, threads = 0, lds = 0;
     auto shape = [&](auto config, int per_cu) {
         typedef decltype(config) C;
@@ -61,11 +69,11 @@ hipError_t launch_tiled(TileKind tile, int which, GemmI8Args args, hipStream_t s
         shape(F8Narrow(), 1);
     else
         shape(F8Cfg(), 1);
-    if (!attr_set[tile][which].load(std::memory_order_acquire)) {
+    if (!attr_set[row][which].load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        attr_set[tile][which].store(true, std::memory_order_release);
+        attr_set[row][which].store(true, std::memory_order_release);
     }
     kernel<<<grid, threads, lds, stream>>>(args);
     return hipGetLastError();

@@ -24,22 +24,25 @@ hipError_t launch(void (*kernel)(GemmI8Args), std::atomic<bool> *attr_set, GemmI
     return hipGetLastError();
 }
 
-// The kernels of a form on 256x256 (_w) and 256x128 tiles (_w128) and their launcher.  One wave per SIMD: all 512 registers
-// are a lane's.
-#define SB_WIDE_KERNEL(name, OUT, COLSCALE, POST, BN)                                     \
+// The kernels of a form on 256x256 (_w; _w1: one stage and one tile per workgroup) and 256x128 tiles (_w128) and their launcher.
+// One wave per SIMD: all 512 registers are a lane's.
+#define SB_WIDE_KERNEL(name, OUT, COLSCALE, POST, BN, ONE_STAGE)                          \
     __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void name( \
         GemmI8Args p) {                                                                   \
-        gemm_i8_wide_body<OUT, COLSCALE, MATH_I8, POST, BN>(p);                           \
+        gemm_i8_wide_body<OUT, COLSCALE, MATH_I8, POST, BN, ONE_STAGE>(p);                \
     }
 #define SB_WIDE(name, OUT, COLSCALE, POST)                                                \
-    SB_WIDE_KERNEL(name##_w, OUT, COLSCALE, POST, 256)                                    \
-    SB_WIDE_KERNEL(name##_w128, OUT, COLSCALE, POST, 128)                                 \
+    SB_WIDE_KERNEL(name##_w, OUT, COLSCALE, POST, 256, false)                             \
+    SB_WIDE_KERNEL(name##_w1, OUT, COLSCALE, POST, 256, true)                             \
+    SB_WIDE_KERNEL(name##_w128, OUT, COLSCALE, POST, 128, false)                          \
     hipError_t name(bool narrow, const GemmI8Args &args, hipStream_t stream) {            \
         typedef WideI8Cfg<MATH_I8, COLSCALE, POST, 256> C;                                \
         typedef WideI8Cfg<MATH_I8, COLSCALE, POST, 128> C128;                             \
-        static std::atomic<bool> attr_set[2]; /* zero-initialized */                      \
-        return narrow ? launch<C128>(name##_w128, &attr_set[0], args, stream)             \
-                      : launch<C>(name##_w, &attr_set[1], args, stream);                  \
+        static std::atomic<bool> attr_set[3]; /* zero-initialized */                      \
+        if (narrow) return launch<C128>(name##_w128, &attr_set[0], args, stream);         \
+        if (one_stage(args.M, args.N, args.K, num_compute_units()))                       \
+            return launch<C>(name##_w1, &attr_set[1], args, stream);                      \
+        return launch<C>(name##_w, &attr_set[2], args, stream);                           \
     }
 // A small-tile instance: K a multiple of 128 (_k) and K = 64 mod 128 (_h).  Two waves per SIMD (two workgroups per compute
 // unit): at most 256 registers a lane.

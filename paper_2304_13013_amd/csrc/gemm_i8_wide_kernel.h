@@ -98,7 +98,10 @@ struct WideI8Cfg {
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-template <int OUT, bool COLSCALE, int MATH, bool POST, int BN = 256>
+// ONE_STAGE: the contraction is one stage and no workgroup has a second tile.  Instances of their own, which make no requests
+// past the stage and multiply both halves block by block, so that the epilogue starts at once (one round of 256x256 tiles, K =
+// 128: 7.3 -> 7.0 us, K = 64: 7.6 -> 7.1; as a way through the other instances, those lost 0.4 %).
+template <int OUT, bool COLSCALE, int MATH, bool POST, int BN = 256, bool ONE_STAGE = false>
 __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void lds_void;
@@ -184,17 +187,11 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
             l_a_bytes = l_b_bytes = 0;
     };
     next_tile_sources();
-    // A workgroup whose only tile has one stage makes no requests past it, and multiplies both halves block by block, so that
-    // the epilogue starts at once (ONLY; one round of 256x256 tiles, K = 128: 7.3 -> 7.0 us, K = 64: 7.6 -> 7.1).
-    bool only_stage = false;
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (S == 2 && s == 1) only_stage = l_a_bytes == 0;
-        if (!only_stage) {
+    for (int s = 0; s < (ONE_STAGE ? 1 : S); ++s) {
 #pragma unroll
-            for (int i = 0; i < C::LPW; ++i) issue_req(s, i);
-        }
-        advance();
+        for (int i = 0; i < C::LPW; ++i) issue_req(s, i);
+        if (!ONE_STAGE) advance();
     }
 
     // ---- Fragments: 16 (float8: 32) bytes of one row a lane.  Which bytes of k a lane holds does not matter as long as both
@@ -238,10 +235,7 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
     if (OUT != OUT_I32 && !COLSCALE) tensor_scale = F8 ? p.state_tensor[0] : p.state_tensor[0] / 16129.0f;
     asm volatile("" : "+v"(tensor_scale));
 
-    if (only_stage)
-        wait_vmcnt<0>();
-    else
-        wait_vmcnt<(S - 1) * C::LPW>();
+    wait_vmcnt<(ONE_STAGE ? 0 : (S - 1) * C::LPW)>();
     block_barrier();
 #pragma unroll
     for (int i = 0; i < C::NREADS; ++i) issue_read(i, 0, 0);
@@ -505,17 +499,12 @@ __device__ __forceinline__ void gemm_i8_wide_body(const GemmI8Args &p) {
         return;
     }
     int ring = 0;
-    // The paths below keep the fragments in registers of their own: no copy to those before the reads have landed.
-    wait_lds_reads();
-    pin_frags(0);
-    if constexpr (S == 2 && !POST) {  // both fragment buffers and bias and layer-scale do not fit the registers
-        if (only_stage) {
+    if constexpr (ONE_STAGE) {
 #pragma unroll
-            for (int i = 0; i < C::NREADS; ++i) issue_read(i, 1, 0);
-            epi_begin(t, ring);
-            period(I0(), KOnly());
-            return;
-        }
+        for (int i = 0; i < C::NREADS; ++i) issue_read(i, 1, 0);
+        epi_begin(t, ring);
+        period(I0(), KOnly());
+        return;
     }
     period(I0(), KFirst());
     for (int round = 1;; ++round) {

@@ -161,12 +161,14 @@ def test_half_stages_and_last_rows(oracle, M, N, K):
 # per workgroup, partial in both directions.  At these lengths the epilogue of a tile stands in the first half stage of the
 # next one, right before its hand-over.
 LARGE = [(16385, 1472, 64), (8449, 2880, 128), (20011, 2240, 192), (14000, 3264, 256), (12345, 2240, 320), (12345, 2240, 384)]
+# One stage and at most one tile per workgroup (instances of their own): half a stage and a whole one, partial both ways.
+ONE_STAGE = [(25615, 320, 64), (25615, 320, 128), (2501, 4032, 128)]
 # 128x128 tiles: the same for a single stage, two and five; one tile per workgroup and more than fit the GPU at once.
 SMALL_TILES = [(3000, 704, 64), (33000, 320, 128), (3000, 704, 192), (3000, 704, 256), (3000, 704, 576), (3000, 704, 640)]
 
 
 # The other sizes: a single column of partial tiles (128x128), and short contractions on whichever tile the output takes.
-@pytest.mark.parametrize("M,N,K", LARGE + SMALL_TILES + [(33000, 64, 64), (33000, 2304, 64), (8449, 1088, 128), (17000, 2240, 192),
+@pytest.mark.parametrize("M,N,K", LARGE + ONE_STAGE + SMALL_TILES + [(33000, 64, 64), (33000, 2304, 64), (8449, 1088, 128), (17000, 2240, 192),
                                                          (16700, 2112, 320)])
 def test_large_tiles(oracle, M, N, K):
     test_half_stages_and_last_rows(oracle, M, N, K)
@@ -189,9 +191,9 @@ TILES_F8 = [(16448, 1024, 1024), (16385, 960, 1152), (6304, 832, 1152), (1999, 2
 NARROW_F8 = [(6304, 768, 3072), (5431, 960, 4096), (22069, 1472, 384)]
 
 
-# Every pair of formats on each tile: 256x256 with one stage a tile and with two, 256x128, 128x128 with one stage, also with more
+# Every pair of formats on each tile: 256x256 with one stage a tile and with two, one stage in one round, 256x128, 128x128 with one stage, also with more
 # tiles than fit the GPU at once; partial in both directions.
-FORMATS_F8 = {"256": [(8449, 2880, 128), (14000, 3264, 256)], "256x128": [(5431, 960, 4096)],
+FORMATS_F8 = {"256": [(8449, 2880, 128), (14000, 3264, 256)], "one stage": [(25615, 320, 128)], "256x128": [(5431, 960, 4096)],
               "128": [(3000, 704, 128), (33000, 320, 128)]}
 
 

@@ -32,6 +32,7 @@ int plan_weight_gradient(long long b, long long n, long long m, int ncu, int *ou
     out[4] = sb::least_pieces(b, n, m, ncu);
     return p.small;
 }
+int one_stage(long long M, long long N, long long K, int ncu) { return sb::one_stage(M, N, K, ncu); }
 int persistent_grid(long long tiles, int slots) { return sb::persistent_grid(tiles, slots); }
 int adamw_blocks(long long count) { return sb::adamw_blocks(count); }
 long long adamw_elements_at_least(long long blocks, long long n) { return sb::adamw_elements_at_least(blocks, n); }
@@ -69,6 +70,7 @@ def rules(tmp_path_factory):
     rules.plan_product.restype = ctypes.c_longlong
     rules.plan_tiles.argtypes = rules.plan_product.argtypes
     rules.plan_tiles.restype = ctypes.c_longlong
+    rules.one_stage.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     rules.persistent_grid.argtypes = [ctypes.c_longlong, ctypes.c_int]
     rules.adamw_blocks.argtypes = [ctypes.c_longlong]
     rules.adamw_elements_at_least.argtypes = [ctypes.c_longlong] * 2
@@ -169,11 +171,13 @@ def only(rules, tile, M, N, K, kind, out_bytes):
 def test_sizes_of_the_gpu_tests_reach_every_tile(rules):
     import test_dispatch_gpu as sizes
     for form in FORMS:  # each listed size runs what its list is named for, whichever the output and scale
-        assert all(only(rules, TILES_256, *s, *form) for s in sizes.LARGE), form
+        assert all(only(rules, TILES_256, *s, *form) and not rules.one_stage(*s, 256) for s in sizes.LARGE), form
+        assert all(only(rules, TILES_256, *s, *form) and rules.one_stage(*s, 256) for s in sizes.ONE_STAGE), form
         assert all(only(rules, TILES_128, *s, *form) for s in sizes.SMALL_TILES), form
     for out_bytes in (2, 4):
-        for name, tile in (("256", TILES_256), ("256x128", TILES_256X128), ("128", TILES_128)):
+        for name, tile in (("256", TILES_256), ("one stage", TILES_256), ("256x128", TILES_256X128), ("128", TILES_128)):
             assert all(only(rules, tile, *s, F8, out_bytes) for s in sizes.FORMATS_F8[name]), (name, out_bytes)
+    assert all(rules.one_stage(*s, 256) == (name == "one stage") for name in ("256", "one stage") for s in sizes.FORMATS_F8[name])
     stages = lambda listed: {(-(-K // 128), K % 128) for _, _, K in listed}
     assert stages(sizes.LARGE) >= {(s, h) for s in (1, 2, 3) for h in (0, 64)}
     assert stages(sizes.SMALL_TILES) >= {(s, h) for s in (1, 2, 5) for h in (0, 64)}
@@ -236,6 +240,18 @@ def test_sizes_of_the_gpu_tests_reach_both_weight_gradients(rules):
     plans = [(-(-n // 128) * -(-m // 128), *weight_gradient(rules, b, n, m)) for b, n, m in sizes.MANY_SMALL_DW]
     assert all(items > 512 and small and splits == 1 for items, small, splits, *_ in plans)
     assert {pieces for _, _, _, _, pieces, *_ in plans} == {1, 7}
+
+
+# The instances of one stage are for launches in which no workgroup has a second tile, on any XCD.
+@pytest.mark.parametrize("ncu", [256, 304, 60, 8])
+def test_one_stage_is_one_tile_per_workgroup(rules, ncu):
+    for M in list(range(1, 9000, 83)) + [32768, 65536, 70000]:
+        for N in (64, 256, 320, 2048, 8192, 65536):
+            tiles = -(-M // 256) * -(-N // 256)
+            one = rules.one_stage(M, N, 128, ncu)
+            assert not rules.one_stage(M, N, 192, ncu)
+            assert not one or -(-tiles // 8) <= rules.persistent_grid(tiles, ncu) // 8
+            assert bool(one) == (tiles <= ncu // 8 * 8)
 
 
 @pytest.mark.parametrize("slots", [8, 64, 256, 512, 608])
