@@ -29,14 +29,18 @@ struct CeilTraits<CEIL_I8> {
     typedef v4i Frag;
     typedef v4i Acc;
     static constexpr int FRAGS = 8, OPS = 2 * 16 * 16 * 64;
-    static __device__ __forceinline__ void mma(Frag b, Frag a, Acc &c) { asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a)); }
+    static __device__ __forceinline__ void mma(Frag b, Frag a, Acc &c) {
+        asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
+    }
 };
 template <>
 struct CeilTraits<CEIL_BF16> {
     typedef v8bf Frag;
     typedef v4f Acc;
     static constexpr int FRAGS = 8, OPS = 2 * 16 * 16 * 32;
-    static __device__ __forceinline__ void mma(Frag b, Frag a, Acc &c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a)); }
+    static __device__ __forceinline__ void mma(Frag b, Frag a, Acc &c) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
+    }
 };
 template <>
 struct CeilTraits<CEIL_F8> {
@@ -49,8 +53,8 @@ struct CeilTraits<CEIL_F8> {
 };
 
 // a, b: operand bytes; wave w of the grid takes its fragment f of either operand at byte (w * kBufs * FRAGS + f) * 64 *
-// sizeof(Frag) modulo the buffer's length (a_bytes, b_bytes: multiples of 64 * sizeof(Frag)).  sink receives one value per lane so that
-// the accumulators stay live.
+// sizeof(Frag) modulo the buffer's length (a_bytes, b_bytes: multiples of 64 * sizeof(Frag)).  sink receives one value per
+// lane so that the accumulators stay live.
 template <int KIND>
 __device__ __forceinline__ void mfma_loop_body(const unsigned char *a, size_t a_bytes, const unsigned char *b,
                                                size_t b_bytes, int iters, float *sink) {

@@ -137,9 +137,9 @@ struct ProductPlan {
 //   their stores if there are many or K is small, and gain nothing reliable.  Where the number of rounds stays nothing is
 //   split off, and neither where the partial row is the only one (fewer than 256 rows of a very wide output).
 //   WHOLE ROUNDS.  More than a partial row is left: other tiles do those rows.  It has to save 5 % by the estimates.
-// Against one kernel for all rows and the 128x128 and 256x256 tiles alone, 1200 products of all kinds run 4 to 8 % faster in
-// the mean (256x128 tiles and whole rounds: 6304 x 768, K = 3072 24.2 / 20.4 us; 8000 x 1024, K = 4096 37.0 / 30.5;
-// 11237 x 2880, K = 1088 44.4 / 37.7; 30000 x 1280, K = 4096 153 / 137).
+// us on 128x128, 256x128 and 256x256 tiles alone / so: 6304 x 768, K = 3072 24.1, 19.9, 31.3 / 20.1; 8000 x 1024, K = 4096 37.5,
+// 29.9, 43.1 / 29.7; 11237 x 2880, K = 1088 49.8, 39.2, 46.4 / 39.4; 30000 x 1280, K = 4096 169, 130, 134 / 124 (whole rounds);
+// 16448 x 1024, K = 4096 87.5, 68.8, 78.9 / 54.0 (last rows).
 inline ProductPlan plan_product(int64_t M, int64_t N, int64_t K, ProductKind kind, int out_bytes, int ncu) {
     ProductPlan plan{0, M, TILES_256, DIRECT_NONE};
     int split = DIRECT_NONE;
@@ -264,8 +264,8 @@ struct WeightGradTime {
 
 // The fastest by the estimates that sums in least_pieces or more; the split that the pieces are of, unless another saves 6 %
 // (what looks 3 % better loses 5 to 13 % in one of ten: 23446 tokens, 576 -> 1792 66.6 against 75.6 us).  Measured against that
-// split always (us): 28030 tokens, 320 -> 192 405 / 25; 5214 tokens, 256 -> 448 81 / 14; 197 tokens, 768 -> 3072 9.8 / 5.6; 0.73
-// of the time in the mean over 400 weight gradients.
+// split always (us): 28030 tokens, 320 -> 192 405 / 25; 5214 tokens, 256 -> 448 81 / 14; 197 tokens, 768 -> 3072 9.8 / 5.6; 0.72
+// of the time in the mean over 5541 weight gradients (eight-wave kernel before), 32 of them 5 to 11 % slower.
 template <class Int>
 inline WeightGradPlan plan_weight_gradient_in(int64_t b, int64_t n, int64_t m, int ncu) {
     const int64_t stages = (b + DW_STAGE - 1) / DW_STAGE;

@@ -20,14 +20,15 @@
 //     half, one per four instructions (16 per 32 or 48 of them: 4 to 10 % slower; spread over both halves: the same).
 //   * The epilogue of a tile is interleaved with the first half stage of the next one: a block's accumulators are read
 //     just before the instruction that starts them again from zero, and converted in its shadow and the next ones'.  The last
-//     tile's epilogue follows its own last instructions at a distance (3588 x 2560, K = 128: 7.8 -> 7.4 us).
+//     tile's epilogue follows its own last instructions at a distance (3588 x 2560, K = 128: 7.8 -> 7.4 us; 7.1 on the
+//     instances of one stage).
 //     Results go through a wave-private LDS patch (padded rows) and leave as 16-byte non-temporal stores in row segments of
 //     256 (float8: 128) bytes.
 //   * Row states, column states, bias and layer-scale of a tile are requested into LDS with its first stage.
 // 256x128 tiles (waves of 128x64, half the accumulators) are for products whose 256x256 tiles do not fill the GPU or fill its
 // last round badly.  A stage is 48 KiB and three fit; its requests are spread over two half stages, and land a stage later.
-// Against 128x128 tiles, two workgroups per compute unit (us): 6304 x 768, K = 3072 24.2 -> 20.4; 8000 x 1024, K = 4096 37.0
-// -> 30.5; against 256x256 tiles: 6304 x 3072, K = 768 21.7 -> 20.3; 11237 x 2880, K = 1088 43.5 -> 37.3.
+// 128x128 tiles, two workgroups per compute unit / 256x256 tiles / these (us): 6304 x 768, K = 3072 24.1 / 31.3 / 19.9; 8000 x
+// 1024, K = 4096 37.5 / 43.1 / 29.9; 6304 x 3072, K = 768 23.1 / 21.5 / 19.6; 11237 x 2880, K = 1088 49.8 / 46.4 / 39.2.
 //
 // All loops count on a constant number of vector-memory operations: past the last tile the requests go on with an empty
 // buffer resource, rows past the end lie beyond the output's resource and columns past the end are sent there.
